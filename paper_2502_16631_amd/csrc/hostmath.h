@@ -15,6 +15,9 @@ uint32_t host_crc32c(const void* p, uint64_t n, uint32_t prev = 0);
 // CRC(A || B) from CRC(A), CRC(B) and |B|.
 uint32_t crc_combine(uint32_t crc_a, uint32_t crc_b, uint64_t len_b);
 
+// a * b modulo P (the value of gf_mul, in a few host instructions).
+uint32_t host_gf_mul(uint32_t a, uint32_t b);
+
 // x^(8n) and x^(-8n) modulo P (reflected representation).
 uint32_t xpow8(uint64_t n);
 uint32_t xinvpow8(uint64_t n);
