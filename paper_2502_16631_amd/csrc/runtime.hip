@@ -2329,8 +2329,10 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     }
     for (uint64_t w = 0; w < W && !merged; ++w) {
         const int s = (int)(w % nslots);
-        // a tail split keeps the payload where one window holds it
-        hipStream_t cs = c->s_copy[tail ? 0 : w % ncs];
+        // a tail split keeps the payload where one window holds it. The
+        // codec's windows go up one after another: two uploads at a time end
+        // together, a window later than one at a time
+        hipStream_t cs = c->s_copy[tail || (codec && !(o && o->copy_streams)) ? 0 : w % ncs];
         uint8_t* sp = c->staging.as<uint8_t>() + (tail ? wbeg[w] : (uint64_t)s * slot);
         if (slot_used[s] && !tail) HIPCHK(hipStreamWaitEvent(cs, ev[W + s], 0));
         slot_used[s] = true;
