@@ -116,8 +116,9 @@ typedef struct {
 typedef struct {
     uint64_t first_bad_chunk;   /* UINT64_MAX if none                                       */
     int32_t  hip_error;         /* first failing hipError_t, 0 if none                      */
-    uint32_t windows;           /* staging windows used (a plain restore of >= 512 MiB held  */
-                                /* by one window is launched as two parts and reports 2)    */
+    uint32_t windows;           /* staging windows used (1 for a restore that reads a pinned image */
+                                /* where it is; a plain restore of a pageable image of >= 512 MiB  */
+                                /* held by one window is launched as two parts and reports 2)      */
     uint64_t n_logical;         /* N: sum of allocation sizes                               */
     uint64_t n_payload;         /* D: payload bytes                                         */
     uint64_t n_chunks;
@@ -141,13 +142,15 @@ typedef struct {
      *          (codec)  [4] host link: first to last payload copy, wall time
      *          [5] finalize (per-allocation combine, table digests, tables copied
      *          out)  [6] unused  [7] whole call, wall time;
-     * restore: [0] validate (tables up, digest, offsets scan, host checks), wall
+     * restore: [0] validate (host checks of the tables), wall
      *          time  [1] base check of a delta (a plain full restore runs it on
      *          the device beside the upload: its HIP-event time; otherwise the
-     *          host waits for it: wall time)  [2] host link: first to
-     *          last payload copy, wall time  [3] scatter + fused verify kernels
-     *          (codec decode included)  [4] strict re-read  [5] finalize
-     *          (per-allocation check)  [6] unused  [7] whole call, wall time. */
+     *          host waits for it: wall time)  [2] host link: from the first
+     *          payload work queued to the end, wall time  [3] scatter + fused
+     *          verify kernels (codec decode and zero fill included; at the
+     *          link's rate where they read a pinned image themselves)
+     *          [4] strict re-read  [5] offsets scan and per-allocation check
+     *          [6] unused  [7] whole call, wall time. */
     uint64_t ns_stage[8];
 } ckpt_result;
 

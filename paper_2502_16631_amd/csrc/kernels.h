@@ -25,6 +25,8 @@ struct ChunkJob {
     uint8_t* slot;               // staging window (dump: written; restore: read)
     const uint64_t* off;         // restore: payload offset of chunk g
     uint64_t slot_base;          // restore: payload offset of the window start
+    const uint64_t* list;        // restore: the chunks to take, ticket t the chunk list[g0 + t] (DATA chunks
+                                 // only), or nullptr: chunks g0 + t
     uint64_t* status;            // dump: look-back status, indexed by g - g0
     uint64_t* wtotal;            // dump: payload bytes of the window
     unsigned long long* bad;     // verify / restore: lowest failing chunk (init ~0)
@@ -69,6 +71,9 @@ struct OffJob {
     uint32_t* err;
     uint32_t epoch;
     uint32_t pad;
+    const uint32_t* rlen;        // codec layout: record length of PACKED chunk g at [g], or nullptr
+    uint64_t* list;              // DATA chunks of the range in order, or nullptr
+    uint64_t* status2;           // look-back of the list positions (with list), one word per tile
     uint64_t g_base;             // the scan covers global chunks [g_base, g_base + n_chunks); off, kind
                                  // and amap are indexed globally, windows and wb relative to g_base
 };
@@ -88,6 +93,26 @@ struct CombineJob {
     int pad;
 };
 
+// What a call needs on the device before its chunk kernels, in one launch:
+// the descriptors and tables brought from pinned host memory, the chunk map,
+// and the words that start at a known value. Regions must not overlap; all
+// are whole, aligned 32-bit words.
+struct SetupJob {
+    static constexpr int kMaxFills = 8, kMaxCopies = 4;
+    const AllocDesc* src;        // pinned host descriptors
+    AllocDesc* dst;              // device descriptors
+    uint32_t n_allocs;
+    uint32_t C;
+    uint32_t* map;               // chunk map
+    int n_fills, n_copies;
+    struct Fill { uint32_t* p; uint64_t n; uint32_t v; uint32_t pad; } fill[kMaxFills];
+    struct Copy { uint32_t* dst; const uint32_t* src; uint64_t n; } copy[kMaxCopies];
+    void add_fill(void* p, uint64_t words, uint32_t v) { fill[n_fills++] = {static_cast<uint32_t*>(p), words, v, 0}; }
+    void add_copy(void* d, const void* s, uint64_t bytes) {
+        copy[n_copies++] = {static_cast<uint32_t*>(d), static_cast<const uint32_t*>(s), bytes / 4};
+    }
+};
+
 // Validation of a restore inside a captured graph: *gate = 1 when the
 // tables digest combined from the device's two halves equals the expected
 // value, the kinds are all ZERO or DATA and the payload total equals the
@@ -104,11 +129,23 @@ struct GateJob {
 };
 
 bool tile_supported(int T, int K);
+hipError_t launch_setup(const SetupJob& job, hipStream_t s);
+// n <= 64 64-bit device words to pinned host memory.
+hipError_t launch_report(uint64_t* host, const uint64_t* dev, uint32_t n, hipStream_t s);
 hipError_t launch_gate(const GateJob& job, hipStream_t s);
 hipError_t launch_chunks(int T, int K, int mode, const JobList& jl, int grid, hipStream_t s);
 hipError_t chunks_occupancy(int T, int K, int mode, int* blocks_per_cu);
 hipError_t launch_offsets(const OffJob& job, int grid, hipStream_t s);
 hipError_t launch_combine(const CombineJob& job, hipStream_t s);
+// Zero-fill of the ZERO chunks of [job.g0, job.g1) (restore; uses allocs,
+// amap, ec, kind_in, ref_crc, bad and gate).
+hipError_t launch_zero(const ChunkJob& job, int grid, hipStream_t s);
+// Copy of n bytes (a multiple of 16) between device and pinned host memory
+// by kLinkCus work-groups, each alone on its CU.
+constexpr int kLinkCus = 8;
+hipError_t launch_link_copy(void* dst, const void* src, uint64_t n, hipStream_t s);
+// launch_offsets (grid work-groups; 0: none) and launch_combine in one launch.
+hipError_t launch_offsets_combine(const OffJob& off, int grid, const CombineJob& job, hipStream_t s);
 hipError_t launch_chunk_map(const AllocDesc* allocs, uint32_t n_allocs, uint32_t C, uint32_t* map, hipStream_t s);
 hipError_t launch_store_descs(AllocDesc* dst, const AllocDesc& a, const AllocDesc& b, hipStream_t s);
 hipError_t launch_fill64(uint64_t* p, uint64_t v, uint64_t n, hipStream_t s);

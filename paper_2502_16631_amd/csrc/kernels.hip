@@ -415,7 +415,9 @@ k_chunks(JobList jl) {
         uint32_t jj = 0;
         while (jj + 1 < jl.n_jobs && jl.prefix[jj + 1] <= tk) ++jj;
         const ChunkJob& job = jl.job[jj];
-        const uint64_t g = job.g0 + (tk - jl.prefix[jj]);
+        uint64_t g = job.g0 + (tk - jl.prefix[jj]);
+        if constexpr (MODE == kModeRestore)
+            if (job.list) g = job.list[g];
         // Opaque per-chunk copies of per-lane values: without them the
         // compiler hoists 32 multiples of the lane constant and one address
         // per row out of the loop, which costs ~50 VGPRs per lane.
@@ -835,10 +837,11 @@ k_dump_stream(JobList jl) {
     }
 }
 
-__global__ void __launch_bounds__(256) k_offsets(OffJob job) {
+__device__ inline void offsets_wg(const OffJob& job) {
     __shared__ uint32_t s_tk[2];
     __shared__ uint64_t s_wsum[4];
-    __shared__ uint64_t s_off;
+    __shared__ uint32_t s_wcnt[4];
+    __shared__ uint64_t s_off, s_pos;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     for (uint32_t it = 0;; ++it) {
         if (tid == 0) s_tk[it & 1] = atomicAdd(job.ticket, 1u);
@@ -859,6 +862,7 @@ __global__ void __launch_bounds__(256) k_offsets(OffJob job) {
             if (kd == kData) { plen = (len + 15) & ~15ull; cd = 1; }
             else if (kd == kZero) cz = 1;
             else if (kd == kUnchanged) cu = 1;
+            else if (kd == kPacked && job.rlen) plen = job.rlen[gg];
             else ci = 1;
         }
         // block scan of plen
@@ -872,6 +876,7 @@ __global__ void __launch_bounds__(256) k_offsets(OffJob job) {
         // kind counts
         const uint64_t bz = __ballot(cz), bd = __ballot(cd), bu = __ballot(cu), bi = __ballot(ci);
         if (lane == 0) {
+            s_wcnt[wave] = (uint32_t)__popcll(bd);
             if (bz) atomicAdd(&job.counts[0], (unsigned long long)__popcll(bz));
             if (bd) atomicAdd(&job.counts[1], (unsigned long long)__popcll(bd));
             if (bu) atomicAdd(&job.counts[2], (unsigned long long)__popcll(bu));
@@ -885,12 +890,24 @@ __global__ void __launch_bounds__(256) k_offsets(OffJob job) {
             total += s_wsum[w];
         }
         const uint64_t local = before + x - plen;
-        if (tid < 64) {
+        // one wave walks back for the payload offsets, another for the list
+        // positions
+        if (wave == 0) {
             const uint64_t e = lookback(job.status, tile, total, job.epoch, job.err);
-            if (tid == 0) s_off = e;
+            if (lane == 0) s_off = e;
+        } else if (wave == 1 && job.list) {
+            const uint64_t e = lookback(job.status2, tile, s_wcnt[0] + s_wcnt[1] + s_wcnt[2] + s_wcnt[3], job.epoch,
+                                        job.err);
+            if (lane == 0) s_pos = e;
         }
         __syncthreads();
         const uint64_t o = s_off + local;
+        if (cd && job.list) {
+            uint32_t r = (uint32_t)__popcll(bd & ((1ull << lane) - 1));
+#pragma unroll
+            for (int w = 0; w < 4; ++w) r += w < wave ? s_wcnt[w] : 0;
+            job.list[s_pos + r] = gg;
+        }
         if (g < job.n_chunks) {
             job.off[gg] = o;
             if (g % job.per_window == 0) job.wb[g / job.per_window] = o;
@@ -898,6 +915,8 @@ __global__ void __launch_bounds__(256) k_offsets(OffJob job) {
         }
     }
 }
+
+__global__ void __launch_bounds__(256) k_offsets(OffJob job) { offsets_wg(job); }
 
 __global__ void k_gate(GateJob j) {
     if (threadIdx.x != 0) return;
@@ -914,13 +933,12 @@ __device__ inline uint32_t xpow8(uint64_t n, const uint32_t* x2n) {   // x^(8n)
     return r;
 }
 
-__global__ void __launch_bounds__(256) k_combine(CombineJob job) {
+__device__ inline void combine_wg(const CombineJob& job, uint32_t a) {
     __shared__ uint32_t s_red[4];
     __shared__ uint32_t s_x2n[64];
     const int tid = threadIdx.x;
     if (tid < 64) s_x2n[tid] = job.ec->x2n[tid];
     __syncthreads();
-    const uint32_t a = blockIdx.x;
     const AllocDesc ad = job.allocs[a];
     const uint64_t C = job.C;
     const uint64_t nk = (ad.size + C - 1) / C;
@@ -955,12 +973,101 @@ __global__ void __launch_bounds__(256) k_combine(CombineJob job) {
     }
 }
 
+__global__ void __launch_bounds__(256) k_combine(CombineJob job) { combine_wg(job, blockIdx.x); }
+
+// The payload offsets and the per-allocation check of a restore need nothing
+// but the tables and nothing of each other: one launch (the first n_off
+// work-groups scan, one more per allocation combines) in place of two.
+__global__ void __launch_bounds__(256) k_offsets_combine(OffJob off, CombineJob job, uint32_t n_off) {
+    if (blockIdx.x < n_off) offsets_wg(off);
+    else combine_wg(job, blockIdx.x - n_off);
+}
+
+// Zero-fill of a restore's ZERO chunks, apart from its DATA chunks: those
+// wait for the host link, these for nothing, and HBM takes the stores beside
+// the link's reads. Bound by HBM writes; grid-stride, since a chunk of
+// another kind costs one uniform byte load.
+__global__ void __launch_bounds__(256) k_zero(ChunkJob j) {
+    if (j.gate && *j.gate == 0) return;
+    const uint32_t tid = threadIdx.x, C = j.C;
+    for (uint64_t g = j.g0 + blockIdx.x; g < j.g1; g += gridDim.x) {
+        if (j.kind_in[g] != kZero) continue;
+        const AllocDesc* ad = j.allocs + j.amap[g];
+        const uint64_t k = g - ad->first, nk = (ad->size + C - 1) / C;
+        const bool tail = k + 1 == nk && ad->tail_len != C;
+        const uint32_t len = tail ? ad->tail_len : C;
+        uint8_t* p = reinterpret_cast<uint8_t*>(ad->ptr) + k * C;
+        const v4u z = vzero();
+#pragma unroll 4
+        for (uint32_t i = 16 * tid; i + 16 <= len; i += 16 * 256) __builtin_nontemporal_store(z, (gv4*)(p + i));
+        if (tid < (len & 15)) ((gu8*)p)[(len & ~15u) + tid] = 0;
+        // the digest of len zero bytes
+        if (tid == 0 && j.ref_crc[g] != ~(tail ? ad->tail_init : j.ec->full_init)) atomicMin(j.bad, (unsigned long long)g);
+    }
+}
+
+// Host-link copy, beside kernels that read and write HBM. Bound by the link:
+// eight work-groups with 32 KiB in flight each carry 56 GB/s. (Copy engines
+// carry 57 or 30, depending on the engine a stream gets.) A CU answers its
+// vector memory operations in order, so whatever shares a CU with a wave that
+// waits for the link waits with it: a 2 GiB fill beside such a copy took 4.9
+// instead of 0.44 ms. Each work-group therefore claims all vector registers
+// of its CU (512 threads of 256 registers) and has it to itself.
+__global__ void __launch_bounds__(512) k_link_copy(v4u* dst, const v4u* src, uint64_t n16) {
+    asm volatile("" ::: "v255");
+    constexpr uint64_t U = 4, TILE = U * 512;
+    uint64_t b = blockIdx.x * TILE;
+    for (; b + TILE <= n16; b += gridDim.x * TILE) {
+        v4u x[U];
+#pragma unroll
+        for (int u = 0; u < (int)U; ++u) x[u] = ((gcv4*)src)[b + u * 512 + threadIdx.x];
+#pragma unroll
+        for (int u = 0; u < (int)U; ++u) ((gv4*)dst)[b + u * 512 + threadIdx.x] = x[u];
+    }
+    for (uint64_t i = b + threadIdx.x; i < n16 && i < b + TILE; i += 512) ((gv4*)dst)[i] = ((gcv4*)src)[i];
+}
+
 // Chunk -> allocation map: work-group a writes a over its chunk range.
 __global__ void __launch_bounds__(256) k_chunk_map(const AllocDesc* allocs, uint32_t n, uint32_t C, uint32_t* map) {
     for (uint32_t a = blockIdx.x; a < n; a += gridDim.x) {
         const uint64_t first = allocs[a].first, nk = (allocs[a].size + C - 1) / C;
         for (uint64_t k = threadIdx.x; k < nk; k += blockDim.x) map[first + k] = a;
     }
+}
+
+// Set-up of a call (SetupJob). Latency-bound: a few kilobytes for a small
+// table, whose eight launches and uploads took 40-80 us one after another;
+// one launch reads pinned host memory itself (the link's latency once) and
+// takes 6 us. Large tables: 2 MB of image tables at the link's rate, spread
+// over the whole grid. Each part is a grid-stride loop of its own.
+__global__ void __launch_bounds__(256) k_setup(SetupJob j) {
+    const uint64_t t = blockIdx.x * 256ull + threadIdx.x, step = gridDim.x * 256ull;
+    for (int i = 0; i < j.n_copies; ++i) {
+        const SetupJob::Copy c = j.copy[i];
+        if (((reinterpret_cast<uint64_t>(c.src) | reinterpret_cast<uint64_t>(c.dst)) & 15) == 0) {
+            const uint64_t n4 = c.n / 4;
+            for (uint64_t w = t; w < n4; w += step) ((gv4*)c.dst)[w] = ((gcv4*)c.src)[w];
+            for (uint64_t w = 4 * n4 + t; w < c.n; w += step) c.dst[w] = c.src[w];
+        } else {
+            for (uint64_t w = t; w < c.n; w += step) c.dst[w] = c.src[w];
+        }
+    }
+    for (int i = 0; i < j.n_fills; ++i) {
+        const SetupJob::Fill f = j.fill[i];
+        for (uint64_t w = t; w < f.n; w += step) f.p[w] = f.v;
+    }
+    const uint64_t dw = j.n_allocs * (sizeof(AllocDesc) / 16);
+    for (uint64_t w = t; w < dw; w += step) ((gv4*)j.dst)[w] = ((gcv4*)j.src)[w];
+    for (uint32_t a = blockIdx.x; a < j.n_allocs; a += gridDim.x) {
+        const uint64_t first = j.src[a].first, nk = (j.src[a].size + j.C - 1) / j.C;
+        for (uint64_t k = threadIdx.x; k < nk; k += 256) j.map[first + k] = a;
+    }
+}
+
+// Results of a call to pinned host memory: a one-wave launch in place of a
+// copy, which queues behind the payload on a copy engine.
+__global__ void k_report(uint64_t* host, const uint64_t* dev, uint32_t n) {
+    if (threadIdx.x < n) __hip_atomic_store((gu64*)&host[threadIdx.x], dev[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Two descriptors passed by value (kernel arguments are captured at launch,
@@ -1076,6 +1183,26 @@ hipError_t launch_offsets(const OffJob& job, int grid, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_setup(const SetupJob& j, hipStream_t s) {
+    if (j.n_fills > SetupJob::kMaxFills || j.n_copies > SetupJob::kMaxCopies) return hipErrorInvalidValue;
+    // a block per allocation (its map range), enough blocks for the words
+    uint64_t words = j.n_allocs * 16ull;
+    for (int i = 0; i < j.n_fills; ++i) words = words > j.fill[i].n ? words : j.fill[i].n;
+    for (int i = 0; i < j.n_copies; ++i) words = words > j.copy[i].n ? words : j.copy[i].n;
+    uint64_t blocks = (words + 1023) / 1024;
+    if (blocks < j.n_allocs) blocks = j.n_allocs;
+    if (blocks > 2048) blocks = 2048;
+    if (blocks == 0) blocks = 1;
+    hipLaunchKernelGGL(k_setup, dim3((unsigned)blocks), dim3(256), 0, s, j);
+    return hipGetLastError();
+}
+
+hipError_t launch_report(uint64_t* host, const uint64_t* dev, uint32_t n, hipStream_t s) {
+    if (n > 64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, host, dev, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_gate(const GateJob& job, hipStream_t s) {
     hipLaunchKernelGGL(k_gate, dim3(1), dim3(64), 0, s, job);
     return hipGetLastError();
@@ -1084,6 +1211,29 @@ hipError_t launch_gate(const GateJob& job, hipStream_t s) {
 hipError_t launch_combine(const CombineJob& job, hipStream_t s) {
     if (job.n_allocs == 0) return hipSuccess;
     hipLaunchKernelGGL(k_combine, dim3(job.n_allocs), dim3(256), 0, s, job);
+    return hipGetLastError();
+}
+
+hipError_t launch_zero(const ChunkJob& j, int grid, hipStream_t s) {
+    if (!j.amap || grid < 1) return hipErrorInvalidValue;
+    if (j.g1 <= j.g0) return hipSuccess;
+    hipLaunchKernelGGL(k_zero, dim3(grid), dim3(256), 0, s, j);
+    return hipGetLastError();
+}
+
+hipError_t launch_link_copy(void* dst, const void* src, uint64_t n, hipStream_t s) {
+    if (((reinterpret_cast<uint64_t>(dst) | reinterpret_cast<uint64_t>(src) | n) & 15) != 0) return hipErrorInvalidValue;
+    if (n == 0) return hipSuccess;
+    const uint64_t tiles = (n + 32767) / 32768;
+    hipLaunchKernelGGL(k_link_copy, dim3((unsigned)(tiles < (uint64_t)kLinkCus ? tiles : kLinkCus)), dim3(512), 0, s,
+                       static_cast<v4u*>(dst), static_cast<const v4u*>(src), n / 16);
+    return hipGetLastError();
+}
+
+hipError_t launch_offsets_combine(const OffJob& off, int grid, const CombineJob& job, hipStream_t s) {
+    if (grid < 0) return hipErrorInvalidValue;
+    if (grid + job.n_allocs == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_offsets_combine, dim3(grid + job.n_allocs), dim3(256), 0, s, off, job, (uint32_t)grid);
     return hipGetLastError();
 }
 

@@ -192,7 +192,7 @@ struct ckpt_ctx {
     uint64_t use_clock = 0;
     // device buffers
     mk::StatusBuf status;
-    mk::DevBuf descs, ctl, arc, kinds, prevcrc, off, wb, staging, dig, amap, rlen, cmeta;
+    mk::DevBuf descs, ctl, arc, kinds, prevcrc, off, wb, staging, dig, amap, rlen, cmeta, list;
     std::map<std::pair<int, uint32_t>, mk::DevBuf> consts;    // (T, C) -> EngineConsts
     std::map<uint32_t, mk::DevBuf> cconsts;                   // C -> CodecConsts
     std::map<std::tuple<int, int, int>, int> occ;          // (T, K, mode) -> blocks per CU
@@ -202,6 +202,9 @@ struct ckpt_ctx {
     // pinned host scratch for small transfers
     uint8_t* hsmall = nullptr;
     uint64_t hsmall_cap = 0;
+    // pinned host copy of a call's descriptors, which the set-up kernel reads
+    mk::AllocDesc* hdesc = nullptr;
+    uint64_t hdesc_cap = 0;
     // pinned host scratch for per-chunk tables, and a second compute stream
     // (codec dumps: encode on it while the main stream sizes later pieces)
     uint8_t* hpin = nullptr;
@@ -220,6 +223,14 @@ namespace mk {
 // Plain restores of at least this many bytes held by one staging window are
 // launched as all chunks but the last 1/64, then those.
 constexpr uint64_t kTailMinBytes = 512ull << 20;
+
+// Work-groups of a restore launch that reads a pinned image over the host
+// link (512 threads, 64 KiB in flight each).
+constexpr int kLinkGrid = 64;
+// The ranges a restore may stage the first ones of, and the least payload
+// worth it.
+constexpr uint64_t kHeadGrid = 64;
+constexpr uint64_t kMinHead = 1ull << 20;
 
 // Storage hooks. A dump told of a sink reports every payload copy into the
 // image as it is queued (segments of at most kSinkSegment bytes), so the

@@ -316,12 +316,12 @@ static void count_kinds(const uint8_t* kinds, uint64_t b, uint64_t e, uint64_t n
 }
 
 // Plain layout: the image's kinds counted into n[4], and the payload bytes
-// of the chunks before each of the ascending `bounds` into at[]. The payload
-// total is the return value.
-uint64_t scan_kinds(const ImageView& v, const std::vector<uint64_t>& bounds, uint64_t* at, uint64_t n[4]) {
+// and the number of DATA chunks before each of the ascending `bounds` into
+// at[] and rank[]. The payload total is the return value.
+uint64_t scan_kinds(const ImageView& v, const std::vector<uint64_t>& bounds, uint64_t* at, uint64_t* rank, uint64_t n[4]) {
     uint64_t pos = 0, g = 0;
     size_t bi = 0;
-    for (; bi < bounds.size() && bounds[bi] == 0; ++bi) at[bi] = 0;
+    for (; bi < bounds.size() && bounds[bi] == 0; ++bi) at[bi] = rank[bi] = 0;
     for (uint64_t a = 0; a < v.n_allocs; ++a) {
         const uint64_t size = get64(v.recs + 32 * a + 8), end = g + ceil_div(size, v.C);
         const uint64_t short_by = (end - g) * v.C - round16(size);   // of the allocation's last chunk
@@ -332,7 +332,10 @@ uint64_t scan_kinds(const ImageView& v, const std::vector<uint64_t>& bounds, uin
             pos += (n[1] - before) * v.C;
             if (e == end && v.kinds[e - 1] == kData) pos -= short_by;
             g = e;
-            for (; bi < bounds.size() && bounds[bi] == g; ++bi) at[bi] = pos;
+            for (; bi < bounds.size() && bounds[bi] == g; ++bi) {
+                at[bi] = pos;
+                rank[bi] = n[1];
+            }
         }
     }
     return pos;
@@ -439,6 +442,18 @@ hipError_t ensure_hsmall(ckpt_ctx* c, uint64_t n) {
     c->hsmall_cap = 0;
     hipError_t e = pinned_small((void**)&c->hsmall, n);
     if (e == hipSuccess) c->hsmall_cap = n;
+    return e;
+}
+
+// Pinned host copy of a call's descriptors (a context starts with room for
+// kNaMaxAllocs of them).
+hipError_t ensure_hdesc(ckpt_ctx* c, uint64_t n) {
+    if (n <= c->hdesc_cap) return hipSuccess;
+    if (c->hdesc) (void)hipHostFree(c->hdesc);
+    c->hdesc = nullptr;
+    c->hdesc_cap = 0;
+    hipError_t e = pinned_small((void**)&c->hdesc, n * sizeof(AllocDesc));
+    if (e == hipSuccess) c->hdesc_cap = n;
     return e;
 }
 
@@ -596,6 +611,14 @@ static hipError_t ensure_copy_streams(ckpt_ctx* c, uint32_t n) {
     return hipSuccess;
 }
 
+static hipError_t ensure_side_streams(ckpt_ctx* c) {
+    for (hipStream_t* s : {&c->s_aux, &c->s_meta}) {
+        hipError_t e = *s ? hipSuccess : hipStreamCreateWithFlags(s, hipStreamNonBlocking);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 extern "C" int ckpt_ctx_create(int device, uint64_t staging_budget, ckpt_ctx** out) {
     if (!out) return CKPT_EINVAL;
     *out = nullptr;
@@ -616,6 +639,7 @@ extern "C" int ckpt_ctx_create(int device, uint64_t staging_budget, ckpt_ctx** o
     if (e == hipSuccess) e = ensure_events(c, 16);
     if (e == hipSuccess) e = ensure_tevents(c, 4 * kCodecPieces);
     if (e == hipSuccess) e = ensure_hsmall(c, 256 << 10);   // read-backs of up to ~32k windows
+    if (e == hipSuccess) e = ensure_hdesc(c, kNaMaxAllocs);
     for (int i = 0; i < 8 && e == hipSuccess; ++i) e = hipEventCreate(&c->sev[i]);
     if (e == hipSuccess) e = na_setup(device);
     c->hconsts = new EngineConsts();
@@ -642,7 +666,7 @@ extern "C" void ckpt_ctx_destroy(ckpt_ctx* c) {
     for (hipEvent_t e : c->tevents) hipEventDestroy(e);
     c->status.release();
     DevBuf* bufs[] = {&c->descs, &c->ctl, &c->arc, &c->kinds, &c->prevcrc, &c->off, &c->wb,
-                      &c->staging, &c->dig, &c->amap, &c->rlen, &c->cmeta};
+                      &c->staging, &c->dig, &c->amap, &c->rlen, &c->cmeta, &c->list};
     for (DevBuf* b : bufs) b->release();
     for (auto& kv : c->consts) kv.second.release();
     for (auto& kv : c->cconsts) kv.second.release();
@@ -655,6 +679,7 @@ extern "C" void ckpt_ctx_destroy(ckpt_ctx* c) {
     }
     if (c->hsmall) hipHostFree(c->hsmall);
     if (c->hpin) (void)hipHostFree(c->hpin);
+    if (c->hdesc) (void)hipHostFree(c->hdesc);
     for (hipStream_t s : {c->s_aux, c->s_meta})
         if (s) {
             (void)hipStreamSynchronize(s);
@@ -1272,8 +1297,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         if ((e = B.rlen->ensure(4 * nc)) != hipSuccess) return e;
         if ((e = B.cmeta->ensure((uint64_t)kPackMeta * nc)) != hipSuccess) return e;
         if ((e = ensure_hpin(c, 12 * nc)) != hipSuccess) return e;
-        if (!c->s_aux && (e = hipStreamCreateWithFlags(&c->s_aux, hipStreamNonBlocking)) != hipSuccess) return e;
-        if (!c->s_meta && (e = hipStreamCreateWithFlags(&c->s_meta, hipStreamNonBlocking)) != hipSuccess) return e;
+        if ((e = ensure_side_streams(c)) != hipSuccess) return e;
         uint64_t* off_h = reinterpret_cast<uint64_t*>(c->hpin);
         rlen_h = reinterpret_cast<uint32_t*>(c->hpin + 8 * nc);
         // the image at its upper bound (records never exceed their chunks)
@@ -1823,18 +1847,25 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     } else {
         wins = plan_windows(d, nc, C, slot, per_alloc);
     }
-    // A plain restore of at least kTailMinBytes held by one window runs as a
-    // launch over all chunks but the last 1/64 and a launch over those, both
-    // uploads on one copy stream: the long launch runs while the short tail
-    // is uploaded (the tail's upload ends before the long launch does, so the
-    // device never waits idle between the two).
     // Batched form: a full plain image held by one window restores as one
     // captured graph per table shape (restore_graph below); a delta, a codec
     // image, an on-demand or file-gated restore takes the launches below.
     const bool use_graph = o && (o->flags & CKPT_OPT_GRAPH) && !some && !gate && !codec && !per_alloc &&
                            !(v.flags & kFlagDelta) && nc > 0 && wins.size() == 1;
-    const bool tail = !use_graph && !per_alloc && !codec && !gate && !(o && o->window_bytes) && wins.size() == 1 &&
-                      nc >= 128 && nc * C >= kTailMinBytes;
+    // A pinned image is read by the restore kernels straight from host
+    // memory: no staging, no copies, no windows (but those of a file still
+    // being loaded and of the per-allocation form, a launch each). A few
+    // work-groups reach the link's rate (kLinkGrid), where a copy engine
+    // reached 57 or 30 GB/s depending on the engine the stream got.
+    const bool direct = img->pinned && !use_graph;
+    if (direct && !per_alloc && !gate && nc > 0) wins = {Window{0, nc}};
+    // A plain pageable image of at least kTailMinBytes held by one window
+    // runs as a launch over all chunks but the last 1/64 and a launch over
+    // those, both uploads on one copy stream: the long launch runs while the
+    // short tail is uploaded (the tail's upload ends before the long launch
+    // does, so the device never waits idle between the two).
+    const bool tail = !use_graph && !direct && !per_alloc && !codec && !gate && !(o && o->window_bytes) &&
+                      wins.size() == 1 && nc >= 128 && nc * C >= kTailMinBytes;
     const uint64_t g_tail = tail ? nc - nc / 64 : 0;
     if (tail) wins = {Window{0, g_tail}, Window{g_tail, nc}};
     const uint64_t W = wins.size();
@@ -1849,11 +1880,13 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     HIPCHK(c->off.ensure(8 * std::max<uint64_t>(nc, 1)));
     if (codec) HIPCHK(c->rlen.ensure(4 * std::max<uint64_t>(nc, 1)));
     HIPCHK(c->wb.ensure(8 * (W + 2)));
-    HIPCHK(c->staging.ensure((uint64_t)nslots * slot));
-    HIPCHK(c->status.ensure(8 * (ceil_div(nc, 256) + 64), c->s_main));
-    // ctl: ticket[1] | counts[4] u64 | bad u64 | bad2 u64 | err (+pad) | bad3 u64 | window tickets[W + 2]
+    if (!direct) HIPCHK(c->staging.ensure((uint64_t)nslots * slot));
+    const uint64_t tiles = ceil_div(nc, 256) + 64;   // look-back words of the offsets scan, twice
+    HIPCHK(c->status.ensure(16 * tiles, c->s_main));
+    // ctl: ticket[1] | counts[4] u64 | bad u64 | bad2 u64 | err (+pad) | bad3 u64 | bas u64 | bgate (+pad) |
+    // window tickets[W + 2]
     const uint64_t ctl_cnt = 64, ctl_bad = ctl_cnt + 32, ctl_bad2 = ctl_bad + 8, ctl_err = ctl_bad2 + 8,
-                   ctl_bad3 = ctl_err + 8, ctl_wtk = ctl_bad3 + 8;
+                   ctl_bad3 = ctl_err + 8, ctl_bas = ctl_bad3 + 8, ctl_wtk = ctl_bas + 16;
     HIPCHK(c->ctl.ensure(ctl_wtk + 4 * (W + 2) + 64));
     HIPCHK(ensure_hsmall(c, 8 * (W + 2) + 128));
     HIPCHK(ensure_events(c, std::max<size_t>(2 * W + (size_t)nslots + 2, ncs)));
@@ -1862,9 +1895,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     const EngineConsts* ec;
     HIPCHK(get_consts(c, T, C, &ec));
     uint8_t* ctl = c->ctl.as<uint8_t>();
-    // after the window tickets (in the buffer's 64-byte tail): a delta's base
-    // check result and the gate it sets for the restore launches
-    const uint64_t ctl_bas = (ctl_wtk + 4 * (W + 2) + 7) & ~7ull;
+    // a delta's base check result and the gate it sets for the restore launches
     unsigned long long* bas = reinterpret_cast<unsigned long long*>(ctl + ctl_bas);
     uint32_t* bgate = reinterpret_cast<uint32_t*>(ctl + ctl_bas + 8);
     uint32_t* ticket = reinterpret_cast<uint32_t*>(ctl);
@@ -2090,15 +2121,35 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     // 100 us; 27 GB in 412k chunks: 0.15 against 0.32 ms), and nothing below
     // waits for the device until the end.
     if (host_crc32c(v.recs, tl) != v.tables_crc) return CKPT_ECORRUPT;
-    std::vector<uint64_t> pre;   // codec: payload offset of every chunk
     std::vector<uint64_t> wbeg(W), wend(W);   // payload ranges of the windows
     uint64_t n_packed = 0, nz = 0, nd = 0, nu = 0, total = 0;
+    // payload offsets and numbers of DATA chunks before the ascending bounds:
+    // the windows', or where one launch restores everything a grid of kHeadGrid
+    // ranges, of which the first ones may be staged (below)
+    const bool whole = direct && !per_alloc && !gate && nc > 0;
+    std::vector<uint64_t> bounds;
+    if (whole) {
+        for (uint64_t i = 0; i <= kHeadGrid; ++i) bounds.push_back(nc * i / kHeadGrid);
+    } else {
+        for (const Window& w : wins) {   // in chunk order
+            bounds.push_back(w.g0);
+            bounds.push_back(w.g1);
+        }
+    }
+    std::vector<uint64_t> at(bounds.size()), rank(bounds.size());
     if (codec) {
-        pre.assign(nc + 1, 0);
+        size_t bi = 0;
+        auto mark = [&](uint64_t g) {
+            for (; bi < bounds.size() && bounds[bi] == g; ++bi) {
+                at[bi] = total;
+                rank[bi] = nd - n_packed;
+            }
+        };
         for (uint64_t a = 0; a < v.n_allocs; ++a) {
             const uint64_t nk = ceil_div(d[a].size, C);
             for (uint64_t k = 0; k < nk; ++k) {
                 const uint64_t gg = d[a].first + k;
+                mark(gg);
                 const uint64_t r = record_len(v, gg, k + 1 == nk ? d[a].tail_len : C);
                 if (r == kBadRecord) return CKPT_ECORRUPT;
                 const uint8_t kd = v.kinds[gg];
@@ -2106,30 +2157,21 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
                 nd += kd == kData || kd == kPacked;
                 nu += kd == kUnchanged;
                 n_packed += kd == kPacked;
-                pre[gg + 1] = pre[gg] + r;
+                total += r;
             }
         }
-        total = pre[nc];
-        for (uint64_t w = 0; w < W; ++w) {
-            wbeg[w] = pre[wins[w].g0];
-            wend[w] = pre[wins[w].g1];
-        }
+        mark(nc);
     } else {
-        std::vector<uint64_t> bounds(2 * W), at(2 * W);   // ascending: windows are in chunk order
-        for (uint64_t w = 0; w < W; ++w) {
-            bounds[2 * w] = wins[w].g0;
-            bounds[2 * w + 1] = wins[w].g1;
-        }
         uint64_t kn[4] = {0, 0, 0, 0};
-        total = scan_kinds(v, bounds, at.data(), kn);
+        total = scan_kinds(v, bounds, at.data(), rank.data(), kn);
         nz = kn[0];
         nd = kn[1];
         nu = kn[2];
         if (kn[3]) return CKPT_ECORRUPT;
-        for (uint64_t w = 0; w < W; ++w) {
-            wbeg[w] = at[2 * w];
-            wend[w] = at[2 * w + 1];
-        }
+    }
+    for (uint64_t w = 0; w < W; ++w) {
+        wbeg[w] = whole ? 0 : at[2 * w];
+        wend[w] = whole ? total : at[2 * w + 1];
     }
     if ((nu && !(v.flags & kFlagDelta)) || total != v.D) return CKPT_ECORRUPT;
     // PACKED records are decoded by kernels built for a range of chunk sizes
@@ -2150,26 +2192,63 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             if (table->v[a].id != d[a].id || table->v[a].size != d[a].size) return CKPT_EMISMATCH;
     }
 
-    // tables up, payload offsets
+    // Where the chunks are not all DATA, the device holds the kinds apart: DATA
+    // chunks are taken from a list, ZERO chunks filled by a kernel of their
+    // own. While the device reads the UNCHANGED chunks (a delta's base check)
+    // and fills the ZERO ones, a link copy brings the head of the payload to
+    // staging: as much as the link carries in that time (56 GB/s against 3.1
+    // and 4.8 TB/s). The rest is read directly.
+    const bool base_overlap = nu && !some && !codec;
+    const bool split = whole && (nz || nu || n_packed);
+    uint64_t hi = 0;   // ranges of the head
+    if (split) {
+        const uint64_t most = std::min(c->budget, (base_overlap ? nu * C / 56 : 0) + nz * C / 86);
+        while (hi < kHeadGrid && at[hi + 1] <= most) ++hi;
+        if (at[hi] < kMinHead) hi = 0;
+        HIPCHK(c->list.ensure(8 * nc));
+    }
+    const uint64_t head = at.empty() ? 0 : at[hi];
+    if (hi) {
+        HIPCHK(ensure_side_streams(c));
+        HIPCHK(c->staging.ensure(head));
+        HIPCHK(launch_link_copy(c->staging.p, v.payload, head, c->s_aux));
+        HIPCHK(hipEventRecord(c->events[0], c->s_aux));
+    }
+
+    // tables up, payload offsets, and the per-allocation check (the image's
+    // chunk digests combined against its allocation digests)
     HIPCHK(c->amap.ensure(4 * std::max<uint64_t>(nc, 1)));
-    HIPCHK(hipMemcpyAsync(c->descs.p, d.data(), sizeof(AllocDesc) * d.size(), hipMemcpyHostToDevice, c->s_main));
-    HIPCHK(launch_chunk_map(c->descs.as<AllocDesc>(), (uint32_t)d.size(), C, c->amap.as<uint32_t>(), c->s_main));
-    HIPCHK(hipMemcpyAsync(c->arc.p, v.recs, len_a, hipMemcpyHostToDevice, c->s_main));
-    HIPCHK(hipMemcpyAsync(kind_dev, v.kinds, len_b, hipMemcpyHostToDevice, c->s_main));
-    HIPCHK(launch_fill32(reinterpret_cast<uint32_t*>(ctl), 0, ctl_bad / 4, c->s_main));
-    HIPCHK(launch_fill64(reinterpret_cast<uint64_t*>(bad), ~0ull, 2, c->s_main));
-    HIPCHK(launch_fill32(err, 0, 2, c->s_main));
-    HIPCHK(launch_fill32(wtk, 0, W + 2, c->s_main));
-    HIPCHK(launch_fill64(reinterpret_cast<uint64_t*>(bad3), ~0ull, 1, c->s_main));
-    uint64_t* hq = reinterpret_cast<uint64_t*>(c->hsmall + 64);   // [4..7]: bad, bad2, err, bad3
-    if (codec && nc) {
-        HIPCHK(hipMemcpyAsync(c->off.p, pre.data(), 8 * nc, hipMemcpyHostToDevice, c->s_main));
-        HIPCHK(hipMemcpyAsync(c->rlen.p, v.rlens, 4 * nc, hipMemcpyHostToDevice, c->s_main));
-    } else if (nc) {
+    HIPCHK(ensure_hdesc(c, d.size()));
+    if (!d.empty()) memcpy(c->hdesc, d.data(), sizeof(AllocDesc) * d.size());
+    SetupJob sj;
+    memset(&sj, 0, sizeof(sj));
+    sj.src = c->hdesc;
+    sj.dst = c->descs.as<AllocDesc>();
+    sj.n_allocs = (uint32_t)d.size();
+    sj.C = C;
+    sj.map = c->amap.as<uint32_t>();
+    sj.add_fill(ctl, ctl_bad / 4, 0);
+    sj.add_fill(bad, 4, ~0u);    // bad, bad2
+    sj.add_fill(err, 2, 0);
+    sj.add_fill(bad3, 4, ~0u);   // bad3, bas
+    sj.add_fill(bgate, 2 + W + 2, 0);
+    if (img->pinned) {
+        sj.add_copy(c->arc.p, v.recs, len_a);
+        sj.add_copy(kind_dev, v.kinds, len_b);
+        if (codec) sj.add_copy(c->rlen.p, v.rlens, 4 * nc);
+    } else {
+        HIPCHK(hipMemcpyAsync(c->arc.p, v.recs, len_a, hipMemcpyHostToDevice, c->s_main));
+        HIPCHK(hipMemcpyAsync(kind_dev, v.kinds, len_b, hipMemcpyHostToDevice, c->s_main));
+        if (codec && nc) HIPCHK(hipMemcpyAsync(c->rlen.p, v.rlens, 4 * nc, hipMemcpyHostToDevice, c->s_main));
+    }
+    HIPCHK(launch_setup(sj, c->s_main));
+    uint64_t* hq = reinterpret_cast<uint64_t*>(c->hsmall + 64);   // [4..8]: bad, bad2, err, bad3, bas
+    OffJob oj;
+    memset(&oj, 0, sizeof(oj));
+    int off_grid = 0;
+    if (nc) {
         uint32_t ep;
         HIPCHK(c->status.next(c->s_main, &ep));
-        OffJob oj;
-        memset(&oj, 0, sizeof(oj));
         oj.allocs = c->descs.as<AllocDesc>();
         oj.n_allocs = v.n_allocs;
         oj.C = C;
@@ -2185,9 +2264,24 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         oj.counts = counts;
         oj.err = err;
         oj.epoch = ep;
-        const uint64_t tiles = ceil_div(nc, 256);
-        HIPCHK(launch_offsets(oj, (int)std::min<uint64_t>(tiles, 8ull * c->num_cu), c->s_main));
+        oj.rlen = codec ? c->rlen.as<uint32_t>() : nullptr;
+        oj.list = split ? c->list.as<uint64_t>() : nullptr;
+        oj.status2 = c->status.words() + tiles;
+        off_grid = (int)std::min<uint64_t>(ceil_div(nc, 256), 8ull * c->num_cu);
     }
+    CombineJob cj;
+    memset(&cj, 0, sizeof(cj));
+    cj.allocs = c->descs.as<AllocDesc>();
+    cj.n_allocs = (uint32_t)v.n_allocs;
+    cj.C = C;
+    cj.crc = crc_dev;
+    cj.ec = ec;
+    cj.recs = c->arc.as<uint8_t>();
+    cj.bad = bad2;
+    cj.mode = kCombineCheck;
+    if (timing) HIPCHK(hipEventRecord(c->sev[2], c->s_main));
+    HIPCHK(launch_offsets_combine(oj, off_grid, cj, c->s_main));
+    if (timing) HIPCHK(hipEventRecord(c->sev[3], c->s_main));
 
     // Verify-mode pass over the chunks being restored (all of them, or the
     // listed allocations' windows, up to kMaxJobs windows per launch): the
@@ -2212,6 +2306,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         hipError_t e;
         if (!some) {
             if ((e = grid_for(c, T, K, kModeVerify, nc, &grid)) != hipSuccess) return e;
+            if (hi) grid -= grid * kLinkCus / c->num_cu;   // the link copy's CUs take no other work
             return launch_chunks(T, K, kModeVerify, one_job(j, wtk + W), grid, c->s_main);
         }
         for (uint64_t w0 = 0; w0 < W; w0 += kMaxJobs) {
@@ -2240,9 +2335,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     // launches, so nothing is written unless it passed, and the result is
     // read with the others at the end); codec and on-demand restores wait
     // for the check first.
-    const bool base_overlap = nu && !some && !codec;
     if (nu && base_overlap) {
-        HIPCHK(launch_fill64(reinterpret_cast<uint64_t*>(bas), ~0ull, 1, c->s_main));
         if (timing) HIPCHK(hipEventRecord(c->tevents[2 * W], c->s_main));
         HIPCHK(verify_pass(0, bas));
         if (timing) HIPCHK(hipEventRecord(c->tevents[2 * W + 1], c->s_main));
@@ -2260,22 +2353,49 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     uint32_t* const rgate = base_overlap ? bgate : nullptr;
     const uint64_t t_based = now_ns();
 
-    // 3) windows: payload slice up, scatter + verify
+    // 3) scatter + verify; staged: window by window, payload slice up first
     std::vector<hipEvent_t>& ev = c->events;   // [0,W): copied; [W, W+nslots): slot free
     std::vector<bool> slot_used(nslots, false);
     const uint64_t t_link0 = now_ns();
     uint64_t moved_all = 0;
     for (uint64_t w = 0; w < W; ++w) moved_all += wend[w] - wbeg[w];
-    // On-demand restore whose payload fits the staging: the listed
-    // allocations' records go up in one copy per contiguous payload run (on
-    // the copy streams in turn), then the windows are restored by launches of
-    // up to kMaxJobs windows each.
-    const bool merged = some && W > 0 && moved_all <= (uint64_t)nslots * slot;
+    auto restore_job = [&](uint64_t w) {
+        ChunkJob j;
+        memset(&j, 0, sizeof(j));
+        j.allocs = c->descs.as<AllocDesc>();
+        j.n_allocs = (uint32_t)v.n_allocs;
+        j.C = C;
+        j.amap = c->amap.as<uint32_t>();
+        j.g0 = wins[w].g0;
+        j.g1 = wins[w].g1;
+        j.ec = ec;
+        j.kind_in = kind_dev;
+        j.ref_crc = crc_dev;
+        // read only: a restore's slot
+        j.slot = const_cast<uint8_t*>(v.payload);
+        j.off = c->off.as<uint64_t>();
+        j.bad = bad;
+        j.err = err;
+        j.gate = rgate;
+        return j;
+    };
+    // grids: a launch that reads host memory takes no more work-groups than
+    // the link can feed
+    auto restore_grid = [&](uint64_t chunks, int* grid) -> hipError_t {
+        hipError_t e = grid_for(c, T, K, kModeRestore, chunks, grid);
+        if (direct) *grid = std::min(*grid, kLinkGrid);
+        return e;
+    };
+    // On-demand restore whose payload fits the staging (or is read where it
+    // is): the listed allocations' records go up in one copy per contiguous
+    // payload run (on the copy streams in turn), then the windows are
+    // restored by launches of up to kMaxJobs windows each.
+    const bool merged = some && W > 0 && (direct || moved_all <= (uint64_t)nslots * slot);
     if (merged) {
         std::vector<uint64_t> sofs(W + 1, 0);
         for (uint64_t w = 0; w < W; ++w) sofs[w + 1] = sofs[w] + (wend[w] - wbeg[w]);
         uint64_t runs = 0;
-        for (uint64_t w = 0; w < W;) {
+        for (uint64_t w = 0; w < W && !direct;) {
             uint64_t e = w + 1;
             while (e < W && wend[e - 1] == wbeg[e]) ++e;
             const uint64_t len = wend[e - 1] - wbeg[w];
@@ -2297,21 +2417,11 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             uint64_t tot = 0;
             for (uint64_t w = l * kMaxJobs; w < std::min<uint64_t>(W, (l + 1) * kMaxJobs); ++w) {
                 ChunkJob& j = jl.job[jl.n_jobs];
-                j.allocs = c->descs.as<AllocDesc>();
-                j.n_allocs = (uint32_t)v.n_allocs;
-                j.C = C;
-                j.amap = c->amap.as<uint32_t>();
-                j.g0 = wins[w].g0;
-                j.g1 = wins[w].g1;
-                j.ec = ec;
-                j.kind_in = kind_dev;
-                j.ref_crc = crc_dev;
-                j.slot = c->staging.as<uint8_t>() + sofs[w];
-                j.off = c->off.as<uint64_t>();
-                j.slot_base = wbeg[w];
-                j.bad = bad;
-                j.err = err;
-                j.gate = rgate;
+                j = restore_job(w);
+                if (!direct) {
+                    j.slot = c->staging.as<uint8_t>() + sofs[w];
+                    j.slot_base = wbeg[w];
+                }
                 jl.prefix[jl.n_jobs] = tot;
                 tot += j.g1 - j.g0;
                 jl.n_jobs++;
@@ -2319,60 +2429,83 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             jl.prefix[jl.n_jobs] = tot;
             jl.ticket = wtk + l;
             int grid;
-            HIPCHK(grid_for(c, T, K, kModeRestore, tot, &grid));
+            HIPCHK(restore_grid(tot, &grid));
             if (timing) HIPCHK(hipEventRecord(c->tevents[2 * l], c->s_main));
             HIPCHK(launch_chunks(T, K, kModeRestore, jl, grid, c->s_main));
-            if (n_packed)
-                HIPCHK(launch_unpack(jl, c->rlen.as<uint32_t>(), cc, unpack_grid(c, tot), c->s_main));
+            if (n_packed) HIPCHK(launch_unpack(jl, c->rlen.as<uint32_t>(), cc, unpack_grid(c, tot), c->s_main));
             if (timing) HIPCHK(hipEventRecord(c->tevents[2 * l + 1], c->s_main));
         }
     }
-    for (uint64_t w = 0; w < W && !merged; ++w) {
+    if (split) {
+        ChunkJob j = restore_job(0);
+        if (timing) HIPCHK(hipEventRecord(c->tevents[0], c->s_main));
+        if (nz) {
+            const uint64_t wgs = 4ull * (c->num_cu - (hi ? kLinkCus : 0));
+            HIPCHK(launch_zero(j, (int)std::min<uint64_t>(nc, wgs), c->s_main));
+        }
+        // the head from staging, then the rest from host memory
+        for (int part = 0; part < 2; ++part) {
+            const uint64_t b = part ? hi : 0, e = part ? kHeadGrid : hi;
+            if (b == e) continue;
+            if (!part) {
+                HIPCHK(hipStreamWaitEvent(c->s_main, ev[0], 0));
+                j.slot = c->staging.as<uint8_t>();
+            } else {
+                j.slot = const_cast<uint8_t*>(v.payload);
+            }
+            ChunkJob jd = j;
+            jd.list = c->list.as<uint64_t>();
+            jd.g0 = rank[b];
+            jd.g1 = rank[e];
+            int grid;
+            if (jd.g1 > jd.g0) {
+                if (part) HIPCHK(restore_grid(jd.g1 - jd.g0, &grid));
+                else HIPCHK(grid_for(c, T, K, kModeRestore, jd.g1 - jd.g0, &grid));
+                HIPCHK(launch_chunks(T, K, kModeRestore, one_job(jd, wtk + part), grid, c->s_main));
+            }
+            j.g0 = bounds[b];
+            j.g1 = bounds[e];
+            if (n_packed) {
+                grid = unpack_grid(c, j.g1 - j.g0);
+                HIPCHK(launch_unpack(one_job(j, wtk + part), c->rlen.as<uint32_t>(), cc, grid, c->s_main));
+            }
+        }
+        if (timing) HIPCHK(hipEventRecord(c->tevents[1], c->s_main));
+    }
+    for (uint64_t w = 0; w < W && !merged && !split; ++w) {
         const int s = (int)(w % nslots);
         // a tail split keeps the payload where one window holds it. The
         // codec's windows go up one after another: two uploads at a time end
         // together, a window later than one at a time
         hipStream_t cs = c->s_copy[tail || (codec && !(o && o->copy_streams)) ? 0 : w % ncs];
-        uint8_t* sp = c->staging.as<uint8_t>() + (tail ? wbeg[w] : (uint64_t)s * slot);
-        if (slot_used[s] && !tail) HIPCHK(hipStreamWaitEvent(cs, ev[W + s], 0));
-        slot_used[s] = true;
         const uint64_t len = wend[w] - wbeg[w];
-        if (len > slot) return CKPT_ECORRUPT;
         if (gate && !gate->wait(kHeader + tl + wend[w])) {
             // the image's file could not be read: let queued work finish
             hipStreamSynchronize(c->s_main);
             for (uint32_t i = 0; i < ncs; ++i) hipStreamSynchronize(c->s_copy[i]);
             return CKPT_EIO;
         }
-        if (len) HIPCHK(hipMemcpyAsync(sp, v.payload + wbeg[w], len, hipMemcpyHostToDevice, cs));
-        HIPCHK(hipEventRecord(ev[w], cs));
-        HIPCHK(hipStreamWaitEvent(c->s_main, ev[w], 0));
-        ChunkJob j;
-        memset(&j, 0, sizeof(j));
-        j.allocs = c->descs.as<AllocDesc>();
-        j.n_allocs = (uint32_t)v.n_allocs;
-        j.C = C;
-        j.amap = c->amap.as<uint32_t>();
-        j.g0 = wins[w].g0;
-        j.g1 = wins[w].g1;
-        j.ec = ec;
-        j.kind_in = kind_dev;
-        j.ref_crc = crc_dev;
-        j.slot = sp;
-        j.off = c->off.as<uint64_t>();
-        j.slot_base = wbeg[w];
-        j.bad = bad;
-        j.err = err;
-        j.gate = rgate;
+        ChunkJob j = restore_job(w);
+        if (!direct) {
+            uint8_t* sp = c->staging.as<uint8_t>() + (tail ? wbeg[w] : (uint64_t)s * slot);
+            if (slot_used[s] && !tail) HIPCHK(hipStreamWaitEvent(cs, ev[W + s], 0));
+            slot_used[s] = true;
+            if (len > slot) return CKPT_ECORRUPT;
+            if (len) HIPCHK(hipMemcpyAsync(sp, v.payload + wbeg[w], len, hipMemcpyHostToDevice, cs));
+            HIPCHK(hipEventRecord(ev[w], cs));
+            HIPCHK(hipStreamWaitEvent(c->s_main, ev[w], 0));
+            j.slot = sp;
+            j.slot_base = wbeg[w];
+        }
         int grid;
-        HIPCHK(grid_for(c, T, K, kModeRestore, j.g1 - j.g0, &grid));
+        HIPCHK(restore_grid(j.g1 - j.g0, &grid));
         if (timing) HIPCHK(hipEventRecord(c->tevents[2 * w], c->s_main));
         const JobList jl = one_job(j, wtk + w);
         HIPCHK(launch_chunks(T, K, kModeRestore, jl, grid, c->s_main));
         if (n_packed)
             HIPCHK(launch_unpack(jl, c->rlen.as<uint32_t>(), cc, unpack_grid(c, j.g1 - j.g0), c->s_main));
         if (timing) HIPCHK(hipEventRecord(c->tevents[2 * w + 1], c->s_main));
-        HIPCHK(hipEventRecord(ev[W + s], c->s_main));
+        if (!direct) HIPCHK(hipEventRecord(ev[W + s], c->s_main));
     }
     // strict mode: every restored chunk re-read from HBM once all writes are
     // done, its CRC-32C checked again (the fused check ran on the data in
@@ -2383,21 +2516,8 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         HIPCHK(verify_pass(kJobVerifyAll, bad3));
         if (timing) HIPCHK(hipEventRecord(c->sev[1], c->s_main));
     }
-    // 4) whole-allocation CRCs
-    if (timing) HIPCHK(hipEventRecord(c->sev[2], c->s_main));
-    CombineJob cj;
-    memset(&cj, 0, sizeof(cj));
-    cj.allocs = c->descs.as<AllocDesc>();
-    cj.n_allocs = (uint32_t)v.n_allocs;
-    cj.C = C;
-    cj.crc = crc_dev;
-    cj.ec = ec;
-    cj.recs = c->arc.as<uint8_t>();
-    cj.bad = bad2;
-    cj.mode = kCombineCheck;
-    HIPCHK(launch_combine(cj, c->s_main));
-    if (timing) HIPCHK(hipEventRecord(c->sev[3], c->s_main));
-    HIPCHK(hipMemcpyAsync(hq + 4, bad, 32, hipMemcpyDeviceToHost, c->s_main));   // bad, bad2, err, bad3
+    // 4) the results
+    HIPCHK(launch_report(hq + 4, reinterpret_cast<uint64_t*>(bad), 5, c->s_main));
     HIPCHK(hipStreamSynchronize(c->s_main));
     for (uint32_t i = 0; i < ncs; ++i) HIPCHK(hipStreamSynchronize(c->s_copy[i]));
     const uint64_t t_link1 = now_ns();
@@ -2405,13 +2525,9 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         if (res) res->hip_error = (int32_t)hipErrorLaunchTimeOut;
         return CKPT_EHIP;
     }
-    if (base_overlap) {
-        uint64_t hbas = 0;
-        HIPCHK(hipMemcpy(&hbas, bas, 8, hipMemcpyDeviceToHost));
-        if (hbas != kNoChunk) {   // the restore launches were gated off: nothing was written
-            if (res) res->first_bad_chunk = hbas;
-            return CKPT_EBASE;
-        }
+    if (base_overlap && hq[8] != kNoChunk) {   // the restore launches were gated off: nothing was written
+        if (res) res->first_bad_chunk = hq[8];
+        return CKPT_EBASE;
     }
     if (res) {
         uint64_t moved = 0, logical = 0;

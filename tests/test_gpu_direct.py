@@ -1,0 +1,128 @@
+"""Paths that read or write a pinned image straight over the host link,
+against the staged paths that a pageable image takes (byte equality)."""
+import contextlib
+import os
+import sys
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+
+from paper_2502_16631_amd import mickpt as mk  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    c = mk.ckpt_ctx_create(0, 1 << 30)
+    yield c
+    mk.ckpt_ctx_destroy(c)
+
+
+@contextlib.contextmanager
+def pageable():
+    """Images made inside are in pageable memory."""
+    os.environ["MICKPT_HOST_PAGEABLE"] = "1"
+    try:
+        yield
+    finally:
+        del os.environ["MICKPT_HOST_PAGEABLE"]
+
+
+def state(c, seed, zero_mib):
+    """Allocations whose chunk counts straddle the tables' tiles (256 chunks)
+    and whose tails are ragged, a data allocation on each side of zero_mib
+    MiB of zeros; the values compress, so that the codec packs them."""
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    sizes = [255 * c + 5, 0, 256 * c, 257 * c + c - 1, 3, zero_mib << 20, 16, 100 * c + 16, 1]
+    out = []
+    for i, s in enumerate(sizes):
+        if s == zero_mib << 20:
+            t = torch.zeros(s, dtype=torch.uint8, device="cuda")
+        else:
+            t = torch.randint(0, 256, (s,), dtype=torch.uint8, device="cuda", generator=gen)
+            t[::2] &= 7
+            t[c:3 * c] = 0
+        out.append((100 + i, t))
+    return out
+
+
+def blank(table):
+    return [(i, torch.full_like(t, 0xA5)) for i, t in table]
+
+
+def same(a, b):
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for (_, x), (_, y) in zip(a, b))
+
+
+@pytest.mark.parametrize("c,zero_mib,flags", [(4096, 1, 0), (65536, 1, 0), (65536, 300, 0), (262144, 200, 0),
+                                              (16384, 200, mk.OPT_CODEC), (65536, 1, mk.OPT_CODEC),
+                                              (65536, 300, mk.OPT_CODEC)])
+def test_restores_from_pinned_and_pageable_images(ctx, c, zero_mib, flags):
+    """Full image and delta, with the payload's head staged beside the zero
+    fill (the larger zero_mib) and without, against the state; the damaged
+    base and the damaged payload are reported as by the staged path."""
+    opts = mk.make_opts(chunk_size=c, flags=flags)
+    base = state(c, 7, zero_mib)
+    new = [(i, t.clone()) for i, t in base]
+    for _, t in new[2:4] + new[5:6]:
+        t[c:2 * c] = 9
+        t[-3:] = 1
+    bad_base = [(i, t.clone()) for i, t in base]
+    bad_base[3][1][200 * c] ^= 1
+    got = []
+    for where in (contextlib.nullcontext, pageable):
+        with where():
+            rc, img, _ = mk.ckpt_dump(ctx, base, opts=opts)
+            assert rc == 0
+            rc, delta, _ = mk.ckpt_dump(ctx, new, prev=img, opts=opts)
+            assert rc == 0
+        to = blank(base)
+        rc, res = mk.ckpt_restore(ctx, img, to, opts=mk.make_opts(strict_verify=1))
+        assert rc == 0
+        same(to, base)
+        counts = [res.n_zero, res.n_data, res.n_unchanged, res.n_packed]
+        rc, res = mk.ckpt_restore(ctx, delta, to)
+        assert rc == 0
+        same(to, new)
+        counts += [res.n_zero, res.n_data, res.n_unchanged, res.n_packed]
+        keep = [(i, t.clone()) for i, t in bad_base]
+        rc, res = mk.ckpt_restore(ctx, delta, keep)
+        assert rc == mk.CKPT_EBASE
+        same(keep, bad_base)   # nothing was written
+        counts.append(res.first_bad_chunk)
+        v = img.view()
+        v[v.size - 40 * c] ^= 0x10
+        rc, res = mk.ckpt_restore(ctx, img, to)
+        assert rc == mk.CKPT_ECORRUPT
+        v[v.size - 40 * c] ^= 0x10
+        got.append((counts, res.first_bad_chunk, img.tobytes(), delta.tobytes()))
+    assert got[0] == got[1]
+
+
+def test_a_reused_image_buffer_is_read_anew(ctx):
+    """Images of one size follow each other in one pinned buffer: a restore
+    reads what the host memory holds now."""
+    c = 65536
+    for seed in range(4):
+        table = state(c, 20 + seed, 1)
+        rc, img, _ = mk.ckpt_dump(ctx, table, opts=mk.make_opts(chunk_size=c))
+        assert rc == 0
+        data = img.tobytes()
+        img.free()
+        rc, imp = mk.ckpt_image_import(np.frombuffer(data, np.uint8))   # written by the host
+        assert rc == 0
+        to = blank(table)
+        assert mk.ckpt_restore(ctx, imp, to)[0] == 0
+        same(to, table)
+        rc, _ = mk.ckpt_restore_some(ctx, imp, [(i, t) for i, t in blank(table)[2:4]])
+        assert rc == 0
+        imp.free()
