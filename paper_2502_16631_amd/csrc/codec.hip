@@ -400,6 +400,7 @@ __global__ void __launch_bounds__(NT) k_unpack(JobList jl, const uint32_t* rlen,
     __shared__ unsigned long long s_w[2 * NW];
     __shared__ uint32_t s_red[NW];
     const int tid = threadIdx.x;
+    if (blockIdx.x == 0 && tid == 0 && jl.job[0].stamp) *jl.job[0].stamp = wall_clock64();
     for (int i = tid; i < 16 * 256; i += NT) s_tab[i] = cc->tab[i];
     const uint32_t lanec = cc->lane[tid], full_init = cc->full_init;
     const uint32_t C = jl.job[0].C, L = C / 8;

@@ -34,10 +34,14 @@ struct ChunkJob {
     uint32_t epoch;              // look-back epoch of this launch (1 .. 2^22-1)
     uint32_t flags;              // kJob*
     const uint32_t* gate;        // restore / verify: when set and 0 at launch, the launch does nothing
+    uint64_t* stamp;             // (of a launch's first job) device clock at the kernel's start, or nullptr
 };
 // verify mode: check every chunk of the range whatever its kind (the strict
 // re-read after a restore), not only UNCHANGED ones
 constexpr uint32_t kJobVerifyAll = 1;
+// dump mode: slot is pinned host memory (plain stores in place of
+// non-temporal ones, which carry 48 instead of 56 GB/s over the link)
+constexpr uint32_t kJobHostSlot = 2;
 
 // Several jobs in one persistent launch (continuous batching): the jobs'
 // chunk ranges are laid end to end in one ticket space; every job keeps its
@@ -91,6 +95,7 @@ struct CombineJob {
     unsigned long long* bad;     // check mode
     int mode;
     int pad;
+    uint64_t* stamp;             // device clock at the kernel's start, or nullptr
 };
 
 // What a call needs on the device before its chunk kernels, in one launch:
@@ -99,6 +104,7 @@ struct CombineJob {
 // are whole, aligned 32-bit words.
 struct SetupJob {
     static constexpr int kMaxFills = 8, kMaxCopies = 4;
+    uint64_t* stamp;             // device clock at the kernel's start, or nullptr (must not be filled here)
     const AllocDesc* src;        // pinned host descriptors
     AllocDesc* dst;              // device descriptors
     uint32_t n_allocs;
@@ -108,6 +114,22 @@ struct SetupJob {
     struct Fill { uint32_t* p; uint64_t n; uint32_t v; uint32_t pad; } fill[kMaxFills];
     struct Copy { uint32_t* dst; const uint32_t* src; uint64_t n; } copy[kMaxCopies];
     void add_fill(void* p, uint64_t words, uint32_t v) { fill[n_fills++] = {static_cast<uint32_t*>(p), words, v, 0}; }
+    void add_copy(void* d, const void* s, uint64_t bytes) {
+        copy[n_copies++] = {static_cast<uint32_t*>(d), static_cast<const uint32_t*>(s), bytes / 4};
+    }
+};
+
+// The end of a dump in one launch: the per-allocation combine (write mode,
+// one work-group each), table words to the host image, and result words of
+// earlier kernels to pinned host memory.
+struct FinishJob {
+    CombineJob c;
+    int n_copies;
+    uint32_t n_rep;              // 64-bit result words, <= 62; rep[n_rep] and [n_rep + 1] take the device
+                                 // clock at the kernel's start and end
+    SetupJob::Copy copy[4];
+    uint64_t* rep;
+    const uint64_t* rep_src;
     void add_copy(void* d, const void* s, uint64_t bytes) {
         copy[n_copies++] = {static_cast<uint32_t*>(d), static_cast<const uint32_t*>(s), bytes / 4};
     }
@@ -130,8 +152,10 @@ struct GateJob {
 
 bool tile_supported(int T, int K);
 hipError_t launch_setup(const SetupJob& job, hipStream_t s);
-// n <= 64 64-bit device words to pinned host memory.
-hipError_t launch_report(uint64_t* host, const uint64_t* dev, uint32_t n, hipStream_t s);
+hipError_t launch_finish(const FinishJob& job, hipStream_t s);
+// n <= 63 64-bit device words to pinned host memory; with clock, host[n]
+// takes the device clock.
+hipError_t launch_report(uint64_t* host, const uint64_t* dev, uint32_t n, bool clock, hipStream_t s);
 hipError_t launch_gate(const GateJob& job, hipStream_t s);
 hipError_t launch_chunks(int T, int K, int mode, const JobList& jl, int grid, hipStream_t s);
 hipError_t chunks_occupancy(int T, int K, int mode, int* blocks_per_cu);

@@ -46,6 +46,12 @@ __device__ inline uint64_t ld_relaxed(uint64_t* p) {
     return __hip_atomic_load((gu64*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The device clock (constant rate) where a call's stages begin: an event
+// record per stage costs the queue a packet each, 15-30 us of a short call.
+__device__ inline void stamp(uint64_t* p) {
+    if (p && blockIdx.x == 0 && threadIdx.x == 0) *p = wall_clock64();
+}
+
 __device__ inline uint64_t wave_sum_u64(uint64_t v) {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
@@ -373,6 +379,7 @@ k_chunks(JobList jl) {
 
     const int tid = threadIdx.x;
     const bool active = T >= 64 || tid < T;
+    stamp(jl.job[0].stamp);
     // a restore that its graph's validation rejected writes nothing
     if constexpr (MODE == kModeRestore || MODE == kModeVerify)
         if (jl.job[0].gate && *jl.job[0].gate == 0) return;
@@ -673,6 +680,7 @@ k_dump_stream(JobList jl) {
 
     const int tid = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
+    stamp(jl.job[0].stamp);
     const EngineConsts* ec = jl.job[0].ec;
     for (int i = tid; i < 16 * 256; i += T) s_dt[i] = ec->dt[i];
     const uint32_t lanec = ec->lane[tid];
@@ -827,7 +835,10 @@ k_dump_stream(JobList jl) {
             lds_barrier();
             const uint64_t excl = s_off;
             if (kd == kData) {
-                if (full) store_rows_padded<T, K, true>(v, job.slot + excl, C, ltid, true);
+                // (host slot: the stores before the digest took 56 instead of
+                // 36 us for 16 chunks, the ticket's return queues behind them)
+                if (job.flags & kJobHostSlot) store_rows_padded<T, K>(v, job.slot + excl, len16, ltid, true);
+                else if (full) store_rows_padded<T, K, true>(v, job.slot + excl, C, ltid, true);
                 else store_rows_padded<T, K, true>(v, job.slot + excl, len16, ltid, true);
             }
             if (g + 1 == job.g1 && tid == 0) *job.wtotal = excl + plen;
@@ -936,6 +947,7 @@ __device__ inline uint32_t xpow8(uint64_t n, const uint32_t* x2n) {   // x^(8n)
 __device__ inline void combine_wg(const CombineJob& job, uint32_t a) {
     __shared__ uint32_t s_red[4];
     __shared__ uint32_t s_x2n[64];
+    __shared__ uint32_t s_mul[4 * 256];
     const int tid = threadIdx.x;
     if (tid < 64) s_x2n[tid] = job.ec->x2n[tid];
     __syncthreads();
@@ -944,27 +956,40 @@ __device__ inline void combine_wg(const CombineJob& job, uint32_t a) {
     const uint64_t nk = (ad.size + C - 1) / C;
     const uint64_t m = (nk + 255) / 256;
     const uint64_t k0 = (uint64_t)tid * m, k1 = k0 + m < nk ? k0 + m : nk;
-    uint32_t contrib = 0;
-    if (k0 < k1) {
-        const uint32_t full_x = job.ec->full_x;
-        uint32_t acc = 0;
+    const uint32_t full_x = job.ec->full_x;
+    uint32_t contrib = 0, acc = 0;
+    if (m >= 8) {
+        // a lane's chain of m products by one constant, each waiting for the
+        // one before: by table (the product is linear in each byte), four
+        // lookups in place of the multiply's 157 instructions. The table costs
+        // four multiplies per lane (a 1 GiB allocation in 64 KiB chunks, m =
+        // 64: 22 -> 9 us)
+        for (int b = 0; b < 4; ++b) s_mul[b * 256 + tid] = gf_mul_v((uint32_t)tid << (8 * b), full_x);
+        __syncthreads();
         for (uint64_t k = k0; k < k1; ++k) {
-            const uint32_t xk = (k + 1 == nk) ? ad.tail_x : full_x;
-            acc = gf_mul_v(acc, xk) ^ job.crc[ad.first + k];
+            acc = k + 1 == nk ? gf_mul_v(acc, ad.tail_x)
+                              : xor3(s_mul[acc & 255], s_mul[256 + ((acc >> 8) & 255)], s_mul[512 + ((acc >> 16) & 255)]) ^
+                                    s_mul[768 + (acc >> 24)];
+            acc ^= job.crc[ad.first + k];
         }
+    } else {
+        for (uint64_t k = k0; k < k1; ++k) acc = gf_mul_v(acc, k + 1 == nk ? ad.tail_x : full_x) ^ job.crc[ad.first + k];
+    }
+    if (k0 < k1) {
         const uint64_t end = k1 == nk ? ad.size : k1 * C;
         contrib = gf_mul_v(acc, xpow8(ad.size - end, s_x2n));
     }
     const uint32_t crc = wg_xor<4>(contrib, s_red);
-    if (tid == 0) {
-        if (job.mode == kCombineWrite) {
-            uint8_t* rec = job.recs + 32ull * a;
-            reinterpret_cast<uint64_t*>(rec)[0] = ad.id;
-            reinterpret_cast<uint64_t*>(rec)[1] = ad.size;
-            reinterpret_cast<uint64_t*>(rec)[2] = ad.first;
-            reinterpret_cast<uint32_t*>(rec)[6] = crc;
-            reinterpret_cast<uint32_t*>(rec)[7] = 0;
-        } else if (job.mode == kCombineCheck) {
+    if (job.mode == kCombineWrite) {
+        // one 32-byte store: the records may lie in host memory
+        const uint32_t w[8] = {(uint32_t)ad.id, (uint32_t)(ad.id >> 32), (uint32_t)ad.size, (uint32_t)(ad.size >> 32),
+                               (uint32_t)ad.first, (uint32_t)(ad.first >> 32), crc, 0};
+        uint32_t x = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x = tid == i ? w[i] : x;
+        if (tid < 8) reinterpret_cast<uint32_t*>(job.recs + 32ull * a)[tid] = x;
+    } else if (tid == 0) {
+        if (job.mode == kCombineCheck) {
             const uint32_t want = reinterpret_cast<const uint32_t*>(job.recs + 32ull * a)[6];
             if (want != crc) atomicMin(job.bad, (unsigned long long)ad.first);
         } else {
@@ -979,6 +1004,7 @@ __global__ void __launch_bounds__(256) k_combine(CombineJob job) { combine_wg(jo
 // but the tables and nothing of each other: one launch (the first n_off
 // work-groups scan, one more per allocation combines) in place of two.
 __global__ void __launch_bounds__(256) k_offsets_combine(OffJob off, CombineJob job, uint32_t n_off) {
+    stamp(job.stamp);
     if (blockIdx.x < n_off) offsets_wg(off);
     else combine_wg(job, blockIdx.x - n_off);
 }
@@ -988,6 +1014,7 @@ __global__ void __launch_bounds__(256) k_offsets_combine(OffJob off, CombineJob 
 // the link's reads. Bound by HBM writes; grid-stride, since a chunk of
 // another kind costs one uniform byte load.
 __global__ void __launch_bounds__(256) k_zero(ChunkJob j) {
+    stamp(j.stamp);
     if (j.gate && *j.gate == 0) return;
     const uint32_t tid = threadIdx.x, C = j.C;
     for (uint64_t g = j.g0 + blockIdx.x; g < j.g1; g += gridDim.x) {
@@ -1035,23 +1062,26 @@ __global__ void __launch_bounds__(256) k_chunk_map(const AllocDesc* allocs, uint
     }
 }
 
+// Words of c, one grid-stride part: lane t of `step` lanes.
+__device__ inline void copy_words(const SetupJob::Copy& c, uint64_t t, uint64_t step) {
+    if (((reinterpret_cast<uint64_t>(c.src) | reinterpret_cast<uint64_t>(c.dst)) & 15) == 0) {
+        const uint64_t n4 = c.n / 4;
+        for (uint64_t w = t; w < n4; w += step) ((gv4*)c.dst)[w] = ((gcv4*)c.src)[w];
+        for (uint64_t w = 4 * n4 + t; w < c.n; w += step) c.dst[w] = c.src[w];
+    } else {
+        for (uint64_t w = t; w < c.n; w += step) c.dst[w] = c.src[w];
+    }
+}
+
 // Set-up of a call (SetupJob). Latency-bound: a few kilobytes for a small
 // table, whose eight launches and uploads took 40-80 us one after another;
 // one launch reads pinned host memory itself (the link's latency once) and
 // takes 6 us. Large tables: 2 MB of image tables at the link's rate, spread
 // over the whole grid. Each part is a grid-stride loop of its own.
 __global__ void __launch_bounds__(256) k_setup(SetupJob j) {
+    stamp(j.stamp);
     const uint64_t t = blockIdx.x * 256ull + threadIdx.x, step = gridDim.x * 256ull;
-    for (int i = 0; i < j.n_copies; ++i) {
-        const SetupJob::Copy c = j.copy[i];
-        if (((reinterpret_cast<uint64_t>(c.src) | reinterpret_cast<uint64_t>(c.dst)) & 15) == 0) {
-            const uint64_t n4 = c.n / 4;
-            for (uint64_t w = t; w < n4; w += step) ((gv4*)c.dst)[w] = ((gcv4*)c.src)[w];
-            for (uint64_t w = 4 * n4 + t; w < c.n; w += step) c.dst[w] = c.src[w];
-        } else {
-            for (uint64_t w = t; w < c.n; w += step) c.dst[w] = c.src[w];
-        }
-    }
+    for (int i = 0; i < j.n_copies; ++i) copy_words(j.copy[i], t, step);
     for (int i = 0; i < j.n_fills; ++i) {
         const SetupJob::Fill f = j.fill[i];
         for (uint64_t w = t; w < f.n; w += step) f.p[w] = f.v;
@@ -1064,10 +1094,32 @@ __global__ void __launch_bounds__(256) k_setup(SetupJob j) {
     }
 }
 
+// The end of a dump (FinishJob). Latency-bound for a small table (combine,
+// table digests, five copies and their waits took 50-90 us; this one launch
+// 12); for a large one the tables go out at the link's rate beside the
+// payload instead of behind it on a copy engine.
+__global__ void __launch_bounds__(256) k_finish(FinishJob j) {
+    const uint64_t t0 = wall_clock64();
+    if (blockIdx.x < j.c.n_allocs) {
+        combine_wg(j.c, blockIdx.x);
+    } else {
+        const uint64_t t = (blockIdx.x - j.c.n_allocs) * 256ull + threadIdx.x;
+        const uint64_t step = (gridDim.x - j.c.n_allocs) * 256ull;
+        for (int i = 0; i < j.n_copies; ++i) copy_words(j.copy[i], t, step);
+    }
+    if (blockIdx.x + 1 == gridDim.x && j.rep && threadIdx.x < j.n_rep + 2) {
+        const uint32_t i = threadIdx.x;
+        const uint64_t w = i < j.n_rep ? j.rep_src[i] : i == j.n_rep ? t0 : wall_clock64();
+        __hip_atomic_store((gu64*)&j.rep[i], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
 // Results of a call to pinned host memory: a one-wave launch in place of a
 // copy, which queues behind the payload on a copy engine.
-__global__ void k_report(uint64_t* host, const uint64_t* dev, uint32_t n) {
-    if (threadIdx.x < n) __hip_atomic_store((gu64*)&host[threadIdx.x], dev[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+__global__ void k_report(uint64_t* host, const uint64_t* dev, uint32_t n, bool clock) {
+    const uint32_t t = threadIdx.x;
+    if (t < n || (clock && t == n))
+        __hip_atomic_store((gu64*)&host[t], t < n ? dev[t] : wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Two descriptors passed by value (kernel arguments are captured at launch,
@@ -1197,9 +1249,18 @@ hipError_t launch_setup(const SetupJob& j, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_report(uint64_t* host, const uint64_t* dev, uint32_t n, hipStream_t s) {
-    if (n > 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, host, dev, n);
+hipError_t launch_finish(const FinishJob& j, hipStream_t s) {
+    if (j.n_copies > 4 || j.n_rep > 62 || j.c.mode != kCombineWrite) return hipErrorInvalidValue;
+    uint64_t words = 0;
+    for (int i = 0; i < j.n_copies; ++i) words = words > j.copy[i].n ? words : j.copy[i].n;
+    const uint64_t blocks = j.c.n_allocs + (words == 0 ? 1 : words < 256 * 1024 ? (words + 1023) / 1024 : 256);
+    hipLaunchKernelGGL(k_finish, dim3((unsigned)blocks), dim3(256), 0, s, j);
+    return hipGetLastError();
+}
+
+hipError_t launch_report(uint64_t* host, const uint64_t* dev, uint32_t n, bool clock, hipStream_t s) {
+    if (n > 63) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, host, dev, n, clock);
     return hipGetLastError();
 }
 

@@ -186,6 +186,7 @@ struct ckpt_ctx {
     uint64_t budget = 0;
     size_t digest_capacity = 8;                           // resident digest tables kept
     int num_cu = 0;
+    int wall_khz = 100000;                                // rate of the device clock (wall_clock64)
     hipStream_t s_main = nullptr;
     std::vector<hipStream_t> s_copy;
     std::mutex mu;
@@ -227,6 +228,9 @@ constexpr uint64_t kTailMinBytes = 512ull << 20;
 // Work-groups of a restore launch that reads a pinned image over the host
 // link (512 threads, 64 KiB in flight each).
 constexpr int kLinkGrid = 64;
+// A full dump of at most this many bytes in one launch writes its payload
+// straight into a pinned image.
+constexpr uint64_t kDirectDump = 64ull << 20;
 // The ranges a restore may stage the first ones of, and the least payload
 // worth it.
 constexpr uint64_t kHeadGrid = 64;
@@ -269,9 +273,7 @@ constexpr uint64_t kNaTables = na_round(32ull * kNaMaxAllocs + 5 * kNaMaxChunks 
 constexpr uint64_t kNaStatus = 0;
 constexpr uint64_t kNaCtl = kNaStatus + 8 * kNaStatusWords;
 constexpr uint64_t kNaConsts = kNaCtl + (64 << 10);          // chunk engine constants (T, C)
-constexpr uint64_t kNaDConsts = kNaConsts + (32 << 10);      // table-digest engine constants
-constexpr uint64_t kNaDig = kNaDConsts + (32 << 10);
-constexpr uint64_t kNaDescs = kNaDig + (64 << 10);
+constexpr uint64_t kNaDescs = kNaConsts + (32 << 10);
 constexpr uint64_t kNaAmap = kNaDescs + 64ull * kNaMaxAllocs;
 constexpr uint64_t kNaArc = kNaAmap + 4 * kNaMaxChunks;
 constexpr uint64_t kNaKinds = kNaArc + kNaTables;
@@ -291,7 +293,6 @@ struct NaDevice {
     bool cleared = false;
     int T = 0;
     uint32_t C = 0;
-    bool dconsts = false;
 };
 
 // A fixed-buffer dump: the caller's host buffer and the device's array
@@ -326,6 +327,11 @@ void make_desc(AllocDesc* d, uint64_t id, const void* ptr, uint64_t size, uint64
                uint32_t C);
 JobList one_job(const ChunkJob& j, uint32_t* ticket);
 void digest_insert(ckpt_ctx* c, uint64_t uid, const uint32_t* crc_dev, uint64_t nc, hipStream_t s);
+// Room for the resident digest table of image uid, to be filled on a stream
+// before the table is used; nullptr when none is kept. digest_drop forgets a
+// table (its work queued or done).
+uint32_t* digest_reserve(ckpt_ctx* c, uint64_t uid, uint64_t nc);
+void digest_drop(ckpt_ctx* c, uint64_t uid);
 // The resident digest table of image uid (nc chunks), or nullptr. With pin
 // the entry is pinned until digest_unpin: it stays resident while a request
 // that outlives this call reads it.

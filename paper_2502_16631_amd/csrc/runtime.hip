@@ -498,6 +498,11 @@ uint64_t span_ns(hipEvent_t a, hipEvent_t b) {
     return (uint64_t)((double)ms * 1e6);
 }
 
+// Time between two stamps of the device clock, in ns; 0 if either is missing.
+uint64_t stamp_ns(const ckpt_ctx* c, uint64_t a, uint64_t b) {
+    return a && b > a ? (b - a) * 1000000ull / (uint64_t)c->wall_khz : 0;
+}
+
 hipError_t ensure_events(ckpt_ctx* c, size_t n) {
     while (c->events.size() < n) {
         hipEvent_t e;
@@ -566,7 +571,13 @@ void fill_result(ckpt_result* res) {
 }
 
 // Make the context's main stream wait for prior work on the caller's stream.
+// When that has none pending (the query of the null stream covers the
+// blocking streams as well) there is nothing to wait for: a query takes
+// 0.1 us, the event and the wait 10-30.
 hipError_t order_after(ckpt_ctx* c, void* stream) {
+    const hipError_t q = hipStreamQuery(static_cast<hipStream_t>(stream));
+    if (q != hipErrorNotReady) return q;
+    (void)hipGetLastError();   // not ready: no failure
     hipError_t e = hipEventRecord(c->ev_order, static_cast<hipStream_t>(stream));
     if (e == hipSuccess) e = hipStreamWaitEvent(c->s_main, c->ev_order, 0);
     return e;
@@ -631,6 +642,10 @@ extern "C" int ckpt_ctx_create(int device, uint64_t staging_budget, ckpt_ctx** o
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) != hipSuccess) { delete c; return CKPT_EHIP; }
     c->num_cu = prop.multiProcessorCount;
+    if (hipDeviceGetAttribute(&c->wall_khz, hipDeviceAttributeWallClockRate, device) != hipSuccess || c->wall_khz <= 0) {
+        (void)hipGetLastError();
+        c->wall_khz = 100000;
+    }
     // Set-up: streams, events, pinned scratch and the device's static array
     // are made here once, so that a no-allocation dump makes none of them.
     hipError_t e = hipStreamCreateWithFlags(&c->s_main, hipStreamNonBlocking);
@@ -750,15 +765,6 @@ hipError_t mk::digest_enqueue(ckpt_ctx* c, const DigestPlan& p, uint32_t* out_ho
     return hipMemcpyAsync(out_host, base + p.off_out, 8, hipMemcpyDeviceToHost, s);
 }
 
-static int device_table_digests(ckpt_ctx* c, const uint8_t* recs_crc, uint64_t len_a, const uint8_t* kinds_pad,
-                                uint64_t len_b, uint32_t* out_host /* [2], pinned */, ckpt_result* res,
-                                DevBuf* dig = nullptr, const EngineConsts* ec = nullptr) {
-    DigestPlan p;
-    HIPCHK(digest_prepare(c, dig ? dig : &c->dig, recs_crc, len_a, kinds_pad, len_b, &p, c->s_main, ec));
-    HIPCHK(digest_enqueue(c, p, out_host, c->s_main));
-    return CKPT_OK;
-}
-
 // ------------------------------------------------------------ resident digest tables
 const uint32_t* mk::digest_lookup(ckpt_ctx* c, uint64_t uid, uint64_t nc, bool pin) {
     auto it = c->digests.find(uid);
@@ -773,23 +779,23 @@ void mk::digest_unpin(ckpt_ctx* c, uint64_t uid) {
     if (it != c->digests.end() && it->second.pins) it->second.pins--;
 }
 
-// Keep an image's digest table resident (copied from crc_dev on stream s;
-// the caller synchronizes s before the table is used).
-void mk::digest_insert(ckpt_ctx* c, uint64_t uid, const uint32_t* crc_dev, uint64_t nc, hipStream_t s) {
-    if (!nc) return;
-    if (c->digests.count(uid)) return;   // an image is dumped once; its table never changes
+// Room to keep an image's digest table resident.
+uint32_t* mk::digest_reserve(ckpt_ctx* c, uint64_t uid, uint64_t nc) {
+    if (!nc) return nullptr;
+    if (c->digests.count(uid)) return nullptr;   // an image is dumped once; its table never changes
     // An evicted table's buffer takes the new table when it is large enough:
     // freeing device memory waits for all work on the device, which in the
     // served loop would stall every request in flight. Buffers are sized in
     // powers of two, so that more of them fit a later table. (No launch still
-    // reads a victim: tables read by requests in flight are pinned, and a
-    // plain dump has finished before its call returns.)
+    // reads a victim: tables read by requests in flight are pinned, a dump
+    // under way reserves its table after the one it reads was looked up, and
+    // a plain dump has finished before its call returns.)
     DevBuf spare;
     if (c->digests.size() >= c->digest_capacity) {
         // tables pinned by requests in flight are never evicted; with every
         // entry pinned the new table is not kept
         const uint64_t victim = digest_victim(c->digests, 0);
-        if (!victim) return;
+        if (!victim) return nullptr;
         spare = c->digests[victim].crc;
         c->digests.erase(victim);
     }
@@ -800,14 +806,47 @@ void mk::digest_insert(ckpt_ctx* c, uint64_t uid, const uint32_t* crc_dev, uint6
         de.crc = spare;
     else
         spare.release();
-    if (de.crc.ensure(de.crc.p ? 4 * nc : want) == hipSuccess &&
-        hipMemcpyAsync(de.crc.p, crc_dev, 4 * nc, hipMemcpyDeviceToDevice, s) == hipSuccess) {
-        de.n_chunks = nc;
-        de.last_use = ++c->use_clock;
-    } else {
-        de.crc.release();
-        c->digests.erase(uid);
+    if (de.crc.ensure(de.crc.p ? 4 * nc : want) != hipSuccess) {
+        digest_drop(c, uid);
+        return nullptr;
     }
+    de.n_chunks = nc;
+    de.last_use = ++c->use_clock;
+    return de.crc.as<uint32_t>();
+}
+
+void mk::digest_drop(ckpt_ctx* c, uint64_t uid) {
+    auto it = c->digests.find(uid);
+    if (it == c->digests.end()) return;
+    it->second.crc.release();
+    c->digests.erase(it);
+}
+
+// Keep an image's digest table resident (copied from crc_dev on stream s;
+// the caller synchronizes s before the table is used).
+void mk::digest_insert(ckpt_ctx* c, uint64_t uid, const uint32_t* crc_dev, uint64_t nc, hipStream_t s) {
+    uint32_t* to = digest_reserve(c, uid, nc);
+    if (to && hipMemcpyAsync(to, crc_dev, 4 * nc, hipMemcpyDeviceToDevice, s) != hipSuccess) digest_drop(c, uid);
+}
+
+// Whether [p, p + n) lies in one pinned host allocation, which kernels reach
+// at the same address, and starts 16-byte aligned.
+static bool pinned_range(const void* p, uint64_t n) {
+    if (reinterpret_cast<uintptr_t>(p) & 15) return false;
+    hipPointerAttribute_t at;
+    void* base = nullptr;
+    size_t size = 0;
+    hipDeviceptr_t q = const_cast<void*>(p);
+    const bool ok = hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeHost &&
+                    at.devicePointer == p &&
+                    hipPointerGetAttribute(&base, HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR, q) == hipSuccess &&
+                    hipPointerGetAttribute(&size, HIP_POINTER_ATTRIBUTE_RANGE_SIZE, q) == hipSuccess;
+    if (!ok) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const uint8_t* b = static_cast<uint8_t*>(base);
+    return p >= b && static_cast<const uint8_t*>(p) + n <= b + size;
 }
 
 // ------------------------------------------------------------ dump
@@ -825,7 +864,7 @@ static void drain(ckpt_ctx* c) {
 
 // Device buffers of one dump: the context's own, or slices of the array.
 struct DumpBufs {
-    DevBuf *descs, *arc, *kinds, *staging, *ctl, *amap, *prevcrc, *off, *wb, *dig, *rlen, *cmeta;
+    DevBuf *descs, *arc, *kinds, *staging, *ctl, *amap, *prevcrc, *off, *wb, *rlen, *cmeta;
     StatusBuf* status;
 };
 
@@ -844,6 +883,10 @@ int mk::dump_impl(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image* 
 // the host has waited for window w, so any number of windows needs a fixed
 // set of buffers and events.
 constexpr uint64_t kRing = 4;
+// Result words of a dump in pinned memory: window totals, error, (pad, kind
+// counts,) the set-up's and the chunk kernel's stamps, the last kernel's two.
+constexpr uint32_t kRepErr = kRing + 1, kRepStamps = kRing + 7, kRepWords = kRing + 9;
+constexpr uint64_t kHwWords = kRepWords + 3;
 
 static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image* prev, ckpt_image** out,
                     const ckpt_opts* o, void* stream, ckpt_result* res, PayloadSink* sink, const NaCall* na) {
@@ -922,9 +965,9 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     if (!na && (uint64_t)nslots * slot > c->budget && nslots > 1) return CKPT_ENOMEM;
 
     // device buffers: the context's own, or slices of the static array
-    DevBuf na_bufs[9];
+    DevBuf na_bufs[8];
     DumpBufs B = {&c->descs, &c->arc, &c->kinds, &c->staging, &c->ctl, &c->amap, &c->prevcrc, &c->off, &c->wb,
-                  &c->dig, &c->rlen, &c->cmeta, &c->status};
+                  &c->rlen, &c->cmeta, &c->status};
     if (na) {
         uint8_t* base = na->dev->ptr;
         na_bufs[0].attach(base + kNaDescs, 64ull * kNaMaxAllocs);
@@ -934,12 +977,23 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         na_bufs[4].attach(base + kNaCtl, 64 << 10);
         na_bufs[5].attach(base + kNaAmap, 4 * kNaMaxChunks);
         na_bufs[6].attach(base + kNaPrev, 4 * kNaMaxChunks);
-        na_bufs[7].attach(base + kNaDig, 64 << 10);
-        B = {&na_bufs[0], &na_bufs[1], &na_bufs[2], &na_bufs[3], &na_bufs[4], &na_bufs[5], &na_bufs[6], &na_bufs[8],
-             &na_bufs[8], &na_bufs[7], &na_bufs[8], &na_bufs[8], &na->dev->status};   // [8]: empty, never used
+        B = {&na_bufs[0], &na_bufs[1], &na_bufs[2], &na_bufs[3], &na_bufs[4], &na_bufs[5], &na_bufs[6], &na_bufs[7],
+             &na_bufs[7], &na_bufs[7], &na_bufs[7], &na->dev->status};   // [7]: empty, never used
     }
 
-    const bool timing = !(o && (o->flags & CKPT_OPT_NO_TIMING));
+    const bool use_graph = o && (o->flags & CKPT_OPT_GRAPH) && wins.size() == 1 && !per_alloc;
+    const bool two_pass = prev != nullptr && wins.size() == 1 && !use_graph && nc > 0 && !na;
+    // A short full dump writes its payload straight into the image, when that
+    // is pinned: no staging, no wait for the payload's length, no copy (8
+    // allocations of 16 MiB: 420 -> 340 us). The image is then allocated at
+    // the payload's bound, which is why longer dumps do not: a state half of
+    // zeros would pin twice its image. The kernel holds the device for as
+    // long as the link takes, 1.2 ms at the longest.
+    const bool small = wins.size() == 1 && nc > 0 && !use_graph && !codec && !per_alloc && !sink && !two_pass &&
+                       upper <= kDirectDump;
+    // stage times: of a short dump by stamps, else by events
+    const bool stamped = small && !(o && (o->flags & CKPT_OPT_NO_TIMING));
+    const bool timing = !stamped && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     HIPCHK(hipSetDevice(c->device));
     if (!na) HIPCHK(ensure_copy_streams(c, ncs));
     HIPCHK(order_after(c, stream));
@@ -959,19 +1013,18 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     HIPCHK(B.status->ensure(8 * (max_win + 64), c->s_main));
     const uint64_t W = wins.size();
     const uint64_t codec_p = codec ? (W == 1 ? std::min<uint64_t>(kCodecPieces, nc) : W) : 0;   // codec pieces
-    // ctl: tickets[n_tk] | wtot[kRing + 1] (u64) | err (+pad) | counts[4] (u64); window tickets and
-    // totals on the ring, codec pieces' tickets by piece
+    // ctl: tickets[n_tk] | wtot[kRing + 1] (u64) | err (+pad) | counts[4] (u64) | stamps[2] (u64); window
+    // tickets and totals on the ring, codec pieces' tickets by piece
     const uint64_t n_tk = std::max<uint64_t>(std::max<uint64_t>(kRing, 2 * kCodecPieces + 2), codec_p) + 1;
     const uint64_t ctl_tk = 0, ctl_wt = round16(4 * (n_tk + 1)),
-                   ctl_err = ctl_wt + 8 * (kRing + 1), ctl_cnt = ctl_err + 16;
-    HIPCHK(B.ctl->ensure(ctl_err + 64));
-    HIPCHK(ensure_hsmall(c, 8 * (kRing + 1) + 64 + 8 * kCodecPieces));   // ring totals, digests, piece lengths
+                   ctl_err = ctl_wt + 8 * (kRing + 1), ctl_cnt = ctl_err + 16, ctl_end = ctl_cnt + 48;
+    HIPCHK(B.ctl->ensure(ctl_end));
+    HIPCHK(ensure_hsmall(c, 8 * kHwWords + 8 * kCodecPieces));   // results, piece lengths
     // events: [0, kRing) window done, [kRing, kRing + nslots) slot free; codec pieces: 4 per piece
     HIPCHK(ensure_events(c, std::max<size_t>(std::max<size_t>(kRing + (size_t)nslots + 2, 4 * codec_p + 1),
                                              kCodecPieces + 1)));
     if (timing) HIPCHK(ensure_tevents(c, std::max<uint64_t>(2 * std::max<uint64_t>(kRing, 2 * codec_p), 4 * kCodecPieces)));
     const EngineConsts* ec;
-    const EngineConsts* dig_ec = nullptr;   // table-digest engine constants (array slice), or the cache's
     if (na) {
         // engine constants in the array, rebuilt when the tile or chunk size
         // changes (host build space of the context; the copy completes before
@@ -985,28 +1038,23 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             nd.T = T;
             nd.C = C;
         }
-        if (!nd.dconsts) {
-            int dT, dK;
-            pick_tile(16384, 0, &dT, &dK);
-            build_engine_consts(c->hconsts, dT, 16384);
-            HIPCHK(hipMemcpyAsync(nd.ptr + kNaDConsts, c->hconsts, sizeof(EngineConsts), hipMemcpyHostToDevice,
-                                  c->s_main));
-            HIPCHK(hipStreamSynchronize(c->s_main));
-            nd.dconsts = true;
-        }
         ec = reinterpret_cast<const EngineConsts*>(nd.ptr + kNaConsts);
-        dig_ec = reinterpret_cast<const EngineConsts*>(nd.ptr + kNaDConsts);
     } else {
         HIPCHK(get_consts(c, T, C, &ec));
     }
 
+    // set-up in one launch: descriptors, chunk map, control words, zero padding
+    // after the kinds (the kinds themselves are written by the chunk kernel)
+    SetupJob sj;
+    memset(&sj, 0, sizeof(sj));
     // resident digest table of the previous image
     const uint32_t* prev_dev = nullptr;
     if (prev && pv.n_chunks) {
         prev_dev = digest_lookup(c, prev->uid, pv.n_chunks);
         if (!prev_dev) {
             HIPCHK(B.prevcrc->ensure(4 * pv.n_chunks));
-            HIPCHK(hipMemcpyAsync(B.prevcrc->p, pv.crcs, 4 * pv.n_chunks, hipMemcpyHostToDevice, c->s_main));
+            if (prev->pinned && !use_graph) sj.add_copy(B.prevcrc->p, pv.crcs, 4 * pv.n_chunks);
+            else HIPCHK(hipMemcpyAsync(B.prevcrc->p, pv.crcs, 4 * pv.n_chunks, hipMemcpyHostToDevice, c->s_main));
             prev_dev = B.prevcrc->as<uint32_t>();
         }
     }
@@ -1016,12 +1064,21 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     uint64_t* wtot = reinterpret_cast<uint64_t*>(ctl + ctl_wt);
     uint32_t* err = reinterpret_cast<uint32_t*>(ctl + ctl_err);
     unsigned long long* counts = reinterpret_cast<unsigned long long*>(ctl + ctl_cnt);
+    uint64_t* stamps = reinterpret_cast<uint64_t*>(ctl + ctl_cnt + 32);
     HIPCHK(B.amap->ensure(4 * std::max<uint64_t>(nc, 1)));
-    HIPCHK(hipMemcpyAsync(B.descs->p, d.data(), sizeof(AllocDesc) * n, hipMemcpyHostToDevice, c->s_main));
-    HIPCHK(launch_chunk_map(B.descs->as<AllocDesc>(), n, C, B.amap->as<uint32_t>(), c->s_main));
-    HIPCHK(launch_fill32(reinterpret_cast<uint32_t*>(ctl), 0, (ctl_err + 64) / 4, c->s_main));
-    // kinds buffer: zero padding after the kinds (the kinds themselves are written by the kernel)
-    HIPCHK(launch_fill32(B.kinds->as<uint32_t>(), 0, ceil_div(tl - 32ull * n - 4 * nc, 4), c->s_main));
+    if (!use_graph) {   // the graph holds its own
+        HIPCHK(ensure_hdesc(c, n));
+        if (n) memcpy(c->hdesc, d.data(), sizeof(AllocDesc) * n);
+        sj.src = c->hdesc;
+        sj.dst = B.descs->as<AllocDesc>();
+        sj.n_allocs = n;
+        sj.C = C;
+        sj.map = B.amap->as<uint32_t>();
+        sj.add_fill(ctl, (ctl_cnt + 32) / 4, 0);
+        sj.stamp = stamped ? stamps : nullptr;
+        sj.add_fill(B.kinds->p, ceil_div(tl - 32ull * n - 4 * nc, 4), 0);
+        HIPCHK(launch_setup(sj, c->s_main));
+    }
     if (timing) HIPCHK(hipEventRecord(c->sev[1], c->s_main));
 
     // With one staging slot and several windows (per-allocation launches
@@ -1042,12 +1099,16 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         na_img.pinned = false;
         im = &na_img;
         himg = na->out;
-    } else if (W > 1 && !stage_all) {
+    } else if ((W > 1 && !stage_all) || small) {
         im = image_new(kHeader + tl + upper);
         if (!im) return CKPT_ENOMEM;
         himg = im->p;
         if (sink) sink->begin(im);
     }
+    // the device can write the image's tables, and all of a small image
+    const bool host_tables = na ? pinned_range(na->out, kHeader + tl) : true;
+    const bool direct = small && (na ? na->cap >= kHeader + tl + upper && pinned_range(na->out, kHeader + tl + upper)
+                                     : im->pinned);
     // the image can take a payload of D bytes (the caller's buffer is fixed)
     auto fits = [&](uint64_t D) { return !na || kHeader + tl + D <= na->cap; };
     // payload bytes [pay, pay + len) of the image from device memory, on
@@ -1114,11 +1175,13 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         j.crc_out = crc_dev;
         j.kind_out = kind_dev;
         j.prev_crc = prev_dev;
-        j.slot = B.staging->as<uint8_t>() + (stage_all ? base : (uint64_t)s * slot);
+        j.slot = direct ? himg + kHeader + tl : B.staging->as<uint8_t>() + (stage_all ? base : (uint64_t)s * slot);
+        j.flags = direct ? kJobHostSlot : 0;
         j.status = B.status->words();
         j.wtotal = wtot + q;
         j.err = err;
         j.epoch = ep;
+        j.stamp = stamped ? stamps + 1 : nullptr;
         int grid;
         e = grid_for(c, T, K, kModeDump, j.g1 - j.g0, &grid);
         if (e != hipSuccess) return e;
@@ -1126,7 +1189,8 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         e = launch_chunks(T, K, kModeDump, one_job(j, tickets + q), grid, c->s_main);
         if (e != hipSuccess) return e;
         if (timing && (e = hipEventRecord(c->tevents[2 * q + 1], c->s_main)) != hipSuccess) return e;
-        e = hipMemcpyAsync(hw + q, wtot + q, 8, hipMemcpyDeviceToHost, c->s_main);
+        if (direct) return hipSuccess;   // its length comes with the results
+        e = launch_report(hw + q, wtot + q, 1, false, c->s_main);
         if (e != hipSuccess) return e;
         return hipEventRecord(ev[q], c->s_main);
     };
@@ -1134,15 +1198,12 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     uint64_t pos = 0, t_link0 = 0, kern_ns = 0;
     hipError_t e = hipSuccess;
     const uint64_t len_a = 32ull * n + 4 * nc, len_b = tl - len_a - rl_bytes;
-    uint32_t* hdig = reinterpret_cast<uint32_t*>(c->hsmall + 8 * (kRing + 1));
-    const bool use_graph = o && (o->flags & CKPT_OPT_GRAPH) && W == 1 && !per_alloc;
     // A delta dump in one window takes three passes per piece (launch_delta):
     // digests and kinds, the payload offsets (scan over the kinds), then the
     // DATA chunks gathered to their records. A delta's kinds depend on the
     // digests, so a single pass would hold every chunk's look-back until its
     // digest is done; its payload is small, so the extra read of D costs
     // little.
-    const bool two_pass = prev != nullptr && W == 1 && !use_graph && nc > 0 && !na;
     uint64_t delta_pieces = 0;
     // the DATA chunks of [g0, g1) to their records at c->off, in staging
     // from sp on, which holds the payload from offset base
@@ -1178,7 +1239,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         const uint64_t P = std::min<uint64_t>(kCodecPieces, nc);
         if ((e = B.off->ensure(8 * nc)) != hipSuccess) return e;
         if ((e = B.wb->ensure(16 * P)) != hipSuccess) return e;
-        uint64_t* htot = reinterpret_cast<uint64_t*>(c->hsmall + 8 * (kRing + 1) + 64);   // [P] piece lengths
+        uint64_t* htot = hw + kHwWords;   // [P] piece lengths
         std::vector<uint64_t> gb(P + 1);
         for (uint64_t i = 0; i <= P; ++i) gb[i] = nc * i / P;
         for (uint64_t i = 0; i < P; ++i) {
@@ -1432,12 +1493,8 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             if ((e = ge->status.ensure(8 * (nc + 64))) != hipSuccess) return fail(e);
             if ((e = hipMemcpy(ge->descs.p, d.data(), sizeof(AllocDesc) * n, hipMemcpyHostToDevice)) != hipSuccess)
                 return fail(e);
-            DigestPlan dp;
-            if ((e = digest_prepare(c, &ge->dig, B.arc->as<uint8_t>(), len_a, kind_dev, len_b, &dp, c->s_main)) != hipSuccess)
-                return fail(e);
-            int grid, gd;
+            int grid;
             if ((e = grid_for(c, T, K, kModeDump, nc, &grid)) != hipSuccess) return fail(e);
-            if ((e = grid_for(c, dp.T, dp.K, kModeDigest, std::max<uint64_t>(dp.nk, 1), &gd)) != hipSuccess) return fail(e);
             if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return fail(e);
             // every replay clears the graph's own look-back words first, so
             // one epoch serves all replays
@@ -1447,7 +1504,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             hipError_t ce = hipSuccess;
             auto step = [&ce](hipError_t r) { if (ce == hipSuccess) ce = r; };
             // every replay clears what must start at zero with fill kernels
-            step(launch_fill32(reinterpret_cast<uint32_t*>(ctl), 0, (ctl_err + 64) / 4, c->s_main));
+            step(launch_fill32(reinterpret_cast<uint32_t*>(ctl), 0, ctl_end / 4, c->s_main));
             step(launch_fill32(B.kinds->as<uint32_t>(), 0, ceil_div(len_b, 4), c->s_main));
             step(launch_fill64(ge->status.as<uint64_t>(), 0, nc + 64, c->s_main));
             step(launch_chunk_map(ge->descs.as<AllocDesc>(), n, C, B.amap->as<uint32_t>(), c->s_main));
@@ -1469,7 +1526,8 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             j.err = err;
             j.epoch = ep;
             if (nc) step(launch_chunks(T, K, kModeDump, one_job(j, tickets), grid, c->s_main));
-            step(hipMemcpyAsync(hw, wtot, 8, hipMemcpyDeviceToHost, c->s_main));
+            // the payload's length and the error word
+            step(launch_report(hw, wtot, kRepErr + 1, false, c->s_main));
             CombineJob gcj;
             memset(&gcj, 0, sizeof(gcj));
             gcj.allocs = ge->descs.as<AllocDesc>();
@@ -1480,8 +1538,6 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             gcj.recs = B.arc->as<uint8_t>();
             gcj.mode = kCombineWrite;
             step(launch_combine(gcj, c->s_main));
-            step(digest_enqueue(c, dp, hdig, c->s_main));
-            step(hipMemcpyAsync(hdig + 2, err, 4, hipMemcpyDeviceToHost, c->s_main));
             hipError_t ee = hipStreamEndCapture(c->s_main, &graph);
             if (ce == hipSuccess) ce = ee;
             if (ce == hipSuccess) ce = hipGraphInstantiate(&ge->exec, graph, nullptr, nullptr, 0);
@@ -1517,7 +1573,8 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         if (W && codec) e = launch_codec(&pos);
         else if (W && two_pass) e = launch_delta(&pos);
         else if (W) e = launch_window(0, 0);
-        for (uint64_t w = 0; w < W && e == hipSuccess && !codec && !two_pass; ++w) {
+        if (direct) t_link0 = now_ns();
+        for (uint64_t w = 0; w < W && e == hipSuccess && !codec && !two_pass && !direct; ++w) {
             const uint64_t q = w % kRing;
             if (w > 0 && !ahead) {
                 e = launch_window(w, pos);
@@ -1573,49 +1630,73 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         }
         if (e != hipSuccess) return fail(e);
 
-        // per-allocation CRCs -> AllocRec[] (in the device arc buffer)
-        if (timing && (e = hipEventRecord(c->sev[2], c->s_main)) != hipSuccess) return fail(e);
-        CombineJob cj;
-        memset(&cj, 0, sizeof(cj));
-        cj.allocs = B.descs->as<AllocDesc>();
-        cj.n_allocs = n;
-        cj.C = C;
-        cj.crc = crc_dev;
-        cj.ec = ec;
-        cj.recs = B.arc->as<uint8_t>();
-        cj.mode = kCombineWrite;
-        if ((e = launch_combine(cj, c->s_main)) != hipSuccess) return fail(e);
-        // table digests
-        int rc = device_table_digests(c, B.arc->as<uint8_t>(), len_a, kind_dev, len_b, hdig, res, B.dig, dig_ec);
-        if (rc) return fail(hipErrorUnknown);
     }
-    const uint64_t D = pos;
+    uint64_t D = pos;   // (a direct dump's comes with the results)
     if (!alloc_image(D)) return fail(hipErrorOutOfMemory);   // a table without chunks
-    // tables into the image
-    if ((e = hipMemcpyAsync(himg + kHeader, B.arc->p, len_a, hipMemcpyDeviceToHost, c->s_main)) != hipSuccess)
-        return fail(e);
-    if (codec) memcpy(himg + kHeader + len_a, rlen_h, rl_bytes);   // little-endian host
-    if ((e = hipMemcpyAsync(himg + kHeader + len_a + rl_bytes, kind_dev, len_b, hipMemcpyDeviceToHost, c->s_main)) !=
-        hipSuccess)
-        return fail(e);
-    if ((e = hipMemcpyAsync(hdig + 2, err, 4, hipMemcpyDeviceToHost, c->s_main)) != hipSuccess) return fail(e);
-    if (timing && !use_graph && (e = hipEventRecord(c->sev[3], c->s_main)) != hipSuccess) return fail(e);
-    if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return fail(e);
+    // The end, in one launch: per-allocation CRCs to AllocRec[], the tables
+    // into the image (a pageable one takes them by copies), the digest table
+    // to its resident place, the results.
+    const bool tables_direct = na ? host_tables : im->pinned;
+    uint8_t* htab = himg + kHeader;
+    if (timing && !use_graph && (e = hipEventRecord(c->sev[2], c->s_main)) != hipSuccess) return fail(e);
+    FinishJob fj;
+    memset(&fj, 0, sizeof(fj));
+    fj.c.mode = kCombineWrite;
+    if (!use_graph) {   // a graph's records are in the device arc buffer already
+        fj.c.allocs = B.descs->as<AllocDesc>();
+        fj.c.n_allocs = n;
+        fj.c.C = C;
+        fj.c.crc = crc_dev;
+        fj.c.ec = ec;
+        fj.c.recs = tables_direct ? htab : B.arc->as<uint8_t>();
+        fj.rep = hw;
+        fj.rep_src = wtot;
+        fj.n_rep = kRepWords;
+    }
+    if (tables_direct) {
+        if (use_graph) fj.add_copy(htab, B.arc->p, 32ull * n);
+        fj.add_copy(htab + 32ull * n, crc_dev, 4 * nc);
+        fj.add_copy(htab + len_a + rl_bytes, kind_dev, len_b);
+    }
+    // keep this image's digest table resident for later delta dumps (not
+    // for the caller's buffer of a no-allocation dump: that would allocate)
+    uint32_t* resident = na ? nullptr : digest_reserve(c, im->uid, nc);
+    if (resident) fj.add_copy(resident, crc_dev, 4 * nc);
+    auto fail_late = [&](hipError_t err_) {
+        (void)hipStreamSynchronize(c->s_main);
+        if (resident) digest_drop(c, im->uid);
+        return fail(err_);
+    };
+    if ((e = launch_finish(fj, c->s_main)) != hipSuccess) return fail_late(e);
+    if (!tables_direct) {
+        if ((e = hipMemcpyAsync(htab, B.arc->p, len_a, hipMemcpyDeviceToHost, c->s_main)) != hipSuccess)
+            return fail_late(e);
+        if ((e = hipMemcpyAsync(htab + len_a + rl_bytes, kind_dev, len_b, hipMemcpyDeviceToHost, c->s_main)) !=
+            hipSuccess)
+            return fail_late(e);
+    }
+    if (timing && !use_graph && (e = hipEventRecord(c->sev[3], c->s_main)) != hipSuccess) return fail_late(e);
+    if (codec) memcpy(htab + len_a, rlen_h, rl_bytes);   // little-endian host
+    if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return fail_late(e);
+    if (direct) {
+        D = hw[0];
+        if (D > upper) return fail_late(hipErrorIllegalState);
+    }
+    if (stamped) kern_ns = stamp_ns(c, hw[kRepStamps + 1], hw[kRepWords]);
     // the kinds are in the image now: counted while the payload copies run
     uint64_t n_kind[4] = {0, 0, 0, 0};   // ZERO, DATA, UNCHANGED, PACKED
     if (res) {
         count_kinds(himg + kHeader + len_a + rl_bytes, 0, nc, n_kind);
     }
-    for (uint32_t i = 0; i < ncs; ++i)
-        if ((e = hipStreamSynchronize(c->s_copy[i])) != hipSuccess) return fail(e);
+    // the tables' digest, on the host as well: 0.1 ms for 27 GB in 64 KiB
+    // chunks, beside the payload copies
+    const uint32_t tcrc = host_crc32c(htab, tl);
+    for (uint32_t i = 0; i < ncs && !direct; ++i)
+        if ((e = hipStreamSynchronize(c->s_copy[i])) != hipSuccess) return fail_late(e);
     const uint64_t t_link1 = now_ns();
-    if (hdig[2] != 0) return fail(hipErrorLaunchTimeOut);
+    if ((uint32_t)hw[kRepErr] != 0) return fail_late(hipErrorLaunchTimeOut);
 
     // header
-    const uint32_t sd = hdig[0];
-    uint32_t tcrc = sd;
-    if (codec) tcrc = crc_combine(tcrc, host_crc32c(rlen_h, rl_bytes), rl_bytes);
-    tcrc = crc_combine(tcrc, hdig[1], len_b);
     uint8_t* h = himg;
     memcpy(h, "MICKPT01", 8);
     put32(h + 8, 1);
@@ -1631,10 +1712,6 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     put32(h + 60, host_crc32c(h, 60));
     im->n = kHeader + tl + D;
 
-    // keep this image's digest table resident for later delta dumps (not
-    // for the caller's buffer of a no-allocation dump: that would allocate)
-    if (!na) digest_insert(c, im->uid, crc_dev, nc, c->s_main);
-    if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return fail(e);
     if (res) {
         res->windows = (uint32_t)W;
         res->n_logical = N;
@@ -1642,11 +1719,16 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         res->n_chunks = nc;
         res->link_bytes = D + tl + kHeader;
         res->ns_link = t_link0 ? t_link1 - t_link0 : 0;
-        res->ns_kernel = !timing ? 0 : (codec && W) ? timed_ns(c, codec_pairs) : use_graph ? timed_ns(c, 1) : kern_ns;
+        res->ns_kernel = stamped ? kern_ns : !timing ? 0 : (codec && W) ? timed_ns(c, codec_pairs) : use_graph ? timed_ns(c, 1) : kern_ns;
         if (timing && two_pass)
             for (uint64_t i = 0; i < delta_pieces; ++i) res->ns_kernel += span_ns(c->tevents[4 * i], c->tevents[4 * i + 3]);
         res->ns_total = now_ns() - t_start;
         // per-stage report (see ckpt_result.ns_stage)
+        if (stamped) {
+            res->ns_stage[0] = stamp_ns(c, hw[kRepStamps], hw[kRepStamps + 1]);
+            res->ns_stage[1] = kern_ns;
+            res->ns_stage[5] = stamp_ns(c, hw[kRepWords], hw[kRepWords + 1]);
+        }
         if (timing) {
             if (!use_graph) res->ns_stage[0] = span_ns(c->sev[0], c->sev[1]);
             if (two_pass) {
@@ -1757,8 +1839,10 @@ namespace {
 // A delta's restore launches write only if its base check found no chunk
 // that differs from the base: *gate = (*bad == none). (The chunk kernels'
 // restore mode does nothing when its gate word is 0.)
-__global__ void k_base_gate(uint32_t* gate, const unsigned long long* bad) {
-    if (threadIdx.x == 0) *gate = *bad == ~0ull ? 1u : 0u;
+__global__ void k_base_gate(uint32_t* gate, const unsigned long long* bad, uint64_t* stamp) {
+    if (threadIdx.x != 0) return;
+    *gate = *bad == ~0ull ? 1u : 0u;
+    if (stamp) *stamp = wall_clock64();
 }
 }  // namespace
 
@@ -1884,17 +1968,22 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     const uint64_t tiles = ceil_div(nc, 256) + 64;   // look-back words of the offsets scan, twice
     HIPCHK(c->status.ensure(16 * tiles, c->s_main));
     // ctl: ticket[1] | counts[4] u64 | bad u64 | bad2 u64 | err (+pad) | bad3 u64 | bas u64 | bgate (+pad) |
-    // window tickets[W + 2]
+    // stamps[4] u64 | window tickets[W + 2]
     const uint64_t ctl_cnt = 64, ctl_bad = ctl_cnt + 32, ctl_bad2 = ctl_bad + 8, ctl_err = ctl_bad2 + 8,
-                   ctl_bad3 = ctl_err + 8, ctl_bas = ctl_bad3 + 8, ctl_wtk = ctl_bas + 16;
+                   ctl_bad3 = ctl_err + 8, ctl_bas = ctl_bad3 + 8, ctl_stm = ctl_bas + 16, ctl_wtk = ctl_stm + 32;
     HIPCHK(c->ctl.ensure(ctl_wtk + 4 * (W + 2) + 64));
-    HIPCHK(ensure_hsmall(c, 8 * (W + 2) + 128));
+    HIPCHK(ensure_hsmall(c, 8 * (W + 2) + 256));
     HIPCHK(ensure_events(c, std::max<size_t>(2 * W + (size_t)nslots + 2, ncs)));
-    const bool timing = !(o && (o->flags & CKPT_OPT_NO_TIMING));
-    if (timing) HIPCHK(ensure_tevents(c, 2 * W + 2));
+    // stage times: by stamps where the launches are few (split or one window),
+    // else by events
+    const bool stamped = direct && W <= 1 && !(o && (o->flags & CKPT_OPT_NO_TIMING));
+    const bool timing = !stamped && !(o && (o->flags & CKPT_OPT_NO_TIMING));
+    if (timing || (stamped && o && o->strict_verify)) HIPCHK(ensure_tevents(c, 2 * W + 2));
     const EngineConsts* ec;
     HIPCHK(get_consts(c, T, C, &ec));
     uint8_t* ctl = c->ctl.as<uint8_t>();
+    // offsets scan, first scatter launch, base check, its end
+    uint64_t* stamps = reinterpret_cast<uint64_t*>(ctl + ctl_stm);
     // a delta's base check result and the gate it sets for the restore launches
     unsigned long long* bas = reinterpret_cast<unsigned long long*>(ctl + ctl_bas);
     uint32_t* bgate = reinterpret_cast<uint32_t*>(ctl + ctl_bas + 8);
@@ -2231,7 +2320,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     sj.add_fill(bad, 4, ~0u);    // bad, bad2
     sj.add_fill(err, 2, 0);
     sj.add_fill(bad3, 4, ~0u);   // bad3, bas
-    sj.add_fill(bgate, 2 + W + 2, 0);
+    sj.add_fill(bgate, 2 + 8 + W + 2, 0);   // and the stamps and tickets
     if (img->pinned) {
         sj.add_copy(c->arc.p, v.recs, len_a);
         sj.add_copy(kind_dev, v.kinds, len_b);
@@ -2242,7 +2331,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         if (codec && nc) HIPCHK(hipMemcpyAsync(c->rlen.p, v.rlens, 4 * nc, hipMemcpyHostToDevice, c->s_main));
     }
     HIPCHK(launch_setup(sj, c->s_main));
-    uint64_t* hq = reinterpret_cast<uint64_t*>(c->hsmall + 64);   // [4..8]: bad, bad2, err, bad3, bas
+    uint64_t* hq = reinterpret_cast<uint64_t*>(c->hsmall + 64);   // [4..14]: bad, bad2, err, bad3, bas, (gate,) stamps[4], end
     OffJob oj;
     memset(&oj, 0, sizeof(oj));
     int off_grid = 0;
@@ -2279,6 +2368,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     cj.recs = c->arc.as<uint8_t>();
     cj.bad = bad2;
     cj.mode = kCombineCheck;
+    cj.stamp = stamped ? stamps : nullptr;
     if (timing) HIPCHK(hipEventRecord(c->sev[2], c->s_main));
     HIPCHK(launch_offsets_combine(oj, off_grid, cj, c->s_main));
     if (timing) HIPCHK(hipEventRecord(c->sev[3], c->s_main));
@@ -2302,6 +2392,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         j.bad = badp;
         j.err = err;
         j.flags = flags;
+        j.stamp = stamped && !flags ? stamps + 2 : nullptr;
         int grid;
         hipError_t e;
         if (!some) {
@@ -2339,7 +2430,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         if (timing) HIPCHK(hipEventRecord(c->tevents[2 * W], c->s_main));
         HIPCHK(verify_pass(0, bas));
         if (timing) HIPCHK(hipEventRecord(c->tevents[2 * W + 1], c->s_main));
-        hipLaunchKernelGGL(k_base_gate, dim3(1), dim3(64), 0, c->s_main, bgate, bas);
+        hipLaunchKernelGGL(k_base_gate, dim3(1), dim3(64), 0, c->s_main, bgate, bas, stamped ? stamps + 3 : nullptr);
         HIPCHK(hipGetLastError());
     } else if (nu) {
         HIPCHK(verify_pass(0, bad));
@@ -2359,6 +2450,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     const uint64_t t_link0 = now_ns();
     uint64_t moved_all = 0;
     for (uint64_t w = 0; w < W; ++w) moved_all += wend[w] - wbeg[w];
+    bool stamp_taken = false;
     auto restore_job = [&](uint64_t w) {
         ChunkJob j;
         memset(&j, 0, sizeof(j));
@@ -2377,6 +2469,9 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         j.bad = bad;
         j.err = err;
         j.gate = rgate;
+        // the first launch of all takes the stamp
+        j.stamp = stamped && !stamp_taken ? stamps + 1 : nullptr;
+        stamp_taken = true;
         return j;
     };
     // grids: a launch that reads host memory takes no more work-groups than
@@ -2442,6 +2537,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         if (nz) {
             const uint64_t wgs = 4ull * (c->num_cu - (hi ? kLinkCus : 0));
             HIPCHK(launch_zero(j, (int)std::min<uint64_t>(nc, wgs), c->s_main));
+            j.stamp = nullptr;
         }
         // the head from staging, then the rest from host memory
         for (int part = 0; part < 2; ++part) {
@@ -2462,12 +2558,14 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
                 if (part) HIPCHK(restore_grid(jd.g1 - jd.g0, &grid));
                 else HIPCHK(grid_for(c, T, K, kModeRestore, jd.g1 - jd.g0, &grid));
                 HIPCHK(launch_chunks(T, K, kModeRestore, one_job(jd, wtk + part), grid, c->s_main));
+                j.stamp = nullptr;
             }
             j.g0 = bounds[b];
             j.g1 = bounds[e];
             if (n_packed) {
                 grid = unpack_grid(c, j.g1 - j.g0);
                 HIPCHK(launch_unpack(one_job(j, wtk + part), c->rlen.as<uint32_t>(), cc, grid, c->s_main));
+                j.stamp = nullptr;
             }
         }
         if (timing) HIPCHK(hipEventRecord(c->tevents[1], c->s_main));
@@ -2512,12 +2610,12 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     // registers as it was written)
     const bool strict = o && o->strict_verify;
     if (strict) {
-        if (timing) HIPCHK(hipEventRecord(c->sev[0], c->s_main));
+        if (timing || stamped) HIPCHK(hipEventRecord(c->sev[0], c->s_main));
         HIPCHK(verify_pass(kJobVerifyAll, bad3));
-        if (timing) HIPCHK(hipEventRecord(c->sev[1], c->s_main));
+        if (timing || stamped) HIPCHK(hipEventRecord(c->sev[1], c->s_main));
     }
     // 4) the results
-    HIPCHK(launch_report(hq + 4, reinterpret_cast<uint64_t*>(bad), 5, c->s_main));
+    HIPCHK(launch_report(hq + 4, reinterpret_cast<uint64_t*>(bad), 10, true, c->s_main));
     HIPCHK(hipStreamSynchronize(c->s_main));
     for (uint32_t i = 0; i < ncs; ++i) HIPCHK(hipStreamSynchronize(c->s_copy[i]));
     const uint64_t t_link1 = now_ns();
@@ -2544,15 +2642,24 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         res->n_packed = n_packed;
         res->link_bytes = moved + tl + kHeader;
         res->ns_link = t_link1 - t_link0;
-        res->ns_kernel = timing ? timed_ns(c, merged ? ceil_div(W, (uint64_t)kMaxJobs) : W) : 0;
+        // stamps: hq[10] offsets scan, [11] scatter, [12] base check, [13] its end, [14] the report
+        const uint64_t strict_ns = strict && (timing || stamped) ? span_ns(c->sev[0], c->sev[1]) : 0;
+        const uint64_t scatter_ns = stamp_ns(c, hq[11], hq[14]);
+        res->ns_kernel = timing    ? timed_ns(c, merged ? ceil_div(W, (uint64_t)kMaxJobs) : W)
+                         : stamped ? scatter_ns - std::min(scatter_ns, strict_ns)
+                                   : 0;
         res->ns_total = now_ns() - t_start;
         res->ns_stage[0] = t_valid - t_start;
-        res->ns_stage[1] = !nu ? 0 : (base_overlap && timing) ? span_ns(c->tevents[2 * W], c->tevents[2 * W + 1])
-                                                               : t_based - t_valid;
+        if (nu) {
+            res->ns_stage[1] = t_based - t_valid;
+            if (base_overlap && timing) res->ns_stage[1] = span_ns(c->tevents[2 * W], c->tevents[2 * W + 1]);
+            if (base_overlap && stamped) res->ns_stage[1] = stamp_ns(c, hq[12], hq[13]);
+        }
         res->ns_stage[2] = res->ns_link;
         res->ns_stage[3] = res->ns_kernel;
-        if (timing && strict) res->ns_stage[4] = span_ns(c->sev[0], c->sev[1]);
+        res->ns_stage[4] = strict_ns;
         if (timing) res->ns_stage[5] = span_ns(c->sev[2], c->sev[3]);
+        if (stamped) res->ns_stage[5] = stamp_ns(c, hq[10], base_overlap ? hq[12] : hq[11]);
         res->ns_stage[7] = res->ns_total;
     }
     // the lowest failing chunk of the fused and the strict checks, then the

@@ -126,3 +126,36 @@ def test_a_reused_image_buffer_is_read_anew(ctx):
         rc, _ = mk.ckpt_restore_some(ctx, imp, [(i, t) for i, t in blank(table)[2:4]])
         assert rc == 0
         imp.free()
+
+
+@pytest.mark.parametrize("c", [1024, 16384, 65536, 262144])
+def test_short_dumps_into_pinned_and_pageable_memory(ctx, c):
+    """A full dump and a delta of a few chunks, and dump_into with the
+    caller's buffer pinned (aligned or not, with room for the payload's bound
+    or just for the payload) and pageable: the same image."""
+    opts = mk.make_opts(chunk_size=c)
+    table = [(i, t) for i, t in state(c, 11, 1) if t.numel() < 8 << 20] + [(999, torch.zeros(5 * c, dtype=torch.uint8, device="cuda"))]
+    rc, img, res = mk.ckpt_dump(ctx, table, opts=opts)
+    assert rc == 0
+    with pageable():
+        rc, img2, _ = mk.ckpt_dump(ctx, table, opts=opts)
+        assert rc == 0
+    want = img.view()
+    assert np.array_equal(want, img2.view())
+    room = want.size + (8 << 20) + 32
+    pinned = torch.empty(room, dtype=torch.uint8, pin_memory=True).numpy()
+    for out in (pinned, pinned[8:], pinned[16:16 + want.size], np.zeros(room, np.uint8)):
+        out[:] = 0xEE
+        rc, n, r = mk.ckpt_dump_into(ctx, table, out, opts=opts)
+        assert rc == 0 and n == want.size and r.n_payload == res.n_payload
+        assert np.array_equal(out[:n], want) and (out[n:] == 0xEE).all()
+    rc, n, _ = mk.ckpt_dump_into(ctx, table, pinned[:want.size - 16], opts=opts)
+    assert rc == mk.CKPT_ENOMEM and n == 0
+    table[2][1][:c] = 77
+    got = []
+    for where in (contextlib.nullcontext, pageable):
+        with where():
+            rc, delta, r = mk.ckpt_dump(ctx, table, prev=img, opts=opts)
+            assert rc == 0
+            got.append((delta.tobytes(), r.n_unchanged, r.n_data, r.n_payload))
+    assert got[0] == got[1] and got[0][1] > 0
