@@ -77,7 +77,9 @@ struct OffJob {
     uint32_t pad;
     const uint32_t* rlen;        // codec layout: record length of PACKED chunk g at [g], or nullptr
     uint64_t* list;              // DATA chunks of the range in order, or nullptr
+    uint64_t* n_list;            // their number (with list), or nullptr
     uint64_t* status2;           // look-back of the list positions (with list), one word per tile
+    uint64_t* stamp;             // k_offsets: device clock at the kernel's start, or nullptr
     uint64_t g_base;             // the scan covers global chunks [g_base, g_base + n_chunks); off, kind
                                  // and amap are indexed globally, windows and wb relative to g_base
 };
@@ -149,6 +151,14 @@ struct GateJob {
     const uint64_t* expect;              // [2]: tables digest, D (written before each launch)
     uint32_t* gate;
 };
+
+// Digest pass over whole memory (classify and verify of chunks of at least
+// kScanMinChunk bytes): group width T of the engine constants for chunk size
+// C, and the launch. job.ec must hold the constants for (scan_width(C), C);
+// cus: CUs the launch may fill.
+constexpr uint32_t kScanMinChunk = 8192;
+inline int scan_width(uint32_t C) { return C <= 65536 ? 64 : 512; }
+hipError_t launch_scan(bool verify, const JobList& jl, int cus, hipStream_t s);
 
 bool tile_supported(int T, int K);
 hipError_t launch_setup(const SetupJob& job, hipStream_t s);

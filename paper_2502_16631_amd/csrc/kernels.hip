@@ -848,6 +848,185 @@ k_dump_stream(JobList jl) {
     }
 }
 
+// Digest pass: classify (digest and kind of every chunk) or verify (digest
+// against the image's, of UNCHANGED chunks or all), nothing written but a
+// few bytes per chunk. Bound by HBM reads and by the digest's table lookups
+// in LDS (one per byte, ~6 TB/s over the chip).
+//
+// T threads share a chunk: one wave up to 64 KiB, a work-group of eight waves
+// above, where there may be too few chunks for a wave each. A group reads its
+// chunk in batches of eight rows (16 T bytes each) and the batches of its
+// chunks are one stream: while a batch is digested from registers the next
+// one, of the same chunk or of the group's next chunk, is on its way to other
+// registers, so that reads stay in flight across chunk ends, and a wave on
+// its own needs no barrier at all. A lane's multiply to its place costs 157
+// instructions per chunk whatever the rows, so few lanes with many rows each
+// take a third less work per byte than 512 lanes with eight.
+template <int T, bool VERIFY>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+k_scan(JobList jl) {
+    constexpr int B = 8;                        // rows per batch
+    constexpr uint32_t R = 16u * T, BB = R * B;  // bytes per row and batch
+    constexpr int NG = 512 / T, NW = T / 64;
+    __shared__ uint32_t s_dt[16 * 256];
+    __shared__ uint32_t s_red[2][8], s_any[2][8];
+    const int tid = threadIdx.x;
+    stamp(jl.job[0].stamp);
+    if (VERIFY && jl.job[0].gate && *jl.job[0].gate == 0) return;
+    const EngineConsts* ec = jl.job[0].ec;
+    for (int i = tid; i < 16 * 256; i += 512) s_dt[i] = ec->dt[i];
+    const uint32_t lt = (uint32_t)tid % T;
+    const uint32_t lanec = ec->lane[lt];
+    const uint32_t full_init = ec->full_init;
+    const uint32_t C = jl.job[0].C, log2c = 31 - __builtin_clz(C);
+    const uint32_t nb = C / BB;
+    const uint64_t total = jl.prefix[jl.n_jobs];
+    const uint64_t stride = (uint64_t)gridDim.x * NG;
+    uint64_t tk = (uint64_t)blockIdx.x * NG + __builtin_amdgcn_readfirstlane((uint32_t)tid / T);
+    __syncthreads();
+
+    struct At {   // uniform over the group
+        uint64_t g, ptr;
+        uint32_t jj, len, init, unshift, ref;
+        bool cmp, ok;
+    };
+    // the group's next chunk from ticket tk on
+    auto next = [&]() {
+        At c{};
+        for (; tk < total; tk += stride) {
+            uint32_t jj = 0;
+            while (jj + 1 < jl.n_jobs && jl.prefix[jj + 1] <= tk) ++jj;
+            const ChunkJob& job = jl.job[jj];
+            const uint64_t g = job.g0 + (tk - jl.prefix[jj]);
+            if (VERIFY && !(job.flags & kJobVerifyAll)) {
+                const uint64_t a = reinterpret_cast<uint64_t>(job.kind_in) + g;
+                const uint32_t w = ld_const(reinterpret_cast<const uint32_t*>(a & ~3ull));
+                if (((w >> (8 * (a & 3))) & 255) != kUnchanged) continue;
+            }
+            const uint32_t al = job.amap ? ld_const(job.amap + g) : find_alloc(job.allocs, job.n_allocs, g);
+            const AllocDesc* ad = job.allocs + al;
+            const uint64_t k = g - ld_const(&ad->first);
+            const uint64_t nk = (ld_const(&ad->size) + C - 1) >> log2c;
+            c.g = g;
+            c.jj = jj;
+            c.ptr = ld_const(&ad->ptr) + (k << log2c);
+            c.len = k + 1 == nk ? ld_const(&ad->tail_len) : C;
+            c.init = c.len == C ? full_init : ld_const(&ad->tail_init);
+            c.unshift = ld_const(&ad->tail_unshift);
+            if constexpr (VERIFY) {
+                c.ref = ld_const(job.ref_crc + g);
+            } else {
+                const uint64_t pf = ld_const(&ad->prev_first);
+                c.cmp = job.prev_crc != nullptr && pf != ~0ull;
+                if (c.cmp) c.ref = ld_const(job.prev_crc + pf + k);
+            }
+            c.ok = true;
+            tk += stride;
+            break;
+        }
+        return c;
+    };
+    // Every batch is exactly B loads, so that the waits for the older of two
+    // batches in flight count past the younger: a block outside the chunk is
+    // read from the tables' constants instead and cleared in fix().
+    const uint8_t* const safe = reinterpret_cast<const uint8_t*>(ec->dt) + 16 * lt;
+    auto load = [&](v4u (&v)[B], const At& c, uint32_t bi) {
+        const uint32_t o = bi * BB + 16u * lt;
+        const uint8_t* p = reinterpret_cast<const uint8_t*>(c.ptr) + o;
+        if ((bi + 1) * BB <= c.len) {
+#pragma unroll
+            for (int r = 0; r < B; ++r) v[r] = gload(p + r * R);
+        } else {
+#pragma unroll
+            for (int r = 0; r < B; ++r) v[r] = gload(o + r * R + 16u <= c.len ? p + r * R : safe);
+        }
+    };
+    // a short chunk's batch: blocks past its end are zeros, the one across it
+    // is read byte by byte
+    auto fix = [&](v4u (&v)[B], const At& c, uint32_t bi) {
+        const uint32_t o = bi * BB + 16u * lt;
+        v4u part = vzero();
+        int at = -1;
+#pragma unroll
+        for (int r = 0; r < B; ++r)
+            if (o + r * R < c.len && o + r * R + 16u > c.len) at = r;
+        if (at >= 0) part = load_partial(reinterpret_cast<const uint8_t*>(c.ptr) + o + at * R, c.len - (o + at * R));
+#pragma unroll
+        for (int r = 0; r < B; ++r)
+            if (o + r * R + 16u > c.len) v[r] = r == at ? part : vzero();
+    };
+    At cur = next();
+    if (!cur.ok) return;   // (T 512: uniform over the work-group)
+    uint32_t bi = 0, acc = 0, orw = 0, parity = 0;
+    // classify: the wave's results, chunk n in lane n % 64, stored 64 at a time
+    // (a store per chunk would be waited for with the next batch's loads)
+    uint32_t n = 0, r_crc = 0, r_at = 0, r_kind = 0;
+    auto flush = [&](uint32_t m) {
+        const ChunkJob& job = jl.job[0];
+        if ((uint32_t)(tid & 63) < m) {
+            job.crc_out[job.g0 + r_at] = r_crc;
+            job.kind_out[job.g0 + r_at] = (uint8_t)r_kind;
+        }
+    };
+    v4u va[B], vb[B];
+    load(va, cur, 0);
+    // one batch: the stream's next one on its way, then this one digested
+    auto step = [&](v4u (&v)[B], v4u (&w)[B]) -> bool {
+        const bool last = bi + 1 == nb;
+        At nx = cur;
+        if (last) {
+            nx = next();
+            if (!nx.ok) nx.len = 0;   // (its loads read the constants)
+        }
+        load(w, nx, last ? 0 : bi + 1);
+        if (cur.len != C) fix(v, cur, bi);
+#pragma unroll
+        for (int r = 0; r < B; ++r) orw |= or4(v[r]);
+        acc = crc_rows<B>(v, acc, s_dt);
+        ++bi;
+        if (!last) return true;
+        uint32_t lc = lanec;
+        asm volatile("" : "+v"(lc));
+        uint32_t raw = wave_xor(gf_mul_v(acc, lc));
+        uint32_t any = __ballot(orw != 0) != 0;
+        if constexpr (NW > 1) {
+            if ((tid & 63) == 0) {
+                s_red[parity][tid >> 6] = raw;
+                s_any[parity][tid >> 6] = any;
+            }
+            lds_barrier();
+            raw = 0;
+            any = 0;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                raw ^= s_red[parity][i];
+                any |= s_any[parity][i];
+            }
+            parity ^= 1;   // the other buffer next: no second barrier
+        }
+        if (cur.len != C) raw = gf_mul_v(raw, cur.unshift);
+        const uint32_t crc = ~(raw ^ cur.init);
+        if constexpr (VERIFY) {
+            if (lt == 0 && crc != cur.ref) atomicMin(jl.job[cur.jj].bad, (unsigned long long)cur.g);
+        } else if (NW == 1 || tid < 64) {
+            if ((uint32_t)(tid & 63) == (n & 63)) {
+                r_crc = crc;
+                r_at = (uint32_t)(cur.g - jl.job[0].g0);
+                r_kind = !any ? kZero : cur.cmp && cur.ref == crc ? kUnchanged : kData;
+            }
+            if ((++n & 63) == 0) flush(64);
+        }
+        cur = nx;
+        bi = acc = orw = 0;
+        return cur.ok;
+    };
+    for (;;) {
+        if (!step(va, vb)) break;
+        if (!step(vb, va)) break;
+    }
+    if (!VERIFY && (NW == 1 || tid < 64)) flush(n & 63);
+}
+
 __device__ inline void offsets_wg(const OffJob& job) {
     __shared__ uint32_t s_tk[2];
     __shared__ uint64_t s_wsum[4];
@@ -919,6 +1098,8 @@ __device__ inline void offsets_wg(const OffJob& job) {
             for (int w = 0; w < 4; ++w) r += w < wave ? s_wcnt[w] : 0;
             job.list[s_pos + r] = gg;
         }
+        if (job.list && job.n_list && g + 1 == job.n_chunks)
+            *job.n_list = s_pos + s_wcnt[0] + s_wcnt[1] + s_wcnt[2] + s_wcnt[3];
         if (g < job.n_chunks) {
             job.off[gg] = o;
             if (g % job.per_window == 0) job.wb[g / job.per_window] = o;
@@ -927,7 +1108,10 @@ __device__ inline void offsets_wg(const OffJob& job) {
     }
 }
 
-__global__ void __launch_bounds__(256) k_offsets(OffJob job) { offsets_wg(job); }
+__global__ void __launch_bounds__(256) k_offsets(OffJob job) {
+    stamp(job.stamp);
+    offsets_wg(job);
+}
 
 __global__ void k_gate(GateJob j) {
     if (threadIdx.x != 0) return;
@@ -1153,17 +1337,26 @@ hipError_t launch_tk(int mode, const JobList& jl, int grid, hipStream_t s) {
             }
             hipLaunchKernelGGL((k_chunks<T, K, kModeDump>), dim3(grid), dim3(NT), 0, s, jl);
             break;
+        // (classify and verify of larger chunks: launch_scan)
         case kModeClassify:
-            if constexpr (T >= 64) {
-                if (jl.job[0].C == 16u * T * K) {
-                    hipLaunchKernelGGL((k_dump_stream<T, K, true>), dim3(grid), dim3(T), 0, s, jl);
-                    break;
+            if constexpr (16u * T * K < kScanMinChunk) {
+                if constexpr (T >= 64) {
+                    if (jl.job[0].C == 16u * T * K) {
+                        hipLaunchKernelGGL((k_dump_stream<T, K, true>), dim3(grid), dim3(T), 0, s, jl);
+                        break;
+                    }
                 }
+                hipLaunchKernelGGL((k_chunks<T, K, kModeClassify>), dim3(grid), dim3(NT), 0, s, jl);
+                break;
             }
-            hipLaunchKernelGGL((k_chunks<T, K, kModeClassify>), dim3(grid), dim3(NT), 0, s, jl);
-            break;
+            return hipErrorInvalidValue;
+        case kModeVerify:
+            if constexpr (16u * T * K < kScanMinChunk) {
+                hipLaunchKernelGGL((k_chunks<T, K, kModeVerify>), dim3(grid), dim3(NT), 0, s, jl);
+                break;
+            }
+            return hipErrorInvalidValue;
         case kModeDigest: hipLaunchKernelGGL((k_chunks<T, K, kModeDigest>), dim3(grid), dim3(NT), 0, s, jl); break;
-        case kModeVerify: hipLaunchKernelGGL((k_chunks<T, K, kModeVerify>), dim3(grid), dim3(NT), 0, s, jl); break;
         case kModeRestore: hipLaunchKernelGGL((k_chunks<T, K, kModeRestore>), dim3(grid), dim3(NT), 0, s, jl); break;
         default: return hipErrorInvalidValue;
     }
@@ -1185,17 +1378,23 @@ hipError_t occ_tk(int mode, int* n) {
             }
             return e;
         }
-        case kModeClassify: {
-            hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeClassify>, NT, 0);
-            if constexpr (T >= 64) {
-                int m = 0;
-                if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, k_dump_stream<T, K, true>, T, 0);
-                if (e == hipSuccess && m < *n) *n = m;
+        case kModeClassify:
+            if constexpr (16u * T * K < kScanMinChunk) {
+                hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeClassify>, NT, 0);
+                if constexpr (T >= 64) {
+                    int m = 0;
+                    if (e == hipSuccess)
+                        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&m, k_dump_stream<T, K, true>, T, 0);
+                    if (e == hipSuccess && m < *n) *n = m;
+                }
+                return e;
             }
-            return e;
-        }
+            return hipErrorInvalidValue;
+        case kModeVerify:
+            if constexpr (16u * T * K < kScanMinChunk)
+                return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeVerify>, NT, 0);
+            return hipErrorInvalidValue;
         case kModeDigest: return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeDigest>, NT, 0);
-        case kModeVerify: return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeVerify>, NT, 0);
         case kModeRestore: return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeRestore>, NT, 0);
         default: return hipErrorInvalidValue;
     }
@@ -1221,6 +1420,26 @@ hipError_t launch_chunks(int T, int K, int mode, const JobList& jl, int grid, hi
     MK_TILES(MK_LAUNCH)
 #undef MK_LAUNCH
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_scan(bool verify, const JobList& jl, int cus, hipStream_t s) {
+    if (jl.n_jobs < 1 || jl.n_jobs > (uint32_t)kMaxJobs || cus < 1 || jl.job[0].C < kScanMinChunk)
+        return hipErrorInvalidValue;
+    const uint64_t total = jl.prefix[jl.n_jobs];
+    if (total == 0) return hipSuccess;
+    if (!verify && (jl.n_jobs != 1 || total > 0xFFFFFFFFull)) return hipErrorInvalidValue;
+    // two work-groups per CU (128 registers a lane)
+    const int T = scan_width(jl.job[0].C);
+    const uint64_t wgs = T == 64 ? (total + 7) / 8 : total;
+    const unsigned grid = (unsigned)(wgs < 2ull * cus ? wgs : 2ull * cus);
+    if (T == 64) {
+        if (verify) hipLaunchKernelGGL((k_scan<64, true>), dim3(grid), dim3(512), 0, s, jl);
+        else hipLaunchKernelGGL((k_scan<64, false>), dim3(grid), dim3(512), 0, s, jl);
+    } else {
+        if (verify) hipLaunchKernelGGL((k_scan<512, true>), dim3(grid), dim3(512), 0, s, jl);
+        else hipLaunchKernelGGL((k_scan<512, false>), dim3(grid), dim3(512), 0, s, jl);
+    }
+    return hipGetLastError();
 }
 
 hipError_t chunks_occupancy(int T, int K, int mode, int* n) {

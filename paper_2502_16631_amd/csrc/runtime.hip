@@ -240,61 +240,6 @@ uint64_t record_len(const ImageView& v, uint64_t g, uint64_t len) {
     return want;
 }
 
-int parse_image(const uint8_t* img, uint64_t len, ImageView* v, bool check_tables) {
-    if (len < kHeader || memcmp(img, "MICKPT01", 8) != 0) return CKPT_ECORRUPT;
-    if (host_crc32c(img, 60) != get32(img + 60)) return CKPT_ECORRUPT;
-    const uint32_t version = get32(img + 8);
-    v->flags = get32(img + 12);
-    v->C = get32(img + 16);
-    v->n_allocs = get32(img + 20);
-    v->n_chunks = get64(img + 24);
-    v->D = get64(img + 32);
-    v->base_state = get32(img + 40);
-    const uint32_t reserved = get32(img + 44);
-    v->N = get64(img + 48);
-    v->tables_crc = get32(img + 56);
-    if (version != 1 || (v->flags & ~(kFlagDelta | kFlagCodec)) || reserved != 0 || !valid_chunk(v->C))
-        return CKPT_ECORRUPT;
-    if (v->n_chunks > (1ull << 40) || v->n_allocs > (1u << 24)) return CKPT_ECORRUPT;
-    const bool codec = v->flags & kFlagCodec;
-    v->tl = tables_len(v->n_allocs, v->n_chunks, codec);
-    if (len != kHeader + v->tl + v->D) return CKPT_ECORRUPT;
-    v->recs = img + kHeader;
-    v->crcs = v->recs + 32ull * v->n_allocs;
-    v->rlens = codec ? v->crcs + 4 * v->n_chunks : nullptr;
-    v->kinds = v->crcs + (codec ? 8 : 4) * v->n_chunks;
-    v->payload = img + kHeader + v->tl;
-    // allocation records: chunk grid, sizes, padding
-    uint64_t g = 0, total = 0;
-    for (uint64_t a = 0; a < v->n_allocs; ++a) {
-        const uint8_t* r = v->recs + 32 * a;
-        if (get64(r + 16) != g || get32(r + 28) != 0) return CKPT_ECORRUPT;
-        g += ceil_div(get64(r + 8), v->C);
-        total += get64(r + 8);
-        if (g > v->n_chunks) return CKPT_ECORRUPT;
-    }
-    if (g != v->n_chunks || total != v->N) return CKPT_ECORRUPT;
-    if (!(v->flags & 1u) && v->base_state != 0) return CKPT_ECORRUPT;
-    for (const uint8_t* p = v->kinds + v->n_chunks; p < v->recs + v->tl; ++p)
-        if (*p) return CKPT_ECORRUPT;
-    if (check_tables) {
-        if (host_crc32c(v->recs, v->tl) != v->tables_crc) return CKPT_ECORRUPT;
-        // kinds and payload length
-        uint64_t dsum = 0;
-        for (uint64_t a = 0, gg = 0; a < v->n_allocs; ++a) {
-            const uint64_t size = get64(v->recs + 32 * a + 8), nk = ceil_div(size, v->C);
-            for (uint64_t k = 0; k < nk; ++k, ++gg) {
-                const uint64_t rl = record_len(*v, gg, k + 1 == nk ? size - k * v->C : v->C);
-                if (rl == kBadRecord) return CKPT_ECORRUPT;
-                dsum += rl;
-            }
-        }
-        if (dsum != v->D) return CKPT_ECORRUPT;
-        v->state_digest = host_crc32c(v->recs, 32ull * v->n_allocs + 4 * v->n_chunks);
-    }
-    return CKPT_OK;
-}
-
 // Kinds of the chunks [b, e), counted without branches (vectorized, and no
 // mispredictions on mixed kinds): ZERO, DATA, UNCHANGED, others.
 static void count_kinds(const uint8_t* kinds, uint64_t b, uint64_t e, uint64_t n[4]) {
@@ -339,6 +284,67 @@ uint64_t scan_kinds(const ImageView& v, const std::vector<uint64_t>& bounds, uin
         }
     }
     return pos;
+}
+
+int parse_image(const uint8_t* img, uint64_t len, ImageView* v, bool check_tables) {
+    if (len < kHeader || memcmp(img, "MICKPT01", 8) != 0) return CKPT_ECORRUPT;
+    if (host_crc32c(img, 60) != get32(img + 60)) return CKPT_ECORRUPT;
+    const uint32_t version = get32(img + 8);
+    v->flags = get32(img + 12);
+    v->C = get32(img + 16);
+    v->n_allocs = get32(img + 20);
+    v->n_chunks = get64(img + 24);
+    v->D = get64(img + 32);
+    v->base_state = get32(img + 40);
+    const uint32_t reserved = get32(img + 44);
+    v->N = get64(img + 48);
+    v->tables_crc = get32(img + 56);
+    if (version != 1 || (v->flags & ~(kFlagDelta | kFlagCodec)) || reserved != 0 || !valid_chunk(v->C))
+        return CKPT_ECORRUPT;
+    if (v->n_chunks > (1ull << 40) || v->n_allocs > (1u << 24)) return CKPT_ECORRUPT;
+    const bool codec = v->flags & kFlagCodec;
+    v->tl = tables_len(v->n_allocs, v->n_chunks, codec);
+    if (len != kHeader + v->tl + v->D) return CKPT_ECORRUPT;
+    v->recs = img + kHeader;
+    v->crcs = v->recs + 32ull * v->n_allocs;
+    v->rlens = codec ? v->crcs + 4 * v->n_chunks : nullptr;
+    v->kinds = v->crcs + (codec ? 8 : 4) * v->n_chunks;
+    v->payload = img + kHeader + v->tl;
+    // allocation records: chunk grid, sizes, padding
+    uint64_t g = 0, total = 0;
+    for (uint64_t a = 0; a < v->n_allocs; ++a) {
+        const uint8_t* r = v->recs + 32 * a;
+        if (get64(r + 16) != g || get32(r + 28) != 0) return CKPT_ECORRUPT;
+        g += ceil_div(get64(r + 8), v->C);
+        total += get64(r + 8);
+        if (g > v->n_chunks) return CKPT_ECORRUPT;
+    }
+    if (g != v->n_chunks || total != v->N) return CKPT_ECORRUPT;
+    if (!(v->flags & 1u) && v->base_state != 0) return CKPT_ECORRUPT;
+    for (const uint8_t* p = v->kinds + v->n_chunks; p < v->recs + v->tl; ++p)
+        if (*p) return CKPT_ECORRUPT;
+    if (check_tables) {
+        if (host_crc32c(v->recs, v->tl) != v->tables_crc) return CKPT_ECORRUPT;
+        // kinds and payload length
+        uint64_t dsum = 0;
+        if (!codec) {
+            uint64_t n[4] = {0, 0, 0, 0};
+            dsum = scan_kinds(*v, {}, nullptr, nullptr, n);
+            if (n[3] || (n[2] && !(v->flags & kFlagDelta))) return CKPT_ECORRUPT;
+        } else {
+            for (uint64_t a = 0, gg = 0; a < v->n_allocs; ++a) {
+                const uint64_t size = get64(v->recs + 32 * a + 8), nk = ceil_div(size, v->C);
+                for (uint64_t k = 0; k < nk; ++k, ++gg) {
+                    const uint64_t rl = record_len(*v, gg, k + 1 == nk ? size - k * v->C : v->C);
+                    if (rl == kBadRecord) return CKPT_ECORRUPT;
+                    dsum += rl;
+                }
+            }
+        }
+        if (dsum != v->D) return CKPT_ECORRUPT;
+        v->state_digest = host_crc32c(v->recs, 32ull * v->n_allocs + 4 * v->n_chunks);
+    }
+    return CKPT_OK;
 }
 
 }  // namespace mk
@@ -546,6 +552,35 @@ JobList one_job(const ChunkJob& j, uint32_t* ticket) {
     jl.ticket = ticket;
     jl.n_jobs = 1;
     return jl;
+}
+
+// Digests and kinds of the chunks of j. Chunks of at least kScanMinChunk
+// bytes take the digest pass; smaller ones, too short for its batches, the
+// ticketed kernel of their tile.
+hipError_t launch_classify(ckpt_ctx* c, int T, int K, ChunkJob j, uint32_t* ticket, hipStream_t s) {
+    hipError_t e;
+    if (j.C >= kScanMinChunk) {
+        if ((e = get_consts(c, scan_width(j.C), j.C, &j.ec)) != hipSuccess) return e;
+        return launch_scan(false, one_job(j, ticket), c->num_cu, s);
+    }
+    int grid;
+    if ((e = grid_for(c, T, K, kModeClassify, j.g1 - j.g0, &grid)) != hipSuccess) return e;
+    return launch_chunks(T, K, kModeClassify, one_job(j, ticket), grid, s);
+}
+
+// Verify mode over the jobs of jl, on at most `cus` CUs.
+hipError_t launch_verify(ckpt_ctx* c, int T, int K, JobList& jl, int cus, hipStream_t s) {
+    const uint32_t C = jl.job[0].C;
+    hipError_t e;
+    if (C >= kScanMinChunk) {
+        const EngineConsts* ec;
+        if ((e = get_consts(c, scan_width(C), C, &ec)) != hipSuccess) return e;
+        for (uint32_t i = 0; i < jl.n_jobs; ++i) jl.job[i].ec = ec;
+        return launch_scan(true, jl, cus, s);
+    }
+    int grid;
+    if ((e = grid_for(c, T, K, kModeVerify, jl.prefix[jl.n_jobs], &grid)) != hipSuccess) return e;
+    return launch_chunks(T, K, kModeVerify, jl, std::max(1, grid * cus / c->num_cu), s);
 }
 
 // Staging windows: whole chunks, at most `slot` bytes of payload each.
@@ -864,7 +899,7 @@ static void drain(ckpt_ctx* c) {
 
 // Device buffers of one dump: the context's own, or slices of the array.
 struct DumpBufs {
-    DevBuf *descs, *arc, *kinds, *staging, *ctl, *amap, *prevcrc, *off, *wb, *rlen, *cmeta;
+    DevBuf *descs, *arc, *kinds, *staging, *ctl, *amap, *prevcrc, *off, *wb, *rlen, *cmeta, *list;
     StatusBuf* status;
 };
 
@@ -884,9 +919,14 @@ int mk::dump_impl(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image* 
 // set of buffers and events.
 constexpr uint64_t kRing = 4;
 // Result words of a dump in pinned memory: window totals, error, (pad, kind
-// counts,) the set-up's and the chunk kernel's stamps, the last kernel's two.
-constexpr uint32_t kRepErr = kRing + 1, kRepStamps = kRing + 7, kRepWords = kRing + 9;
+// counts,) stamps (set-up, chunk kernel, three for each of the first pieces
+// of a delta), the last kernel's two stamps.
+constexpr uint32_t kStampPieces = 16, kStamps = 2 + 3 * kStampPieces;
+constexpr uint32_t kRepErr = kRing + 1, kRepStamps = kRing + 7, kRepWords = kRepStamps + kStamps;
 constexpr uint64_t kHwWords = kRepWords + 3;
+// Pieces of a delta's pipeline (launch_delta): at most this many when their
+// number follows from the staging, and the least bytes of state worth one.
+constexpr uint64_t kMaxDeltaPieces = 64, kDeltaPiece = 128ull << 20;
 
 static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image* prev, ckpt_image** out,
                     const ckpt_opts* o, void* stream, ckpt_result* res, PayloadSink* sink, const NaCall* na) {
@@ -967,7 +1007,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     // device buffers: the context's own, or slices of the static array
     DevBuf na_bufs[8];
     DumpBufs B = {&c->descs, &c->arc, &c->kinds, &c->staging, &c->ctl, &c->amap, &c->prevcrc, &c->off, &c->wb,
-                  &c->rlen, &c->cmeta, &c->status};
+                  &c->rlen, &c->cmeta, &c->list, &c->status};
     if (na) {
         uint8_t* base = na->dev->ptr;
         na_bufs[0].attach(base + kNaDescs, 64ull * kNaMaxAllocs);
@@ -978,11 +1018,49 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         na_bufs[5].attach(base + kNaAmap, 4 * kNaMaxChunks);
         na_bufs[6].attach(base + kNaPrev, 4 * kNaMaxChunks);
         B = {&na_bufs[0], &na_bufs[1], &na_bufs[2], &na_bufs[3], &na_bufs[4], &na_bufs[5], &na_bufs[6], &na_bufs[7],
-             &na_bufs[7], &na_bufs[7], &na_bufs[7], &na->dev->status};   // [7]: empty, never used
+             &na_bufs[7], &na_bufs[7], &na_bufs[7], &na_bufs[7], &na->dev->status};   // [7]: empty, never used
     }
 
     const bool use_graph = o && (o->flags & CKPT_OPT_GRAPH) && wins.size() == 1 && !per_alloc;
-    const bool two_pass = prev != nullptr && wins.size() == 1 && !use_graph && nc > 0 && !na;
+    // A delta's pipeline (launch_delta): its pieces' bounds and their places in
+    // staging. With room for everything each piece has its own part; else the
+    // pieces go round a ring of slots.
+    bool two_pass = prev != nullptr && nc > 0 && !use_graph && !codec && !na && !(per_alloc && wins.size() > 1);
+    std::vector<uint64_t> piece;   // first chunks, and nc
+    if (two_pass) {
+        const uint64_t all = nc * C;
+        if (wins.size() > 1 && o && o->window_bytes) {
+            for (const Window& w : wins) piece.push_back(w.g0);   // the caller's windows
+        } else if (wins.size() > 1 && ceil_div(all, 8) > c->budget / 3) {
+            const uint64_t per = std::max<uint64_t>(1, c->budget / 4 / C);
+            for (uint64_t g = 0; g < nc; g += per) piece.push_back(g);
+        } else if (wins.size() == 1 && all < 8 * kDeltaPiece) {
+            const uint64_t p = std::min<uint64_t>(nc, std::max<uint64_t>(1, all / kDeltaPiece));
+            for (uint64_t i = 0; i < p; ++i) piece.push_back(nc * i / p);
+        } else {
+            // short first pieces, so that the link starts early, and short last
+            // ones, so that little is left to copy when the last digest ends
+            static const uint32_t at32[] = {0, 2, 5, 9, 13, 17, 21, 25, 29, 31};
+            for (uint32_t x : at32)
+                if (piece.empty() || nc * x / 32 > piece.back()) piece.push_back(nc * x / 32);
+        }
+        piece.push_back(nc);
+        if (wins.size() > 1) {
+            uint64_t most = 0;
+            for (size_t i = 0; i + 1 < piece.size(); ++i) most = std::max(most, piece[i + 1] - piece[i]);
+            slot = most * C;
+            nslots = (int)std::min<uint64_t>(piece.size() - 1, std::max<uint64_t>(2, c->budget / slot));
+            if (o && o->slots) nslots = std::min(nslots, std::max(2, (int)o->slots));
+        }
+        if (piece.size() - 1 > kMaxDeltaPieces) {
+            two_pass = false;   // a great many windows: one pass each
+            pick_staging(c, o, nc, C, &slot, &nslots);
+        }
+    }
+    const uint64_t n_pieces = two_pass ? piece.size() - 1 : 0;
+    const bool ring = two_pass && wins.size() > 1;
+    // One short piece: gathered straight into a pinned image.
+    const bool small_delta = two_pass && !ring && n_pieces == 1 && !sink && upper <= kDirectDump;
     // A short full dump writes its payload straight into the image, when that
     // is pinned: no staging, no wait for the payload's length, no copy (8
     // allocations of 16 MiB: 420 -> 340 us). The image is then allocated at
@@ -992,7 +1070,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     const bool small = wins.size() == 1 && nc > 0 && !use_graph && !codec && !per_alloc && !sink && !two_pass &&
                        upper <= kDirectDump;
     // stage times: of a short dump by stamps, else by events
-    const bool stamped = small && !(o && (o->flags & CKPT_OPT_NO_TIMING));
+    const bool stamped = (small || two_pass) && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     const bool timing = !stamped && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     HIPCHK(hipSetDevice(c->device));
     if (!na) HIPCHK(ensure_copy_streams(c, ncs));
@@ -1010,20 +1088,21 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         HIPCHK(launch_fill64(B.status->words(), 0, kNaStatusWords, c->s_main));
         na->dev->cleared = true;
     }
+    if (two_pass)   // two scans over 256-chunk tiles, each with words of its own
+        for (uint64_t i = 0; i < n_pieces; ++i) max_win = std::max(max_win, 2 * ceil_div(piece[i + 1] - piece[i], 256));
     HIPCHK(B.status->ensure(8 * (max_win + 64), c->s_main));
     const uint64_t W = wins.size();
     const uint64_t codec_p = codec ? (W == 1 ? std::min<uint64_t>(kCodecPieces, nc) : W) : 0;   // codec pieces
-    // ctl: tickets[n_tk] | wtot[kRing + 1] (u64) | err (+pad) | counts[4] (u64) | stamps[2] (u64); window
+    // ctl: tickets[n_tk] | wtot[kRing + 1] (u64) | err (+pad) | counts[4] (u64) | stamps (u64); window
     // tickets and totals on the ring, codec pieces' tickets by piece
-    const uint64_t n_tk = std::max<uint64_t>(std::max<uint64_t>(kRing, 2 * kCodecPieces + 2), codec_p) + 1;
+    const uint64_t n_tk = std::max<uint64_t>({kRing, 2 * n_pieces + 2, codec_p}) + 1;
     const uint64_t ctl_tk = 0, ctl_wt = round16(4 * (n_tk + 1)),
-                   ctl_err = ctl_wt + 8 * (kRing + 1), ctl_cnt = ctl_err + 16, ctl_end = ctl_cnt + 48;
+                   ctl_err = ctl_wt + 8 * (kRing + 1), ctl_cnt = ctl_err + 16, ctl_end = ctl_cnt + 32 + 8 * kStamps;
     HIPCHK(B.ctl->ensure(ctl_end));
-    HIPCHK(ensure_hsmall(c, 8 * kHwWords + 8 * kCodecPieces));   // results, piece lengths
+    HIPCHK(ensure_hsmall(c, 8 * kHwWords + 16 * n_pieces));   // results; pieces' payload bounds
     // events: [0, kRing) window done, [kRing, kRing + nslots) slot free; codec pieces: 4 per piece
-    HIPCHK(ensure_events(c, std::max<size_t>(std::max<size_t>(kRing + (size_t)nslots + 2, 4 * codec_p + 1),
-                                             kCodecPieces + 1)));
-    if (timing) HIPCHK(ensure_tevents(c, std::max<uint64_t>(2 * std::max<uint64_t>(kRing, 2 * codec_p), 4 * kCodecPieces)));
+    HIPCHK(ensure_events(c, std::max<size_t>({kRing + (size_t)nslots + 2, 4 * codec_p + 1, 2 * n_pieces})));
+    if (timing) HIPCHK(ensure_tevents(c, 2 * std::max<uint64_t>(kRing, 2 * codec_p)));
     const EngineConsts* ec;
     if (na) {
         // engine constants in the array, rebuilt when the tile or chunk size
@@ -1075,6 +1154,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         sj.C = C;
         sj.map = B.amap->as<uint32_t>();
         sj.add_fill(ctl, (ctl_cnt + 32) / 4, 0);
+        sj.add_fill(stamps + 1, 2 * (kStamps - 1), 0);
         sj.stamp = stamped ? stamps : nullptr;
         sj.add_fill(B.kinds->p, ceil_div(tl - 32ull * n - 4 * nc, 4), 0);
         HIPCHK(launch_setup(sj, c->s_main));
@@ -1099,7 +1179,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         na_img.pinned = false;
         im = &na_img;
         himg = na->out;
-    } else if ((W > 1 && !stage_all) || small) {
+    } else if ((W > 1 && !stage_all && !two_pass) || small || small_delta) {
         im = image_new(kHeader + tl + upper);
         if (!im) return CKPT_ENOMEM;
         himg = im->p;
@@ -1107,6 +1187,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     }
     // the device can write the image's tables, and all of a small image
     const bool host_tables = na ? pinned_range(na->out, kHeader + tl) : true;
+    const bool gather_direct = small_delta && im->pinned;
     const bool direct = small && (na ? na->cap >= kHeader + tl + upper && pinned_range(na->out, kHeader + tl + upper)
                                      : im->pinned);
     // the image can take a payload of D bytes (the caller's buffer is fixed)
@@ -1204,7 +1285,6 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     // digests, so a single pass would hold every chunk's look-back until its
     // digest is done; its payload is small, so the extra read of D costs
     // little.
-    uint64_t delta_pieces = 0;
     // the DATA chunks of [g0, g1) to their records at c->off, in staging
     // from sp on, which holds the payload from offset base
     auto gather_job = [&](uint64_t g0, uint64_t g1, uint8_t* sp, uint64_t base) {
@@ -1221,117 +1301,130 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         gj.slot_base = base;
         return gj;
     };
-    // The delta dump in one window runs as a pipeline over kCodecPieces pieces
-    // of equal chunk counts. On the main stream, per piece: digests and kinds
-    // (classify), the piece's payload offsets relative to its own start (scan)
-    // and its DATA chunks gathered into its own part of staging (from its
-    // first chunk's bound g0 C on); the piece's payload length comes back to
-    // the host, which places the piece after the earlier ones and queues its
-    // copy-out while the main stream works on later pieces. The image is
-    // allocated once the first piece's length is known, at that length scaled
-    // to all chunks plus a margin: a delta's only firm bound is the whole
-    // state, which would hold that much pinned memory for a small image. A
-    // payload that outgrows the estimate moves, with what was copied so far,
-    // to an image of the bound (with a file sink, the bound from the start).
+    // The delta dump runs as a pipeline over its pieces. On the main stream,
+    // per piece: digests and kinds (classify), the piece's payload offsets
+    // relative to its own start (scan) and its DATA chunks gathered into its
+    // place in staging; the piece's payload length comes back to the host,
+    // which places the piece after the earlier ones and queues its copy-out
+    // while the main stream works on later pieces (on a ring, a piece is
+    // launched once the copy-out of the one before it in its slot is queued).
+    // The image is allocated once the first piece's length is known, at that
+    // length scaled to all chunks plus a margin: a delta's only firm bound is
+    // the whole state, which would hold that much pinned memory for a small
+    // image. A payload that outgrows the estimate moves, with what was copied
+    // so far, to a larger image (with a file sink, the bound from the start).
     // Returns the payload length in *D_out.
+    auto launch_piece = [&](uint64_t i) -> hipError_t {
+        hipError_t e;
+        const uint64_t g0 = piece[i], g1 = piece[i + 1];
+        uint64_t* st = stamped && i < kStampPieces ? stamps + 2 + 3 * i : nullptr;
+        uint32_t ep;
+        if ((e = B.status->next(c->s_main, &ep)) != hipSuccess) return e;
+        ChunkJob j;
+        memset(&j, 0, sizeof(j));
+        j.allocs = B.descs->as<AllocDesc>();
+        j.n_allocs = n;
+        j.C = C;
+        j.amap = B.amap->as<uint32_t>();
+        j.g0 = g0;
+        j.g1 = g1;
+        j.ec = ec;
+        j.crc_out = crc_dev;
+        j.kind_out = kind_dev;
+        j.prev_crc = prev_dev;
+        j.err = err;
+        j.epoch = ep;
+        j.stamp = st;
+        if ((e = launch_classify(c, T, K, j, tickets + 2 * i, c->s_main)) != hipSuccess) return e;
+        const uint64_t tiles = ceil_div(g1 - g0, 256);
+        OffJob oj;
+        memset(&oj, 0, sizeof(oj));
+        oj.allocs = B.descs->as<AllocDesc>();
+        oj.n_allocs = n;
+        oj.C = C;
+        oj.amap = B.amap->as<uint32_t>();
+        oj.n_chunks = g1 - g0;
+        oj.g_base = g0;
+        oj.kind = kind_dev;
+        oj.off = B.off->as<uint64_t>();
+        oj.per_window = g1 - g0 + 1;
+        oj.wb = hw + kHwWords + 2 * i;   // pinned: the piece's length in the second word
+        oj.n_windows = 1;
+        oj.status = B.status->words();
+        oj.ticket = tickets + 2 * i + 1;
+        oj.counts = counts;
+        oj.err = err;
+        oj.epoch = ep;
+        oj.list = B.list->as<uint64_t>() + g0;
+        oj.n_list = B.wb->as<uint64_t>() + i;
+        oj.status2 = B.status->words() + tiles;
+        oj.stamp = st ? st + 1 : nullptr;
+        if ((e = launch_offsets(oj, (int)std::min<uint64_t>(tiles, 8ull * c->num_cu), c->s_main)) != hipSuccess) return e;
+        if (ring && i >= (uint64_t)nslots &&   // the slot's payload is copied out
+            (e = hipStreamWaitEvent(c->s_main, ev[n_pieces + i - nslots], 0)) != hipSuccess)
+            return e;
+        uint8_t* sp = gather_direct ? himg + kHeader + tl
+                                    : B.staging->as<uint8_t>() + (ring ? (i % nslots) * slot : g0 * C);
+        GatherJob gj = gather_job(g0, g1, sp, 0);
+        gj.list = oj.list;
+        gj.n_list = oj.n_list;
+        gj.stamp = st ? st + 2 : nullptr;
+        if ((e = launch_gather(gj, 4 * c->num_cu, c->s_main)) != hipSuccess) return e;
+        return gather_direct ? hipSuccess : hipEventRecord(ev[i], c->s_main);
+    };
     auto launch_delta = [&](uint64_t* D_out) -> hipError_t {
         hipError_t e;
-        const uint64_t P = std::min<uint64_t>(kCodecPieces, nc);
+        const uint64_t P = n_pieces;
         if ((e = B.off->ensure(8 * nc)) != hipSuccess) return e;
-        if ((e = B.wb->ensure(16 * P)) != hipSuccess) return e;
-        uint64_t* htot = hw + kHwWords;   // [P] piece lengths
-        std::vector<uint64_t> gb(P + 1);
-        for (uint64_t i = 0; i <= P; ++i) gb[i] = nc * i / P;
-        for (uint64_t i = 0; i < P; ++i) {
-            const uint64_t g0 = gb[i], g1 = gb[i + 1];
-            uint32_t ep;
-            if ((e = B.status->next(c->s_main, &ep)) != hipSuccess) return e;
-            ChunkJob j;
-            memset(&j, 0, sizeof(j));
-            j.allocs = B.descs->as<AllocDesc>();
-            j.n_allocs = n;
-            j.C = C;
-            j.amap = B.amap->as<uint32_t>();
-            j.g0 = g0;
-            j.g1 = g1;
-            j.ec = ec;
-            j.crc_out = crc_dev;
-            j.kind_out = kind_dev;
-            j.prev_crc = prev_dev;
-            j.err = err;
-            j.epoch = ep;
-            int grid;
-            if ((e = grid_for(c, T, K, kModeClassify, g1 - g0, &grid)) != hipSuccess) return e;
-            if (timing && (e = hipEventRecord(c->tevents[4 * i], c->s_main)) != hipSuccess) return e;
-            if ((e = launch_chunks(T, K, kModeClassify, one_job(j, tickets + 2 * i), grid, c->s_main)) != hipSuccess)
-                return e;
-            if (timing && (e = hipEventRecord(c->tevents[4 * i + 1], c->s_main)) != hipSuccess) return e;
-            OffJob oj;
-            memset(&oj, 0, sizeof(oj));
-            oj.allocs = B.descs->as<AllocDesc>();
-            oj.n_allocs = n;
-            oj.C = C;
-            oj.amap = B.amap->as<uint32_t>();
-            oj.n_chunks = g1 - g0;
-            oj.g_base = g0;
-            oj.kind = kind_dev;
-            oj.off = B.off->as<uint64_t>();
-            oj.per_window = g1 - g0 + 1;
-            oj.wb = B.wb->as<uint64_t>() + 2 * i;
-            oj.n_windows = 1;
-            oj.status = B.status->words();
-            oj.ticket = tickets + 2 * i + 1;
-            oj.counts = counts;
-            oj.err = err;
-            oj.epoch = ep;
-            const uint64_t tiles = ceil_div(g1 - g0, 256);
-            if ((e = launch_offsets(oj, (int)std::min<uint64_t>(tiles, 8ull * c->num_cu), c->s_main)) != hipSuccess)
-                return e;
-            if (timing && (e = hipEventRecord(c->tevents[4 * i + 2], c->s_main)) != hipSuccess) return e;
-            uint8_t* sp = B.staging->as<uint8_t>() + g0 * C;
-            if ((e = launch_gather(gather_job(g0, g1, sp, 0), pack_grid(c, g1 - g0), c->s_main)) != hipSuccess)
-                return e;
-            if (timing && (e = hipEventRecord(c->tevents[4 * i + 3], c->s_main)) != hipSuccess) return e;
-            if ((e = hipMemcpyAsync(htot + i, B.wb->as<uint64_t>() + 2 * i + 1, 8, hipMemcpyDeviceToHost,
-                                    c->s_main)) != hipSuccess)
-                return e;
-            if ((e = hipEventRecord(ev[i], c->s_main)) != hipSuccess) return e;
+        if ((e = B.wb->ensure(8 * P)) != hipSuccess) return e;
+        if ((e = B.list->ensure(8 * nc)) != hipSuccess) return e;
+        if (gather_direct) {
+            t_link0 = now_ns();
+            return launch_piece(0);
         }
-        uint64_t D = 0, cap = 0;   // payload so far; payload capacity of the image
+        const uint64_t ahead = ring ? std::min<uint64_t>(P, nslots) : P;
+        for (uint64_t i = 0; i < ahead; ++i)
+            if ((e = launch_piece(i)) != hipSuccess) return e;
+        uint64_t D = 0, cap = im ? upper : 0;   // payload so far; payload capacity of the image
         for (uint64_t i = 0; i < P; ++i) {
-            const uint64_t g0 = gb[i], g1 = gb[i + 1];
+            const uint64_t g0 = piece[i], g1 = piece[i + 1];
             if ((e = hipEventSynchronize(ev[i])) != hipSuccess) return e;
-            const uint64_t Di = htot[i];
+            const uint64_t Di = hw[kHwWords + 2 * i + 1];
             if (Di > (g1 - g0) * C || D + Di > upper) return hipErrorIllegalState;
-            if (!im) {
-                const uint64_t est = sink ? upper
-                                          : std::min<uint64_t>(upper, ceil_div(Di * nc, g1 - g0) + Di / 4 + (64ull << 20));
-                im = image_new(kHeader + tl + est);
-                if (!im) return hipErrorOutOfMemory;
+            if (!im || D + Di > cap) {
+                const uint64_t guess = (D + Di) / g1 * nc + (D + Di) / 4 + (64ull << 20);
+                const uint64_t est = sink ? upper : std::min(upper, std::max({guess, D + Di, im ? 2 * cap : 0}));
+                ckpt_image* big = image_new(kHeader + tl + est);
+                if (!big) return hipErrorOutOfMemory;
+                if (im) {
+                    // outgrown: what was copied so far moves along
+                    for (uint32_t k = 0; k < ncs; ++k)
+                        if ((e = hipStreamSynchronize(c->s_copy[k])) != hipSuccess) {
+                            image_release(big);
+                            return e;
+                        }
+                    memcpy(big->p + kHeader + tl, himg + kHeader + tl, D);
+                    image_release(im);
+                }
+                im = big;
                 himg = im->p;
                 cap = est;
                 if (sink) sink->begin(im);
-            } else if (D + Di > cap) {
-                // outgrown: an image of the bound, with the payload copied so far
-                for (uint32_t k = 0; k < ncs; ++k)
-                    if ((e = hipStreamSynchronize(c->s_copy[k])) != hipSuccess) return e;
-                ckpt_image* big = image_new(kHeader + tl + upper);
-                if (!big) return hipErrorOutOfMemory;
-                memcpy(big->p + kHeader + tl, himg + kHeader + tl, D);
-                image_release(im);
-                im = big;
-                himg = im->p;
-                cap = upper;
             }
             if (Di) {
-                hipStream_t cs = c->s_copy[i % ncs];
+                hipStream_t cs = c->s_copy[ring ? 0 : i % ncs];
                 if (!t_link0) t_link0 = now_ns();
                 if ((e = hipStreamWaitEvent(cs, ev[i], 0)) != hipSuccess) return e;
-                if ((e = copy_out(D, B.staging->as<uint8_t>() + g0 * C, Di, cs)) != hipSuccess) return e;
+                if ((e = copy_out(D, B.staging->as<uint8_t>() + (ring ? (i % nslots) * slot : g0 * C), Di, cs)) !=
+                    hipSuccess)
+                    return e;
             }
             D += Di;
+            if (ring && i + nslots < P) {
+                if ((e = hipEventRecord(ev[P + i], c->s_copy[0])) != hipSuccess) return e;
+                if ((e = launch_piece(i + nslots)) != hipSuccess) return e;
+            }
         }
-        delta_pieces = P;
         *D_out = D;
         return hipSuccess;
     };
@@ -1394,16 +1487,13 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         const uint64_t P = codec_p;
         std::vector<uint64_t> gb(P + 1);
         for (uint64_t i = 0; i <= P; ++i) gb[i] = one ? nc * i / P : (i < P ? wins[i].g0 : nc);
-        int grid;
         for (uint64_t i = 0; i < P; ++i) {
             const uint64_t g0 = gb[i], g1 = gb[i + 1];
             j.g0 = pj.g0 = g0;
             j.g1 = pj.g1 = g1;
             if (timing && (e = hipEventRecord(c->tevents[2 * i], c->s_main)) != hipSuccess) return e;
             if (g1 > g0) {
-                if ((e = grid_for(c, T, K, kModeClassify, g1 - g0, &grid)) != hipSuccess) return e;
-                if ((e = launch_chunks(T, K, kModeClassify, one_job(j, tickets + i), grid, c->s_main)) != hipSuccess)
-                    return e;
+                if ((e = launch_classify(c, T, K, j, tickets + i, c->s_main)) != hipSuccess) return e;
                 if ((e = launch_pack(pj, false, pack_grid(c, g1 - g0), c->s_main)) != hipSuccess) return e;
             }
             if (timing && (e = hipEventRecord(c->tevents[2 * i + 1], c->s_main)) != hipSuccess) return e;
@@ -1678,11 +1768,29 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     if (timing && !use_graph && (e = hipEventRecord(c->sev[3], c->s_main)) != hipSuccess) return fail_late(e);
     if (codec) memcpy(htab + len_a, rlen_h, rl_bytes);   // little-endian host
     if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return fail_late(e);
-    if (direct) {
-        D = hw[0];
+    if (direct || gather_direct) {
+        D = gather_direct ? hw[kHwWords + 1] : hw[0];
         if (D > upper) return fail_late(hipErrorIllegalState);
     }
-    if (stamped) kern_ns = stamp_ns(c, hw[kRepStamps + 1], hw[kRepWords]);
+    // stage times by stamps
+    uint64_t st_ns[4] = {0, 0, 0, 0};   // chunk kernels, scan, gather; set-up
+    if (stamped) {
+        const uint64_t* st = hw + kRepStamps;
+        if (two_pass) {
+            for (uint64_t i = 0; i < std::min<uint64_t>(n_pieces, kStampPieces); ++i) {
+                const uint64_t* p = st + 2 + 3 * i;
+                const uint64_t end = i + 1 < std::min<uint64_t>(n_pieces, kStampPieces) ? p[3] : hw[kRepWords];
+                st_ns[0] += stamp_ns(c, p[0], p[1]);
+                st_ns[1] += stamp_ns(c, p[1], p[2]);
+                st_ns[2] += stamp_ns(c, p[2], end);
+            }
+            kern_ns = st_ns[0] + st_ns[1] + st_ns[2];
+            st_ns[3] = stamp_ns(c, st[0], st[2]);
+        } else {
+            kern_ns = st_ns[0] = stamp_ns(c, st[1], hw[kRepWords]);
+            st_ns[3] = stamp_ns(c, st[0], st[1]);
+        }
+    }
     // the kinds are in the image now: counted while the payload copies run
     uint64_t n_kind[4] = {0, 0, 0, 0};   // ZERO, DATA, UNCHANGED, PACKED
     if (res) {
@@ -1691,7 +1799,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     // the tables' digest, on the host as well: 0.1 ms for 27 GB in 64 KiB
     // chunks, beside the payload copies
     const uint32_t tcrc = host_crc32c(htab, tl);
-    for (uint32_t i = 0; i < ncs && !direct; ++i)
+    for (uint32_t i = 0; i < ncs && !direct && !gather_direct; ++i)
         if ((e = hipStreamSynchronize(c->s_copy[i])) != hipSuccess) return fail_late(e);
     const uint64_t t_link1 = now_ns();
     if ((uint32_t)hw[kRepErr] != 0) return fail_late(hipErrorLaunchTimeOut);
@@ -1713,31 +1821,23 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     im->n = kHeader + tl + D;
 
     if (res) {
-        res->windows = (uint32_t)W;
+        res->windows = (uint32_t)(ring ? n_pieces : W);
         res->n_logical = N;
         res->n_payload = D;
         res->n_chunks = nc;
         res->link_bytes = D + tl + kHeader;
         res->ns_link = t_link0 ? t_link1 - t_link0 : 0;
         res->ns_kernel = stamped ? kern_ns : !timing ? 0 : (codec && W) ? timed_ns(c, codec_pairs) : use_graph ? timed_ns(c, 1) : kern_ns;
-        if (timing && two_pass)
-            for (uint64_t i = 0; i < delta_pieces; ++i) res->ns_kernel += span_ns(c->tevents[4 * i], c->tevents[4 * i + 3]);
         res->ns_total = now_ns() - t_start;
         // per-stage report (see ckpt_result.ns_stage)
         if (stamped) {
-            res->ns_stage[0] = stamp_ns(c, hw[kRepStamps], hw[kRepStamps + 1]);
-            res->ns_stage[1] = kern_ns;
+            res->ns_stage[0] = st_ns[3];
+            for (int i = 0; i < 3; ++i) res->ns_stage[1 + i] = st_ns[i];
             res->ns_stage[5] = stamp_ns(c, hw[kRepWords], hw[kRepWords + 1]);
         }
         if (timing) {
             if (!use_graph) res->ns_stage[0] = span_ns(c->sev[0], c->sev[1]);
-            if (two_pass) {
-                for (uint64_t i = 0; i < delta_pieces; ++i) {
-                    res->ns_stage[1] += span_ns(c->tevents[4 * i], c->tevents[4 * i + 1]);
-                    res->ns_stage[2] += span_ns(c->tevents[4 * i + 1], c->tevents[4 * i + 2]);
-                    res->ns_stage[3] += span_ns(c->tevents[4 * i + 2], c->tevents[4 * i + 3]);
-                }
-            } else if (codec && W) {
+            if (codec && W) {
                 uint64_t main_ns = 0, aux_ns = 0;   // classify + size pass; gather + encode
                 for (uint64_t i = 0; i < codec_pairs / 2; ++i) {
                     main_ns += span_ns(c->tevents[2 * i], c->tevents[2 * i + 1]);
@@ -2061,9 +2161,12 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             if ((e = digest_prepare(c, &ge->dig, c->arc.as<uint8_t>(), len_a, kind_dev, len_b, &dp, c->s_main)) !=
                 hipSuccess)
                 return drop(e);
-            int grid, vgrid;
+            int grid;
             if ((e = grid_for(c, T, K, kModeRestore, nc, &grid)) != hipSuccess) return drop(e);
-            if ((e = grid_for(c, T, K, kModeVerify, nc, &vgrid)) != hipSuccess) return drop(e);
+            const EngineConsts* sec;   // of the strict re-read: made before the capture
+            if (C >= kScanMinChunk && (e = get_consts(c, scan_width(C), C, &sec)) != hipSuccess) return drop(e);
+            int vgrid;
+            if (C < kScanMinChunk && (e = grid_for(c, T, K, kModeVerify, nc, &vgrid)) != hipSuccess) return drop(e);
             // the digest plan's small tables are prepared; nothing of it is captured
             if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return drop(e);
             hipGraph_t graph = nullptr;
@@ -2130,7 +2233,8 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             if (strict) {
                 j.bad = bad3;
                 j.flags = kJobVerifyAll;
-                step(launch_chunks(T, K, kModeVerify, one_job(j, wtk + 1), vgrid, c->s_main));
+                JobList vl = one_job(j, wtk + 1);
+                step(launch_verify(c, T, K, vl, c->num_cu, c->s_main));
             }
             CombineJob cj;
             memset(&cj, 0, sizeof(cj));
@@ -2393,12 +2497,12 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         j.err = err;
         j.flags = flags;
         j.stamp = stamped && !flags ? stamps + 2 : nullptr;
-        int grid;
         hipError_t e;
+        // the link copy's CUs take no other work
+        const int cus = c->num_cu - (hi ? kLinkCus : 0);
         if (!some) {
-            if ((e = grid_for(c, T, K, kModeVerify, nc, &grid)) != hipSuccess) return e;
-            if (hi) grid -= grid * kLinkCus / c->num_cu;   // the link copy's CUs take no other work
-            return launch_chunks(T, K, kModeVerify, one_job(j, wtk + W), grid, c->s_main);
+            JobList jl = one_job(j, wtk + W);
+            return launch_verify(c, T, K, jl, cus, c->s_main);
         }
         for (uint64_t w0 = 0; w0 < W; w0 += kMaxJobs) {
             JobList jl;
@@ -2414,8 +2518,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             }
             jl.prefix[jl.n_jobs] = tot;
             jl.ticket = wtk + W;
-            if ((e = grid_for(c, T, K, kModeVerify, tot, &grid)) != hipSuccess) return e;
-            if ((e = launch_chunks(T, K, kModeVerify, jl, grid, c->s_main)) != hipSuccess) return e;
+            if ((e = launch_verify(c, T, K, jl, cus, c->s_main)) != hipSuccess) return e;
         }
         return hipSuccess;
     };

@@ -556,11 +556,8 @@ void restore_validated(ckpt_server* s, Req* r) {
         j.ref_crc = reinterpret_cast<const uint32_t*>(L.arc.as<uint8_t>() + 32ull * r->n);
         j.bad = reinterpret_cast<unsigned long long*>(ctl + 40);
         j.err = reinterpret_cast<uint32_t*>(ctl + 56);
-        int grid;
-        SCHK(grid_for(c, T, K, kModeVerify, r->nc, &grid));
-        uint32_t* tk = next_ticket_slot(s);
-        SCHK(launch_fill32(tk, 0, 1, s->s_rest));
-        SCHK(launch_chunks(T, K, kModeVerify, one_job(j, tk), grid, s->s_rest));
+        JobList jl = one_job(j, nullptr);   // (verify takes no tickets)
+        SCHK(launch_verify(c, T, K, jl, c->num_cu, s->s_rest));
         SCHK(hipMemcpyAsync(L.hs + 64, ctl + 40, 8, hipMemcpyDeviceToHost, s->s_rest));
         SCHK(hipEventRecord(L.fin, s->s_rest));
         r->phase = kVerify;

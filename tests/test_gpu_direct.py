@@ -12,7 +12,9 @@ torch = pytest.importorskip("torch")
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 
+from oracle import oracle as corc  # noqa: E402
 from paper_2502_16631_amd import mickpt as mk  # noqa: E402
+import workloads  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -159,3 +161,40 @@ def test_short_dumps_into_pinned_and_pageable_memory(ctx, c):
             assert rc == 0
             got.append((delta.tobytes(), r.n_unchanged, r.n_data, r.n_payload))
     assert got[0] == got[1] and got[0][1] > 0
+
+
+@pytest.mark.parametrize("c", [4096, 8192, 16384, 65536, 131072, 1 << 20])
+@pytest.mark.parametrize("budget", [128 << 20, 150 << 20, 1 << 30])
+def test_deltas_in_pieces_match_the_oracle(c, budget):
+    """Delta dumps as one short piece, several pieces, and pieces round a ring
+    of staging slots (a budget smaller than the state), at chunk sizes on both
+    sides of each digest kernel's range, with ragged tails, rewritten runs,
+    chunks that become zero and a changed last byte; the image outgrows the
+    first piece's estimate (the state's second half is rewritten whole)."""
+    gen = torch.Generator(device="cuda").manual_seed(c + budget)
+    sizes = [c + 1, 7, 3 * c, 0, 9 * c + 16, (40 << 20) + 5, (40 << 20) // c * c, c - 1, (130 << 20) + 3]
+    table = [(i, torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda", generator=gen))
+             for i, n in enumerate(sizes)]
+    table[4][1][c:4 * c] = 0
+    ctx = mk.ckpt_ctx_create(0, budget)
+    try:
+        opts = mk.make_opts(chunk_size=c)
+        rc, base, _ = mk.ckpt_dump(ctx, table, opts=opts)
+        assert rc == 0
+        orc, obase = corc.dump(workloads.host_copy(table), c)
+        assert orc == 0 and np.array_equal(base.view(), obase)
+        before = [(i, t.clone()) for i, t in table]
+        workloads.mutate_runs(table, seed=c, chunk=c, frac=0.05, run_mean=3)
+        table[2][1][c:2 * c] = 0
+        table[8][1][-1] ^= 1
+        table[8][1][-(60 << 20):] ^= 3
+        torch.cuda.synchronize()
+        rc, delta, res = mk.ckpt_dump(ctx, table, prev=base, opts=opts)
+        assert rc == 0, mk.ckpt_strerror(rc)
+        orc, odelta = corc.dump(workloads.host_copy(table), c, prev=obase)
+        assert orc == 0 and np.array_equal(delta.view(), odelta)
+        rc, _ = mk.ckpt_restore(ctx, delta, before, opts=mk.make_opts(strict_verify=1))
+        assert rc == 0
+        same(before, table)
+    finally:
+        mk.ckpt_ctx_destroy(ctx)
