@@ -34,7 +34,7 @@ namespace mk {
 constexpr uint32_t kCodecMinChunk = 4096;    // one 16-byte row per lane
 constexpr uint32_t kCodecMaxChunk = 65536;   // records are staged in LDS
 constexpr int kCodecThreads = 256;
-constexpr uint64_t kCodecPieces = 8;         // a codec dump's encode / copy-out pipeline depth
+constexpr uint64_t kCodecPieces = 8;         // windows of a staged codec restore
 constexpr uint32_t kRecordHead = 48;
 // What the size pass keeps of a PACKED chunk for its encode: the record head
 // (48 bytes), the 8 planes' 16-byte dictionaries and their used entries

@@ -463,17 +463,6 @@ hipError_t ensure_hdesc(ckpt_ctx* c, uint64_t n) {
     return e;
 }
 
-// Pinned host scratch for per-chunk tables (codec record lengths and offsets).
-hipError_t ensure_hpin(ckpt_ctx* c, uint64_t n) {
-    if (n <= c->hpin_cap) return hipSuccess;
-    if (c->hpin) (void)hipHostFree(c->hpin);
-    c->hpin = nullptr;
-    c->hpin_cap = 0;
-    hipError_t e = pinned_small((void**)&c->hpin, n);
-    if (e == hipSuccess) c->hpin_cap = n;
-    return e;
-}
-
 hipError_t ensure_tevents(ckpt_ctx* c, size_t n) {
     while (c->tevents.size() < n) {
         hipEvent_t e;
@@ -657,12 +646,8 @@ static hipError_t ensure_copy_streams(ckpt_ctx* c, uint32_t n) {
     return hipSuccess;
 }
 
-static hipError_t ensure_side_streams(ckpt_ctx* c) {
-    for (hipStream_t* s : {&c->s_aux, &c->s_meta}) {
-        hipError_t e = *s ? hipSuccess : hipStreamCreateWithFlags(s, hipStreamNonBlocking);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+static hipError_t ensure_side_stream(ckpt_ctx* c) {
+    return c->s_aux ? hipSuccess : hipStreamCreateWithFlags(&c->s_aux, hipStreamNonBlocking);
 }
 
 extern "C" int ckpt_ctx_create(int device, uint64_t staging_budget, ckpt_ctx** out) {
@@ -687,7 +672,7 @@ extern "C" int ckpt_ctx_create(int device, uint64_t staging_budget, ckpt_ctx** o
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_order, hipEventDisableTiming);
     if (e == hipSuccess) e = ensure_copy_streams(c, 2);
     if (e == hipSuccess) e = ensure_events(c, 16);
-    if (e == hipSuccess) e = ensure_tevents(c, 4 * kCodecPieces);
+    if (e == hipSuccess) e = ensure_tevents(c, 16);
     if (e == hipSuccess) e = ensure_hsmall(c, 256 << 10);   // read-backs of up to ~32k windows
     if (e == hipSuccess) e = ensure_hdesc(c, kNaMaxAllocs);
     for (int i = 0; i < 8 && e == hipSuccess; ++i) e = hipEventCreate(&c->sev[i]);
@@ -728,13 +713,11 @@ extern "C" void ckpt_ctx_destroy(ckpt_ctx* c) {
         ge.status.release();
     }
     if (c->hsmall) hipHostFree(c->hsmall);
-    if (c->hpin) (void)hipHostFree(c->hpin);
     if (c->hdesc) (void)hipHostFree(c->hdesc);
-    for (hipStream_t s : {c->s_aux, c->s_meta})
-        if (s) {
-            (void)hipStreamSynchronize(s);
-            (void)hipStreamDestroy(s);
-        }
+    if (c->s_aux) {
+        (void)hipStreamSynchronize(c->s_aux);
+        (void)hipStreamDestroy(c->s_aux);
+    }
     delete c;
 }
 
@@ -892,7 +875,6 @@ static void drain(ckpt_ctx* c) {
     (void)hipStreamSynchronize(c->s_main);
     for (hipStream_t s : c->s_copy) (void)hipStreamSynchronize(s);
     if (c->s_aux) (void)hipStreamSynchronize(c->s_aux);
-    if (c->s_meta) (void)hipStreamSynchronize(c->s_meta);
     (void)hipGetLastError();   // the error is reported by the return code
 }
 
@@ -924,9 +906,11 @@ constexpr uint64_t kRing = 4;
 constexpr uint32_t kStampPieces = 16, kStamps = 2 + 3 * kStampPieces;
 constexpr uint32_t kRepErr = kRing + 1, kRepStamps = kRing + 7, kRepWords = kRepStamps + kStamps;
 constexpr uint64_t kHwWords = kRepWords + 3;
-// Pieces of a delta's pipeline (launch_delta): at most this many when their
-// number follows from the staging, and the least bytes of state worth one.
-constexpr uint64_t kMaxDeltaPieces = 64, kDeltaPiece = 128ull << 20;
+// Pieces of a delta's or a codec dump's pipeline (launch_pieces): at most this
+// many in a delta, and the least bytes of state worth one. (A piece of a delta
+// costs 25 us of small launches; a codec piece's passes take 2 ms per GiB,
+// which the link waits for once.)
+constexpr uint64_t kMaxDeltaPieces = 64, kDeltaPiece = 128ull << 20, kCodecPiece = 16ull << 20;
 
 static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image* prev, ckpt_image** out,
                     const ckpt_opts* o, void* stream, ckpt_result* res, PayloadSink* sink, const NaCall* na) {
@@ -1022,20 +1006,20 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     }
 
     const bool use_graph = o && (o->flags & CKPT_OPT_GRAPH) && wins.size() == 1 && !per_alloc;
-    // A delta's pipeline (launch_delta): its pieces' bounds and their places in
-    // staging. With room for everything each piece has its own part; else the
-    // pieces go round a ring of slots.
-    bool two_pass = prev != nullptr && nc > 0 && !use_graph && !codec && !na && !(per_alloc && wins.size() > 1);
+    // The pipeline of a delta or codec dump (launch_pieces): its pieces' bounds
+    // and their places in staging. With room for everything each piece has its
+    // own part; else the pieces go round a ring of slots.
+    bool two_pass = (prev != nullptr || codec) && nc > 0 && !use_graph && !na && !(per_alloc && wins.size() > 1);
     std::vector<uint64_t> piece;   // first chunks, and nc
     if (two_pass) {
-        const uint64_t all = nc * C;
+        const uint64_t all = nc * C, least = codec ? kCodecPiece : kDeltaPiece;
         if (wins.size() > 1 && o && o->window_bytes) {
             for (const Window& w : wins) piece.push_back(w.g0);   // the caller's windows
         } else if (wins.size() > 1 && ceil_div(all, 8) > c->budget / 3) {
             const uint64_t per = std::max<uint64_t>(1, c->budget / 4 / C);
             for (uint64_t g = 0; g < nc; g += per) piece.push_back(g);
-        } else if (wins.size() == 1 && all < 8 * kDeltaPiece) {
-            const uint64_t p = std::min<uint64_t>(nc, std::max<uint64_t>(1, all / kDeltaPiece));
+        } else if (wins.size() == 1 && all < 8 * least) {
+            const uint64_t p = std::min<uint64_t>(nc, std::max<uint64_t>(1, all / least));
             for (uint64_t i = 0; i < p; ++i) piece.push_back(nc * i / p);
         } else {
             // short first pieces, so that the link starts early, and short last
@@ -1052,7 +1036,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             nslots = (int)std::min<uint64_t>(piece.size() - 1, std::max<uint64_t>(2, c->budget / slot));
             if (o && o->slots) nslots = std::min(nslots, std::max(2, (int)o->slots));
         }
-        if (piece.size() - 1 > kMaxDeltaPieces) {
+        if (piece.size() - 1 > kMaxDeltaPieces && !codec) {
             two_pass = false;   // a great many windows: one pass each
             pick_staging(c, o, nc, C, &slot, &nslots);
         }
@@ -1060,7 +1044,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     const uint64_t n_pieces = two_pass ? piece.size() - 1 : 0;
     const bool ring = two_pass && wins.size() > 1;
     // One short piece: gathered straight into a pinned image.
-    const bool small_delta = two_pass && !ring && n_pieces == 1 && !sink && upper <= kDirectDump;
+    const bool small_delta = two_pass && !codec && !ring && n_pieces == 1 && !sink && upper <= kDirectDump;
     // A short full dump writes its payload straight into the image, when that
     // is pinned: no staging, no wait for the payload's length, no copy (8
     // allocations of 16 MiB: 420 -> 340 us). The image is then allocated at
@@ -1092,17 +1076,16 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         for (uint64_t i = 0; i < n_pieces; ++i) max_win = std::max(max_win, 2 * ceil_div(piece[i + 1] - piece[i], 256));
     HIPCHK(B.status->ensure(8 * (max_win + 64), c->s_main));
     const uint64_t W = wins.size();
-    const uint64_t codec_p = codec ? (W == 1 ? std::min<uint64_t>(kCodecPieces, nc) : W) : 0;   // codec pieces
     // ctl: tickets[n_tk] | wtot[kRing + 1] (u64) | err (+pad) | counts[4] (u64) | stamps (u64); window
-    // tickets and totals on the ring, codec pieces' tickets by piece
-    const uint64_t n_tk = std::max<uint64_t>({kRing, 2 * n_pieces + 2, codec_p}) + 1;
+    // tickets and totals on the ring, pieces' tickets by piece
+    const uint64_t n_tk = std::max<uint64_t>(kRing, 2 * n_pieces + 2) + 1;
     const uint64_t ctl_tk = 0, ctl_wt = round16(4 * (n_tk + 1)),
                    ctl_err = ctl_wt + 8 * (kRing + 1), ctl_cnt = ctl_err + 16, ctl_end = ctl_cnt + 32 + 8 * kStamps;
     HIPCHK(B.ctl->ensure(ctl_end));
     HIPCHK(ensure_hsmall(c, 8 * kHwWords + 16 * n_pieces));   // results; pieces' payload bounds
-    // events: [0, kRing) window done, [kRing, kRing + nslots) slot free; codec pieces: 4 per piece
-    HIPCHK(ensure_events(c, std::max<size_t>({kRing + (size_t)nslots + 2, 4 * codec_p + 1, 2 * n_pieces})));
-    if (timing) HIPCHK(ensure_tevents(c, 2 * std::max<uint64_t>(kRing, 2 * codec_p)));
+    // events: [0, kRing) window done, [kRing, kRing + nslots) slot free; pieces: done, slot free
+    HIPCHK(ensure_events(c, std::max<size_t>(kRing + (size_t)nslots + 2, 2 * n_pieces)));
+    if (timing) HIPCHK(ensure_tevents(c, 2 * kRing));
     const EngineConsts* ec;
     if (na) {
         // engine constants in the array, rebuilt when the tile or chunk size
@@ -1220,7 +1203,6 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     auto fail = [&](hipError_t e) {
         hipStreamSynchronize(c->s_main);
         if (c->s_aux) hipStreamSynchronize(c->s_aux);
-        if (c->s_meta) hipStreamSynchronize(c->s_meta);
         for (uint32_t i = 0; i < ncs; ++i) hipStreamSynchronize(c->s_copy[i]);
         (void)hipGetLastError();   // the error is reported by the return code
         if (sink) sink->end();     // nothing reads the image after this
@@ -1301,19 +1283,23 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         gj.slot_base = base;
         return gj;
     };
-    // The delta dump runs as a pipeline over its pieces. On the main stream,
-    // per piece: digests and kinds (classify), the piece's payload offsets
-    // relative to its own start (scan) and its DATA chunks gathered into its
-    // place in staging; the piece's payload length comes back to the host,
-    // which places the piece after the earlier ones and queues its copy-out
-    // while the main stream works on later pieces (on a ring, a piece is
-    // launched once the copy-out of the one before it in its slot is queued).
-    // The image is allocated once the first piece's length is known, at that
-    // length scaled to all chunks plus a margin: a delta's only firm bound is
-    // the whole state, which would hold that much pinned memory for a small
-    // image. A payload that outgrows the estimate moves, with what was copied
-    // so far, to a larger image (with a file sink, the bound from the start).
-    // Returns the payload length in *D_out.
+    // A delta or codec dump runs as a pipeline over its pieces. On the main
+    // stream, per piece: digests and kinds (classify; codec: record lengths,
+    // DATA becoming PACKED where the record is shorter), the piece's payload
+    // offsets relative to its own start (scan), and its DATA chunks gathered
+    // and PACKED records encoded into its place in staging; the piece's payload
+    // length comes back to the host, which places the piece after the earlier
+    // ones and queues its copy-out while the main stream works on later pieces
+    // (on a ring, a piece is launched once the copy-out of the one before it in
+    // its slot is queued). The image is allocated once the first piece's length
+    // is known, at that length scaled to all chunks plus a margin: a delta's
+    // only firm bound is the whole state, which would hold that much pinned
+    // memory for a small image. A payload that outgrows the estimate moves,
+    // with what was copied so far, to a larger image (with a file sink or the
+    // codec, whose records are not much shorter than their chunks, the bound
+    // from the start). Returns the payload length in *D_out.
+    PackJob pj;
+    memset(&pj, 0, sizeof(pj));
     auto launch_piece = [&](uint64_t i) -> hipError_t {
         hipError_t e;
         const uint64_t g0 = piece[i], g1 = piece[i + 1];
@@ -1336,6 +1322,19 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         j.epoch = ep;
         j.stamp = st;
         if ((e = launch_classify(c, T, K, j, tickets + 2 * i, c->s_main)) != hipSuccess) return e;
+        if (codec) {
+            pj.allocs = j.allocs;
+            pj.amap = j.amap;
+            pj.g0 = g0;
+            pj.g1 = g1;
+            pj.C = C;
+            pj.kind = kind_dev;
+            pj.rlen = B.rlen->as<uint32_t>();
+            pj.off = B.off->as<uint64_t>();
+            pj.err = err;
+            pj.meta = B.cmeta->as<uint8_t>();
+            if ((e = launch_pack(pj, false, pack_grid(c, g1 - g0), c->s_main)) != hipSuccess) return e;
+        }
         const uint64_t tiles = ceil_div(g1 - g0, 256);
         OffJob oj;
         memset(&oj, 0, sizeof(oj));
@@ -1355,6 +1354,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         oj.counts = counts;
         oj.err = err;
         oj.epoch = ep;
+        oj.rlen = codec ? B.rlen->as<uint32_t>() : nullptr;
         oj.list = B.list->as<uint64_t>() + g0;
         oj.n_list = B.wb->as<uint64_t>() + i;
         oj.status2 = B.status->words() + tiles;
@@ -1370,14 +1370,20 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         gj.n_list = oj.n_list;
         gj.stamp = st ? st + 2 : nullptr;
         if ((e = launch_gather(gj, 4 * c->num_cu, c->s_main)) != hipSuccess) return e;
+        if (codec) {
+            pj.slot = sp;
+            if ((e = launch_pack(pj, true, pack_grid(c, g1 - g0), c->s_main)) != hipSuccess) return e;
+        }
         return gather_direct ? hipSuccess : hipEventRecord(ev[i], c->s_main);
     };
-    auto launch_delta = [&](uint64_t* D_out) -> hipError_t {
+    auto launch_pieces = [&](uint64_t* D_out) -> hipError_t {
         hipError_t e;
         const uint64_t P = n_pieces;
         if ((e = B.off->ensure(8 * nc)) != hipSuccess) return e;
         if ((e = B.wb->ensure(8 * P)) != hipSuccess) return e;
         if ((e = B.list->ensure(8 * nc)) != hipSuccess) return e;
+        if (codec && (e = B.rlen->ensure(4 * nc)) != hipSuccess) return e;
+        if (codec && (e = B.cmeta->ensure((uint64_t)kPackMeta * nc)) != hipSuccess) return e;
         if (gather_direct) {
             t_link0 = now_ns();
             return launch_piece(0);
@@ -1393,7 +1399,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             if (Di > (g1 - g0) * C || D + Di > upper) return hipErrorIllegalState;
             if (!im || D + Di > cap) {
                 const uint64_t guess = (D + Di) / g1 * nc + (D + Di) / 4 + (64ull << 20);
-                const uint64_t est = sink ? upper : std::min(upper, std::max({guess, D + Di, im ? 2 * cap : 0}));
+                const uint64_t est = sink || codec ? upper : std::min(upper, std::max({guess, D + Di, im ? 2 * cap : 0}));
                 ckpt_image* big = image_new(kHeader + tl + est);
                 if (!big) return hipErrorOutOfMemory;
                 if (im) {
@@ -1412,7 +1418,9 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
                 if (sink) sink->begin(im);
             }
             if (Di) {
-                hipStream_t cs = c->s_copy[ring ? 0 : i % ncs];
+                // (a codec dump's pieces keep the link busy one by one; two at a
+                // time shared 53 GB/s)
+                hipStream_t cs = c->s_copy[ring || codec ? 0 : i % ncs];
                 if (!t_link0) t_link0 = now_ns();
                 if ((e = hipStreamWaitEvent(cs, ev[i], 0)) != hipSuccess) return e;
                 if ((e = copy_out(D, B.staging->as<uint8_t>() + (ring ? (i % nslots) * slot : g0 * C), Di, cs)) !=
@@ -1425,131 +1433,6 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
                 if ((e = launch_piece(i + nslots)) != hipSuccess) return e;
             }
         }
-        *D_out = D;
-        return hipSuccess;
-    };
-    // Codec dump in pieces: in one window kCodecPieces pieces of equal chunk
-    // counts, else one piece per staging window (on the slot ring; a piece
-    // is encoded into its slot once the piece that used it before has been
-    // copied out). On the main stream, piece after piece: digests and kinds
-    // (classify) and record lengths (size pass; DATA becomes PACKED where the
-    // record is shorter). As each piece's size pass ends, a metadata stream
-    // brings its lengths to pinned host memory, the host extends the payload
-    // offsets over them and the stream takes the piece's offsets back up;
-    // then, on a second compute stream, the piece's DATA chunks are gathered
-    // and its PACKED records encoded, and its copy-out starts when that is
-    // done. The first copy-out so waits for one piece's passes, not for
-    // every chunk's. (Small copies return only once done, so they stay off
-    // the streams whose work the host queues ahead.)
-    uint32_t* rlen_h = nullptr;
-    uint64_t codec_pairs = 0;
-    auto launch_codec = [&](uint64_t* D_out) -> hipError_t {
-        hipError_t e;
-        uint32_t ep;
-        if ((e = B.status->next(c->s_main, &ep)) != hipSuccess) return e;
-        if ((e = B.off->ensure(8 * nc)) != hipSuccess) return e;
-        if ((e = B.rlen->ensure(4 * nc)) != hipSuccess) return e;
-        if ((e = B.cmeta->ensure((uint64_t)kPackMeta * nc)) != hipSuccess) return e;
-        if ((e = ensure_hpin(c, 12 * nc)) != hipSuccess) return e;
-        if ((e = ensure_side_streams(c)) != hipSuccess) return e;
-        uint64_t* off_h = reinterpret_cast<uint64_t*>(c->hpin);
-        rlen_h = reinterpret_cast<uint32_t*>(c->hpin + 8 * nc);
-        // the image at its upper bound (records never exceed their chunks)
-        if (!alloc_image(upper)) return hipErrorOutOfMemory;
-        ChunkJob j;
-        memset(&j, 0, sizeof(j));
-        j.allocs = B.descs->as<AllocDesc>();
-        j.n_allocs = n;
-        j.C = C;
-        j.amap = B.amap->as<uint32_t>();
-        j.ec = ec;
-        j.crc_out = crc_dev;
-        j.kind_out = kind_dev;
-        j.kind_in = kind_dev;
-        j.prev_crc = prev_dev;
-        j.slot = B.staging->as<uint8_t>();
-        j.off = B.off->as<uint64_t>();
-        j.slot_base = 0;
-        j.err = err;
-        j.epoch = ep;
-        PackJob pj;
-        memset(&pj, 0, sizeof(pj));
-        pj.allocs = B.descs->as<AllocDesc>();
-        pj.amap = B.amap->as<uint32_t>();
-        pj.C = C;
-        pj.kind = kind_dev;
-        pj.rlen = B.rlen->as<uint32_t>();
-        pj.off = B.off->as<uint64_t>();
-        pj.slot = B.staging->as<uint8_t>();
-        pj.err = err;
-        pj.meta = B.cmeta->as<uint8_t>();
-        const bool one = W == 1;
-        const uint64_t P = codec_p;
-        std::vector<uint64_t> gb(P + 1);
-        for (uint64_t i = 0; i <= P; ++i) gb[i] = one ? nc * i / P : (i < P ? wins[i].g0 : nc);
-        for (uint64_t i = 0; i < P; ++i) {
-            const uint64_t g0 = gb[i], g1 = gb[i + 1];
-            j.g0 = pj.g0 = g0;
-            j.g1 = pj.g1 = g1;
-            if (timing && (e = hipEventRecord(c->tevents[2 * i], c->s_main)) != hipSuccess) return e;
-            if (g1 > g0) {
-                if ((e = launch_classify(c, T, K, j, tickets + i, c->s_main)) != hipSuccess) return e;
-                if ((e = launch_pack(pj, false, pack_grid(c, g1 - g0), c->s_main)) != hipSuccess) return e;
-            }
-            if (timing && (e = hipEventRecord(c->tevents[2 * i + 1], c->s_main)) != hipSuccess) return e;
-            if ((e = hipEventRecord(ev[i], c->s_main)) != hipSuccess) return e;
-        }
-        uint64_t D = 0;
-        for (uint64_t i = 0; i < P; ++i) {
-            const uint64_t g0 = gb[i], g1 = gb[i + 1];
-            if ((e = hipStreamWaitEvent(c->s_meta, ev[i], 0)) != hipSuccess) return e;
-            if (g1 > g0 && (e = hipMemcpyAsync(rlen_h + g0, pj.rlen + g0, 4 * (g1 - g0), hipMemcpyDeviceToHost,
-                                               c->s_meta)) != hipSuccess)
-                return e;
-            if ((e = hipStreamSynchronize(c->s_meta)) != hipSuccess) return e;
-            const uint64_t lo = D;
-            for (uint64_t g = g0; g < g1; ++g) {
-                off_h[g] = D;
-                D += rlen_h[g];
-            }
-            // records never exceed their chunks (nor a window its slot)
-            if (D > upper || (one ? D : D - lo) > slot) return hipErrorIllegalState;
-            uint8_t* sp = B.staging->as<uint8_t>() + (one ? 0 : (i % nslots) * slot);
-            const uint64_t base = one ? 0 : lo;
-            if (g1 > g0 && (e = hipMemcpyAsync(B.off->as<uint64_t>() + g0, off_h + g0, 8 * (g1 - g0),
-                                               hipMemcpyHostToDevice, c->s_meta)) != hipSuccess)
-                return e;
-            if ((e = hipEventRecord(ev[P + i], c->s_meta)) != hipSuccess) return e;
-            if ((e = hipStreamWaitEvent(c->s_aux, ev[P + i], 0)) != hipSuccess) return e;
-            // the slot's previous piece is copied out
-            if (!one && i >= (uint64_t)nslots && (e = hipStreamWaitEvent(c->s_aux, ev[3 * P + i - nslots], 0)) != hipSuccess)
-                return e;
-            if (timing && (e = hipEventRecord(c->tevents[2 * (P + i)], c->s_aux)) != hipSuccess) return e;
-            if (g1 > g0) {
-                pj.g0 = g0;
-                pj.g1 = g1;
-                pj.slot = sp;
-                pj.slot_base = base;
-                if ((e = launch_gather(gather_job(g0, g1, sp, base), pack_grid(c, g1 - g0), c->s_aux)) != hipSuccess)
-                    return e;
-                if ((e = launch_pack(pj, true, pack_grid(c, g1 - g0), c->s_aux)) != hipSuccess) return e;
-            }
-            if (timing && (e = hipEventRecord(c->tevents[2 * (P + i) + 1], c->s_aux)) != hipSuccess) return e;
-            if ((e = hipEventRecord(ev[2 * P + i], c->s_aux)) != hipSuccess) return e;
-            if (D > lo) {
-                // one copy stream, pieces in order: two concurrent copies
-                // out reached 53 GB/s together against 57 for one
-                hipStream_t cs = c->s_copy[0];
-                if (!t_link0) t_link0 = now_ns();
-                if ((e = hipStreamWaitEvent(cs, ev[2 * P + i], 0)) != hipSuccess) return e;
-                if ((e = copy_out(lo, sp + (lo - base), D - lo, cs)) != hipSuccess) return e;
-            }
-            if ((e = hipEventRecord(ev[3 * P + i], c->s_copy[0])) != hipSuccess) return e;
-        }
-        // the main stream's later work (per-allocation digests, tables, the
-        // error flag) follows every encode
-        if (P && (e = hipStreamWaitEvent(c->s_main, ev[3 * P - 1], 0)) != hipSuccess) return e;
-        codec_pairs = 2 * P;
         *D_out = D;
         return hipSuccess;
     };
@@ -1660,11 +1543,10 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         // a slot of its own (nslots >= 2): its slot-free event then belongs to
         // a copy that has already been issued.
         const bool ahead = nslots >= 2;
-        if (W && codec) e = launch_codec(&pos);
-        else if (W && two_pass) e = launch_delta(&pos);
+        if (W && two_pass) e = launch_pieces(&pos);
         else if (W) e = launch_window(0, 0);
         if (direct) t_link0 = now_ns();
-        for (uint64_t w = 0; w < W && e == hipSuccess && !codec && !two_pass && !direct; ++w) {
+        for (uint64_t w = 0; w < W && e == hipSuccess && !two_pass && !direct; ++w) {
             const uint64_t q = w % kRing;
             if (w > 0 && !ahead) {
                 e = launch_window(w, pos);
@@ -1746,6 +1628,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     if (tables_direct) {
         if (use_graph) fj.add_copy(htab, B.arc->p, 32ull * n);
         fj.add_copy(htab + 32ull * n, crc_dev, 4 * nc);
+        if (codec) fj.add_copy(htab + len_a, B.rlen->p, rl_bytes);
         fj.add_copy(htab + len_a + rl_bytes, kind_dev, len_b);
     }
     // keep this image's digest table resident for later delta dumps (not
@@ -1761,12 +1644,14 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     if (!tables_direct) {
         if ((e = hipMemcpyAsync(htab, B.arc->p, len_a, hipMemcpyDeviceToHost, c->s_main)) != hipSuccess)
             return fail_late(e);
+        if (rl_bytes &&
+            (e = hipMemcpyAsync(htab + len_a, B.rlen->p, rl_bytes, hipMemcpyDeviceToHost, c->s_main)) != hipSuccess)
+            return fail_late(e);
         if ((e = hipMemcpyAsync(htab + len_a + rl_bytes, kind_dev, len_b, hipMemcpyDeviceToHost, c->s_main)) !=
             hipSuccess)
             return fail_late(e);
     }
     if (timing && !use_graph && (e = hipEventRecord(c->sev[3], c->s_main)) != hipSuccess) return fail_late(e);
-    if (codec) memcpy(htab + len_a, rlen_h, rl_bytes);   // little-endian host
     if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return fail_late(e);
     if (direct || gather_direct) {
         D = gather_direct ? hw[kHwWords + 1] : hw[0];
@@ -1827,7 +1712,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         res->n_chunks = nc;
         res->link_bytes = D + tl + kHeader;
         res->ns_link = t_link0 ? t_link1 - t_link0 : 0;
-        res->ns_kernel = stamped ? kern_ns : !timing ? 0 : (codec && W) ? timed_ns(c, codec_pairs) : use_graph ? timed_ns(c, 1) : kern_ns;
+        res->ns_kernel = stamped ? kern_ns : !timing ? 0 : use_graph ? timed_ns(c, 1) : kern_ns;
         res->ns_total = now_ns() - t_start;
         // per-stage report (see ckpt_result.ns_stage)
         if (stamped) {
@@ -1837,17 +1722,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         }
         if (timing) {
             if (!use_graph) res->ns_stage[0] = span_ns(c->sev[0], c->sev[1]);
-            if (codec && W) {
-                uint64_t main_ns = 0, aux_ns = 0;   // classify + size pass; gather + encode
-                for (uint64_t i = 0; i < codec_pairs / 2; ++i) {
-                    main_ns += span_ns(c->tevents[2 * i], c->tevents[2 * i + 1]);
-                    aux_ns += span_ns(c->tevents[2 * (codec_pairs / 2 + i)], c->tevents[2 * (codec_pairs / 2 + i) + 1]);
-                }
-                res->ns_stage[1] = main_ns;
-                res->ns_stage[3] = aux_ns;
-            } else {
-                res->ns_stage[1] = res->ns_kernel;
-            }
+            res->ns_stage[1] = res->ns_kernel;
             if (!use_graph && W) res->ns_stage[5] = span_ns(c->sev[2], c->sev[3]);
         }
         res->ns_stage[4] = res->ns_link;
@@ -2402,7 +2277,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     }
     const uint64_t head = at.empty() ? 0 : at[hi];
     if (hi) {
-        HIPCHK(ensure_side_streams(c));
+        HIPCHK(ensure_side_stream(c));
         HIPCHK(c->staging.ensure(head));
         HIPCHK(launch_link_copy(c->staging.p, v.payload, head, c->s_aux));
         HIPCHK(hipEventRecord(c->events[0], c->s_aux));
