@@ -121,9 +121,19 @@ struct StatusBuf {
 // the epoch taken at capture).
 struct GraphEntry {
     uint64_t key = 0;
-    hipGraphExec_t exec = nullptr;
+    hipGraphExec_t exec = nullptr, exec2 = nullptr;   // exec2: a dump's rest, after the head in exec
     DevBuf descs, dig, status;
     uint64_t last_use = 0;
+    void release() {
+        for (hipGraphExec_t* x : {&exec, &exec2}) {
+            if (*x) (void)hipGraphExecDestroy(*x);
+            *x = nullptr;
+        }
+        descs.release();
+        dig.release();
+        status.release();
+        last_use = 0;
+    }
 };
 
 // A resident digest table of an image: its crc[] on the device, kept for

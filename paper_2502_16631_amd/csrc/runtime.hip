@@ -706,12 +706,7 @@ extern "C" void ckpt_ctx_destroy(ckpt_ctx* c) {
     for (auto& kv : c->consts) kv.second.release();
     for (auto& kv : c->cconsts) kv.second.release();
     for (auto& kv : c->digests) kv.second.crc.release();
-    for (auto& ge : c->graphs) {
-        if (ge.exec) hipGraphExecDestroy(ge.exec);
-        ge.descs.release();
-        ge.dig.release();
-        ge.status.release();
-    }
+    for (auto& ge : c->graphs) ge.release();
     if (c->hsmall) hipHostFree(c->hsmall);
     if (c->hdesc) (void)hipHostFree(c->hdesc);
     if (c->s_aux) {
@@ -911,6 +906,13 @@ constexpr uint64_t kHwWords = kRepWords + 3;
 // costs 25 us of small launches; a codec piece's passes take 2 ms per GiB,
 // which the link waits for once.)
 constexpr uint64_t kMaxDeltaPieces = 64, kDeltaPiece = 128ull << 20, kCodecPiece = 16ull << 20;
+// A full dump's head: one chunk in so many. Its copy-out has to outlast the
+// rest's kernel, which is 50 times as fast as the link (1 GiB: 1.2 against
+// 0.4 ms).
+constexpr uint64_t kHeadShare = 16;
+// Up to this bound the image of a full dump with zeros in its head is
+// allocated on the head's share of them; beyond, once the length is known.
+constexpr uint64_t kGuessMax = 2ull << 30;
 
 static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image* prev, ckpt_image** out,
                     const ckpt_opts* o, void* stream, ckpt_result* res, PayloadSink* sink, const NaCall* na) {
@@ -1006,14 +1008,28 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     }
 
     const bool use_graph = o && (o->flags & CKPT_OPT_GRAPH) && wins.size() == 1 && !per_alloc;
-    // The pipeline of a delta or codec dump (launch_pieces): its pieces' bounds
-    // and their places in staging. With room for everything each piece has its
-    // own part; else the pieces go round a ring of slots.
-    bool two_pass = (prev != nullptr || codec) && nc > 0 && !use_graph && !na && !(per_alloc && wins.size() > 1);
+    // A short full dump writes its payload straight into the image, when that
+    // is pinned: no staging, no wait for the payload's length, no copy (8
+    // allocations of 16 MiB: 420 -> 350 us). The image is then allocated at
+    // the payload's bound, which is why longer dumps do not: a state half of
+    // zeros would pin twice its image. The kernel holds the device for as
+    // long as the link takes, 1.2 ms at the longest.
+    const bool one_pass = !prev && !codec && wins.size() == 1 && nc > 0 && !use_graph && !per_alloc;
+    const bool small = one_pass && !sink && upper <= kDirectDump;
+    // The pipeline of a dump (launch_pieces): its pieces' bounds and their
+    // places in staging. With room for everything each piece has its own part;
+    // else the pieces go round a ring of slots. A longer full dump that fits
+    // one window is launched as a head and the rest, so that the head's
+    // copy-out, which takes longer, runs beside the rest's kernel.
+    const bool plain = (one_pass || use_graph) && !small && !na && nc * C >= kDeltaPiece && nc >= 2 * kHeadShare;
+    bool piped = plain || ((prev != nullptr || codec) && nc > 0 && !use_graph && !na && !(per_alloc && wins.size() > 1));
     std::vector<uint64_t> piece;   // first chunks, and nc
-    if (two_pass) {
+    if (piped) {
         const uint64_t all = nc * C, least = codec ? kCodecPiece : kDeltaPiece;
-        if (wins.size() > 1 && o && o->window_bytes) {
+        if (plain) {
+            piece.push_back(0);
+            piece.push_back(std::max<uint64_t>(1, nc / kHeadShare));
+        } else if (wins.size() > 1 && o && o->window_bytes) {
             for (const Window& w : wins) piece.push_back(w.g0);   // the caller's windows
         } else if (wins.size() > 1 && ceil_div(all, 8) > c->budget / 3) {
             const uint64_t per = std::max<uint64_t>(1, c->budget / 4 / C);
@@ -1037,24 +1053,16 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             if (o && o->slots) nslots = std::min(nslots, std::max(2, (int)o->slots));
         }
         if (piece.size() - 1 > kMaxDeltaPieces && !codec) {
-            two_pass = false;   // a great many windows: one pass each
+            piped = false;   // a great many windows: one pass each
             pick_staging(c, o, nc, C, &slot, &nslots);
         }
     }
-    const uint64_t n_pieces = two_pass ? piece.size() - 1 : 0;
-    const bool ring = two_pass && wins.size() > 1;
+    const uint64_t n_pieces = piped ? piece.size() - 1 : 0;
+    const bool ring = piped && wins.size() > 1;
     // One short piece: gathered straight into a pinned image.
-    const bool small_delta = two_pass && !codec && !ring && n_pieces == 1 && !sink && upper <= kDirectDump;
-    // A short full dump writes its payload straight into the image, when that
-    // is pinned: no staging, no wait for the payload's length, no copy (8
-    // allocations of 16 MiB: 420 -> 340 us). The image is then allocated at
-    // the payload's bound, which is why longer dumps do not: a state half of
-    // zeros would pin twice its image. The kernel holds the device for as
-    // long as the link takes, 1.2 ms at the longest.
-    const bool small = wins.size() == 1 && nc > 0 && !use_graph && !codec && !per_alloc && !sink && !two_pass &&
-                       upper <= kDirectDump;
+    const bool small_delta = piped && !plain && !codec && !ring && n_pieces == 1 && !sink && upper <= kDirectDump;
     // stage times: of a short dump by stamps, else by events
-    const bool stamped = (small || two_pass) && !(o && (o->flags & CKPT_OPT_NO_TIMING));
+    const bool stamped = (small || (piped && !plain)) && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     const bool timing = !stamped && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     HIPCHK(hipSetDevice(c->device));
     if (!na) HIPCHK(ensure_copy_streams(c, ncs));
@@ -1072,7 +1080,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         HIPCHK(launch_fill64(B.status->words(), 0, kNaStatusWords, c->s_main));
         na->dev->cleared = true;
     }
-    if (two_pass)   // two scans over 256-chunk tiles, each with words of its own
+    if (piped)   // two scans over 256-chunk tiles, each with words of its own
         for (uint64_t i = 0; i < n_pieces; ++i) max_win = std::max(max_win, 2 * ceil_div(piece[i + 1] - piece[i], 256));
     HIPCHK(B.status->ensure(8 * (max_win + 64), c->s_main));
     const uint64_t W = wins.size();
@@ -1162,7 +1170,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         na_img.pinned = false;
         im = &na_img;
         himg = na->out;
-    } else if ((W > 1 && !stage_all && !two_pass) || small || small_delta) {
+    } else if ((W > 1 && !stage_all && !piped) || small || small_delta) {
         im = image_new(kHeader + tl + upper);
         if (!im) return CKPT_ENOMEM;
         himg = im->p;
@@ -1300,6 +1308,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     // from the start). Returns the payload length in *D_out.
     PackJob pj;
     memset(&pj, 0, sizeof(pj));
+    hipGraphExec_t graph_exec[2] = {nullptr, nullptr};   // head (or everything), rest
     auto launch_piece = [&](uint64_t i) -> hipError_t {
         hipError_t e;
         const uint64_t g0 = piece[i], g1 = piece[i + 1];
@@ -1321,6 +1330,24 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         j.err = err;
         j.epoch = ep;
         j.stamp = st;
+        if (use_graph) {
+            if (timing && (e = hipEventRecord(c->tevents[2 * i], c->s_main)) != hipSuccess) return e;
+            if ((e = hipGraphLaunch(graph_exec[i], c->s_main)) != hipSuccess) return e;
+            if (timing && (e = hipEventRecord(c->tevents[2 * i + 1], c->s_main)) != hipSuccess) return e;
+            return hipEventRecord(ev[i], c->s_main);
+        }
+        if (plain) {
+            // single pass, as launch_window
+            j.slot = B.staging->as<uint8_t>() + g0 * C;
+            j.status = B.status->words();
+            j.wtotal = hw + kHwWords + 2 * i + 1;   // pinned
+            int grid;
+            if ((e = grid_for(c, T, K, kModeDump, g1 - g0, &grid)) != hipSuccess) return e;
+            if (timing && (e = hipEventRecord(c->tevents[2 * i], c->s_main)) != hipSuccess) return e;
+            if ((e = launch_chunks(T, K, kModeDump, one_job(j, tickets + 2 * i), grid, c->s_main)) != hipSuccess) return e;
+            if (timing && (e = hipEventRecord(c->tevents[2 * i + 1], c->s_main)) != hipSuccess) return e;
+            return hipEventRecord(ev[i], c->s_main);
+        }
         if ((e = launch_classify(c, T, K, j, tickets + 2 * i, c->s_main)) != hipSuccess) return e;
         if (codec) {
             pj.allocs = j.allocs;
@@ -1376,6 +1403,15 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         }
         return gather_direct ? hipSuccess : hipEventRecord(ev[i], c->s_main);
     };
+    // the payload's bound over the chunks before g
+    auto bound_of = [&](uint64_t g) {
+        uint64_t b = 0;
+        for (uint32_t a = 0; a < n && d[a].first < g; ++a) {
+            const uint64_t nk = std::min(ceil_div(d[a].size, C), g - d[a].first);
+            b += std::min(round16(d[a].size), nk * C);
+        }
+        return b;
+    };
     auto launch_pieces = [&](uint64_t* D_out) -> hipError_t {
         hipError_t e;
         const uint64_t P = n_pieces;
@@ -1398,8 +1434,15 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             const uint64_t Di = hw[kHwWords + 2 * i + 1];
             if (Di > (g1 - g0) * C || D + Di > upper) return hipErrorIllegalState;
             if (!im || D + Di > cap) {
-                const uint64_t guess = (D + Di) / g1 * nc + (D + Di) / 4 + (64ull << 20);
-                const uint64_t est = sink || codec ? upper : std::min(upper, std::max({guess, D + Di, im ? 2 * cap : 0}));
+                // scaled to all chunks, and a quarter more
+                uint64_t est = (D + Di) / g1 * nc;
+                est = std::max<uint64_t>({est + est / 4 + (64ull << 20), D + Di, im ? 2 * cap : 0});
+                if (plain && i + 1 < P && upper > kGuessMax && Di < bound_of(g1)) {
+                    if ((e = hipEventSynchronize(ev[i + 1])) != hipSuccess) return e;
+                    est = Di + hw[kHwWords + 2 * i + 3];
+                }
+                if (plain && i + 1 == P) est = D + Di;
+                est = sink || codec ? upper : std::min(upper, est);
                 ckpt_image* big = image_new(kHeader + tl + est);
                 if (!big) return hipErrorOutOfMemory;
                 if (im) {
@@ -1453,10 +1496,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
                 auto victim = c->graphs.begin();
                 for (auto it = c->graphs.begin(); it != c->graphs.end(); ++it)
                     if (it->last_use < victim->last_use) victim = it;
-                if (victim->exec) hipGraphExecDestroy(victim->exec);
-                victim->descs.release();
-                victim->dig.release();
-                victim->status.release();
+                victim->release();
                 c->graphs.erase(victim);
             }
             c->graphs.emplace_back();
@@ -1469,60 +1509,73 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             int grid;
             if ((e = grid_for(c, T, K, kModeDump, nc, &grid)) != hipSuccess) return fail(e);
             if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return fail(e);
-            // every replay clears the graph's own look-back words first, so
-            // one epoch serves all replays
-            const uint32_t ep = 1;
-            hipGraph_t graph = nullptr;
-            if ((e = hipStreamBeginCapture(c->s_main, hipStreamCaptureModeThreadLocal)) != hipSuccess) return fail(e);
-            hipError_t ce = hipSuccess;
-            auto step = [&ce](hipError_t r) { if (ce == hipSuccess) ce = r; };
-            // every replay clears what must start at zero with fill kernels
-            step(launch_fill32(reinterpret_cast<uint32_t*>(ctl), 0, ctl_end / 4, c->s_main));
-            step(launch_fill32(B.kinds->as<uint32_t>(), 0, ceil_div(len_b, 4), c->s_main));
-            step(launch_fill64(ge->status.as<uint64_t>(), 0, nc + 64, c->s_main));
-            step(launch_chunk_map(ge->descs.as<AllocDesc>(), n, C, B.amap->as<uint32_t>(), c->s_main));
-            ChunkJob j;
-            memset(&j, 0, sizeof(j));
-            j.allocs = ge->descs.as<AllocDesc>();
-            j.n_allocs = n;
-            j.C = C;
-            j.amap = B.amap->as<uint32_t>();
-            j.g0 = 0;
-            j.g1 = nc;
-            j.ec = ec;
-            j.crc_out = crc_dev;
-            j.kind_out = kind_dev;
-            j.prev_crc = prev_dev;
-            j.slot = B.staging->as<uint8_t>();
-            j.status = ge->status.as<uint64_t>();
-            j.wtotal = wtot;
-            j.err = err;
-            j.epoch = ep;
-            if (nc) step(launch_chunks(T, K, kModeDump, one_job(j, tickets), grid, c->s_main));
-            // the payload's length and the error word
-            step(launch_report(hw, wtot, kRepErr + 1, false, c->s_main));
-            CombineJob gcj;
-            memset(&gcj, 0, sizeof(gcj));
-            gcj.allocs = ge->descs.as<AllocDesc>();
-            gcj.n_allocs = n;
-            gcj.C = C;
-            gcj.crc = crc_dev;
-            gcj.ec = ec;
-            gcj.recs = B.arc->as<uint8_t>();
-            gcj.mode = kCombineWrite;
-            step(launch_combine(gcj, c->s_main));
-            hipError_t ee = hipStreamEndCapture(c->s_main, &graph);
-            if (ce == hipSuccess) ce = ee;
-            if (ce == hipSuccess) ce = hipGraphInstantiate(&ge->exec, graph, nullptr, nullptr, 0);
-            if (graph) hipGraphDestroy(graph);
-            if (ce != hipSuccess) {
-                ge->exec = nullptr;
-                return fail(ce);
+            // one graph, or (piped) one for the head and one for the rest
+            for (uint64_t i = 0; i < std::max<uint64_t>(1, n_pieces); ++i) {
+                const uint64_t g0 = piped ? piece[i] : 0, g1 = piped ? piece[i + 1] : nc;
+                // every replay clears the graph's own look-back words first, so
+                // one epoch serves all replays
+                const uint32_t ep = 1;
+                hipGraph_t graph = nullptr;
+                if ((e = hipStreamBeginCapture(c->s_main, hipStreamCaptureModeThreadLocal)) != hipSuccess) return fail(e);
+                hipError_t ce = hipSuccess;
+                auto step = [&ce](hipError_t r) { if (ce == hipSuccess) ce = r; };
+                // every replay clears what must start at zero with fill kernels
+                if (i == 0) {
+                    step(launch_fill32(reinterpret_cast<uint32_t*>(ctl), 0, ctl_end / 4, c->s_main));
+                    step(launch_fill32(B.kinds->as<uint32_t>(), 0, ceil_div(len_b, 4), c->s_main));
+                    step(launch_fill64(ge->status.as<uint64_t>(), 0, nc + 64, c->s_main));
+                    step(launch_chunk_map(ge->descs.as<AllocDesc>(), n, C, B.amap->as<uint32_t>(), c->s_main));
+                }
+                ChunkJob j;
+                memset(&j, 0, sizeof(j));
+                j.allocs = ge->descs.as<AllocDesc>();
+                j.n_allocs = n;
+                j.C = C;
+                j.amap = B.amap->as<uint32_t>();
+                j.g0 = g0;
+                j.g1 = g1;
+                j.ec = ec;
+                j.crc_out = crc_dev;
+                j.kind_out = kind_dev;
+                j.prev_crc = prev_dev;
+                j.slot = B.staging->as<uint8_t>() + g0 * C;
+                j.status = ge->status.as<uint64_t>() + g0;
+                j.wtotal = piped ? hw + kHwWords + 2 * i + 1 : wtot;
+                j.err = err;
+                j.epoch = ep;
+                if (nc) step(launch_chunks(T, K, kModeDump, one_job(j, tickets + 2 * i), grid, c->s_main));
+                if (g1 == nc) {
+                    // the payload's length (not piped) and the error word
+                    step(launch_report(hw, wtot, kRepErr + 1, false, c->s_main));
+                    CombineJob gcj;
+                    memset(&gcj, 0, sizeof(gcj));
+                    gcj.allocs = ge->descs.as<AllocDesc>();
+                    gcj.n_allocs = n;
+                    gcj.C = C;
+                    gcj.crc = crc_dev;
+                    gcj.ec = ec;
+                    gcj.recs = B.arc->as<uint8_t>();
+                    gcj.mode = kCombineWrite;
+                    step(launch_combine(gcj, c->s_main));
+                }
+                hipError_t ee = hipStreamEndCapture(c->s_main, &graph);
+                if (ce == hipSuccess) ce = ee;
+                if (ce == hipSuccess) ce = hipGraphInstantiate(i ? &ge->exec2 : &ge->exec, graph, nullptr, nullptr, 0);
+                if (graph) hipGraphDestroy(graph);
+                if (ce != hipSuccess) {
+                    // (the entry has no key of its own any more: it is replaced as the oldest)
+                    ge->release();
+                    return fail(ce);
+                }
             }
         }
         ge->last_use = ++c->use_clock;
+        graph_exec[0] = ge->exec;
+        graph_exec[1] = ge->exec2;
+    }
+    if (use_graph && !piped) {
         if (timing && (e = hipEventRecord(c->tevents[0], c->s_main)) != hipSuccess) return fail(e);
-        if ((e = hipGraphLaunch(ge->exec, c->s_main)) != hipSuccess) return fail(e);
+        if ((e = hipGraphLaunch(graph_exec[0], c->s_main)) != hipSuccess) return fail(e);
         if (timing && (e = hipEventRecord(c->tevents[1], c->s_main)) != hipSuccess) return fail(e);
         if ((e = hipEventRecord(ev[0], c->s_main)) != hipSuccess) return fail(e);
         if ((e = hipEventSynchronize(ev[0])) != hipSuccess) return fail(e);
@@ -1530,10 +1583,10 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         if (dw > upper) return fail(hipErrorIllegalState);
         if (!alloc_image(dw)) return fail(hipErrorOutOfMemory);
         t_link0 = now_ns();
-        // the payload in ncs pieces on the side streams
-        const uint64_t piece = (std::max<uint64_t>(ceil_div(dw, ncs), 1ull << 20) + 4095) & ~4095ull;
-        for (uint32_t i = 0; i < ncs && (uint64_t)i * piece < dw; ++i) {
-            const uint64_t lo = (uint64_t)i * piece, len = std::min(piece, dw - lo);
+        // the payload in ncs parts on the side streams
+        const uint64_t part = (std::max<uint64_t>(ceil_div(dw, ncs), 1ull << 20) + 4095) & ~4095ull;
+        for (uint32_t i = 0; i < ncs && (uint64_t)i * part < dw; ++i) {
+            const uint64_t lo = (uint64_t)i * part, len = std::min(part, dw - lo);
             if ((e = hipStreamWaitEvent(c->s_copy[i], ev[0], 0)) != hipSuccess) return fail(e);
             if ((e = copy_out(lo, B.staging->as<uint8_t>() + lo, len, c->s_copy[i])) != hipSuccess) return fail(e);
         }
@@ -1543,10 +1596,10 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         // a slot of its own (nslots >= 2): its slot-free event then belongs to
         // a copy that has already been issued.
         const bool ahead = nslots >= 2;
-        if (W && two_pass) e = launch_pieces(&pos);
+        if (W && piped) e = launch_pieces(&pos);
         else if (W) e = launch_window(0, 0);
         if (direct) t_link0 = now_ns();
-        for (uint64_t w = 0; w < W && e == hipSuccess && !two_pass && !direct; ++w) {
+        for (uint64_t w = 0; w < W && e == hipSuccess && !piped && !direct; ++w) {
             const uint64_t q = w % kRing;
             if (w > 0 && !ahead) {
                 e = launch_window(w, pos);
@@ -1657,11 +1710,12 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         D = gather_direct ? hw[kHwWords + 1] : hw[0];
         if (D > upper) return fail_late(hipErrorIllegalState);
     }
+    if (plain && timing) kern_ns = timed_ns(c, n_pieces);
     // stage times by stamps
     uint64_t st_ns[4] = {0, 0, 0, 0};   // chunk kernels, scan, gather; set-up
     if (stamped) {
         const uint64_t* st = hw + kRepStamps;
-        if (two_pass) {
+        if (piped) {
             for (uint64_t i = 0; i < std::min<uint64_t>(n_pieces, kStampPieces); ++i) {
                 const uint64_t* p = st + 2 + 3 * i;
                 const uint64_t end = i + 1 < std::min<uint64_t>(n_pieces, kStampPieces) ? p[3] : hw[kRepWords];
@@ -1712,7 +1766,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         res->n_chunks = nc;
         res->link_bytes = D + tl + kHeader;
         res->ns_link = t_link0 ? t_link1 - t_link0 : 0;
-        res->ns_kernel = stamped ? kern_ns : !timing ? 0 : use_graph ? timed_ns(c, 1) : kern_ns;
+        res->ns_kernel = stamped ? kern_ns : !timing ? 0 : use_graph && !piped ? timed_ns(c, 1) : kern_ns;
         res->ns_total = now_ns() - t_start;
         // per-stage report (see ckpt_result.ns_stage)
         if (stamped) {
@@ -2013,10 +2067,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
                 auto victim = c->graphs.begin();
                 for (auto it = c->graphs.begin(); it != c->graphs.end(); ++it)
                     if (it->last_use < victim->last_use) victim = it;
-                if (victim->exec) hipGraphExecDestroy(victim->exec);
-                victim->descs.release();
-                victim->dig.release();
-                victim->status.release();
+                victim->release();
                 c->graphs.erase(victim);
             }
             c->graphs.emplace_back();
