@@ -40,6 +40,10 @@ int parse_image(const uint8_t* img, uint64_t len, ImageView* v, bool check_table
 // kBadRecord when the kind or the record length breaks the format.
 constexpr uint64_t kBadRecord = ~0ull;
 uint64_t record_len(const ImageView& v, uint64_t g, uint64_t len);
+// Plain layout: counts of the image's kinds (ZERO, DATA, UNCHANGED, others)
+// into n[4], payload bytes and DATA chunks before each of the ascending bounds
+// into at[] and rank[]; returns the payload total.
+uint64_t scan_kinds(const ImageView& v, const std::vector<uint64_t>& bounds, uint64_t* at, uint64_t* rank, uint64_t n[4]);
 
 
 
@@ -332,7 +336,6 @@ hipError_t launch_verify(ckpt_ctx* c, int T, int K, JobList& jl, int cus, hipStr
 void make_desc(AllocDesc* d, uint64_t id, const void* ptr, uint64_t size, uint64_t first, uint64_t prev_first,
                uint32_t C);
 JobList one_job(const ChunkJob& j, uint32_t* ticket);
-void digest_insert(ckpt_ctx* c, uint64_t uid, const uint32_t* crc_dev, uint64_t nc, hipStream_t s);
 // Room for the resident digest table of image uid, to be filled on a stream
 // before the table is used; nullptr when none is kept. digest_drop forgets a
 // table (its work queued or done).

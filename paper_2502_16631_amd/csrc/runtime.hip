@@ -835,13 +835,6 @@ void mk::digest_drop(ckpt_ctx* c, uint64_t uid) {
     c->digests.erase(it);
 }
 
-// Keep an image's digest table resident (copied from crc_dev on stream s;
-// the caller synchronizes s before the table is used).
-void mk::digest_insert(ckpt_ctx* c, uint64_t uid, const uint32_t* crc_dev, uint64_t nc, hipStream_t s) {
-    uint32_t* to = digest_reserve(c, uid, nc);
-    if (to && hipMemcpyAsync(to, crc_dev, 4 * nc, hipMemcpyDeviceToDevice, s) != hipSuccess) digest_drop(c, uid);
-}
-
 // Whether [p, p + n) lies in one pinned host allocation, which kernels reach
 // at the same address, and starts 16-byte aligned.
 static bool pinned_range(const void* p, uint64_t n) {

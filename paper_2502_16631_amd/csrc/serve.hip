@@ -58,8 +58,19 @@ constexpr uint64_t kTaskFailed = ~0ull;
 constexpr uint64_t kCopyPiece = 64ull << 20;
 
 struct Lane {
-    DevBuf descs, arc, kinds, ctl, off, wb, staging, dig, prevcrc, amap;
+    DevBuf descs, arc, kinds, ctl, off, wb, staging, prevcrc, amap;
     StatusBuf status;
+    AllocDesc* hd = nullptr;   // pinned: the request's descriptors, which the set-up kernel reads
+    uint64_t hd_cap = 0;
+    hipError_t ensure_hd(uint64_t n) {
+        if (n <= hd_cap) return hipSuccess;
+        if (hd) hipHostFree(hd);
+        hd = nullptr;
+        hd_cap = 0;
+        hipError_t e = pinned_small((void**)&hd, n * sizeof(AllocDesc));
+        if (e == hipSuccess) hd_cap = n;
+        return e;
+    }
     uint8_t* hs = nullptr;   // pinned: per-window payload lengths / offsets, digests, flags
     uint64_t hs_cap = 0;
     uint8_t* ht = nullptr;   // pinned bounce buffer for the tables of pageable images
@@ -102,7 +113,7 @@ struct Lane {
         return hipSuccess;
     }
     void release() {
-        DevBuf* b[] = {&descs, &arc, &kinds, &ctl, &off, &wb, &staging, &dig, &prevcrc, &amap};
+        DevBuf* b[] = {&descs, &arc, &kinds, &ctl, &off, &wb, &staging, &prevcrc, &amap};
         for (DevBuf* x : b) x->release();
         status.release();
         for (hipEvent_t e : ev) hipEventDestroy(e);
@@ -110,10 +121,11 @@ struct Lane {
         if (fin) hipEventDestroy(fin);
         if (hs) hipHostFree(hs);
         if (ht) hipHostFree(ht);
+        if (hd) hipHostFree(hd);
     }
 };
 
-enum Phase { kQueued, kAlloc, kValidate, kVerify, kRun, kFinal, kDrain, kDone };
+enum Phase { kQueued, kAlloc, kVerify, kRun, kFinal, kDrain, kDone };
 
 struct Req {
     uint64_t ticket = 0;
@@ -139,7 +151,7 @@ struct Req {
     uint64_t staged = 0;       // restore: windows whose H2D copy is enqueued
     uint64_t copied = 0;       // dump: windows whose D2H copy is enqueued
     uint64_t pos = 0;          // dump: payload bytes so far
-    uint64_t nu = 0;           // restore: UNCHANGED chunks
+    std::vector<uint64_t> wb;  // restore: payload offset at each window's start, and the total
     bool pinned = true;        // the host image (dump: out, restore: img) is pinned
     uint64_t alloc_bytes = 0;  // dump: image size to allocate
     int drain_rc = 0;          // kDrain: the result once the request's host tasks are done
@@ -354,6 +366,23 @@ uint32_t* next_ticket_slot(ckpt_server* s) {
     } while (0)
 
 // ---------------------------------------------------------------- admission
+void progress_restore(ckpt_server* s, Req* r);
+
+// The request's descriptors and chunk map as part of its set-up launch. (The
+// lane was free: its previous request's launches no longer read L.hd.)
+hipError_t setup_table(Lane& L, Req* r, SetupJob* sj) {
+    hipError_t e = L.amap.ensure(4 * std::max<uint64_t>(r->nc, 1));
+    if (e == hipSuccess) e = L.ensure_hd(r->d.size());
+    if (e != hipSuccess) return e;
+    if (!r->d.empty()) memcpy(L.hd, r->d.data(), sizeof(AllocDesc) * r->d.size());
+    sj->src = L.hd;
+    sj->dst = L.descs.as<AllocDesc>();
+    sj->n_allocs = (uint32_t)r->d.size();
+    sj->C = r->C;
+    sj->map = L.amap.as<uint32_t>();
+    return hipSuccess;
+}
+
 void admit_dump(ckpt_server* s, Req* r) {
     ckpt_ctx* c = s->ctx;
     Lane& L = s->lanes[r->lane];
@@ -399,7 +428,7 @@ void admit_dump(ckpt_server* s, Req* r) {
     SCHK(L.status.ensure(8 * (r->per + 64), s->s_dump));
     SCHK(L.ctl.ensure(16 * (r->W + 2) + 64));
     SCHK(L.staging.ensure(2 * s->slot));
-    SCHK(L.ensure_hs(8 * (r->W + 2) + 64));
+    SCHK(L.ensure_hs(8 * (r->W + 4) + 64));   // window lengths; error word and two stamps
     SCHK(L.ensure_events(r->W + 1));
     // the image is allocated by a worker (pinning gigabytes takes tens of
     // milliseconds); the request's first windows may run meanwhile
@@ -413,6 +442,8 @@ void admit_dump(ckpt_server* s, Req* r) {
         t.value = 1;
         host_task(s, t);
     }
+    SetupJob sj;
+    memset(&sj, 0, sizeof(sj));
     if (r->rq.prev && pv.n_chunks) {
         // pinned: later windows of this request read it while other requests
         // complete and insert their own tables
@@ -420,15 +451,15 @@ void admit_dump(ckpt_server* s, Req* r) {
         if (r->prev_dev) r->prev_pinned = r->rq.prev->uid;
         if (!r->prev_dev) {
             SCHK(L.prevcrc.ensure(4 * pv.n_chunks));
-            SCHK(hipMemcpyAsync(L.prevcrc.p, pv.crcs, 4 * pv.n_chunks, hipMemcpyHostToDevice, s->s_dump));
+            if (r->rq.prev->pinned) sj.add_copy(L.prevcrc.p, pv.crcs, 4 * pv.n_chunks);
+            else SCHK(hipMemcpyAsync(L.prevcrc.p, pv.crcs, 4 * pv.n_chunks, hipMemcpyHostToDevice, s->s_dump));
             r->prev_dev = L.prevcrc.as<uint32_t>();
         }
     }
-    SCHK(L.amap.ensure(4 * std::max<uint64_t>(r->nc, 1)));
-    SCHK(hipMemcpyAsync(L.descs.p, r->d.data(), sizeof(AllocDesc) * r->n, hipMemcpyHostToDevice, s->s_dump));
-    SCHK(launch_chunk_map(L.descs.as<AllocDesc>(), r->n, r->C, L.amap.as<uint32_t>(), s->s_dump));
-    SCHK(launch_fill32(L.ctl.as<uint32_t>(), 0, (16 * (r->W + 2) + 64) / 4, s->s_dump));
-    SCHK(launch_fill32(L.kinds.as<uint32_t>(), 0, ceil_div(r->tl - 32ull * r->n - 4 * r->nc, 4), s->s_dump));
+    SCHK(setup_table(L, r, &sj));
+    sj.add_fill(L.ctl.p, (16 * (r->W + 2) + 64) / 4, 0);
+    sj.add_fill(L.kinds.p, ceil_div(r->tl - 32ull * r->n - 4 * r->nc, 4), 0);
+    SCHK(launch_setup(sj, s->s_dump));
     r->phase = kAlloc;
 }
 
@@ -457,46 +488,61 @@ void admit_restore(ckpt_server* s, Req* r) {
     }
     r->per = std::max<uint64_t>(1, s->slot / r->C);
     r->W = ceil_div(std::max<uint64_t>(r->nc, 1), r->per);
+    // tables checked on the host as in the plain form, so that the first
+    // window's upload starts here, not a round trip to the device later
+    // (behind the set-up of every request admitted with it)
+    if (host_crc32c(v.recs, v.tl) != v.tables_crc) { finish(s, r, CKPT_ECORRUPT); return; }
+    std::vector<uint64_t> bounds(r->W + 1), rank(r->W + 1);
+    for (uint64_t w = 0; w <= r->W; ++w) bounds[w] = std::min(r->nc, w * r->per);
+    r->wb.assign(r->W + 1, 0);
+    uint64_t kn[4] = {0, 0, 0, 0};
+    const uint64_t total = scan_kinds(v, bounds, r->wb.data(), rank.data(), kn);
+    if (kn[3] || (kn[2] && !(v.flags & kFlagDelta)) || total != v.D) { finish(s, r, CKPT_ECORRUPT); return; }
+    bool match = v.n_allocs == r->n;
+    for (uint32_t a = 0; match && a < r->n; ++a) match = r->table[a].id == r->d[a].id && r->table[a].size == r->d[a].size;
+    if (!match) { finish(s, r, CKPT_EMISMATCH); return; }
     const uint64_t len_a = 32ull * v.n_allocs + 4 * v.n_chunks, len_b = v.tl - len_a;
     SCHK(L.descs.ensure(sizeof(AllocDesc) * std::max<uint64_t>(v.n_allocs, 1)));
     SCHK(L.arc.ensure(v.tl + 16));
     SCHK(L.kinds.ensure(v.tl + 16));
     SCHK(L.off.ensure(8 * std::max<uint64_t>(v.n_chunks, 1)));
-    SCHK(L.wb.ensure(8 * (r->W + 2)));
+    SCHK(L.wb.ensure(16));
     SCHK(L.status.ensure(8 * (ceil_div(v.n_chunks, 256) + 64), s->s_rest));
-    // ctl: [0] offsets ticket | [8] counts[4] | [40] bad | [48] bad2 | [56] err | [64..] window tickets
-    SCHK(L.ctl.ensure(64 + 4 * (r->W + 4)));
+    // ctl: [0] offsets ticket | [8] counts[4] | [40] bad | [48] bad2 | [56] err
+    SCHK(L.ctl.ensure(64));
     SCHK(L.staging.ensure(2 * s->slot));
-    SCHK(L.ensure_hs(128 + 8 * (r->W + 2)));
+    SCHK(L.ensure_hs(128));
     SCHK(L.ensure_events(r->W + 1));
     uint8_t* ctl = L.ctl.as<uint8_t>();
     hipStream_t st = s->s_rest;
-    SCHK(L.amap.ensure(4 * std::max<uint64_t>(v.n_chunks, 1)));
-    SCHK(hipMemcpyAsync(L.descs.p, r->d.data(), sizeof(AllocDesc) * r->d.size(), hipMemcpyHostToDevice, st));
-    SCHK(launch_chunk_map(L.descs.as<AllocDesc>(), (uint32_t)r->d.size(), r->C, L.amap.as<uint32_t>(), st));
     r->pinned = r->rq.img->pinned;
-    if (r->pinned) {
-        SCHK(hipMemcpyAsync(L.arc.p, v.recs, len_a, hipMemcpyHostToDevice, st));
-        SCHK(hipMemcpyAsync(L.kinds.p, v.kinds, len_b, hipMemcpyHostToDevice, st));
-    } else {
+    SetupJob sj;
+    memset(&sj, 0, sizeof(sj));
+    SCHK(setup_table(L, r, &sj));
+    const uint8_t* tables = v.recs;
+    if (!r->pinned) {
         // tables of a pageable image: host copy into the lane's pinned bounce
-        // buffer (the previous request's uploads from it are done: the lane
-        // was free), then an asynchronous upload
+        // buffer (the previous request's reads of it are done: the lane was free)
         SCHK(L.ensure_ht(v.tl));
         memcpy(L.ht, v.recs, v.tl);
-        SCHK(hipMemcpyAsync(L.arc.p, L.ht, len_a, hipMemcpyHostToDevice, st));
-        SCHK(hipMemcpyAsync(L.kinds.p, L.ht + len_a, len_b, hipMemcpyHostToDevice, st));
+        tables = L.ht;
     }
-    SCHK(launch_fill32(reinterpret_cast<uint32_t*>(ctl), 0, (64 + 4 * (r->W + 4)) / 4, st));
-    SCHK(launch_fill64(reinterpret_cast<uint64_t*>(ctl + 40), ~0ull, 2, st));
-    DigestPlan dp;
-    SCHK(digest_prepare(c, &L.dig, L.arc.as<uint8_t>(), len_a, L.kinds.as<uint8_t>(), len_b, &dp, st));
-    SCHK(digest_enqueue(c, dp, reinterpret_cast<uint32_t*>(L.hs), st));
+    sj.add_copy(L.arc.p, tables, len_a);
+    sj.add_copy(L.kinds.p, tables + len_a, len_b);
+    sj.add_fill(ctl, 10, 0);
+    sj.add_fill(ctl + 40, 4, ~0u);
+    sj.add_fill(ctl + 56, 2, 0);
+    SCHK(launch_setup(sj, st));
+    int T, K;
+    pick_tile(r->C, 0, &T, &K);
+    const EngineConsts* ec;
+    SCHK(get_consts(c, T, r->C, &ec));
+    OffJob oj;
+    memset(&oj, 0, sizeof(oj));
+    int grid = 0;
     if (v.n_chunks) {
         uint32_t ep;
         SCHK(L.status.next(st, &ep));
-        OffJob oj;
-        memset(&oj, 0, sizeof(oj));
         oj.allocs = L.descs.as<AllocDesc>();
         oj.n_allocs = v.n_allocs;
         oj.C = r->C;
@@ -504,45 +550,30 @@ void admit_restore(ckpt_server* s, Req* r) {
         oj.n_chunks = v.n_chunks;
         oj.kind = L.kinds.as<uint8_t>();
         oj.off = L.off.as<uint64_t>();
-        oj.per_window = r->per;
+        oj.per_window = v.n_chunks + 1;
         oj.wb = L.wb.as<uint64_t>();
-        oj.n_windows = r->W;
+        oj.n_windows = 1;
         oj.status = L.status.words();
         oj.ticket = reinterpret_cast<uint32_t*>(ctl);
         oj.counts = reinterpret_cast<unsigned long long*>(ctl + 8);
         oj.err = reinterpret_cast<uint32_t*>(ctl + 56);
         oj.epoch = ep;
-        SCHK(launch_offsets(oj, (int)std::min<uint64_t>(ceil_div(v.n_chunks, 256), 8ull * c->num_cu), st));
-        SCHK(hipMemcpyAsync(L.hs + 128, L.wb.p, 8 * (r->W + 1), hipMemcpyDeviceToHost, st));
+        grid = (int)std::min<uint64_t>(ceil_div(v.n_chunks, 256), 8ull * c->num_cu);
     }
-    SCHK(hipMemcpyAsync(L.hs + 16, ctl + 8, 32, hipMemcpyDeviceToHost, st));
-    SCHK(hipEventRecord(L.fin, st));
-    r->phase = kValidate;
-}
-
-// ---------------------------------------------------------------- restore checks
-void restore_validated(ckpt_server* s, Req* r) {
-    ckpt_ctx* c = s->ctx;
-    Lane& L = s->lanes[r->lane];
-    const ImageView& v = r->v;
-    const uint32_t* dig = reinterpret_cast<const uint32_t*>(L.hs);
-    const uint64_t* cnt = reinterpret_cast<const uint64_t*>(L.hs + 16);
-    const uint64_t len_a = 32ull * v.n_allocs + 4 * v.n_chunks, len_b = v.tl - len_a;
-    if (crc_combine(dig[0], dig[1], len_b) != v.tables_crc) { fail_req(s, r, CKPT_ECORRUPT); return; }
-    const uint64_t nz = cnt[0], nd = cnt[1], nu = cnt[2], ninv = cnt[3];
-    if (ninv || (nu && !(v.flags & 1u)) || nz + nd + nu != v.n_chunks) { fail_req(s, r, CKPT_ECORRUPT); return; }
-    const uint64_t* wb = reinterpret_cast<const uint64_t*>(L.hs + 128);
-    if ((v.n_chunks ? wb[r->W] : 0) != v.D) { fail_req(s, r, CKPT_ECORRUPT); return; }
-    if (v.n_allocs != r->n) { fail_req(s, r, CKPT_EMISMATCH); return; }
-    for (uint32_t a = 0; a < r->n; ++a)
-        if (r->table[a].id != r->d[a].id || r->table[a].size != r->d[a].size) { fail_req(s, r, CKPT_EMISMATCH); return; }
-    r->nu = nu;
-    if (nu) {
-        int T, K;
-        pick_tile(r->C, 0, &T, &K);
-        const EngineConsts* ec;
-        SCHK(get_consts(c, T, r->C, &ec));
-        uint8_t* ctl = L.ctl.as<uint8_t>();
+    // the per-allocation check needs the tables only
+    CombineJob cj;
+    memset(&cj, 0, sizeof(cj));
+    cj.allocs = L.descs.as<AllocDesc>();
+    cj.n_allocs = r->n;
+    cj.C = r->C;
+    cj.crc = reinterpret_cast<const uint32_t*>(L.arc.as<uint8_t>() + 32ull * r->n);
+    cj.ec = ec;
+    cj.recs = L.arc.as<uint8_t>();
+    cj.bad = reinterpret_cast<unsigned long long*>(ctl + 48);
+    cj.mode = kCombineCheck;
+    SCHK(launch_offsets_combine(oj, grid, cj, st));
+    if (kn[2]) {
+        // a delta: its base first
         ChunkJob j;
         memset(&j, 0, sizeof(j));
         j.allocs = L.descs.as<AllocDesc>();
@@ -553,17 +584,18 @@ void restore_validated(ckpt_server* s, Req* r) {
         j.g1 = r->nc;
         j.ec = ec;
         j.kind_in = L.kinds.as<uint8_t>();
-        j.ref_crc = reinterpret_cast<const uint32_t*>(L.arc.as<uint8_t>() + 32ull * r->n);
+        j.ref_crc = cj.crc;
         j.bad = reinterpret_cast<unsigned long long*>(ctl + 40);
         j.err = reinterpret_cast<uint32_t*>(ctl + 56);
         JobList jl = one_job(j, nullptr);   // (verify takes no tickets)
-        SCHK(launch_verify(c, T, K, jl, c->num_cu, s->s_rest));
-        SCHK(hipMemcpyAsync(L.hs + 64, ctl + 40, 8, hipMemcpyDeviceToHost, s->s_rest));
-        SCHK(hipEventRecord(L.fin, s->s_rest));
+        SCHK(launch_verify(c, T, K, jl, c->num_cu, st));
+        SCHK(launch_report(reinterpret_cast<uint64_t*>(L.hs + 64), reinterpret_cast<uint64_t*>(ctl + 40), 1, false, st));
+        SCHK(hipEventRecord(L.fin, st));
         r->phase = kVerify;
         return;
     }
     r->phase = kRun;
+    progress_restore(s, r);   // the first windows on their way up
 }
 
 // ---------------------------------------------------------------- merged launches
@@ -626,18 +658,17 @@ void launch_merged(ckpt_server* s, bool dump) {
             j.kind_out = L.kinds.as<uint8_t>();
             j.prev_crc = r->prev_dev;
             j.status = L.status.words();
-            j.wtotal = reinterpret_cast<uint64_t*>(L.ctl.as<uint8_t>()) + w;
+            j.wtotal = reinterpret_cast<uint64_t*>(L.hs) + w;   // pinned
             j.err = reinterpret_cast<uint32_t*>(L.ctl.as<uint8_t>() + 16 * (r->W + 2));
             // the slot's previous copy must be finished before it is overwritten
             // (a pageable image's copy is: its flag was seen above)
             if (w >= 2 && r->pinned) hipStreamWaitEvent(st, L.slot_ev[w % 2], 0);
         } else {
             uint8_t* ctl = L.ctl.as<uint8_t>();
-            const uint64_t* wb = reinterpret_cast<const uint64_t*>(L.hs + 128);
             j.kind_in = L.kinds.as<uint8_t>();
             j.ref_crc = reinterpret_cast<const uint32_t*>(L.arc.as<uint8_t>() + 32ull * r->n);
             j.off = L.off.as<uint64_t>();
-            j.slot_base = wb[w];
+            j.slot_base = r->wb[w];
             j.bad = reinterpret_cast<unsigned long long*>(ctl + 40);
             j.err = reinterpret_cast<uint32_t*>(ctl + 56);
             if (r->pinned) hipStreamWaitEvent(st, L.ev[w], 0);   // payload copy of this window
@@ -658,8 +689,6 @@ void launch_merged(ckpt_server* s, bool dump) {
     for (Req* r : used) {
         Lane& L = s->lanes[r->lane];
         const uint64_t w = r->launched;
-        if (e == hipSuccess && dump)
-            e = hipMemcpyAsync(L.hs + 8 * w, L.ctl.as<uint64_t>() + w, 8, hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipEventRecord(dump ? L.ev[w] : L.slot_ev[w % 2], st);
         r->launched++;
     }
@@ -702,38 +731,37 @@ void progress_dump(ckpt_server* s, Req* r) {
         r->copied++;
     }
     if (r->phase == kRun && r->copied == r->W) {
-        // tables: per-allocation CRCs, digests, copy-out
+        // the end in one launch: per-allocation CRCs, tables, digest table to
+        // its resident place, error word. Tables go straight into a pinned
+        // image, into the lane's pinned bounce buffer for a pageable one (moved
+        // on the host at the end)
         int T, K;
         pick_tile(r->C, 0, &T, &K);
         const EngineConsts* ec;
         SCHK(get_consts(c, T, r->C, &ec));
         uint32_t* crc_dev = reinterpret_cast<uint32_t*>(L.arc.as<uint8_t>() + 32ull * r->n);
-        CombineJob cj;
-        memset(&cj, 0, sizeof(cj));
-        cj.allocs = L.descs.as<AllocDesc>();
-        cj.n_allocs = r->n;
-        cj.C = r->C;
-        cj.crc = crc_dev;
-        cj.ec = ec;
-        cj.recs = L.arc.as<uint8_t>();
-        cj.mode = kCombineWrite;
-        SCHK(launch_combine(cj, s->s_dump));
         const uint64_t len_a = 32ull * r->n + 4 * r->nc, len_b = r->tl - len_a;
-        uint32_t* hdig = reinterpret_cast<uint32_t*>(L.hs + 8 * (r->W + 1));
-        DigestPlan dp;
-        SCHK(digest_prepare(c, &L.dig, L.arc.as<uint8_t>(), len_a, L.kinds.as<uint8_t>(), len_b, &dp, s->s_dump));
-        SCHK(digest_enqueue(c, dp, hdig, s->s_dump));
-        // tables: straight into a pinned image, through the lane's pinned
-        // bounce buffer for a pageable one (moved on the host at the end)
         uint8_t* tdst = r->out->p + kHeader;
         if (!r->pinned) {
             SCHK(L.ensure_ht(r->tl));
             tdst = L.ht;
         }
-        SCHK(hipMemcpyAsync(tdst, L.arc.p, len_a, hipMemcpyDeviceToHost, s->s_dump));
-        SCHK(hipMemcpyAsync(tdst + len_a, L.kinds.p, len_b, hipMemcpyDeviceToHost, s->s_dump));
-        SCHK(hipMemcpyAsync(hdig + 2, L.ctl.as<uint8_t>() + 16 * (r->W + 2), 4, hipMemcpyDeviceToHost, s->s_dump));
-        digest_insert(c, r->out->uid, crc_dev, r->nc, s->s_dump);
+        FinishJob fj;
+        memset(&fj, 0, sizeof(fj));
+        fj.c.allocs = L.descs.as<AllocDesc>();
+        fj.c.n_allocs = r->n;
+        fj.c.C = r->C;
+        fj.c.crc = crc_dev;
+        fj.c.ec = ec;
+        fj.c.recs = tdst;
+        fj.c.mode = kCombineWrite;
+        fj.add_copy(tdst + 32ull * r->n, crc_dev, 4 * r->nc);
+        fj.add_copy(tdst + len_a, L.kinds.p, len_b);
+        if (uint32_t* resident = digest_reserve(c, r->out->uid, r->nc)) fj.add_copy(resident, crc_dev, 4 * r->nc);
+        fj.rep = reinterpret_cast<uint64_t*>(L.hs + 8 * (r->W + 1));
+        fj.rep_src = reinterpret_cast<uint64_t*>(L.ctl.as<uint8_t>() + 16 * (r->W + 2));   // error word (and zeros)
+        fj.n_rep = 1;
+        SCHK(launch_finish(fj, s->s_dump));
         SCHK(hipEventRecord(L.fin, s->s_dump));
         r->phase = kFinal;
         return;
@@ -742,9 +770,7 @@ void progress_dump(ckpt_server* s, Req* r) {
         if (r->W && !down_done(r, L, r->W - 1)) return;
         if (r->W > 1 && !down_done(r, L, r->W - 2)) return;
         if (r->tasks.load(std::memory_order_acquire) != 0) return;
-        const uint32_t* hdig = reinterpret_cast<const uint32_t*>(L.hs + 8 * (r->W + 1));
-        if (hdig[2]) { fail_req(s, r, CKPT_EHIP); return; }
-        const uint64_t len_a = 32ull * r->n + 4 * r->nc, len_b = r->tl - len_a;
+        if (*reinterpret_cast<const uint32_t*>(L.hs + 8 * (r->W + 1))) { fail_req(s, r, CKPT_EHIP); return; }
         uint8_t* h = r->out->p;
         if (!r->pinned) memcpy(h + kHeader, L.ht, r->tl);
         memcpy(h, "MICKPT01", 8);
@@ -757,7 +783,7 @@ void progress_dump(ckpt_server* s, Req* r) {
         put32(h + 40, r->rq.prev ? r->prev_digest : 0u);
         put32(h + 44, 0);
         put64(h + 48, r->N);
-        put32(h + 56, crc_combine(hdig[0], hdig[1], len_b));
+        put32(h + 56, host_crc32c(h + kHeader, r->tl));
         put32(h + 60, host_crc32c(h, 60));
         r->out->n = kHeader + r->tl + r->pos;
         finish(s, r, CKPT_OK);
@@ -765,13 +791,7 @@ void progress_dump(ckpt_server* s, Req* r) {
 }
 
 void progress_restore(ckpt_server* s, Req* r) {
-    ckpt_ctx* c = s->ctx;
     Lane& L = s->lanes[r->lane];
-    if (r->phase == kValidate) {
-        if (hipEventQuery(L.fin) != hipSuccess) return;
-        restore_validated(s, r);
-        return;
-    }
     if (r->phase == kVerify) {
         if (hipEventQuery(L.fin) != hipSuccess) return;
         const uint64_t bad = *reinterpret_cast<const uint64_t*>(L.hs + 64);
@@ -784,7 +804,7 @@ void progress_restore(ckpt_server* s, Req* r) {
         // stage payload windows ahead of the kernels: two slots; a pinned
         // image by the copy engine on the upload stream, a pageable one by a
         // worker (which first waits for the kernel that last read the slot)
-        const uint64_t* wb = reinterpret_cast<const uint64_t*>(L.hs + 128);
+        const std::vector<uint64_t>& wb = r->wb;
         while (r->staged < r->W && r->staged < r->launched + 2) {
             const uint64_t w = r->staged;
             if (w >= 2 && r->launched < w - 1) break;
@@ -804,23 +824,9 @@ void progress_restore(ckpt_server* s, Req* r) {
             r->staged++;
         }
         if (r->launched == r->W) {
-            int T, K;
-            pick_tile(r->C, 0, &T, &K);
-            const EngineConsts* ec;
-            SCHK(get_consts(c, T, r->C, &ec));
             uint8_t* ctl = L.ctl.as<uint8_t>();
-            CombineJob cj;
-            memset(&cj, 0, sizeof(cj));
-            cj.allocs = L.descs.as<AllocDesc>();
-            cj.n_allocs = r->n;
-            cj.C = r->C;
-            cj.crc = reinterpret_cast<const uint32_t*>(L.arc.as<uint8_t>() + 32ull * r->n);
-            cj.ec = ec;
-            cj.recs = L.arc.as<uint8_t>();
-            cj.bad = reinterpret_cast<unsigned long long*>(ctl + 48);
-            cj.mode = kCombineCheck;
-            SCHK(launch_combine(cj, s->s_rest));
-            SCHK(hipMemcpyAsync(L.hs + 64, ctl + 40, 24, hipMemcpyDeviceToHost, s->s_rest));
+            SCHK(launch_report(reinterpret_cast<uint64_t*>(L.hs + 64), reinterpret_cast<uint64_t*>(ctl + 40), 3, false,
+                               s->s_rest));   // bad, bad2, err
             SCHK(hipEventRecord(L.fin, s->s_rest));
             r->phase = kFinal;
         }
