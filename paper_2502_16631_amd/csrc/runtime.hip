@@ -1032,10 +1032,18 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             for (uint64_t i = 0; i < p; ++i) piece.push_back(nc * i / p);
         } else {
             // short first pieces, so that the link starts early, and short last
-            // ones, so that little is left to copy when the last digest ends
-            static const uint32_t at32[] = {0, 2, 5, 9, 13, 17, 21, 25, 29, 31};
-            for (uint32_t x : at32)
-                if (piece.empty() || nc * x / 32 > piece.back()) piece.push_back(nc * x / 32);
+            // ones, so that little is left to copy when the last digest ends;
+            // whole rounds of the digest pass over its groups where a piece has
+            // some (a last round a third full costs as much as a full one)
+            // (on a ring, pieces small enough for several slots)
+            static const std::vector<uint32_t> few = {0, 2, 8, 16, 24, 30},
+                                               many = {0, 2, 6, 10, 14, 18, 22, 26, 30};
+            const uint64_t round = C < kScanMinChunk ? 1 : 2ull * c->num_cu * (512 / scan_width(C));
+            for (uint32_t x : wins.size() > 1 ? many : few) {
+                uint64_t g = nc * x / 32;
+                if (g > round) g = (g + round / 2) / round * round;
+                if (piece.empty() || (g > piece.back() && g < nc)) piece.push_back(g);
+            }
         }
         piece.push_back(nc);
         if (wins.size() > 1) {
