@@ -83,7 +83,8 @@ typedef struct ckpt_image ckpt_image;   /* an image in host memory (pinned if av
  * for defaults. */
 #define CKPT_OPT_PER_ALLOC  1u   /* launch the kernels once per allocation (baseline form)   */
 #define CKPT_OPT_GRAPH      2u   /* batched form: capture the device stage in a hipGraph and
-                                    replay it (cached per table shape)                      */
+                                    replay it (cached per table shape); a restore of a pinned
+                                    image, a few launches that read it where it is, has none */
 #define CKPT_OPT_NO_TIMING  4u   /* skip per-stage device timing events                      */
 /* Dump only (ignored by restore, where the image says how it is stored):
  * store each full-length DATA chunk as a byte-plane record when that record

@@ -198,3 +198,34 @@ def test_deltas_in_pieces_match_the_oracle(c, budget):
         same(before, table)
     finally:
         mk.ckpt_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("strict", [0, 1])
+def test_graph_restore_of_a_pageable_image(ctx, strict):
+    """The captured restore (pageable images), replayed with new images, and
+    its rejection of damaged tables and payload, against the plain path's
+    answers for the same bytes in pinned memory."""
+    c = 65536
+    opts = mk.make_opts(flags=mk.OPT_GRAPH, strict_verify=strict)
+    to = blank(state(c, 30, 2))
+    for seed in (30, 31, 32):
+        table = state(c, seed, 2)
+        rc, pinned, _ = mk.ckpt_dump(ctx, table, opts=mk.make_opts(chunk_size=c))
+        assert rc == 0
+        with pageable():
+            rc, img = mk.ckpt_image_import(np.frombuffer(pinned.tobytes(), np.uint8))
+            assert rc == 0
+        rc, res = mk.ckpt_restore(ctx, img, to, opts=opts)
+        assert rc == 0 and res.windows == 1
+        same(to, table)
+        for at in (64 + 32 * len(table) + 8, -12345):
+            got = []
+            for im in (pinned, img):
+                v = im.view()
+                v[at] ^= 0x04
+                rc, res = mk.ckpt_restore(ctx, im, to, opts=opts)
+                got.append((rc, res.first_bad_chunk))
+                v[at] ^= 0x04
+            assert got[0] == got[1] and got[0][0] == mk.CKPT_ECORRUPT
+        pinned.free()
+        img.free()
