@@ -242,7 +242,7 @@ constexpr int kLinkGrid = 64;
 constexpr uint64_t kDirectDump = 64ull << 20;
 // The ranges a restore may stage the first ones of, and the least payload
 // worth it.
-constexpr uint64_t kHeadGrid = 64;
+constexpr uint64_t kHeadGrid = 256;
 constexpr uint64_t kMinHead = 1ull << 20;
 
 // Storage hooks. A dump told of a sink reports every payload copy into the
