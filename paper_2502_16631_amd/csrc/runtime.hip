@@ -1038,7 +1038,10 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             // (on a ring, pieces small enough for several slots)
             static const std::vector<uint32_t> few = {0, 2, 8, 16, 24, 30},
                                                many = {0, 2, 6, 10, 14, 18, 22, 26, 30};
-            const uint64_t round = C < kScanMinChunk ? 1 : 2ull * c->num_cu * (512 / scan_width(C));
+            uint64_t round = C < kScanMinChunk ? 1 : 2ull * c->num_cu * (512 / scan_width(C));
+            // (a rounded piece of a state not much longer than a round would
+            // leave no room for two)
+            if (wins.size() > 1 && (nc / 8 + round) * C > c->budget / 3) round = 1;
             for (uint32_t x : wins.size() > 1 ? many : few) {
                 uint64_t g = nc * x / 32;
                 if (g > round) g = (g + round / 2) / round * round;

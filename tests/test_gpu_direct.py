@@ -200,6 +200,31 @@ def test_deltas_in_pieces_match_the_oracle(c, budget):
         mk.ckpt_ctx_destroy(ctx)
 
 
+def test_a_delta_keeps_to_the_staging_budget():
+    """A delta of a state longer than the budget, in chunks so small that a
+    round of the digest pass is half the state, takes no more device memory
+    than the budget and 32 MiB of tables and streams."""
+    c, budget = 65536, 150 << 20
+    table = [(1, torch.randint(0, 256, (390 << 20,), dtype=torch.uint8, device="cuda"))]
+
+    def taken():   # by others than torch
+        torch.cuda.synchronize()
+        free, total = torch.cuda.mem_get_info()
+        return total - free - torch.cuda.memory_reserved()
+
+    before = taken()
+    ctx = mk.ckpt_ctx_create(0, budget)
+    try:
+        rc, base, _ = mk.ckpt_dump(ctx, table, opts=mk.make_opts(chunk_size=c))
+        assert rc == 0
+        table[0][1][5 * c] ^= 1
+        rc, delta, res = mk.ckpt_dump(ctx, table, prev=base, opts=mk.make_opts(chunk_size=c))
+        assert rc == 0 and res.n_data == 1
+        assert taken() - before <= budget + (32 << 20)
+    finally:
+        mk.ckpt_ctx_destroy(ctx)
+
+
 @pytest.mark.parametrize("strict", [0, 1])
 def test_graph_restore_of_a_pageable_image(ctx, strict):
     """The captured restore (pageable images), replayed with new images, and
