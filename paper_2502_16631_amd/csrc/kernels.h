@@ -7,7 +7,8 @@ namespace mk {
 
 // classify: digest and kind of every chunk, nothing else (first pass of a
 // two-pass dump; its last pass, the gather, is k_gather in gather.hip).
-enum Mode : int { kModeDump = 0, kModeDigest = 1, kModeVerify = 2, kModeRestore = 3, kModeClassify = 4 };
+enum Mode : int { kModeDump = 0, kModeDigest = 1, kModeVerify = 2, kModeRestore = 3, kModeClassify = 4,
+                  kModeShort = 5 };   // (launch_short's occupancy)
 
 // One launch of the chunk engine over global chunks [g0, g1).
 struct ChunkJob {
@@ -136,6 +137,36 @@ struct FinishJob {
         copy[n_copies++] = {static_cast<uint32_t*>(d), static_cast<const uint32_t*>(s), bytes / 4};
     }
 };
+
+// A short full dump in one launch (k_dump_short): chunk g by work-group g,
+// allocation a by work-group n_chunks + a. Everything the host prepares and
+// reads is in pinned memory.
+struct ShortChunk {              // 32 bytes
+    const uint8_t* ptr;          // first byte of the chunk
+    uint32_t len;                // valid bytes
+    uint32_t full;               // len is the chunk size
+    uint32_t tail_init, tail_unshift;
+    uint64_t pad;
+};
+static_assert(sizeof(ShortChunk) == 32, "one load's worth");
+struct ShortJob {
+    const ShortChunk* chunks;    // pinned
+    const AllocDesc* allocs;     // pinned
+    uint32_t n_chunks, n_allocs;
+    uint32_t C;
+    uint32_t epoch;              // of status
+    const EngineConsts* ec;
+    uint64_t* status;            // [2 n_chunks]: payload bytes of chunk g; its digest and kind
+    uint8_t* payload;            // the image's, pinned like the tables:
+    uint8_t* recs;
+    uint32_t* crc;
+    uint8_t* kind;
+    uint32_t* resident;          // device copy of the digests, or nullptr
+    uint64_t* rep;               // pinned, cleared by the host: payload bytes, error, device clock at the start,
+                                 // with a chunk read, at the tables' start and end
+};
+constexpr uint32_t kShortRep = 6;
+hipError_t launch_short(int T, int K, const ShortJob& job, hipStream_t s);
 
 // Validation of a restore inside a captured graph: *gate = 1 when the
 // tables digest combined from the device's two halves equals the expected

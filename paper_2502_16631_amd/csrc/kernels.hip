@@ -1306,6 +1306,113 @@ __global__ void k_report(uint64_t* host, const uint64_t* dev, uint32_t n, bool c
         __hip_atomic_store((gu64*)&host[t], t < n ? dev[t] : wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// A result word to pinned host memory.
+__device__ inline void st_host(uint64_t* p, uint64_t v) {
+    __hip_atomic_store((gu64*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A status word of this launch, once it is there (bounded, as lb_walk).
+__device__ inline uint64_t wait_word(uint64_t* p, uint32_t epoch, uint64_t* err) {
+    uint64_t w;
+    for (uint32_t spins = 0; !lb_valid(w = ld_relaxed(p), epoch);) {
+        if (++spins > kMaxSpins) {
+            st_host(err, 1);
+            return 0;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return w;
+}
+
+// Short full dump, C = 16 T K, to a pinned image, set-up and end included.
+// Bound by latencies and the host link. As three launches (set-up, chunks,
+// end) a dump of 16 chunks of 64 KiB took 59 us inside the call, 18 of them
+// for its payload on the link; here 39 (64 of 64 KiB: 125 -> 104, 384: 515 ->
+// 487). The chunks' entries come over the link in one read each, and the end
+// (the tables, the allocations' digests) runs while the payload drains, which
+// is why the payload is stored after the digest. Every work-group is resident
+// (the launch's limit); a chunk's waits only for words that those before it
+// publish before they wait, an allocation's for its chunks' words. The
+// predecessors' payload lengths are read one by one, a thread each: a
+// thousand at most for the usual chunk sizes, and no chain.
+template <int T, int K>
+__global__ void __launch_bounds__(T) k_dump_short(ShortJob j) {
+    constexpr int NW = T / 64;
+    constexpr uint32_t C = 16u * T * K;
+    __shared__ uint32_t s_dt[16 * 256];
+    __shared__ uint32_t s_red[NW];
+    __shared__ uint32_t s_any[NW];
+    __shared__ uint32_t s_sum[NW];
+    const uint32_t tid = threadIdx.x, g = blockIdx.x;
+    const uint64_t tag = (uint64_t)(j.epoch & kEpochMask) << 40;
+    const uint64_t t0 = wall_clock64();
+    if (g >= j.n_chunks) {
+        // the end: allocation a's digests and kinds to the image, its record
+        const uint32_t a = g - j.n_chunks;
+        if (tid < 64) s_dt[tid] = j.ec->x2n[tid];
+        const AllocDesc ad = j.allocs[a];
+        __syncthreads();
+        const uint32_t nk = (uint32_t)((ad.size + C - 1) / C);
+        uint32_t acc = 0;
+        uint64_t t1 = 0;
+        for (uint32_t k = tid; k < nk; k += T) {
+            const uint32_t c = (uint32_t)ad.first + k;
+            const uint64_t w = wait_word(j.status + j.n_chunks + c, j.epoch, j.rep + 1);
+            if (k == tid) t1 = wall_clock64();
+            const uint32_t crc = (uint32_t)w;
+            j.crc[c] = crc;
+            j.kind[c] = (uint8_t)(w >> 32);
+            if (j.resident) j.resident[c] = crc;
+            const uint64_t end = k + 1 == nk ? ad.size : (uint64_t)(k + 1) * C;
+            acc ^= gf_mul_v(crc, xpow8(ad.size - end, s_dt));
+        }
+        const uint32_t crc = wg_xor<NW>(acc, s_red);
+        const uint32_t w[8] = {(uint32_t)ad.id, (uint32_t)(ad.id >> 32), (uint32_t)ad.size, (uint32_t)(ad.size >> 32),
+                               (uint32_t)ad.first, (uint32_t)(ad.first >> 32), crc, 0};
+        uint32_t x = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x = tid == (uint32_t)i ? w[i] : x;
+        if (tid < 8) reinterpret_cast<uint32_t*>(j.recs + 32ull * a)[tid] = x;
+        if (a + 1 == j.n_allocs && tid == 0) {
+            st_host(j.rep + 4, nk ? t1 : t0);
+            st_host(j.rep + 5, wall_clock64());
+        }
+        return;
+    }
+    const ShortChunk sc = j.chunks[g];
+    for (uint32_t i = tid; i < 16 * 256; i += T) s_dt[i] = j.ec->dt[i];
+    const uint32_t lanec = j.ec->lane[tid];
+    v4u v[K];
+    load_rows<T, K>(v, sc.ptr, sc.len, tid, true);
+    uint32_t orw = 0;
+#pragma unroll
+    for (int r = 0; r < K; ++r) orw |= or4(v[r]);
+    const uint32_t any = wg_any_lds<NW>(orw != 0, s_any);   // (and the tables are in LDS)
+    const uint32_t plen = any ? (sc.len + 15u) & ~15u : 0;
+    if (tid == 0) st_relaxed(&j.status[g], kStAgg | tag | plen);
+    if (g == 0 && tid == 0) {
+        st_host(j.rep + 2, t0);
+        st_host(j.rep + 3, wall_clock64());
+    }
+    const uint32_t acc = any ? crc_rows<K>(v, 0, s_dt) : 0;
+    uint32_t raw = wg_xor_lds<NW>(gf_mul_v(acc, lanec), s_red);
+    if (!sc.full) raw = gf_mul_v(raw, sc.tail_unshift);
+    const uint32_t crc = ~(raw ^ (sc.full ? j.ec->full_init : sc.tail_init));
+    if (tid == 0)
+        st_relaxed(&j.status[j.n_chunks + g], kStAgg | tag | (uint64_t)(any ? kData : kZero) << 32 | crc);
+    uint32_t before = 0;
+    for (uint32_t i = tid; i < g; i += T) before += (uint32_t)wait_word(&j.status[i], j.epoch, j.rep + 1);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) before += __shfl_xor(before, m);
+    if ((tid & 63) == 0) s_sum[tid >> 6] = before;
+    lds_barrier();
+    uint32_t excl = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) excl += s_sum[w];
+    store_rows_padded<T, K>(v, j.payload + excl, plen, tid, any != 0);
+    if (g + 1 == j.n_chunks && tid == 0) st_host(j.rep, excl + plen);
+}
+
 // Two descriptors passed by value (kernel arguments are captured at launch,
 // so the host copy may go away at once, also inside a captured graph).
 __global__ void k_store_descs(AllocDesc* dst, AllocDesc a, AllocDesc b) {
@@ -1364,6 +1471,17 @@ hipError_t launch_tk(int mode, const JobList& jl, int grid, hipStream_t s) {
 }
 
 template <int T, int K>
+hipError_t short_tk(const ShortJob& j, hipStream_t s) {
+    if constexpr (T >= 64) {
+        if (j.C == 16u * T * K && j.n_chunks && j.n_allocs) {
+            hipLaunchKernelGGL((k_dump_short<T, K>), dim3(j.n_chunks + j.n_allocs), dim3(T), 0, s, j);
+            return hipGetLastError();
+        }
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int T, int K>
 hipError_t occ_tk(int mode, int* n) {
     constexpr int NT = T < 64 ? 64 : T;
     switch (mode) {
@@ -1396,6 +1514,9 @@ hipError_t occ_tk(int mode, int* n) {
             return hipErrorInvalidValue;
         case kModeDigest: return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeDigest>, NT, 0);
         case kModeRestore: return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeRestore>, NT, 0);
+        case kModeShort:
+            if constexpr (T >= 64) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_dump_short<T, K>, T, 0);
+            return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 }
@@ -1419,6 +1540,13 @@ hipError_t launch_chunks(int T, int K, int mode, const JobList& jl, int grid, hi
 #define MK_LAUNCH(t, k) if (T == t && K == k) return launch_tk<t, k>(mode, jl, grid, s);
     MK_TILES(MK_LAUNCH)
 #undef MK_LAUNCH
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_short(int T, int K, const ShortJob& job, hipStream_t s) {
+#define MK_SHORT(t, k) if (T == t && K == k) return short_tk<t, k>(job, s);
+    MK_TILES(MK_SHORT)
+#undef MK_SHORT
     return hipErrorInvalidValue;
 }
 

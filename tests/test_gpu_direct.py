@@ -200,6 +200,38 @@ def test_deltas_in_pieces_match_the_oracle(c, budget):
         mk.ckpt_ctx_destroy(ctx)
 
 
+@pytest.mark.parametrize("c,chunks", [(1024, 5), (1024, 3000), (4096, 1), (4096, 2290), (4096, 2330), (16384, 700),
+                                      (32768, 63), (65536, 65), (65536, 1009), (65536, 1016), (131072, 130)])
+def test_short_dumps_in_one_launch(ctx, c, chunks):
+    """Short dumps on both sides of the number of work-groups that are
+    resident at once, with empty and one-byte allocations, zero chunks and
+    ragged tails, repeated with other data (status words of the call before),
+    against the oracle."""
+    sizes = [0, 1, c + 15, 0]
+    sizes.append(max(1, (chunks - 3) * c - 1))
+    out = torch.empty(80 << 20, dtype=torch.uint8, pin_memory=True).numpy()
+    out[:] = 0xEE
+    for seed in range(3):
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        table = [(10 - i, torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda", generator=gen))
+                 for i, n in enumerate(sizes)]
+        t = table[-1][1]
+        t[: t.numel() // 3 * seed] = 0
+        orc, want = corc.dump(workloads.host_copy(table), c)
+        assert orc == 0
+        opts = mk.make_opts(chunk_size=c)
+        rc, img, res = mk.ckpt_dump(ctx, table, opts=opts)
+        assert rc == 0 and np.array_equal(img.view(), want)
+        assert res.n_chunks == sum(-(-n // c) for n in sizes)
+        rc, n, _ = mk.ckpt_dump_into(ctx, table, out, opts=opts)
+        assert rc == 0 and np.array_equal(out[:n], want)
+        t[-1] ^= 1   # the digests that the dump kept on the device
+        rc, delta, res = mk.ckpt_dump(ctx, table, prev=img, opts=opts)
+        assert rc == 0 and res.n_data == 1 and res.n_unchanged == res.n_chunks - 1 - res.n_zero
+        img.free()
+        delta.free()
+
+
 def test_a_delta_keeps_to_the_staging_budget():
     """A delta of a state longer than the budget, in chunks so small that a
     round of the digest pass is half the state, takes no more device memory
