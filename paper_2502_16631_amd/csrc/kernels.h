@@ -168,6 +168,32 @@ struct ShortJob {
 constexpr uint32_t kShortRep = 6;
 hipError_t launch_short(int T, int K, const ShortJob& job, hipStream_t s);
 
+// A short full restore from a pinned image in one launch (k_restore_short):
+// the chunks by `groups` work-groups, allocation a by work-group groups + a.
+struct ShortRecord {             // 48 bytes
+    uint8_t* ptr;                // first byte of the chunk
+    const uint8_t* src;          // its record in the image, or nullptr: a ZERO chunk
+    uint32_t len;                // valid bytes
+    uint32_t full;               // len is the chunk size
+    uint32_t tail_init, tail_unshift;
+    uint32_t crc;                // expected digest
+    uint32_t pad[3];
+};
+static_assert(sizeof(ShortRecord) == 48, "whole 16-byte words");
+struct ShortRestoreJob {
+    const ShortRecord* chunks;   // pinned
+    const AllocDesc* allocs;     // pinned
+    uint32_t n_chunks, n_allocs;
+    uint32_t C;
+    uint32_t groups;             // 1 .. n_chunks
+    const EngineConsts* ec;
+    const uint8_t* recs;         // the image's, pinned like its digests
+    const uint32_t* crc;
+    uint64_t* rep;               // pinned: device clock at the start and end of an allocation's check
+    uint8_t* bad;                // pinned, [n_chunks + n_allocs], cleared by the host: 1 where a check failed
+};
+hipError_t launch_short_restore(int T, int K, const ShortRestoreJob& job, hipStream_t s);
+
 // Validation of a restore inside a captured graph: *gate = 1 when the
 // tables digest combined from the device's two halves equals the expected
 // value, the kinds are all ZERO or DATA and the payload total equals the

@@ -1324,6 +1324,17 @@ __device__ inline uint64_t wait_word(uint64_t* p, uint32_t epoch, uint64_t* err)
     return w;
 }
 
+// The digest tables on their way to LDS, without registers in between: they
+// are there once the vector memory counter has drained.
+template <int T>
+__device__ inline void stream_tables(uint32_t* s_dt, const EngineConsts* ec) {
+    const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+#pragma unroll
+    for (int i = 0; i < 1024 / T; ++i)
+        __builtin_amdgcn_global_load_lds((glb_void*)(ec->dt + 4 * (i * T + tid)),
+                                         (lds_void*)(s_dt + 4 * (i * T + wave * 64u)), 16, 0, 0);
+}
+
 // Short full dump, C = 16 T K, to a pinned image, set-up and end included.
 // Bound by latencies and the host link. As three launches (set-up, chunks,
 // end) a dump of 16 chunks of 64 KiB took 59 us inside the call, 18 of them
@@ -1339,7 +1350,7 @@ template <int T, int K>
 __global__ void __launch_bounds__(T) k_dump_short(ShortJob j) {
     constexpr int NW = T / 64;
     constexpr uint32_t C = 16u * T * K;
-    __shared__ uint32_t s_dt[16 * 256];
+    __shared__ __attribute__((aligned(16))) uint32_t s_dt[16 * 256];
     __shared__ uint32_t s_red[NW];
     __shared__ uint32_t s_any[NW];
     __shared__ uint32_t s_sum[NW];
@@ -1379,14 +1390,15 @@ __global__ void __launch_bounds__(T) k_dump_short(ShortJob j) {
         }
         return;
     }
+    stream_tables<T>(s_dt, j.ec);
     const ShortChunk sc = j.chunks[g];
-    for (uint32_t i = tid; i < 16 * 256; i += T) s_dt[i] = j.ec->dt[i];
     const uint32_t lanec = j.ec->lane[tid];
     v4u v[K];
     load_rows<T, K>(v, sc.ptr, sc.len, tid, true);
     uint32_t orw = 0;
 #pragma unroll
     for (int r = 0; r < K; ++r) orw |= or4(v[r]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const uint32_t any = wg_any_lds<NW>(orw != 0, s_any);   // (and the tables are in LDS)
     const uint32_t plen = any ? (sc.len + 15u) & ~15u : 0;
     if (tid == 0) st_relaxed(&j.status[g], kStAgg | tag | plen);
@@ -1411,6 +1423,77 @@ __global__ void __launch_bounds__(T) k_dump_short(ShortJob j) {
     for (int w = 0; w < NW; ++w) excl += s_sum[w];
     store_rows_padded<T, K>(v, j.payload + excl, plen, tid, any != 0);
     if (g + 1 == j.n_chunks && tid == 0) st_host(j.rep, excl + plen);
+}
+
+// Short full restore, C = 16 T K, from a pinned image, set-up, offsets and
+// checks included: the payload offsets come with the entries (the host counts
+// the kinds anyway), an allocation's check reads the image's digests itself.
+// Bound by latencies and the host link: the set-up, the offsets scan and the
+// report were three launches and 20 us beside the one that moves the payload
+// (256 KiB: 45 -> 27 us). No work-group waits for another.
+template <int T, int K>
+__global__ void __launch_bounds__(T) k_restore_short(ShortRestoreJob j) {
+    constexpr int NW = T / 64;
+    constexpr uint32_t C = 16u * T * K, R = 16u * T;
+    __shared__ __attribute__((aligned(16))) uint32_t s_dt[16 * 256];
+    __shared__ uint32_t s_red[NW];
+    __shared__ uint32_t s_any[NW];
+    const uint32_t tid = threadIdx.x, g = blockIdx.x;
+    if (g >= j.groups) {
+        const uint64_t t0 = wall_clock64();
+        const uint32_t a = g - j.groups;
+        if (tid < 64) s_dt[tid] = j.ec->x2n[tid];
+        const AllocDesc ad = j.allocs[a];
+        const uint32_t want = reinterpret_cast<const uint32_t*>(j.recs + 32ull * a)[6];
+        __syncthreads();
+        const uint32_t nk = (uint32_t)((ad.size + C - 1) / C);
+        uint32_t acc = 0;
+        for (uint32_t k = tid; k < nk; k += T) {
+            const uint64_t end = k + 1 == nk ? ad.size : (uint64_t)(k + 1) * C;
+            acc ^= gf_mul_v(j.crc[ad.first + k], xpow8(ad.size - end, s_dt));
+        }
+        const uint32_t crc = wg_xor<NW>(acc, s_red);
+        if (tid == 0 && crc != want) ((gu8*)j.bad)[j.n_chunks + a] = 1;
+        if (a + 1 == j.n_allocs && tid == 0) {
+            st_host(j.rep, t0);
+            st_host(j.rep + 1, wall_clock64());
+        }
+        return;
+    }
+    stream_tables<T>(s_dt, j.ec);
+    ShortRecord sr = j.chunks[g];
+    const uint32_t lanec = j.ec->lane[tid], full_init = j.ec->full_init;
+    for (uint32_t c = g;;) {
+        const uint32_t next = c + j.groups;
+        ShortRecord sn{};
+        if (next < j.n_chunks) sn = j.chunks[next];   // a round trip over the link: early
+        const uint32_t init = sr.full ? full_init : sr.tail_init;
+        v4u v[K];
+        uint32_t padbad = 0;
+        if (!sr.src) {
+#pragma unroll
+            for (int r = 0; r < K; ++r) v[r] = vzero();
+        } else if (sr.full) {
+#pragma unroll
+            for (int r = 0; r < K; ++r) v[r] = gload(sr.src + r * R + 16u * tid);
+        } else {
+            load_rows_staged<T, K>(v, sr.src, sr.len, tid, true, &padbad);
+        }
+        if (c == g) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // for the tables as well
+        store_rows_exact<T, K>(v, sr.ptr, sr.len, tid, true);
+        lds_barrier();
+        uint32_t crc = ~init, pb = 0;
+        if (sr.src) {
+            uint32_t raw = wg_xor_lds<NW>(gf_mul_v(crc_rows<K>(v, 0, s_dt), lanec), s_red);
+            pb = wg_any_lds<NW>(padbad != 0, s_any);
+            if (!sr.full) raw = gf_mul_v(raw, sr.tail_unshift);
+            crc = ~(raw ^ init);
+        }
+        if (tid == 0 && (crc != sr.crc || pb)) ((gu8*)j.bad)[c] = 1;
+        if (next >= j.n_chunks) break;
+        sr = sn;
+        c = next;
+    }
 }
 
 // Two descriptors passed by value (kernel arguments are captured at launch,
@@ -1482,6 +1565,17 @@ hipError_t short_tk(const ShortJob& j, hipStream_t s) {
 }
 
 template <int T, int K>
+hipError_t short_restore_tk(const ShortRestoreJob& j, hipStream_t s) {
+    if constexpr (T >= 64) {
+        if (j.C == 16u * T * K && j.groups && j.groups <= j.n_chunks && j.n_allocs) {
+            hipLaunchKernelGGL((k_restore_short<T, K>), dim3(j.groups + j.n_allocs), dim3(T), 0, s, j);
+            return hipGetLastError();
+        }
+    }
+    return hipErrorInvalidValue;
+}
+
+template <int T, int K>
 hipError_t occ_tk(int mode, int* n) {
     constexpr int NT = T < 64 ? 64 : T;
     switch (mode) {
@@ -1545,6 +1639,13 @@ hipError_t launch_chunks(int T, int K, int mode, const JobList& jl, int grid, hi
 
 hipError_t launch_short(int T, int K, const ShortJob& job, hipStream_t s) {
 #define MK_SHORT(t, k) if (T == t && K == k) return short_tk<t, k>(job, s);
+    MK_TILES(MK_SHORT)
+#undef MK_SHORT
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_short_restore(int T, int K, const ShortRestoreJob& job, hipStream_t s) {
+#define MK_SHORT(t, k) if (T == t && K == k) return short_restore_tk<t, k>(job, s);
     MK_TILES(MK_SHORT)
 #undef MK_SHORT
     return hipErrorInvalidValue;

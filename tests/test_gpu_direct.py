@@ -232,6 +232,67 @@ def test_short_dumps_in_one_launch(ctx, c, chunks):
         delta.free()
 
 
+@pytest.mark.parametrize("c,chunks", [(1024, 5), (1024, 505), (4096, 500), (16384, 64), (32768, 3), (65536, 100),
+                                      (65536, 316), (131072, 20)])
+def test_short_restores_in_one_launch(ctx, c, chunks):
+    """Short restores of a pinned image on both sides of the one launch's
+    limits against the staged path (a pageable image): the state, and the
+    code and first bad chunk for a byte changed in each part that the launch
+    checks (a whole record, a tail, its padding, a ZERO chunk's digest, an
+    allocation's digest)."""
+    sizes = [0, 1, c + 15, 0, 3 * c, max(1, (chunks - 6) * c - 1)]
+    gen = torch.Generator(device="cuda").manual_seed(chunks)
+    table = [(10 - i, torch.randint(1, 256, (n,), dtype=torch.uint8, device="cuda", generator=gen))
+             for i, n in enumerate(sizes)]
+    table[4][1][c:2 * c] = 0
+    rc, img, _ = mk.ckpt_dump(ctx, table, opts=mk.make_opts(chunk_size=c))
+    assert rc == 0
+    clean = img.tobytes()
+    nc = sum(-(-n // c) for n in sizes)
+    tables = 64 + 32 * len(table)
+    payload = len(clean) - img_payload(clean)
+    # payload offsets: 1-byte record, its padding, a whole record, the last record's tail and padding
+    spots = [payload, payload + 1, payload + 16 + 5, len(clean) - 16, len(clean) - 1]
+    for spot in [None] + spots + ["zero", "alloc"]:
+        raw = bytearray(clean)
+        if spot == "zero":
+            raw[tables + 4 * 4] ^= 1          # the ZERO chunk: chunks 1-byte, 2, then 3 * c: its second
+        elif spot == "alloc":
+            raw[64 + 32 * 4 + 24] ^= 1
+        elif spot is not None:
+            raw[spot] ^= 2
+        if isinstance(spot, str):
+            sign(raw)
+        got = []
+        for where in (contextlib.nullcontext, pageable):
+            with where():
+                rc, im = mk.ckpt_image_import(np.frombuffer(bytes(raw), np.uint8))
+                assert rc == 0
+            to = blank(table)
+            rc, res = mk.ckpt_restore(ctx, im, to)
+            if spot is None:
+                assert rc == 0
+                same(to, table)
+                assert res.n_chunks == nc and res.n_zero == 1
+            got.append((rc, res.first_bad_chunk))
+            im.free()
+        assert got[0] == got[1], spot
+        assert spot is None or got[0][0] == mk.CKPT_ECORRUPT
+    img.free()
+
+
+def img_payload(raw):
+    """Payload bytes of an image."""
+    return int.from_bytes(raw[32:40], "little")
+
+
+def sign(raw):
+    """The tables' and the header's digests after a change in the tables."""
+    end = len(raw) - img_payload(raw)
+    raw[56:60] = corc.crc32c(bytes(raw[64:end])).to_bytes(4, "little")
+    raw[60:64] = corc.crc32c(bytes(raw[:60])).to_bytes(4, "little")
+
+
 def test_a_delta_keeps_to_the_staging_budget():
     """A delta of a state longer than the budget, in chunks so small that a
     round of the digest pass is half the state, takes no more device memory
