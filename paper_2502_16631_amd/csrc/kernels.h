@@ -7,8 +7,7 @@ namespace mk {
 
 // classify: digest and kind of every chunk, nothing else (first pass of a
 // two-pass dump; its last pass, the gather, is k_gather in gather.hip).
-enum Mode : int { kModeDump = 0, kModeDigest = 1, kModeVerify = 2, kModeRestore = 3, kModeClassify = 4,
-                  kModeShort = 5 };   // (launch_short's occupancy)
+enum Mode : int { kModeDump = 0, kModeDigest = 1, kModeVerify = 2, kModeRestore = 3, kModeClassify = 4 };
 
 // One launch of the chunk engine over global chunks [g0, g1).
 struct ChunkJob {
@@ -138,8 +137,8 @@ struct FinishJob {
     }
 };
 
-// A short full dump in one launch (k_dump_short): chunk g by work-group g,
-// allocation a by work-group n_chunks + a. Everything the host prepares and
+// A short full dump in one launch (k_dump_short): ticket g takes chunk g,
+// ticket n_chunks + a allocation a. Everything the host prepares and
 // reads is in pinned memory.
 struct ShortChunk {              // 32 bytes
     const uint8_t* ptr;          // first byte of the chunk
@@ -155,6 +154,8 @@ struct ShortJob {
     uint32_t n_chunks, n_allocs;
     uint32_t C;
     uint32_t epoch;              // of status
+    uint32_t* ticket;            // counter, `first` at launch (n_chunks + n_allocs more after it)
+    uint32_t first, pad;
     const EngineConsts* ec;
     uint64_t* status;            // [2 n_chunks]: payload bytes of chunk g; its digest and kind
     uint8_t* payload;            // the image's, pinned like the tables:

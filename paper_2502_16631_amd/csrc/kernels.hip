@@ -1341,11 +1341,12 @@ __device__ inline void stream_tables(uint32_t* s_dt, const EngineConsts* ec) {
 // for its payload on the link; here 39 (64 of 64 KiB: 125 -> 104, 384: 515 ->
 // 487). The chunks' entries come over the link in one read each, and the end
 // (the tables, the allocations' digests) runs while the payload drains, which
-// is why the payload is stored after the digest. Every work-group is resident
-// (the launch's limit); a chunk's waits only for words that those before it
-// publish before they wait, an allocation's for its chunks' words. The
-// predecessors' payload lengths are read one by one, a thread each: a
-// thousand at most for the usual chunk sizes, and no chain.
+// is why the payload is stored after the digest. A chunk's
+// work-group waits only for words that holders of lower tickets publish before
+// they wait, an allocation's for its chunks' words: all of those run, whatever
+// else shares the device. The counter goes on from call to call, so that
+// nothing has to clear it. The predecessors' payload lengths are read one by
+// one, a thread each: no chain, and two thousand chunks at most.
 template <int T, int K>
 __global__ void __launch_bounds__(T) k_dump_short(ShortJob j) {
     constexpr int NW = T / 64;
@@ -1354,9 +1355,13 @@ __global__ void __launch_bounds__(T) k_dump_short(ShortJob j) {
     __shared__ uint32_t s_red[NW];
     __shared__ uint32_t s_any[NW];
     __shared__ uint32_t s_sum[NW];
-    const uint32_t tid = threadIdx.x, g = blockIdx.x;
+    __shared__ uint32_t s_tk;
+    const uint32_t tid = threadIdx.x;
     const uint64_t tag = (uint64_t)(j.epoch & kEpochMask) << 40;
     const uint64_t t0 = wall_clock64();
+    if (tid == 0) s_tk = atomicAdd(j.ticket, 1u) - j.first;
+    lds_barrier();
+    const uint32_t g = __builtin_amdgcn_readfirstlane(s_tk);
     if (g >= j.n_chunks) {
         // the end: allocation a's digests and kinds to the image, its record
         const uint32_t a = g - j.n_chunks;
@@ -1608,9 +1613,6 @@ hipError_t occ_tk(int mode, int* n) {
             return hipErrorInvalidValue;
         case kModeDigest: return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeDigest>, NT, 0);
         case kModeRestore: return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_chunks<T, K, kModeRestore>, NT, 0);
-        case kModeShort:
-            if constexpr (T >= 64) return hipOccupancyMaxActiveBlocksPerMultiprocessor(n, k_dump_short<T, K>, T, 0);
-            return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
     }
 }

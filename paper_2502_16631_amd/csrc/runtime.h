@@ -208,6 +208,9 @@ struct ckpt_ctx {
     // device buffers
     mk::StatusBuf status;
     mk::DevBuf descs, ctl, arc, kinds, prevcrc, off, wb, staging, dig, amap, rlen, cmeta, list;
+    mk::DevBuf ticket;              // ShortJob's counter,
+    uint32_t tickets = 0;           // its value,
+    bool tickets_known = false;     // unless a launch failed
     std::map<std::pair<int, uint32_t>, mk::DevBuf> consts;    // (T, C) -> EngineConsts
     std::map<uint32_t, mk::DevBuf> cconsts;                   // C -> CodecConsts
     std::map<std::tuple<int, int, int>, int> occ;          // (T, K, mode) -> blocks per CU
@@ -244,8 +247,9 @@ constexpr int kLinkGrid = 64;
 // against 494), 60 MiB in 128 KiB chunks 1220 against 1163.
 constexpr uint64_t kShortRestore = 512, kShortBytes = 20ull << 20, kLinkFlight = 3ull << 20;
 // A full dump of at most this many bytes in one launch writes its payload
-// straight into a pinned image.
-constexpr uint64_t kDirectDump = 64ull << 20;
+// straight into a pinned image; of at most so many chunks and allocations,
+// set-up and end are in that launch too.
+constexpr uint64_t kDirectDump = 64ull << 20, kShortDump = 2048;
 // The ranges a restore may stage the first ones of, and the least payload
 // worth it.
 constexpr uint64_t kHeadGrid = 256;

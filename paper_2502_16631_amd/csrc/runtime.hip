@@ -675,6 +675,7 @@ extern "C" int ckpt_ctx_create(int device, uint64_t staging_budget, ckpt_ctx** o
     if (e == hipSuccess) e = ensure_tevents(c, 16);
     if (e == hipSuccess) e = ensure_hsmall(c, 256 << 10);   // read-backs of up to ~32k windows
     if (e == hipSuccess) e = ensure_hdesc(c, kNaMaxAllocs);
+    if (e == hipSuccess) e = c->ticket.ensure(4);
     for (int i = 0; i < 8 && e == hipSuccess; ++i) e = hipEventCreate(&c->sev[i]);
     if (e == hipSuccess) e = na_setup(device);
     c->hconsts = new EngineConsts();
@@ -701,7 +702,7 @@ extern "C" void ckpt_ctx_destroy(ckpt_ctx* c) {
     for (hipEvent_t e : c->tevents) hipEventDestroy(e);
     c->status.release();
     DevBuf* bufs[] = {&c->descs, &c->ctl, &c->arc, &c->kinds, &c->prevcrc, &c->off, &c->wb,
-                      &c->staging, &c->dig, &c->amap, &c->rlen, &c->cmeta, &c->list};
+                      &c->staging, &c->dig, &c->amap, &c->rlen, &c->cmeta, &c->list, &c->ticket};
     for (DevBuf* b : bufs) b->release();
     for (auto& kv : c->consts) kv.second.release();
     for (auto& kv : c->cconsts) kv.second.release();
@@ -1086,18 +1087,13 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     }
     if (piped)   // two scans over 256-chunk tiles, each with words of its own
         for (uint64_t i = 0; i < n_pieces; ++i) max_win = std::max(max_win, 2 * ceil_div(piece[i + 1] - piece[i], 256));
-    // A short dump of whole tiles, few enough that all of its work-groups are
-    // resident, runs as one launch if the image takes the payload (below):
-    // 20 us less than three at any size up to there (256 KiB: 41 against 27,
-    // 24 MiB: 515 against 487; small chunks too, 1 MiB in 4 KiB: 71 against
-    // 47). More chunks need the tickets of the other kernels.
-    bool one_launch = small && C == 16ull * T * K && T >= 64;
-    if (one_launch) {
-        int room;
-        HIPCHK(grid_for(c, T, K, kModeShort, nc + n, &room));
-        one_launch = nc + n <= (uint64_t)room;
-        max_win = std::max(max_win, 2 * nc);
-    }
+    // A short dump of whole tiles runs as one launch if the image takes the
+    // payload (below): 20 us less than three at any size up to there (256
+    // KiB: 41 against 27, 24 MiB: 515 against 487; small chunks too, 1 MiB in
+    // 4 KiB: 71 against 47). Its work-groups read every predecessor's word, so
+    // more chunks are left to the look-back.
+    bool one_launch = small && C == 16ull * T * K && T >= 64 && nc + n <= kShortDump;
+    if (one_launch) max_win = std::max(max_win, 2 * nc);
     HIPCHK(B.status->ensure(8 * (max_win + 64), c->s_main));
     const uint64_t W = wins.size();
     // ctl: tickets[n_tk] | wtot[kRing + 1] (u64) | err (+pad) | counts[4] (u64) | stamps (u64); window
@@ -1741,6 +1737,13 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         j.n_allocs = n;
         j.C = C;
         if ((e = B.status->next(c->s_main, &j.epoch)) != hipSuccess) return fail_late(e);
+        if (!c->tickets_known) {
+            if ((e = launch_fill32(c->ticket.as<uint32_t>(), 0, 1, c->s_main)) != hipSuccess) return fail_late(e);
+            c->tickets = 0;
+        }
+        c->tickets_known = false;   // until the launch is known to be done
+        j.ticket = c->ticket.as<uint32_t>();
+        j.first = c->tickets;
         j.ec = ec;
         j.status = B.status->words();
         j.payload = himg + kHeader + tl;
@@ -1766,7 +1769,11 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     }
     if (timing && !use_graph && (e = hipEventRecord(c->sev[3], c->s_main)) != hipSuccess) return fail_late(e);
     if ((e = hipStreamSynchronize(c->s_main)) != hipSuccess) return fail_late(e);
-    if (one_launch) hw[kRepErr] = rep[1];
+    if (one_launch) {
+        hw[kRepErr] = rep[1];
+        c->tickets += (uint32_t)nc + n;
+        c->tickets_known = true;
+    }
     if (direct || gather_direct) {
         D = gather_direct ? hw[kHwWords + 1] : one_launch ? rep[0] : hw[0];
         if (D > upper) return fail_late(hipErrorIllegalState);

@@ -200,11 +200,10 @@ def test_deltas_in_pieces_match_the_oracle(c, budget):
         mk.ckpt_ctx_destroy(ctx)
 
 
-@pytest.mark.parametrize("c,chunks", [(1024, 5), (1024, 3000), (4096, 1), (4096, 2290), (4096, 2330), (16384, 700),
-                                      (32768, 63), (65536, 65), (65536, 1009), (65536, 1016), (131072, 130)])
+@pytest.mark.parametrize("c,chunks", [(1024, 5), (1024, 3000), (4096, 1), (4096, 2043), (4096, 2044), (16384, 700),
+                                      (32768, 63), (65536, 65), (65536, 1019), (65536, 1025), (131072, 130)])
 def test_short_dumps_in_one_launch(ctx, c, chunks):
-    """Short dumps on both sides of the number of work-groups that are
-    resident at once, with empty and one-byte allocations, zero chunks and
+    """Short dumps on both sides of the one launch's limit, with empty and one-byte allocations, zero chunks and
     ragged tails, repeated with other data (status words of the call before),
     against the oracle."""
     sizes = [0, 1, c + 15, 0]
