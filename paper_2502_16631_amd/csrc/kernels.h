@@ -232,10 +232,6 @@ hipError_t launch_combine(const CombineJob& job, hipStream_t s);
 // Zero-fill of the ZERO chunks of [job.g0, job.g1) (restore; uses allocs,
 // amap, ec, kind_in, ref_crc, bad and gate).
 hipError_t launch_zero(const ChunkJob& job, int grid, hipStream_t s);
-// Copy of n bytes (a multiple of 16) between device and pinned host memory
-// by kLinkCus work-groups, each alone on its CU.
-constexpr int kLinkCus = 8;
-hipError_t launch_link_copy(void* dst, const void* src, uint64_t n, hipStream_t s);
 // launch_offsets (grid work-groups; 0: none) and launch_combine in one launch.
 hipError_t launch_offsets_combine(const OffJob& off, int grid, const CombineJob& job, hipStream_t s);
 hipError_t launch_chunk_map(const AllocDesc* allocs, uint32_t n_allocs, uint32_t C, uint32_t* map, hipStream_t s);

@@ -1217,27 +1217,6 @@ __global__ void __launch_bounds__(256) k_zero(ChunkJob j) {
     }
 }
 
-// Host-link copy, beside kernels that read and write HBM. Bound by the link:
-// eight work-groups with 32 KiB in flight each carry 56 GB/s. (Copy engines
-// carry 57 or 30, depending on the engine a stream gets.) A CU answers its
-// vector memory operations in order, so whatever shares a CU with a wave that
-// waits for the link waits with it: a 2 GiB fill beside such a copy took 4.9
-// instead of 0.44 ms. Each work-group therefore claims all vector registers
-// of its CU (512 threads of 256 registers) and has it to itself.
-__global__ void __launch_bounds__(512) k_link_copy(v4u* dst, const v4u* src, uint64_t n16) {
-    asm volatile("" ::: "v255");
-    constexpr uint64_t U = 4, TILE = U * 512;
-    uint64_t b = blockIdx.x * TILE;
-    for (; b + TILE <= n16; b += gridDim.x * TILE) {
-        v4u x[U];
-#pragma unroll
-        for (int u = 0; u < (int)U; ++u) x[u] = ((gcv4*)src)[b + u * 512 + threadIdx.x];
-#pragma unroll
-        for (int u = 0; u < (int)U; ++u) ((gv4*)dst)[b + u * 512 + threadIdx.x] = x[u];
-    }
-    for (uint64_t i = b + threadIdx.x; i < n16 && i < b + TILE; i += 512) ((gv4*)dst)[i] = ((gcv4*)src)[i];
-}
-
 // Chunk -> allocation map: work-group a writes a over its chunk range.
 __global__ void __launch_bounds__(256) k_chunk_map(const AllocDesc* allocs, uint32_t n, uint32_t C, uint32_t* map) {
     for (uint32_t a = blockIdx.x; a < n; a += gridDim.x) {
@@ -1729,15 +1708,6 @@ hipError_t launch_zero(const ChunkJob& j, int grid, hipStream_t s) {
     if (!j.amap || grid < 1) return hipErrorInvalidValue;
     if (j.g1 <= j.g0) return hipSuccess;
     hipLaunchKernelGGL(k_zero, dim3(grid), dim3(256), 0, s, j);
-    return hipGetLastError();
-}
-
-hipError_t launch_link_copy(void* dst, const void* src, uint64_t n, hipStream_t s) {
-    if (((reinterpret_cast<uint64_t>(dst) | reinterpret_cast<uint64_t>(src) | n) & 15) != 0) return hipErrorInvalidValue;
-    if (n == 0) return hipSuccess;
-    const uint64_t tiles = (n + 32767) / 32768;
-    hipLaunchKernelGGL(k_link_copy, dim3((unsigned)(tiles < (uint64_t)kLinkCus ? tiles : kLinkCus)), dim3(512), 0, s,
-                       static_cast<v4u*>(dst), static_cast<const v4u*>(src), n / 16);
     return hipGetLastError();
 }
 

@@ -223,7 +223,6 @@ struct ckpt_ctx {
     // pinned host copy of a call's descriptors, which the set-up kernel reads
     mk::AllocDesc* hdesc = nullptr;
     uint64_t hdesc_cap = 0;
-    hipStream_t s_aux = nullptr;   // link copies beside the main stream's kernels
     std::vector<hipEvent_t> events;
     std::vector<hipEvent_t> tevents;                      // timing events (begin, end) per launch
     hipEvent_t ev_order = nullptr;                        // orders the main stream after the caller's

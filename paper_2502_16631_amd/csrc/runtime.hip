@@ -646,10 +646,6 @@ static hipError_t ensure_copy_streams(ckpt_ctx* c, uint32_t n) {
     return hipSuccess;
 }
 
-static hipError_t ensure_side_stream(ckpt_ctx* c) {
-    return c->s_aux ? hipSuccess : hipStreamCreateWithFlags(&c->s_aux, hipStreamNonBlocking);
-}
-
 extern "C" int ckpt_ctx_create(int device, uint64_t staging_budget, ckpt_ctx** out) {
     if (!out) return CKPT_EINVAL;
     *out = nullptr;
@@ -710,10 +706,6 @@ extern "C" void ckpt_ctx_destroy(ckpt_ctx* c) {
     for (auto& ge : c->graphs) ge.release();
     if (c->hsmall) hipHostFree(c->hsmall);
     if (c->hdesc) (void)hipHostFree(c->hdesc);
-    if (c->s_aux) {
-        (void)hipStreamSynchronize(c->s_aux);
-        (void)hipStreamDestroy(c->s_aux);
-    }
     delete c;
 }
 
@@ -863,7 +855,6 @@ static bool pinned_range(const void* p, uint64_t n) {
 static void drain(ckpt_ctx* c) {
     (void)hipStreamSynchronize(c->s_main);
     for (hipStream_t s : c->s_copy) (void)hipStreamSynchronize(s);
-    if (c->s_aux) (void)hipStreamSynchronize(c->s_aux);
     (void)hipGetLastError();   // the error is reported by the return code
 }
 
@@ -1226,7 +1217,6 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     std::vector<bool> slot_used(nslots, false);
     auto fail = [&](hipError_t e) {
         hipStreamSynchronize(c->s_main);
-        if (c->s_aux) hipStreamSynchronize(c->s_aux);
         for (uint32_t i = 0; i < ncs; ++i) hipStreamSynchronize(c->s_copy[i]);
         (void)hipGetLastError();   // the error is reported by the return code
         if (sink) sink->end();     // nothing reads the image after this
@@ -1483,9 +1473,10 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
                 if (sink) sink->begin(im);
             }
             if (Di) {
-                // (a codec dump's pieces keep the link busy one by one; two at a
-                // time shared 53 GB/s)
-                hipStream_t cs = c->s_copy[ring || codec ? 0 : i % ncs];
+                // (one by one: two at a time carried 53 GB/s in a codec dump, and
+                // 2 GB of a delta took 44 instead of 36 ms where the second
+                // stream's engine was a slow one)
+                hipStream_t cs = c->s_copy[ring || codec || !(o && o->copy_streams) ? 0 : i % ncs];
                 if (!t_link0) t_link0 = now_ns();
                 if ((e = hipStreamWaitEvent(cs, ev[i], 0)) != hipSuccess) return e;
                 if ((e = copy_out(D, B.staging->as<uint8_t>() + (ring ? (i % nslots) * slot : g0 * C), Di, cs)) !=
@@ -2455,30 +2446,30 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     // Where the chunks are not all DATA, the device holds the kinds apart: DATA
     // chunks are taken from a list, ZERO chunks filled by a kernel of their
     // own. While the device reads the UNCHANGED chunks (a delta's base check)
-    // and fills the ZERO ones, a link copy brings the head of the payload to
+    // and fills the ZERO ones, a copy engine brings the head of the payload to
     // staging: as much as the link carries in that time and before it, while the
-    // tables go up and are checked (53 GB/s beside them, against 3.1 and 4.8
-    // TB/s, 20 us and 0.8 ns a chunk), and to the next range bound, as a head
-    // that ends late costs the difference of 53 to 57 GB/s, one that ends early
-    // leaves the link idle. The rest is read directly. 400 MB of DATA in an
-    // 8 GB delta: 7.63 ms with a head of 99 MB, for the checks and fills alone
-    // and cut down to 64ths, 7.55 with 104 MB, 7.51 with 113 MB.
+    // tables go up and are checked (57 GB/s against 3.1 and 4.8 TB/s, 20 us and
+    // 0.8 ns a chunk), and to the next range bound, as a head that ends late
+    // costs little, one that ends early leaves the link idle. The rest is read
+    // directly. (By an engine, and the event that says it is done recorded
+    // behind the fills: streams share hardware queues, and a copy kernel, or
+    // that event, ahead of them in the main stream's queue holds them up: 44.4
+    // instead of 36.9 ms for 2 GB of DATA in a 40 GB delta, in a process with
+    // other streams. A copy kernel also carries 53 GB/s beside HBM work.)
     const bool base_overlap = nu && !some && !codec;
     const bool split = whole && (nz || nu || n_packed);
     uint64_t hi = 0;   // ranges of the head
     if (split) {
-        const uint64_t work = (base_overlap ? nu * C / 59 : 0) + nz * C / 91;
-        const uint64_t most = work < kMinHead ? 0 : work + (1u << 20) + 42 * nc;
+        const uint64_t work = (base_overlap ? nu * C / 55 : 0) + nz * C / 85;
+        const uint64_t most = work < kMinHead ? 0 : work + (1u << 20) + 45 * nc;
         while (hi < kHeadGrid && at[hi] < most && at[hi + 1] <= std::min<uint64_t>(2 * most, c->budget)) ++hi;
         if (at[hi] < kMinHead) hi = 0;
         HIPCHK(c->list.ensure(8 * nc));
     }
     const uint64_t head = at.empty() ? 0 : at[hi];
     if (hi) {
-        HIPCHK(ensure_side_stream(c));
         HIPCHK(c->staging.ensure(head));
-        HIPCHK(launch_link_copy(c->staging.p, v.payload, head, c->s_aux));
-        HIPCHK(hipEventRecord(c->events[0], c->s_aux));
+        HIPCHK(hipMemcpyAsync(c->staging.p, v.payload, head, hipMemcpyHostToDevice, c->s_copy[0]));
     }
 
     // tables up, payload offsets, and the per-allocation check (the image's
@@ -2571,11 +2562,9 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         j.flags = flags;
         j.stamp = stamped && !flags ? stamps + 2 : nullptr;
         hipError_t e;
-        // the link copy's CUs take no other work
-        const int cus = c->num_cu - (hi ? kLinkCus : 0);
         if (!some) {
             JobList jl = one_job(j, wtk + W);
-            return launch_verify(c, T, K, jl, cus, c->s_main);
+            return launch_verify(c, T, K, jl, c->num_cu, c->s_main);
         }
         for (uint64_t w0 = 0; w0 < W; w0 += kMaxJobs) {
             JobList jl;
@@ -2591,7 +2580,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             }
             jl.prefix[jl.n_jobs] = tot;
             jl.ticket = wtk + W;
-            if ((e = launch_verify(c, T, K, jl, cus, c->s_main)) != hipSuccess) return e;
+            if ((e = launch_verify(c, T, K, jl, c->num_cu, c->s_main)) != hipSuccess) return e;
         }
         return hipSuccess;
     };
@@ -2711,8 +2700,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         ChunkJob j = restore_job(0);
         if (timing) HIPCHK(hipEventRecord(c->tevents[0], c->s_main));
         if (nz) {
-            const uint64_t wgs = 4ull * (c->num_cu - (hi ? kLinkCus : 0));
-            HIPCHK(launch_zero(j, (int)std::min<uint64_t>(nc, wgs), c->s_main));
+            HIPCHK(launch_zero(j, (int)std::min<uint64_t>(nc, 4ull * c->num_cu), c->s_main));
             j.stamp = nullptr;
         }
         // the head from staging, then the rest from host memory
@@ -2720,6 +2708,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             const uint64_t b = part ? hi : 0, e = part ? kHeadGrid : hi;
             if (b == e) continue;
             if (!part) {
+                HIPCHK(hipEventRecord(ev[0], c->s_copy[0]));
                 HIPCHK(hipStreamWaitEvent(c->s_main, ev[0], 0));
                 j.slot = c->staging.as<uint8_t>();
             } else {
