@@ -84,7 +84,7 @@ typedef struct ckpt_image ckpt_image;   /* an image in host memory (pinned if av
 #define CKPT_OPT_PER_ALLOC  1u   /* launch the kernels once per allocation (baseline form)   */
 #define CKPT_OPT_GRAPH      2u   /* batched form: capture the device stage in a hipGraph and
                                     replay it (cached per table shape); a restore of a pinned
-                                    image, a few launches that read it where it is, has none */
+                                    image, whose launches are few, has none                 */
 #define CKPT_OPT_NO_TIMING  4u   /* skip per-stage device timing events                      */
 /* Dump only (ignored by restore, where the image says how it is stored):
  * store each full-length DATA chunk as a byte-plane record when that record
@@ -117,9 +117,9 @@ typedef struct {
 typedef struct {
     uint64_t first_bad_chunk;   /* UINT64_MAX if none                                       */
     int32_t  hip_error;         /* first failing hipError_t, 0 if none                      */
-    uint32_t windows;           /* staging windows used (1 for a restore that reads a pinned image */
-                                /* where it is; a plain restore of a pageable image of >= 512 MiB  */
-                                /* held by one window is launched as two parts and reports 2)      */
+    uint32_t windows;           /* staging windows used (a plain restore of >= 512 MiB held  */
+                                /* by one window is launched as two parts and reports 2; 1   */
+                                /* for a short restore that reads a pinned image in place)   */
     uint64_t n_logical;         /* N: sum of allocation sizes                               */
     uint64_t n_payload;         /* D: payload bytes                                         */
     uint64_t n_chunks;
@@ -149,7 +149,7 @@ typedef struct {
      *          host waits for it: wall time)  [2] host link: from the first
      *          payload work queued to the end, wall time  [3] scatter + fused
      *          verify kernels (codec decode and zero fill included; at the
-     *          link's rate where they read a pinned image themselves)
+     *          link's rate where a short restore reads a pinned image in place)
      *          [4] strict re-read  [5] offsets scan and per-allocation check
      *          [6] unused  [7] whole call, wall time. */
     uint64_t ns_stage[8];
@@ -179,7 +179,11 @@ void ckpt_ctx_destroy(ckpt_ctx* ctx);
  * ZERO either way. prev is borrowed and must have the same chunk size.
  * The allocations must not be modified during the call (the caller's
  * analogue of the paper's lock action). On failure *out = NULL and no
- * allocation has been written. Work is ordered after prior work on stream. */
+ * allocation has been written. Work is ordered after prior work on stream.
+ * Beside other streams' work: payloads cross the link by copy engines, which
+ * slow it by a few per cent, except in dumps and restores of at most 20 MiB:
+ * their kernels write or read a pinned image themselves, which may hold up
+ * launches of other streams for as long as the call lasts (0.4 ms). */
 int  ckpt_dump(ckpt_ctx* ctx, const ckpt_alloc_table* table, const ckpt_image* prev,
                ckpt_image** out, const ckpt_opts* opts, void* stream, ckpt_result* res);
 

@@ -239,20 +239,25 @@ constexpr uint64_t kTailMinBytes = 512ull << 20;
 // Work-groups of a restore launch that reads a pinned image over the host
 // link (512 threads, 64 KiB in flight each).
 constexpr int kLinkGrid = 64;
+// Transfers of at most this many bytes may be made by the kernels of a call
+// themselves, reading or writing a pinned image over the link. They hold up
+// other streams' launches on their CUs for as long as they last (16 MiB: a
+// copy of 256 MiB beside back-to-back restores 344 instead of 102 us, beside
+// dumps 688), so the bound keeps that to 0.4 ms a call, as long as a copy of 1
+// GiB holds the memory; longer transfers are a copy engine's, which slows that
+// copy by 5 %.
+constexpr uint64_t kLinkBytes = 20ull << 20;
+constexpr uint64_t kMinOverlap = 1ull << 20;
 // A full restore of a pinned image of at most this many chunks and allocations
-// and of at most so many bytes is one launch, with kLinkFlight bytes of chunks
+// and of at most kLinkBytes is one launch, with kLinkFlight bytes of chunks
 // in flight (all of 256 chunks of 64 KiB at once: 339 us, 3 MiB: 325). 1 MiB
 // takes 48 instead of 66 us, 16 MiB 334 instead of 343, 24 MiB the same (475-501
 // against 494), 60 MiB in 128 KiB chunks 1220 against 1163.
-constexpr uint64_t kShortRestore = 512, kShortBytes = 20ull << 20, kLinkFlight = 3ull << 20;
-// A full dump of at most this many bytes in one launch writes its payload
+constexpr uint64_t kShortRestore = 512, kLinkFlight = 3ull << 20;
+// A full dump of at most kLinkBytes in one launch writes its payload
 // straight into a pinned image; of at most so many chunks and allocations,
 // set-up and end are in that launch too.
-constexpr uint64_t kDirectDump = 64ull << 20, kShortDump = 2048;
-// The ranges a restore may stage the first ones of, and the least payload
-// worth it.
-constexpr uint64_t kHeadGrid = 256;
-constexpr uint64_t kMinHead = 1ull << 20;
+constexpr uint64_t kShortDump = 2048;
 
 // Storage hooks. A dump told of a sink reports every payload copy into the
 // image as it is queued (segments of at most kSinkSegment bytes), so the

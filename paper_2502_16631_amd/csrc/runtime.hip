@@ -995,12 +995,10 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     const bool use_graph = o && (o->flags & CKPT_OPT_GRAPH) && wins.size() == 1 && !per_alloc;
     // A short full dump writes its payload straight into the image, when that
     // is pinned: no staging, no wait for the payload's length, no copy (8
-    // allocations, 16 MiB: 420 -> 350 us, and 338 in one launch). The image is then allocated at
-    // the payload's bound, which is why longer dumps do not: a state half of
-    // zeros would pin twice its image. The kernel holds the device for as
-    // long as the link takes, 1.2 ms at the longest.
+    // allocations, 16 MiB: 420 -> 350 us, and 330 in one launch). The image is
+    // then allocated at the payload's bound.
     const bool one_pass = !prev && !codec && wins.size() == 1 && nc > 0 && !use_graph && !per_alloc;
-    const bool small = one_pass && !sink && upper <= kDirectDump;
+    const bool small = one_pass && !sink && upper <= kLinkBytes;
     // The pipeline of a dump (launch_pieces): its pieces' bounds and their
     // places in staging. With room for everything each piece has its own part;
     // else the pieces go round a ring of slots. A longer full dump that fits
@@ -1056,7 +1054,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     const uint64_t n_pieces = piped ? piece.size() - 1 : 0;
     const bool ring = piped && wins.size() > 1;
     // One short piece: gathered straight into a pinned image.
-    const bool small_delta = piped && !plain && !codec && !ring && n_pieces == 1 && !sink && upper <= kDirectDump;
+    const bool small_delta = piped && !plain && !codec && !ring && n_pieces == 1 && !sink && upper <= kLinkBytes;
     // stage times: of a short dump by stamps, else by events
     const bool stamped = (small || (piped && !plain)) && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     const bool timing = !stamped && !(o && (o->flags & CKPT_OPT_NO_TIMING));
@@ -2027,26 +2025,42 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     // Batched form: a full plain pageable image held by one window restores as
     // one captured graph per table shape (below); a delta, a codec image, an
     // on-demand or file-gated restore takes the launches below, and so does a
-    // pinned image, whose few launches read it where it is (2000 allocations
-    // of 1 GB: 13.17 ms against 13.89 with the graph and its upload).
+    // pinned image (2000 allocations of 1 GB: 13.44 ms against 13.89 with the
+    // graph).
     const bool use_graph = o && (o->flags & CKPT_OPT_GRAPH) && !img->pinned && !some && !gate && !codec &&
                            !per_alloc && !(v.flags & kFlagDelta) && nc > 0 && wins.size() == 1;
-    // A pinned image is read by the restore kernels straight from host
-    // memory: no staging, no copies, no windows (but those of a file still
-    // being loaded and of the per-allocation form, a launch each). A few
-    // work-groups reach the link's rate (kLinkGrid), where a copy engine
-    // reached 57 or 30 GB/s depending on the engine the stream got.
-    const bool direct = img->pinned;
-    if (direct && !per_alloc && !gate && nc > 0) wins = {Window{0, nc}};
-    // A plain pageable image of at least kTailMinBytes held by one window
-    // runs as a launch over all chunks but the last 1/64 and a launch over
-    // those, both uploads on one copy stream: the long launch runs while the
-    // short tail is uploaded (the tail's upload ends before the long launch
-    // does, so the device never waits idle between the two).
+    // A short payload of a pinned image is read by the restore kernels straight
+    // from host memory: no staging, no copy to wait for. Waves that wait on host
+    // loads hold up the vector memory of their CUs, and with it every launch of
+    // other streams that has work there (a 1 GiB copy beside 4 GiB restores:
+    // 21 ms instead of 0.44), so a longer one goes to staging by a copy engine,
+    // which disturbs nobody, and so does one whose upload runs beside the check
+    // of a delta's base or the fill of ZERO chunks (57 GB/s against 3.1 and 4.8
+    // TB/s) if these last as long as kMinOverlap takes on the link.
+    const uint64_t beside = (v.N - std::min(v.N, v.D)) / (v.flags & kFlagDelta ? 55 : 85);
+    uint64_t moves = v.D;   // bound of the payload this call moves
+    if (some) {
+        moves = 0;
+        for (uint64_t a = 0; a < v.n_allocs; ++a)
+            if (sel[a] >= 0) moves += round16(d[a].size);
+    }
+    const bool direct = img->pinned && !gate && moves <= kLinkBytes && (some || beside < kMinOverlap);
+    // A pinned image whose payload is read where it is, or fits the staging
+    // budget as a whole, is restored from one set of tables.
+    const bool whole = img->pinned && !gate && !per_alloc && nc > 0 &&
+                       (direct || wins.size() == 1 || (v.D <= c->budget && !(o && o->window_bytes)));
+    // Staged as a whole, the payload is uploaded on one copy stream in parts, so
+    // that one part's launches run beside the next one's upload: the codec's
+    // windows, and of a long plain payload (kTailMinBytes) all chunks but the
+    // last 1/64, then those (the short tail's upload ends while the long launch
+    // runs). So is a plain pageable image held by one window.
+    const bool parts = whole && codec && !(o && o->window_bytes) && nc >= 2 * kCodecPieces;
     const bool tail = !use_graph && !direct && !per_alloc && !codec && !gate && !(o && o->window_bytes) &&
-                      wins.size() == 1 && nc >= 128 && nc * C >= kTailMinBytes;
-    const uint64_t g_tail = tail ? nc - nc / 64 : 0;
-    if (tail) wins = {Window{0, g_tail}, Window{g_tail, nc}};
+                      (whole || wins.size() == 1) && nc >= 128 && nc * C >= kTailMinBytes;
+    if (whole && (direct || !parts)) wins = {Window{0, nc}};
+    else if (parts) wins = plan_windows(d, nc, C, ceil_div(nc - nc / 32, kCodecPieces - 1) * C, false);
+    if (tail) wins = {Window{0, nc - nc / 64}, Window{nc - nc / 64, nc}};
+    const bool staged = whole && !direct;
     const uint64_t W = wins.size();
     const uint32_t ncs = (o && o->copy_streams) ? o->copy_streams : 2;
 
@@ -2059,7 +2073,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     HIPCHK(c->off.ensure(8 * std::max<uint64_t>(nc, 1)));
     if (codec) HIPCHK(c->rlen.ensure(4 * std::max<uint64_t>(nc, 1)));
     HIPCHK(c->wb.ensure(8 * (W + 2)));
-    if (!direct) HIPCHK(c->staging.ensure((uint64_t)nslots * slot));
+    if (!direct) HIPCHK(c->staging.ensure(staged ? v.D : (uint64_t)nslots * slot));
     const uint64_t tiles = ceil_div(nc, 256) + 64;   // look-back words of the offsets scan, twice
     HIPCHK(c->status.ensure(16 * tiles, c->s_main));
     // ctl: ticket[1] | counts[4] u64 | bad u64 | bad2 u64 | err (+pad) | bad3 u64 | bas u64 | bgate (+pad) |
@@ -2069,11 +2083,12 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     HIPCHK(c->ctl.ensure(ctl_wtk + 4 * (W + 2) + 64));
     HIPCHK(ensure_hsmall(c, 8 * (W + 2) + 256));
     HIPCHK(ensure_events(c, std::max<size_t>(2 * W + (size_t)nslots + 2, ncs)));
-    // stage times: by stamps where the launches are few (split or one window),
+    // stage times: by stamps where the launches are few and read host memory,
     // else by events
     const bool stamped = direct && W <= 1 && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     const bool timing = !stamped && !(o && (o->flags & CKPT_OPT_NO_TIMING));
-    if (timing || (stamped && o && o->strict_verify)) HIPCHK(ensure_tevents(c, 2 * W + 2));
+    // pairs: the windows' launches, base check, zero fill
+    if (timing) HIPCHK(ensure_tevents(c, 2 * W + 4));
     const EngineConsts* ec;
     HIPCHK(get_consts(c, T, C, &ec));
     uint8_t* ctl = c->ctl.as<uint8_t>();
@@ -2308,18 +2323,11 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     if (host_crc32c(v.recs, tl) != v.tables_crc) return CKPT_ECORRUPT;
     std::vector<uint64_t> wbeg(W), wend(W);   // payload ranges of the windows
     uint64_t n_packed = 0, nz = 0, nd = 0, nu = 0, total = 0;
-    // payload offsets and numbers of DATA chunks before the ascending bounds:
-    // the windows', or where one launch restores everything a grid of kHeadGrid
-    // ranges, of which the first ones may be staged (below)
-    const bool whole = direct && !per_alloc && !gate && nc > 0;
+    // payload offsets and numbers of DATA chunks before the windows' bounds
     std::vector<uint64_t> bounds;
-    if (whole) {
-        for (uint64_t i = 0; i <= kHeadGrid; ++i) bounds.push_back(nc * i / kHeadGrid);
-    } else {
-        for (const Window& w : wins) {   // in chunk order
-            bounds.push_back(w.g0);
-            bounds.push_back(w.g1);
-        }
+    for (const Window& w : wins) {   // in chunk order
+        bounds.push_back(w.g0);
+        bounds.push_back(w.g1);
     }
     std::vector<uint64_t> at(bounds.size()), rank(bounds.size());
     if (codec) {
@@ -2355,8 +2363,8 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         if (kn[3]) return CKPT_ECORRUPT;
     }
     for (uint64_t w = 0; w < W; ++w) {
-        wbeg[w] = whole ? 0 : at[2 * w];
-        wend[w] = whole ? total : at[2 * w + 1];
+        wbeg[w] = at[2 * w];
+        wend[w] = at[2 * w + 1];
     }
     if ((nu && !(v.flags & kFlagDelta)) || total != v.D) return CKPT_ECORRUPT;
     // PACKED records are decoded by kernels built for a range of chunk sizes
@@ -2378,8 +2386,8 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     }
 
     // A short full restore of whole tiles from a pinned image is one launch.
-    if (whole && !codec && !some && !nu && !(o && o->strict_verify) && C == 16ull * T * K && T >= 64 &&
-        nc + n <= kShortRestore && v.N <= kShortBytes) {
+    if (whole && direct && !codec && !nu && !(o && o->strict_verify) && C == 16ull * T * K && T >= 64 &&
+        nc + n <= kShortRestore && v.N <= kLinkBytes) {
         HIPCHK(ensure_hdesc(c, n + nc));   // (48 of 64 bytes a chunk)
         HIPCHK(ensure_hsmall(c, 64 + nc + n));
         memcpy(c->hdesc, d.data(), sizeof(AllocDesc) * n);
@@ -2444,33 +2452,17 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     }
 
     // Where the chunks are not all DATA, the device holds the kinds apart: DATA
-    // chunks are taken from a list, ZERO chunks filled by a kernel of their
-    // own. While the device reads the UNCHANGED chunks (a delta's base check)
-    // and fills the ZERO ones, a copy engine brings the head of the payload to
-    // staging: as much as the link carries in that time and before it, while the
-    // tables go up and are checked (57 GB/s against 3.1 and 4.8 TB/s, 20 us and
-    // 0.8 ns a chunk), and to the next range bound, as a head that ends late
-    // costs little, one that ends early leaves the link idle. The rest is read
-    // directly. (By an engine, and the event that says it is done recorded
-    // behind the fills: streams share hardware queues, and a copy kernel, or
-    // that event, ahead of them in the main stream's queue holds them up: 44.4
-    // instead of 36.9 ms for 2 GB of DATA in a 40 GB delta, in a process with
-    // other streams. A copy kernel also carries 53 GB/s beside HBM work.)
+    // chunks are taken from a list, ZERO chunks filled by a kernel of their own
+    // (which waits for no payload).
     const bool base_overlap = nu && !some && !codec;
     const bool split = whole && (nz || nu || n_packed);
-    uint64_t hi = 0;   // ranges of the head
-    if (split) {
-        const uint64_t work = (base_overlap ? nu * C / 55 : 0) + nz * C / 85;
-        const uint64_t most = work < kMinHead ? 0 : work + (1u << 20) + 45 * nc;
-        while (hi < kHeadGrid && at[hi] < most && at[hi + 1] <= std::min<uint64_t>(2 * most, c->budget)) ++hi;
-        if (at[hi] < kMinHead) hi = 0;
-        HIPCHK(c->list.ensure(8 * nc));
-    }
-    const uint64_t head = at.empty() ? 0 : at[hi];
-    if (hi) {
-        HIPCHK(c->staging.ensure(head));
-        HIPCHK(hipMemcpyAsync(c->staging.p, v.payload, head, hipMemcpyHostToDevice, c->s_copy[0]));
-    }
+    if (split) HIPCHK(c->list.ensure(8 * nc));
+    // The first upload of a staged payload starts here, beside the tables' way
+    // up, the check of a delta's base and the fills. (Its event is recorded
+    // behind those: streams share hardware queues, and that event ahead of them
+    // in the main stream's queue holds them up.)
+    if (staged && wend[0] > wbeg[0])
+        HIPCHK(hipMemcpyAsync(c->staging.p, v.payload, wend[0], hipMemcpyHostToDevice, c->s_copy[0]));
 
     // tables up, payload offsets, and the per-allocation check (the image's
     // chunk digests combined against its allocation digests)
@@ -2696,51 +2688,18 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             if (timing) HIPCHK(hipEventRecord(c->tevents[2 * l + 1], c->s_main));
         }
     }
-    if (split) {
+    if (split && nz) {
         ChunkJob j = restore_job(0);
-        if (timing) HIPCHK(hipEventRecord(c->tevents[0], c->s_main));
-        if (nz) {
-            HIPCHK(launch_zero(j, (int)std::min<uint64_t>(nc, 4ull * c->num_cu), c->s_main));
-            j.stamp = nullptr;
-        }
-        // the head from staging, then the rest from host memory
-        for (int part = 0; part < 2; ++part) {
-            const uint64_t b = part ? hi : 0, e = part ? kHeadGrid : hi;
-            if (b == e) continue;
-            if (!part) {
-                HIPCHK(hipEventRecord(ev[0], c->s_copy[0]));
-                HIPCHK(hipStreamWaitEvent(c->s_main, ev[0], 0));
-                j.slot = c->staging.as<uint8_t>();
-            } else {
-                j.slot = const_cast<uint8_t*>(v.payload);
-            }
-            ChunkJob jd = j;
-            jd.list = c->list.as<uint64_t>();
-            jd.g0 = rank[b];
-            jd.g1 = rank[e];
-            int grid;
-            if (jd.g1 > jd.g0) {
-                if (part) HIPCHK(restore_grid(jd.g1 - jd.g0, &grid));
-                else HIPCHK(grid_for(c, T, K, kModeRestore, jd.g1 - jd.g0, &grid));
-                HIPCHK(launch_chunks(T, K, kModeRestore, one_job(jd, wtk + part), grid, c->s_main));
-                j.stamp = nullptr;
-            }
-            j.g0 = bounds[b];
-            j.g1 = bounds[e];
-            if (n_packed) {
-                grid = unpack_grid(c, j.g1 - j.g0);
-                HIPCHK(launch_unpack(one_job(j, wtk + part), c->rlen.as<uint32_t>(), cc, grid, c->s_main));
-                j.stamp = nullptr;
-            }
-        }
-        if (timing) HIPCHK(hipEventRecord(c->tevents[1], c->s_main));
+        j.g1 = nc;
+        if (timing) HIPCHK(hipEventRecord(c->tevents[2 * W + 2], c->s_main));
+        HIPCHK(launch_zero(j, (int)std::min<uint64_t>(nc, 4ull * c->num_cu), c->s_main));
+        if (timing) HIPCHK(hipEventRecord(c->tevents[2 * W + 3], c->s_main));
     }
-    for (uint64_t w = 0; w < W && !merged && !split; ++w) {
+    for (uint64_t w = 0; w < W && !merged; ++w) {
         const int s = (int)(w % nslots);
-        // a tail split keeps the payload where one window holds it. The
-        // codec's windows go up one after another: two uploads at a time end
-        // together, a window later than one at a time
-        hipStream_t cs = c->s_copy[tail || (codec && !(o && o->copy_streams)) ? 0 : w % ncs];
+        // parts and the codec's windows go up one after another: two uploads at
+        // a time end together, a window later than one at a time
+        hipStream_t cs = c->s_copy[staged || tail || (codec && !(o && o->copy_streams)) ? 0 : w % ncs];
         const uint64_t len = wend[w] - wbeg[w];
         if (gate && !gate->wait(kHeader + tl + wend[w])) {
             // the image's file could not be read: let queued work finish
@@ -2750,25 +2709,35 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         }
         ChunkJob j = restore_job(w);
         if (!direct) {
-            uint8_t* sp = c->staging.as<uint8_t>() + (tail ? wbeg[w] : (uint64_t)s * slot);
-            if (slot_used[s] && !tail) HIPCHK(hipStreamWaitEvent(cs, ev[W + s], 0));
+            const bool own = staged || tail;   // a place of its own in staging
+            uint8_t* sp = c->staging.as<uint8_t>() + (own ? wbeg[w] : (uint64_t)s * slot);
+            if (slot_used[s] && !own) HIPCHK(hipStreamWaitEvent(cs, ev[W + s], 0));
             slot_used[s] = true;
-            if (len > slot) return CKPT_ECORRUPT;
-            if (len) HIPCHK(hipMemcpyAsync(sp, v.payload + wbeg[w], len, hipMemcpyHostToDevice, cs));
+            if (!own && len > slot) return CKPT_ECORRUPT;
+            if (len && !(staged && w == 0))
+                HIPCHK(hipMemcpyAsync(sp, v.payload + wbeg[w], len, hipMemcpyHostToDevice, cs));
             HIPCHK(hipEventRecord(ev[w], cs));
             HIPCHK(hipStreamWaitEvent(c->s_main, ev[w], 0));
             j.slot = sp;
             j.slot_base = wbeg[w];
         }
+        ChunkJob jd = j;
+        if (split) {
+            jd.list = c->list.as<uint64_t>();
+            jd.g0 = rank[2 * w];
+            jd.g1 = rank[2 * w + 1];
+        }
         int grid;
-        HIPCHK(restore_grid(j.g1 - j.g0, &grid));
         if (timing) HIPCHK(hipEventRecord(c->tevents[2 * w], c->s_main));
-        const JobList jl = one_job(j, wtk + w);
-        HIPCHK(launch_chunks(T, K, kModeRestore, jl, grid, c->s_main));
+        if (jd.g1 > jd.g0) {
+            HIPCHK(restore_grid(jd.g1 - jd.g0, &grid));
+            HIPCHK(launch_chunks(T, K, kModeRestore, one_job(jd, wtk + w), grid, c->s_main));
+            j.stamp = nullptr;
+        }
         if (n_packed)
-            HIPCHK(launch_unpack(jl, c->rlen.as<uint32_t>(), cc, unpack_grid(c, j.g1 - j.g0), c->s_main));
+            HIPCHK(launch_unpack(one_job(j, wtk + w), c->rlen.as<uint32_t>(), cc, unpack_grid(c, j.g1 - j.g0), c->s_main));
         if (timing) HIPCHK(hipEventRecord(c->tevents[2 * w + 1], c->s_main));
-        if (!direct) HIPCHK(hipEventRecord(ev[W + s], c->s_main));
+        if (!direct && !staged) HIPCHK(hipEventRecord(ev[W + s], c->s_main));
     }
     // strict mode: every restored chunk re-read from HBM once all writes are
     // done, its CRC-32C checked again (the fused check ran on the data in
@@ -2810,7 +2779,8 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         // stamps: hq[10] offsets scan, [11] scatter, [12] base check, [13] its end, [14] the report
         const uint64_t strict_ns = strict && (timing || stamped) ? span_ns(c->sev[0], c->sev[1]) : 0;
         const uint64_t scatter_ns = stamp_ns(c, hq[11], hq[14]);
-        res->ns_kernel = timing    ? timed_ns(c, merged ? ceil_div(W, (uint64_t)kMaxJobs) : W)
+        res->ns_kernel = timing    ? timed_ns(c, merged ? ceil_div(W, (uint64_t)kMaxJobs) : W) +
+                                         (split && nz ? span_ns(c->tevents[2 * W + 2], c->tevents[2 * W + 3]) : 0)
                          : stamped ? scatter_ns - std::min(scatter_ns, strict_ns)
                                    : 0;
         res->ns_total = now_ns() - t_start;

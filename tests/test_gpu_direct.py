@@ -3,6 +3,7 @@ against the staged paths that a pageable image takes (byte equality)."""
 import contextlib
 import os
 import sys
+import threading
 
 import numpy as np
 import pytest
@@ -346,3 +347,68 @@ def test_graph_restore_of_a_pageable_image(ctx, strict):
             assert got[0] == got[1] and got[0][0] == mk.CKPT_ECORRUPT
         pinned.free()
         img.free()
+
+
+@pytest.mark.parametrize("mib,call", [(60, "restore"), (60, "dump"), (60, "delta"), (512, "restore"), (512, "apply"),
+                                      (64, "some"), (64, "codec")])
+def test_long_calls_leave_other_streams_their_speed(ctx, mib, call):
+    """A device copy on another stream while long calls run back to back in a
+    thread: the link's share of a call is a copy engine's, so the copy keeps
+    its speed (at most 4 times its time alone: it was 6 to 50 times where
+    kernels waited on host memory)."""
+    table = [(i, torch.randint(1, 256, (mib << 18,), dtype=torch.uint8, device="cuda")) for i in range(4)]
+    opts = mk.make_opts(flags=mk.OPT_CODEC if call == "codec" else 0)
+    if call == "codec":
+        for _, t in table:
+            t[::2] &= 7
+    rc, img, _ = mk.ckpt_dump(ctx, table, opts=opts)
+    assert rc == 0
+    for _, t in table:
+        t[: t.numel() // 2] ^= 1
+    torch.cuda.synchronize()
+    rc, delta, _ = mk.ckpt_dump(ctx, table, prev=img, opts=opts)
+    assert rc == 0
+
+    def dump(prev):
+        rc, im, _ = mk.ckpt_dump(ctx, table, prev=prev)
+        assert rc == 0
+        im.free()
+
+    run = {"restore": lambda: mk.ckpt_restore(ctx, img, table), "codec": lambda: mk.ckpt_restore(ctx, img, table),
+           "apply": lambda: mk.ckpt_restore(ctx, delta, table), "some": lambda: mk.ckpt_restore_some(ctx, img, table[1:4]),
+           "dump": lambda: dump(None), "delta": lambda: dump(img)}[call]
+    src = torch.zeros(256 << 20, dtype=torch.uint8, device="cuda")
+    dst, side = torch.empty_like(src), torch.cuda.Stream()
+
+    def copies(n):
+        times = []
+        with torch.cuda.stream(side):
+            for _ in range(n):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                dst.copy_(src)
+                b.record()
+                b.synchronize()
+                times.append(a.elapsed_time(b))
+        return sorted(times)[n // 2]
+
+    copies(5)
+    alone = copies(21)
+    stop, calls = threading.Event(), []
+
+    def loop():
+        while not stop.is_set():
+            run()
+            calls.append(1)
+
+    run()
+    th = threading.Thread(target=loop)
+    th.start()
+    try:
+        copies(5)
+        beside = copies(81)
+    finally:
+        stop.set()
+        th.join()
+    print("%s of %d MiB: copy %.3f ms alone, %.3f beside %d calls" % (call, mib, alone, beside, len(calls)), flush=True)
+    assert len(calls) > 1 and beside <= 4 * alone
