@@ -183,7 +183,7 @@ void ckpt_ctx_destroy(ckpt_ctx* ctx);
  * Beside other streams' work: payloads cross the link by copy engines, which
  * slow it by a few per cent, except in dumps and restores of at most 20 MiB:
  * their kernels write or read a pinned image themselves, which may hold up
- * launches of other streams for as long as the call lasts (0.4 ms). */
+ * launches of other streams for as long as the call lasts (0.5 ms). */
 int  ckpt_dump(ckpt_ctx* ctx, const ckpt_alloc_table* table, const ckpt_image* prev,
                ckpt_image** out, const ckpt_opts* opts, void* stream, ckpt_result* res);
 

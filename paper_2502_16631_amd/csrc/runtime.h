@@ -236,9 +236,6 @@ namespace mk {
 // launched as all chunks but the last 1/64, then those.
 constexpr uint64_t kTailMinBytes = 512ull << 20;
 
-// Work-groups of a restore launch that reads a pinned image over the host
-// link (512 threads, 64 KiB in flight each).
-constexpr int kLinkGrid = 64;
 // Transfers of at most this many bytes may be made by the kernels of a call
 // themselves, reading or writing a pinned image over the link. They hold up
 // other streams' launches on their CUs for as long as they last (16 MiB: a
@@ -246,7 +243,12 @@ constexpr int kLinkGrid = 64;
 // dumps 688), so the bound keeps that to 0.4 ms a call, as long as a copy of 1
 // GiB holds the memory; longer transfers are a copy engine's, which slows that
 // copy by 5 %.
+// Chunks shorter than kLinkMinChunk are not moved so: their launches are
+// slower than the link (restores of 16 MiB: 418 us in 1 KiB chunks, 877 in 256
+// bytes, 13 ms in 16; dumps 510 us, 1.0 ms, 20 ms).
 constexpr uint64_t kLinkBytes = 20ull << 20;
+constexpr uint32_t kLinkMinChunk = 1024;
+inline bool by_kernels(uint64_t bytes, uint32_t C) { return bytes <= kLinkBytes && C >= kLinkMinChunk; }
 constexpr uint64_t kMinOverlap = 1ull << 20;
 // A full restore of a pinned image of at most this many chunks and allocations
 // and of at most kLinkBytes is one launch, with kLinkFlight bytes of chunks
@@ -254,6 +256,15 @@ constexpr uint64_t kMinOverlap = 1ull << 20;
 // takes 48 instead of 66 us, 16 MiB 334 instead of 343, 24 MiB the same (475-501
 // against 494), 60 MiB in 128 KiB chunks 1220 against 1163.
 constexpr uint64_t kShortRestore = 512, kLinkFlight = 3ull << 20;
+// Work-groups of another restore launch that reads a pinned image over the
+// link, of at most `grid` that the device holds: a work-group has one tile of
+// T threads and K rows in flight, and nothing while it digests it (64 tiles of
+// 64 KiB reach the link's rate; 64 of 1 KiB took 926 us for 16 MiB, 3072 take
+// 418).
+inline int link_grid(int T, int K, int grid) {
+    const int n = (int)std::max<uint64_t>(64, kLinkFlight / (16ull * T * K));
+    return std::min(grid, n);
+}
 // A full dump of at most kLinkBytes in one launch writes its payload
 // straight into a pinned image; of at most so many chunks and allocations,
 // set-up and end are in that launch too.

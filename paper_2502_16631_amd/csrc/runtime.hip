@@ -998,7 +998,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     // allocations, 16 MiB: 420 -> 350 us, and 330 in one launch). The image is
     // then allocated at the payload's bound.
     const bool one_pass = !prev && !codec && wins.size() == 1 && nc > 0 && !use_graph && !per_alloc;
-    const bool small = one_pass && !sink && upper <= kLinkBytes;
+    const bool small = one_pass && !sink && by_kernels(upper, C);
     // The pipeline of a dump (launch_pieces): its pieces' bounds and their
     // places in staging. With room for everything each piece has its own part;
     // else the pieces go round a ring of slots. A longer full dump that fits
@@ -1054,7 +1054,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     const uint64_t n_pieces = piped ? piece.size() - 1 : 0;
     const bool ring = piped && wins.size() > 1;
     // One short piece: gathered straight into a pinned image.
-    const bool small_delta = piped && !plain && !codec && !ring && n_pieces == 1 && !sink && upper <= kLinkBytes;
+    const bool small_delta = piped && !plain && !codec && !ring && n_pieces == 1 && !sink && by_kernels(upper, C);
     // stage times: of a short dump by stamps, else by events
     const bool stamped = (small || (piped && !plain)) && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     const bool timing = !stamped && !(o && (o->flags & CKPT_OPT_NO_TIMING));
@@ -2044,7 +2044,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         for (uint64_t a = 0; a < v.n_allocs; ++a)
             if (sel[a] >= 0) moves += round16(d[a].size);
     }
-    const bool direct = img->pinned && !gate && moves <= kLinkBytes && (some || beside < kMinOverlap);
+    const bool direct = img->pinned && !gate && by_kernels(moves, C) && (some || beside < kMinOverlap);
     // A pinned image whose payload is read where it is, or fits the staging
     // budget as a whole, is restored from one set of tables.
     const bool whole = img->pinned && !gate && !per_alloc && nc > 0 &&
@@ -2635,7 +2635,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     // the link can feed
     auto restore_grid = [&](uint64_t chunks, int* grid) -> hipError_t {
         hipError_t e = grid_for(c, T, K, kModeRestore, chunks, grid);
-        if (direct) *grid = std::min(*grid, kLinkGrid);
+        if (direct) *grid = link_grid(T, K, *grid);
         return e;
     };
     // On-demand restore whose payload fits the staging (or is read where it

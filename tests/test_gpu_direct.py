@@ -412,3 +412,9 @@ def test_long_calls_leave_other_streams_their_speed(ctx, mib, call):
         th.join()
     print("%s of %d MiB: copy %.3f ms alone, %.3f beside %d calls" % (call, mib, alone, beside, len(calls)), flush=True)
     assert len(calls) > 1 and beside <= 4 * alone
+
+
+@pytest.mark.parametrize("c,zero_mib", [(16, 1), (512, 1), (1024, 1), (1024, 100), (2048, 1)])
+def test_small_chunks_from_pinned_and_pageable_images(ctx, c, zero_mib):
+    """Chunk sizes on both sides of the least that kernels read over the link."""
+    test_restores_from_pinned_and_pageable_images(ctx, c, zero_mib, 0)

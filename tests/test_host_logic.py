@@ -248,3 +248,28 @@ def test_bench_refuses_more_than_one_gpu():
     assert p.returncode == 2
     assert "one GPU" in p.stderr and "--gpus 2" in p.stderr
     assert p.stdout == ""
+
+
+@pytest.fixture(scope="module")
+def link():
+    so = os.path.join(ROOT, "tests", "emu", "liblink_policy.so")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", "-I", CSRC, "-o", so,
+                           os.path.join(ROOT, "tests", "emu", "link_policy.cpp")])
+    L = ctypes.CDLL(so)
+    L.emu_by_kernels.argtypes = [ctypes.c_uint64, ctypes.c_uint32]
+    return L
+
+
+@pytest.mark.parametrize("c,t,k", SHAPES)
+def test_kernels_on_the_link_keep_it_busy(link, c, t, k):
+    """Work-groups of a restore that reads host memory: as many as hold the
+    3 MiB in flight that the link's rate takes, or all the device has; at
+    least 64; short payloads in chunks that are not tiny only."""
+    for grid in (1, 63, 64, 500, 8192):
+        n = link.emu_link_grid(t, k, grid)
+        assert 1 <= n <= grid
+        assert n == grid or (n >= 64 and n * 16 * t * k >= 3 << 20)
+        assert n <= 64 or n * 16 * t * k <= 3 << 20   # no more than that, for the others' sake
+    assert not link.emu_by_kernels((20 << 20) + 1, c)
+    assert bool(link.emu_by_kernels(20 << 20, c)) == (c >= 1024)
