@@ -32,7 +32,7 @@
 namespace mk {
 
 constexpr uint32_t kCodecMinChunk = 4096;    // one 16-byte row per lane
-constexpr uint32_t kCodecMaxChunk = 65536;   // records are staged in LDS
+constexpr uint32_t kCodecMaxChunk = 65536;   // 16 rows per lane
 constexpr int kCodecThreads = 256;
 constexpr uint64_t kCodecPieces = 8;         // windows of a staged codec restore
 constexpr uint32_t kRecordHead = 48;

@@ -390,17 +390,13 @@ __global__ void __launch_bounds__(NT) k_pack(PackJob j) {
 // positions by a block scan (their count checked against the head), rows
 // decoded, stored to the allocation and digested per lane, 16 bytes per
 // step; the lane digests are combined into the chunk's CRC and compared
-// with the image's. The record is brought into LDS first, every byte once and
-// coalesced: decoding reads the codes twice and the escapes one by one, which
-// host memory (a pinned image) must not see.
+// with the image's.
 template <int K>
 __global__ void __launch_bounds__(NT) k_unpack(JobList jl, const uint32_t* rlen, const CodecConsts* cc) {
-    __shared__ __align__(16) uint8_t s_rec[kCodecMinChunk * K];
     __shared__ uint32_t s_tab[16 * 256];
     __shared__ unsigned long long s_w[2 * NW];
     __shared__ uint32_t s_red[NW];
     const int tid = threadIdx.x;
-    if (blockIdx.x == 0 && tid == 0 && jl.job[0].stamp) *jl.job[0].stamp = wall_clock64();
     for (int i = tid; i < 16 * 256; i += NT) s_tab[i] = cc->tab[i];
     const uint32_t lanec = cc->lane[tid], full_init = cc->full_init;
     const uint32_t C = jl.job[0].C, L = C / 8;
@@ -422,18 +418,7 @@ __global__ void __launch_bounds__(NT) k_unpack(JobList jl, const uint32_t* rlen,
             if (tid == 0) atomicMin(job.bad, (unsigned long long)g);
             continue;
         }
-        const uint8_t* rec = s_rec;
-        {
-            const uint4* from = reinterpret_cast<const uint4*>(job.slot + (job.off[g] - job.slot_base));
-            uint4 x[K];
-#pragma unroll
-            for (int r = 0; r < K; ++r)
-                if (16u * (r * NT + tid) < rl) x[r] = from[r * NT + tid];
-#pragma unroll
-            for (int r = 0; r < K; ++r)
-                if (16u * (r * NT + tid) < rl) reinterpret_cast<uint4*>(s_rec)[r * NT + tid] = x[r];
-        }
-        __syncthreads();
+        const uint8_t* rec = job.slot + (job.off[g] - job.slot_base);
         uint32_t h[12];
         load_bytes<16>(rec, h);
         load_bytes<16>(rec + 16, h + 4);

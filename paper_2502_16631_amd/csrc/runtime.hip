@@ -417,7 +417,7 @@ hipError_t get_codec_consts(ckpt_ctx* c, uint32_t C, const CodecConsts** out) {
     return hipSuccess;
 }
 
-// Grid of the codec decode: two work-groups per CU (LDS-bound), grid-stride.
+// Grid of the codec decode: two work-groups per CU (its registers), grid-stride.
 int unpack_grid(const ckpt_ctx* c, uint64_t chunks) {
     return (int)std::max<uint64_t>(1, std::min<uint64_t>(chunks, 2ull * c->num_cu));
 }
@@ -2044,7 +2044,9 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         for (uint64_t a = 0; a < v.n_allocs; ++a)
             if (sel[a] >= 0) moves += round16(d[a].size);
     }
-    const bool direct = img->pinned && !gate && by_kernels(moves, C) && (some || beside < kMinOverlap);
+    // (The codec's decode reads its records in pieces, twice, which host memory
+    // must not see.)
+    const bool direct = img->pinned && !gate && !codec && by_kernels(moves, C) && (some || beside < kMinOverlap);
     // A pinned image whose payload is read where it is, or fits the staging
     // budget as a whole, is restored from one set of tables.
     const bool whole = img->pinned && !gate && !per_alloc && nc > 0 &&
@@ -2386,7 +2388,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     }
 
     // A short full restore of whole tiles from a pinned image is one launch.
-    if (whole && direct && !codec && !nu && !(o && o->strict_verify) && C == 16ull * T * K && T >= 64 &&
+    if (whole && direct && !nu && !(o && o->strict_verify) && C == 16ull * T * K && T >= 64 &&
         nc + n <= kShortRestore && v.N <= kLinkBytes) {
         HIPCHK(ensure_hdesc(c, n + nc));   // (48 of 64 bytes a chunk)
         HIPCHK(ensure_hsmall(c, 64 + nc + n));

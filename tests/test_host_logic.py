@@ -273,3 +273,23 @@ def test_kernels_on_the_link_keep_it_busy(link, c, t, k):
         assert n <= 64 or n * 16 * t * k <= 3 << 20   # no more than that, for the others' sake
     assert not link.emu_by_kernels((20 << 20) + 1, c)
     assert bool(link.emu_by_kernels(20 << 20, c)) == (c >= 1024)
+
+
+def test_decode_kernels_keep_their_registers_and_two_groups_per_cu(tmp_path):
+    """The codec's decode kernels as the compiler reports them for gfx950: no
+    scratch, and registers (512 per lane and SIMD) and LDS (160 KiB) for the
+    two work-groups of 256 threads per CU that their grid counts on."""
+    flags = re.search(r"^FLAGS=\((.*?)\)$", open(os.path.join(CSRC, "..", "build.sh")).read(), re.S | re.M).group(1)
+    p = subprocess.run(["hipcc"] + flags.split() + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
+                        os.path.join(CSRC, "codec.hip"), "-o", str(tmp_path / "codec.o")],
+                       capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stderr
+    seen = 0
+    for part in p.stderr.split("Function Name: ")[1:]:
+        if "k_unpack" not in part.split()[0]:
+            continue
+        seen += 1
+        use = {k: int(re.search(k + r"[^:\n]*: (\d+)", part).group(1)) for k in ("VGPRs", "AGPRs", "ScratchSize", "LDS Size")}
+        print(part.split()[0], use)
+        assert use["ScratchSize"] == 0 and use["VGPRs"] + use["AGPRs"] <= 256 and use["LDS Size"] <= 80 << 10
+    assert seen == 5
