@@ -378,8 +378,9 @@ k_chunks(JobList jl) {
     __shared__ uint64_t s_off;
 
     const int tid = threadIdx.x;
+    constexpr bool kTickets = MODE == kModeDump || MODE == kModeRestore;
     const bool active = T >= 64 || tid < T;
-    stamp(jl.job[0].stamp);
+    if constexpr (!kTickets) stamp(jl.job[0].stamp);
     // a restore that its graph's validation rejected writes nothing
     if constexpr (MODE == kModeRestore || MODE == kModeVerify)
         if (jl.job[0].gate && *jl.job[0].gate == 0) return;
@@ -403,8 +404,10 @@ k_chunks(JobList jl) {
     // the verify, digest and classify modes take chunks grid-stride,
     // so a chunk they skip costs no atomic and no barrier (a barrier follows
     // each chunk they process, for the LDS reductions).
-    constexpr bool kTickets = MODE == kModeDump || MODE == kModeRestore;
-    if (kTickets && tid == 0) s_tk[0] = atomicAdd(jl.ticket, 1u);
+    if (kTickets && tid == 0) {
+        s_tk[0] = atomicAdd(jl.ticket, 1u);
+        stamp(jl.job[0].stamp);   // (at the kernel's top it costs the dump mode a register)
+    }
     bool dirty = false;
     for (uint32_t it = 0;; ++it) {
         uint64_t tk;

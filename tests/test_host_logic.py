@@ -275,21 +275,33 @@ def test_kernels_on_the_link_keep_it_busy(link, c, t, k):
     assert bool(link.emu_by_kernels(20 << 20, c)) == (c >= 1024)
 
 
-def test_decode_kernels_keep_their_registers_and_two_groups_per_cu(tmp_path):
-    """The codec's decode kernels as the compiler reports them for gfx950: no
-    scratch, and registers (512 per lane and SIMD) and LDS (160 KiB) for the
-    two work-groups of 256 threads per CU that their grid counts on."""
-    flags = re.search(r"^FLAGS=\((.*?)\)$", open(os.path.join(CSRC, "..", "build.sh")).read(), re.S | re.M).group(1)
+def resources(source, tmp_path):
+    """What the compiler reports of a source's kernels for gfx950, by mangled name."""
+    build = open(os.path.join(CSRC, "..", "build.sh")).read()
+    flags = " ".join(re.search(r"^%s=\((.*?)\)$" % f, build, re.S | re.M).group(1) for f in
+                     (("FLAGS", "KFLAGS") if source == "kernels.hip" else ("FLAGS",)))
     p = subprocess.run(["hipcc"] + flags.split() + ["--cuda-device-only", "-Rpass-analysis=kernel-resource-usage", "-c",
-                        os.path.join(CSRC, "codec.hip"), "-o", str(tmp_path / "codec.o")],
-                       capture_output=True, text=True, timeout=300)
+                        os.path.join(CSRC, source), "-o", str(tmp_path / "out.o")],
+                       capture_output=True, text=True, timeout=600)
     assert p.returncode == 0, p.stderr
-    seen = 0
-    for part in p.stderr.split("Function Name: ")[1:]:
-        if "k_unpack" not in part.split()[0]:
-            continue
-        seen += 1
-        use = {k: int(re.search(k + r"[^:\n]*: (\d+)", part).group(1)) for k in ("VGPRs", "AGPRs", "ScratchSize", "LDS Size")}
-        print(part.split()[0], use)
-        assert use["ScratchSize"] == 0 and use["VGPRs"] + use["AGPRs"] <= 256 and use["LDS Size"] <= 80 << 10
-    assert seen == 5
+    keys = ("VGPRs", "AGPRs", "ScratchSize", "LDS Size")
+    return {part.split()[0]: {k: int(re.search(k + r"[^:\n]*: (\d+)", part).group(1)) for k in keys}
+            for part in p.stderr.split("Function Name: ")[1:]}
+
+
+def test_decode_kernels_keep_their_registers_and_two_groups_per_cu(tmp_path):
+    """The codec's decode kernels: no scratch, and registers (512 per lane and
+    SIMD) and LDS (160 KiB) for the two work-groups of 256 threads per CU that
+    their grid counts on."""
+    use = {k: u for k, u in resources("codec.hip", tmp_path).items() if "k_unpack" in k}
+    assert len(use) == 5
+    for k, u in use.items():
+        assert u["ScratchSize"] == 0 and u["VGPRs"] + u["AGPRs"] <= 256 and u["LDS Size"] <= 80 << 10, (k, u)
+
+
+def test_chunk_kernels_that_spill(tmp_path):
+    """Two shapes of the dump mode of k_chunks keep one value in scratch (the
+    cap of 128 registers is worth more), and no other kernel does."""
+    spill = {k: u["ScratchSize"] for k, u in resources("kernels.hip", tmp_path).items() if u["ScratchSize"]}
+    assert {re.search(r"k_chunksILi(\d+)ELi8ELi0E", k).group(1) for k in spill} == {"512", "1024"}
+    assert set(spill.values()) == {8}
