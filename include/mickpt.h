@@ -126,7 +126,8 @@ typedef struct {
     uint64_t n_zero, n_data, n_unchanged;
     uint64_t link_bytes;        /* bytes moved over the host link                           */
     uint64_t ns_total;          /* wall time of the call                                    */
-    uint64_t ns_kernel;         /* summed device time of the chunk kernels                  */
+    uint64_t ns_kernel;         /* summed device time of the chunk kernels (of a delta or    */
+                                /* codec dump of more than 64 pieces: of the first 64)       */
     uint64_t ns_link;           /* wall time from first to last host-link copy              */
     uint64_t n_packed;          /* PACKED chunks (codec records; not counted in n_data)     */
     uint64_t reserved[3];
@@ -142,7 +143,8 @@ typedef struct {
      *          window)  [3] gather (delta in one window) or gather + encode
      *          (codec)  [4] host link: first to last payload copy, wall time
      *          [5] finalize (per-allocation combine, table digests, tables copied
-     *          out)  [6] unused  [7] whole call, wall time;
+     *          out)  [6] unused  [7] whole call, wall time; [1] to [3] of a
+     *          delta or codec dump in more than 64 pieces: the first 64;
      * restore: [0] validate (host checks of the tables), wall
      *          time  [1] base check of a delta (a plain full restore runs it on
      *          the device beside the upload: its HIP-event time; otherwise the

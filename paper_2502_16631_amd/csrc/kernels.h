@@ -127,7 +127,7 @@ struct SetupJob {
 struct FinishJob {
     CombineJob c;
     int n_copies;
-    uint32_t n_rep;              // 64-bit result words, <= 62; rep[n_rep] and [n_rep + 1] take the device
+    uint32_t n_rep;              // 64-bit result words, <= 254; rep[n_rep] and [n_rep + 1] take the device
                                  // clock at the kernel's start and end
     SetupJob::Copy copy[4];
     uint64_t* rep;

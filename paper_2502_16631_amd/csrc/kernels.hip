@@ -1682,7 +1682,7 @@ hipError_t launch_setup(const SetupJob& j, hipStream_t s) {
 }
 
 hipError_t launch_finish(const FinishJob& j, hipStream_t s) {
-    if (j.n_copies > 4 || j.n_rep > 62 || j.c.mode != kCombineWrite) return hipErrorInvalidValue;
+    if (j.n_copies > 4 || j.n_rep > 254 || j.c.mode != kCombineWrite) return hipErrorInvalidValue;
     uint64_t words = 0;
     for (int i = 0; i < j.n_copies; ++i) words = words > j.copy[i].n ? words : j.copy[i].n;
     const uint64_t blocks = j.c.n_allocs + (words == 0 ? 1 : words < 256 * 1024 ? (words + 1023) / 1024 : 256);

@@ -881,11 +881,12 @@ int mk::dump_impl(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image* 
 // set of buffers and events.
 constexpr uint64_t kRing = 4;
 // Result words of a dump in pinned memory: window totals, error, (pad, kind
-// counts,) stamps (set-up, chunk kernel, three for each of the first pieces
-// of a delta), the last kernel's two stamps.
-constexpr uint32_t kStampPieces = 16, kStamps = 2 + 3 * kStampPieces;
-constexpr uint32_t kRepErr = kRing + 1, kRepStamps = kRing + 7, kRepWords = kRepStamps + kStamps;
-constexpr uint64_t kHwWords = kRepWords + 3;
+// counts,) stamps (set-up, chunk kernel, three for each of a delta's or codec
+// dump's first kStampPieces pieces, the next piece's first), of which a call
+// reports those that it uses, then the last kernel's two stamps.
+constexpr uint32_t kStampPieces = 64, kStamps = 3 + 3 * kStampPieces;
+constexpr uint32_t kRepErr = kRing + 1, kRepStamps = kRing + 7;
+constexpr uint64_t kHwWords = kRepStamps + kStamps + 3;
 // Pieces of a delta's or a codec dump's pipeline (launch_pieces): at most this
 // many in a delta, and the least bytes of state worth one. (A piece of a delta
 // costs 25 us of small launches; a codec piece's passes take 2 ms per GiB,
@@ -1339,7 +1340,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         j.prev_crc = prev_dev;
         j.err = err;
         j.epoch = ep;
-        j.stamp = st;
+        j.stamp = stamped && i <= kStampPieces ? stamps + 2 + 3 * i : nullptr;
         if (use_graph) {
             if (timing && (e = hipEventRecord(c->tevents[2 * i], c->s_main)) != hipSuccess) return e;
             if ((e = hipGraphLaunch(graph_exec[i], c->s_main)) != hipSuccess) return e;
@@ -1675,6 +1676,8 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     const bool tables_direct = na ? host_tables : im->pinned;
     uint8_t* htab = himg + kHeader;
     if (timing && !use_graph && (e = hipEventRecord(c->sev[2], c->s_main)) != hipSuccess) return fail(e);
+    const uint32_t rep_words =
+        kRepStamps + (!stamped ? 0 : piped ? 3 + 3 * (uint32_t)std::min<uint64_t>(n_pieces, kStampPieces) : 2);
     FinishJob fj;
     memset(&fj, 0, sizeof(fj));
     fj.c.mode = kCombineWrite;
@@ -1687,7 +1690,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         fj.c.recs = tables_direct ? htab : B.arc->as<uint8_t>();
         fj.rep = hw;
         fj.rep_src = wtot;
-        fj.n_rep = kRepWords;
+        fj.n_rep = rep_words;
     }
     if (tables_direct) {
         if (use_graph) fj.add_copy(htab, B.arc->p, 32ull * n);
@@ -1775,7 +1778,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         if (piped) {
             for (uint64_t i = 0; i < std::min<uint64_t>(n_pieces, kStampPieces); ++i) {
                 const uint64_t* p = st + 2 + 3 * i;
-                const uint64_t end = i + 1 < std::min<uint64_t>(n_pieces, kStampPieces) ? p[3] : hw[kRepWords];
+                const uint64_t end = i + 1 < n_pieces ? p[3] : hw[rep_words];
                 st_ns[0] += stamp_ns(c, p[0], p[1]);
                 st_ns[1] += stamp_ns(c, p[1], p[2]);
                 st_ns[2] += stamp_ns(c, p[2], end);
@@ -1788,7 +1791,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             const uint64_t seen = now_ns() - t_link0;
             kern_ns = st_ns[0] = seen - std::min(st_ns[3], seen);
         } else {
-            kern_ns = st_ns[0] = stamp_ns(c, st[1], hw[kRepWords]);
+            kern_ns = st_ns[0] = stamp_ns(c, st[1], hw[rep_words]);
             st_ns[3] = stamp_ns(c, st[0], st[1]);
         }
     }
@@ -1834,7 +1837,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         if (stamped) {
             res->ns_stage[0] = st_ns[3];
             for (int i = 0; i < 3; ++i) res->ns_stage[1 + i] = st_ns[i];
-            res->ns_stage[5] = one_launch ? stamp_ns(c, rep[4], rep[5]) : stamp_ns(c, hw[kRepWords], hw[kRepWords + 1]);
+            res->ns_stage[5] = one_launch ? stamp_ns(c, rep[4], rep[5]) : stamp_ns(c, hw[rep_words], hw[rep_words + 1]);
         }
         if (timing) {
             if (!use_graph) res->ns_stage[0] = span_ns(c->sev[0], c->sev[1]);

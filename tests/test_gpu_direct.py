@@ -418,3 +418,44 @@ def test_long_calls_leave_other_streams_their_speed(ctx, mib, call):
 def test_small_chunks_from_pinned_and_pageable_images(ctx, c, zero_mib):
     """Chunk sizes on both sides of the least that kernels read over the link."""
     test_restores_from_pinned_and_pageable_images(ctx, c, zero_mib, 0)
+
+
+@pytest.mark.parametrize("pieces", [16, 17, 64, 65, 256])
+def test_stage_times_of_many_pieces(ctx, pieces):
+    """A codec dump in many pieces, each in a staging slot of its own: every
+    piece counts to its own stages (digests and sizes take longer than gather
+    and encode; the later pieces' were the 16th one's gather), up to the 64
+    that are reported."""
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    t = torch.randint(0, 256, (pieces << 20,), dtype=torch.uint8, device="cuda", generator=gen)
+    t[::2] &= 7
+    opts = mk.make_opts(chunk_size=65536, window_bytes=1 << 20, slots=pieces, flags=mk.OPT_CODEC)
+    for _ in range(3):
+        rc, img, res = mk.ckpt_dump(ctx, [(1, t)], opts=opts)
+        assert rc == 0 and res.windows == pieces
+        img.free()
+    st = list(res.ns_stage)
+    print(pieces, st, res.ns_kernel, flush=True)
+    assert all(x > 0 for x in st[1:4]) and st[3] < st[1]
+    assert res.ns_kernel == sum(st[1:4]) <= st[7]
+    if pieces == 256:
+        assert res.ns_kernel <= st[7] / 2
+
+
+def test_stage_times_of_an_on_demand_codec_restore(ctx):
+    """16 MiB that do not compress and a little that does, restored on demand:
+    the launch over the first counts to the scatter stage, not to the offsets
+    scan before it (0.3 ms, all of it, where the second launch took its stamp)."""
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    table = [(i, torch.randint(0, 256, (n << 20,), dtype=torch.uint8, device="cuda", generator=gen))
+             for i, n in enumerate((16, 1, 1))]
+    table[1][1][::2] &= 7
+    rc, img, res = mk.ckpt_dump(ctx, table, opts=mk.make_opts(flags=mk.OPT_CODEC))
+    assert rc == 0 and res.n_packed == 16
+    for _ in range(3):
+        rc, res = mk.ckpt_restore_some(ctx, img, table[:2])
+        assert rc == 0
+    st = list(res.ns_stage)
+    print(st, flush=True)
+    assert st[3] > 0 and st[5] < 100000
+    img.free()
