@@ -192,6 +192,7 @@ struct ckpt_image {
     uint64_t n = 0;
     uint64_t cap = 0;
     uint64_t uid = 0;   // identity: key of the image's resident digest table
+    uint64_t spare = 0; // capacity beyond n that counts against the room for such images
     bool pinned = true;
 };
 

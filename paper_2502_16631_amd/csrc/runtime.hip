@@ -65,6 +65,7 @@ struct PinnedPool {
     std::multimap<uint64_t, void*> free_;   // capacity -> buffer
     uint64_t cached = 0, live = 0;
     uint64_t budget = 56ull << 30;          // MICKPT_PINNED_BUDGET overrides (bytes)
+    uint64_t spare = 0;                     // bytes of live images beyond their length (SpareHold)
     PinnedPool() {
         if (const char* env = getenv("MICKPT_PINNED_BUDGET")) budget = strtoull(env, nullptr, 0);
     }
@@ -132,6 +133,33 @@ PinnedPool& pool() {
     static PinnedPool* p = new PinnedPool();   // never destroyed: buffers may outlive statics
     return *p;
 }
+
+// Room for an image allocated before its length is known, at the payload's
+// bound (a dump that starts to fill it earlier): all images together may be
+// longer than their contents by a sixteenth of the pinned budget, so that
+// states full of zeros do not use it up; a dump that gets no room allocates
+// the image once its length is known.
+struct SpareHold {
+    uint64_t n = 0;
+    bool take(uint64_t bytes) {
+        PinnedPool& p = pool();
+        std::lock_guard<std::mutex> g(p.mu);
+        if (p.spare + bytes > p.budget / 16) return false;
+        p.spare += bytes;
+        n += bytes;
+        return true;
+    }
+    // all but `bytes` of it given back, those handed to the caller
+    uint64_t keep(uint64_t bytes) {
+        PinnedPool& p = pool();
+        std::lock_guard<std::mutex> g(p.mu);
+        bytes = std::min(bytes, n);
+        p.spare -= n - bytes;
+        n = 0;
+        return bytes;
+    }
+    ~SpareHold() { (void)keep(0); }
+};
 
 // Small pinned host buffers (read-backs, bounce buffers): when the driver's
 // pinned limit is reached, cached image buffers are given back until the
@@ -218,6 +246,8 @@ ckpt_image* mk::image_new(uint64_t cap) {
 
 void mk::image_release(ckpt_image* im) {
     if (!im) return;
+    SpareHold spare;
+    spare.n = im->spare;
     if (im->pinned) pool().put(im->p, im->cap);
     else pageable_pool().put(im->p, im->cap);
     delete im;
@@ -896,9 +926,9 @@ constexpr uint64_t kMaxDeltaPieces = 64, kDeltaPiece = 128ull << 20, kCodecPiece
 // rest's kernel, which is 50 times as fast as the link (1 GiB: 1.2 against
 // 0.4 ms).
 constexpr uint64_t kHeadShare = 16;
-// Up to this bound the image of a full dump with zeros in its head is
-// allocated on the head's share of them; beyond, once the length is known.
-constexpr uint64_t kGuessMax = 2ull << 30;
+// Longer states do without: their image is allocated once its length is known
+// (27 GB: 10 of 484 ms more).
+constexpr uint64_t kHeadMax = 2ull << 30;
 
 static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image* prev, ckpt_image** out,
                     const ckpt_opts* o, void* stream, ckpt_result* res, PayloadSink* sink, const NaCall* na) {
@@ -999,13 +1029,15 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     // allocations, 16 MiB: 420 -> 350 us, and 330 in one launch). The image is
     // then allocated at the payload's bound.
     const bool one_pass = !prev && !codec && wins.size() == 1 && nc > 0 && !use_graph && !per_alloc;
-    const bool small = one_pass && !sink && by_kernels(upper, C);
+    SpareHold spare;
+    const bool small = one_pass && !sink && by_kernels(upper, C) && (na || spare.take(upper));
     // The pipeline of a dump (launch_pieces): its pieces' bounds and their
     // places in staging. With room for everything each piece has its own part;
     // else the pieces go round a ring of slots. A longer full dump that fits
     // one window is launched as a head and the rest, so that the head's
     // copy-out, which takes longer, runs beside the rest's kernel.
-    const bool plain = (one_pass || use_graph) && !small && !na && nc * C >= kDeltaPiece && nc >= 2 * kHeadShare;
+    const bool plain = (one_pass || use_graph) && !small && !na && !sink && nc * C >= kDeltaPiece &&
+                       nc >= 2 * kHeadShare && upper <= kHeadMax && spare.take(upper);
     bool piped = plain || ((prev != nullptr || codec) && nc > 0 && !use_graph && !na && !(per_alloc && wins.size() > 1));
     std::vector<uint64_t> piece;   // first chunks, and nc
     if (piped) {
@@ -1168,6 +1200,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     // bound; pinned host memory is limited)
     ckpt_image* im = nullptr;
     uint8_t* himg = nullptr;
+    uint64_t asked = 0;   // payload capacity of an image allocated before that
     ckpt_image na_img;   // the caller's buffer (no-allocation dump)
     if (na) {
         if (na->cap < kHeader + tl) return CKPT_ENOMEM;
@@ -1180,6 +1213,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         im = image_new(kHeader + tl + upper);
         if (!im) return CKPT_ENOMEM;
         himg = im->p;
+        asked = upper;
         if (sink) sink->begin(im);
     }
     // the device can write the image's tables, and all of a small image
@@ -1414,15 +1448,6 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         }
         return gather_direct ? hipSuccess : hipEventRecord(ev[i], c->s_main);
     };
-    // the payload's bound over the chunks before g
-    auto bound_of = [&](uint64_t g) {
-        uint64_t b = 0;
-        for (uint32_t a = 0; a < n && d[a].first < g; ++a) {
-            const uint64_t nk = std::min(ceil_div(d[a].size, C), g - d[a].first);
-            b += std::min(round16(d[a].size), nk * C);
-        }
-        return b;
-    };
     auto launch_pieces = [&](uint64_t* D_out) -> hipError_t {
         hipError_t e;
         const uint64_t P = n_pieces;
@@ -1448,10 +1473,6 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
                 // scaled to all chunks, and a quarter more
                 uint64_t est = (D + Di) / g1 * nc;
                 est = std::max<uint64_t>({est + est / 4 + (64ull << 20), D + Di, im ? 2 * cap : 0});
-                if (plain && i + 1 < P && upper > kGuessMax && Di < bound_of(g1)) {
-                    if ((e = hipEventSynchronize(ev[i + 1])) != hipSuccess) return e;
-                    est = Di + hw[kHwWords + 2 * i + 3];
-                }
                 if (plain && i + 1 == P) est = D + Di;
                 est = sink || codec ? upper : std::min(upper, est);
                 ckpt_image* big = image_new(kHeader + tl + est);
@@ -1468,7 +1489,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
                 }
                 im = big;
                 himg = im->p;
-                cap = est;
+                cap = asked = est;
                 if (sink) sink->begin(im);
             }
             if (Di) {
@@ -1495,7 +1516,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         // ---- batched form: the whole device stage as one captured graph
         uint64_t key = 1469598103934665603ull;
         auto mix = [&key](uint64_t v) { key = (key ^ v) * 1099511628211ull; };
-        mix(n); mix(C); mix((uint64_t)T); mix((uint64_t)K); mix(nc);
+        mix(n); mix(C); mix((uint64_t)T); mix((uint64_t)K); mix(nc); mix(n_pieces);
         for (const AllocDesc& x : d) { mix(x.id); mix(x.ptr); mix(x.size); mix(x.prev_first); }
         const void* ptrs[] = {prev_dev, B.arc->p, B.kinds->p, B.staging->p, B.ctl->p, c->hsmall, ec, B.amap->p};
         for (const void* q : ptrs) mix(reinterpret_cast<uint64_t>(q));
@@ -1823,6 +1844,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     put32(h + 56, tcrc);
     put32(h + 60, host_crc32c(h, 60));
     im->n = kHeader + tl + D;
+    if (!na) im->spare = spare.keep(std::max(asked, D) - D);
 
     if (res) {
         res->windows = (uint32_t)(ring ? n_pieces : W);

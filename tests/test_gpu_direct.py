@@ -2,6 +2,7 @@
 against the staged paths that a pageable image takes (byte equality)."""
 import contextlib
 import os
+import subprocess
 import sys
 import threading
 
@@ -459,3 +460,16 @@ def test_stage_times_of_an_on_demand_codec_restore(ctx):
     print(st, flush=True)
     assert st[3] > 0 and st[5] < 100000
     img.free()
+
+
+@pytest.mark.parametrize("form,budget", [("long", 1 << 30), ("many", 4 << 30), ("graph", 3 << 30), ("short", 1 << 30),
+                                         ("file", 1 << 29)])
+def test_images_of_sparse_states_stay_within_the_pinned_budget(form, budget):
+    """States of a dense sixteenth and zeros behind it: their images together
+    fit the pinned budget, at the states' bounds they would not, so a dump
+    that allocated at the bound would leave some of them pageable."""
+    env = dict(os.environ, MICKPT_PINNED_BUDGET=str(budget))
+    p = subprocess.run([sys.executable, "-u", os.path.join(ROOT, "tests", "pinned_room_case.py"), form], env=env,
+                       capture_output=True, text=True, timeout=100)
+    print(p.stdout[-2000:], p.stderr[-2000:], flush=True)
+    assert p.returncode == 0 and "all pinned" in p.stdout
