@@ -271,6 +271,47 @@ inline int link_grid(int T, int K, int grid) {
 // set-up and end are in that launch too.
 constexpr uint64_t kShortDump = 2048;
 
+// First chunks of the pieces of a delta's or codec dump's pipeline over nc
+// chunks of C bytes: with `ring` round slots in a staging budget that holds
+// two chunks but not all of them, else each with a place of its own. `least`:
+// the least bytes of state worth a piece; `round`: chunks that the digest pass
+// takes at a time.
+inline std::vector<uint64_t> plan_pieces(uint64_t nc, uint32_t C, uint64_t budget, bool ring, uint64_t least,
+                                         uint64_t round) {
+    const uint64_t all = nc * C;
+    std::vector<uint64_t> piece;
+    if (!ring && all < 8 * least) {
+        const uint64_t p = std::min<uint64_t>(nc, std::max<uint64_t>(1, all / least));
+        for (uint64_t i = 0; i < p; ++i) piece.push_back(nc * i / p);
+        return piece;
+    }
+    if (!ring || (all + 7) / 8 <= budget / 3) {
+        // short first pieces, so that the link starts early, and short last
+        // ones, so that little is left to copy when the last digest ends;
+        // whole rounds where a piece has some (a last round a third full costs
+        // as much as a full one)
+        // (on a ring, pieces small enough for several slots)
+        static const std::vector<uint32_t> few = {0, 2, 8, 16, 24, 30}, many = {0, 2, 6, 10, 14, 18, 22, 26, 30};
+        // (a rounded piece of a state not much longer than a round would
+        // leave no room for two)
+        if (ring && (nc / 8 + round) * C > budget / 3) round = 1;
+        for (uint32_t x : ring ? many : few) {
+            uint64_t g = nc * x / 32;
+            if (g > round) g = (g + round / 2) / round * round;
+            if (piece.empty() || (g > piece.back() && g < nc)) piece.push_back(g);
+        }
+        uint64_t most = nc - piece.back();
+        for (size_t i = 1; i < piece.size(); ++i) most = std::max(most, piece[i] - piece[i - 1]);
+        // (few long chunks: a piece of one more than its share may not leave
+        // room for two either)
+        if (!ring || 2 * most * C <= budget) return piece;
+        piece.clear();
+    }
+    const uint64_t per = std::max<uint64_t>(1, budget / 4 / C);
+    for (uint64_t g = 0; g < nc; g += per) piece.push_back(g);
+    return piece;
+}
+
 // Storage hooks. A dump told of a sink reports every payload copy into the
 // image as it is queued (segments of at most kSinkSegment bytes), so the
 // image can go to a file while the rest is still being copied; a restore

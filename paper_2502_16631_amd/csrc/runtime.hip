@@ -1041,35 +1041,15 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     bool piped = plain || ((prev != nullptr || codec) && nc > 0 && !use_graph && !na && !(per_alloc && wins.size() > 1));
     std::vector<uint64_t> piece;   // first chunks, and nc
     if (piped) {
-        const uint64_t all = nc * C, least = codec ? kCodecPiece : kDeltaPiece;
         if (plain) {
             piece.push_back(0);
             piece.push_back(std::max<uint64_t>(1, nc / kHeadShare));
         } else if (wins.size() > 1 && o && o->window_bytes) {
             for (const Window& w : wins) piece.push_back(w.g0);   // the caller's windows
-        } else if (wins.size() > 1 && ceil_div(all, 8) > c->budget / 3) {
-            const uint64_t per = std::max<uint64_t>(1, c->budget / 4 / C);
-            for (uint64_t g = 0; g < nc; g += per) piece.push_back(g);
-        } else if (wins.size() == 1 && all < 8 * least) {
-            const uint64_t p = std::min<uint64_t>(nc, std::max<uint64_t>(1, all / least));
-            for (uint64_t i = 0; i < p; ++i) piece.push_back(nc * i / p);
         } else {
-            // short first pieces, so that the link starts early, and short last
-            // ones, so that little is left to copy when the last digest ends;
-            // whole rounds of the digest pass over its groups where a piece has
-            // some (a last round a third full costs as much as a full one)
-            // (on a ring, pieces small enough for several slots)
-            static const std::vector<uint32_t> few = {0, 2, 8, 16, 24, 30},
-                                               many = {0, 2, 6, 10, 14, 18, 22, 26, 30};
-            uint64_t round = C < kScanMinChunk ? 1 : 2ull * c->num_cu * (512 / scan_width(C));
-            // (a rounded piece of a state not much longer than a round would
-            // leave no room for two)
-            if (wins.size() > 1 && (nc / 8 + round) * C > c->budget / 3) round = 1;
-            for (uint32_t x : wins.size() > 1 ? many : few) {
-                uint64_t g = nc * x / 32;
-                if (g > round) g = (g + round / 2) / round * round;
-                if (piece.empty() || (g > piece.back() && g < nc)) piece.push_back(g);
-            }
+            // whole rounds of the digest pass over its groups
+            const uint64_t round = C < kScanMinChunk ? 1 : 2ull * c->num_cu * (512 / scan_width(C));
+            piece = plan_pieces(nc, C, c->budget, wins.size() > 1, codec ? kCodecPiece : kDeltaPiece, round);
         }
         piece.push_back(nc);
         if (wins.size() > 1) {

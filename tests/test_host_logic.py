@@ -305,3 +305,39 @@ def test_chunk_kernels_that_spill(tmp_path):
     spill = {k: u["ScratchSize"] for k, u in resources("kernels.hip", tmp_path).items() if u["ScratchSize"]}
     assert {re.search(r"k_chunksILi(\d+)ELi8ELi0E", k).group(1) for k in spill} == {"512", "1024"}
     assert set(spill.values()) == {8}
+
+
+def test_pieces_on_a_ring_leave_room_for_two():
+    """The pipeline's pieces over every chunk size and budgets from two chunks
+    up: in order, without gaps, and on a ring (the state does not fit the
+    budget) never so long that two slots exceed it."""
+    so = os.path.join(ROOT, "tests", "emu", "libpiece_policy.so")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", "-I", CSRC, "-o", so,
+                           os.path.join(ROOT, "tests", "emu", "piece_policy.cpp")])
+    L = ctypes.CDLL(so)
+    L.emu_plan_pieces.restype = ctypes.c_uint64
+    L.emu_plan_pieces.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int, ctypes.c_uint64,
+                                  ctypes.c_uint64, ctypes.c_void_p, ctypes.c_uint64]
+    out = np.zeros(4096, np.uint64)
+
+    def plan(nc, c, budget, ring):
+        rnd = 1 if c < 8192 else 4096 if c <= 65536 else 512   # 256 CUs
+        n = L.emu_plan_pieces(nc, c, budget, ring, 128 << 20, rnd, out.ctypes.data, out.size)
+        return np.append(out[:min(n, out.size)], np.uint64(nc)).astype(np.int64), n
+
+    rng = np.random.default_rng(11)
+    for c in [1 << k for k in range(4, 31)]:
+        for _ in range(300):
+            budget = int(max(128 << 20, 2 * c) * np.exp(rng.uniform(0, 5)))
+            nc = budget // c + 1 + int(rng.integers(0, 1 + int(budget // c * np.exp(rng.uniform(-3, 3)))))
+            p, n = plan(nc, c, budget, 1)
+            if n > out.size:
+                continue
+            assert p[0] == 0 and (np.diff(p) > 0).all()
+            assert 2 * int(np.diff(p).max()) * c <= budget, (c, budget, nc)
+            p, n = plan(max(1, budget // c), c, budget, 0)
+            assert p[0] == 0 and (np.diff(p) > 0).all()
+    # chunks of 64 MiB in 250 MiB: pieces of two chunks would need 256
+    p, _ = plan(10, 64 << 20, 250 << 20, 1)
+    assert list(p) == list(range(11))
