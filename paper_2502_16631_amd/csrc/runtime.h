@@ -142,7 +142,7 @@ struct GraphEntry {
 
 // A resident digest table of an image: its crc[] on the device, kept for
 // later delta dumps taken against that image. While pins > 0 a request in
-// flight reads it and it is never evicted.
+// flight reads or fills it and it is never evicted.
 struct DigestEntry {
     DevBuf crc;
     uint64_t n_chunks = 0;
@@ -404,9 +404,11 @@ void make_desc(AllocDesc* d, uint64_t id, const void* ptr, uint64_t size, uint64
                uint32_t C);
 JobList one_job(const ChunkJob& j, uint32_t* ticket);
 // Room for the resident digest table of image uid, to be filled on a stream
-// before the table is used; nullptr when none is kept. digest_drop forgets a
-// table (its work queued or done).
-uint32_t* digest_reserve(ckpt_ctx* c, uint64_t uid, uint64_t nc);
+// before the table is used; nullptr when none is kept. With pin the entry is
+// pinned until digest_unpin: its buffer is not given to another table while a
+// fill that outlives this call is queued. digest_drop forgets a table (its
+// work queued or done).
+uint32_t* digest_reserve(ckpt_ctx* c, uint64_t uid, uint64_t nc, bool pin = false);
 void digest_drop(ckpt_ctx* c, uint64_t uid);
 // The resident digest table of image uid (nc chunks), or nullptr. With pin
 // the entry is pinned until digest_unpin: it stays resident while a request

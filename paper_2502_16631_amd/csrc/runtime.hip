@@ -816,14 +816,14 @@ void mk::digest_unpin(ckpt_ctx* c, uint64_t uid) {
 }
 
 // Room to keep an image's digest table resident.
-uint32_t* mk::digest_reserve(ckpt_ctx* c, uint64_t uid, uint64_t nc) {
+uint32_t* mk::digest_reserve(ckpt_ctx* c, uint64_t uid, uint64_t nc, bool pin) {
     if (!nc) return nullptr;
     if (c->digests.count(uid)) return nullptr;   // an image is dumped once; its table never changes
     // An evicted table's buffer takes the new table when it is large enough:
     // freeing device memory waits for all work on the device, which in the
     // served loop would stall every request in flight. Buffers are sized in
     // powers of two, so that more of them fit a later table. (No launch still
-    // reads a victim: tables read by requests in flight are pinned, a dump
+    // reads or fills a victim: tables of requests in flight are pinned, a dump
     // under way reserves its table after the one it reads was looked up, and
     // a plain dump has finished before its call returns.)
     DevBuf spare;
@@ -848,6 +848,7 @@ uint32_t* mk::digest_reserve(ckpt_ctx* c, uint64_t uid, uint64_t nc) {
     }
     de.n_chunks = nc;
     de.last_use = ++c->use_clock;
+    de.pins = pin;
     return de.crc.as<uint32_t>();
 }
 

@@ -144,6 +144,7 @@ struct Req {
     std::vector<AllocDesc> d;
     const uint32_t* prev_dev = nullptr;
     uint64_t prev_pinned = 0;  // uid of the resident digest table pinned for this request, or 0
+    uint64_t out_pinned = 0;   // dump: uid of the table that its last launch fills, pinned until it is done, or 0
     uint32_t prev_digest = 0;
     ImageView v;               // restore: the image
     // progress
@@ -213,6 +214,10 @@ void finish(ckpt_server* s, Req* r, int rc) {
     if (r->prev_pinned) {
         digest_unpin(s->ctx, r->prev_pinned);   // no launch of the request reads it any more
         r->prev_pinned = 0;
+    }
+    if (r->out_pinned) {
+        digest_unpin(s->ctx, r->out_pinned);   // filled
+        r->out_pinned = 0;
     }
     if (rc != CKPT_OK && r->out) {
         ckpt_image_free(r->out);
@@ -757,7 +762,12 @@ void progress_dump(ckpt_server* s, Req* r) {
         fj.c.mode = kCombineWrite;
         fj.add_copy(tdst + 32ull * r->n, crc_dev, 4 * r->nc);
         fj.add_copy(tdst + len_a, L.kinds.p, len_b);
-        if (uint32_t* resident = digest_reserve(c, r->out->uid, r->nc)) fj.add_copy(resident, crc_dev, 4 * r->nc);
+        // pinned: other calls on the context may need room for tables before
+        // this launch runs, on other streams
+        if (uint32_t* resident = digest_reserve(c, r->out->uid, r->nc, true)) {
+            r->out_pinned = r->out->uid;
+            fj.add_copy(resident, crc_dev, 4 * r->nc);
+        }
         fj.rep = reinterpret_cast<uint64_t*>(L.hs + 8 * (r->W + 1));
         fj.rep_src = reinterpret_cast<uint64_t*>(L.ctl.as<uint8_t>() + 16 * (r->W + 2));   // error word (and zeros)
         fj.n_rep = 1;

@@ -168,3 +168,62 @@ def test_pageable_images_through_host_workers(ctx):
             assert rc == 0 and np.array_equal(img.view(), base[k].view())
     finally:
         del os.environ["MICKPT_HOST_PAGEABLE"]
+
+
+def test_plain_dumps_beside_served_ones_keep_both_digest_tables():
+    """Served dumps whose last launches are queued behind long copies, beside
+    plain dumps on the same context, more than the resident digest tables it
+    keeps: no table's buffer passes on while its fill is queued, so every
+    image's later delta finds exactly the chunk rewritten since."""
+    import threading
+    ctx = mk.ckpt_ctx_create(0, 4 << 30)
+    srv = mk.ckpt_serve_create(ctx)
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    served = [[(i, torch.randint(1, 256, (48 << 20,), dtype=torch.uint8, device="cuda", generator=gen))]
+              for i in range(16)]
+    small = [[(100 + i, torch.randint(1, 256, (1 << 20,), dtype=torch.uint8, device="cuda", generator=gen))]
+             for i in range(4)]
+    opts = mk.make_opts(chunk_size=2048)   # 512 chunks
+    got, stop = [], threading.Event()
+
+    def plain():
+        k = 0
+        while not stop.is_set():
+            table = small[k % len(small)]
+            rc, img, _ = mk.ckpt_dump(ctx, table, opts=opts)
+            assert rc == 0
+            got.append((img, table))
+            if len(got) > 200:
+                got.pop(0)
+            k += 1
+
+    try:
+        th = threading.Thread(target=plain)
+        th.start()
+        for rep in range(6):
+            tickets = [mk.ckpt_serve_submit(srv, mk.REQ_DUMP, t, tenant=i)[1] for i, t in enumerate(served)]
+            mk.ckpt_serve_drain(srv)
+            images = []
+            for x in tickets:
+                done, rc, img, _ = mk.ckpt_serve_poll(srv, x)
+                assert done and rc == 0
+                images.append(img)
+            for img, t in zip(images, served):
+                t[0][1][5 * 65536] ^= 1
+                torch.cuda.synchronize()
+                rc, delta, res = mk.ckpt_dump(ctx, t, prev=img, opts=mk.make_opts(chunk_size=65536))
+                assert rc == 0 and (res.n_data, res.n_unchanged) == (1, res.n_chunks - 1)
+                delta.free()
+                img.free()
+        stop.set()
+        th.join()
+        assert len(got) > 130
+        for img, t in got:
+            rc, delta, res = mk.ckpt_dump(ctx, t, prev=img, opts=opts)
+            assert rc == 0 and (res.n_data, res.n_unchanged) == (0, res.n_chunks)
+            delta.free()
+    finally:
+        stop.set()
+        th.join()
+        mk.ckpt_serve_destroy(srv)
+        mk.ckpt_ctx_destroy(ctx)
