@@ -473,3 +473,28 @@ def test_images_of_sparse_states_stay_within_the_pinned_budget(form, budget):
                        capture_output=True, text=True, timeout=100)
     print(p.stdout[-2000:], p.stderr[-2000:], flush=True)
     assert p.returncode == 0 and "all pinned" in p.stdout
+
+
+@pytest.mark.parametrize("c,chunks", [(1024, 506), (1024, 507), (65536, 321), (65536, 322)])
+def test_short_restores_at_the_limits_of_one_launch(ctx, c, chunks):
+    """The last restores that are one launch and the first that are not (512
+    chunks and allocations; 20 MiB), with every check's damage; which it was
+    shows in the report (one launch is its kernel time as the host sees it)."""
+    test_short_restores_in_one_launch(ctx, c, chunks)
+    sizes = [0, 1, c + 15, 0, 3 * c, (chunks - 6) * c - 1]
+    table = [(i, torch.ones(n, dtype=torch.uint8, device="cuda")) for i, n in enumerate(sizes)]
+    rc, img, _ = mk.ckpt_dump(ctx, table, opts=mk.make_opts(chunk_size=c))
+    assert rc == 0
+    rc, res = mk.ckpt_restore(ctx, img, table)
+    assert rc == 0 and res.n_chunks == chunks
+    one = chunks + len(sizes) <= 512 and sum(sizes) <= 20 << 20
+    assert one == (chunks in (506, 321))
+    assert (res.ns_stage[3] == res.ns_link) == one
+    img.free()
+
+
+@pytest.mark.parametrize("chunks", [321, 322])
+def test_short_dumps_at_the_limit_of_kernels_on_the_link(ctx, chunks):
+    """The last size that kernels write to the image themselves (20 MiB) and
+    the first that a copy engine does."""
+    test_short_dumps_in_one_launch(ctx, 65536, chunks)
