@@ -17,7 +17,7 @@ __device__ inline void copy_part(const GatherJob& j, uint64_t g, uint32_t lo, ui
     const uint64_t nk = (ad->size + C - 1) / C;
     const uint32_t len = (k + 1 == nk) ? ad->tail_len : C;
     const uint4* src = reinterpret_cast<const uint4*>(ad->ptr + k * C);
-    uint4* dst = reinterpret_cast<uint4*>(j.slot + (j.off[g] - j.slot_base));
+    uint4* dst = reinterpret_cast<uint4*>(j.slot + j.off[g]);
     const uint32_t full = (hi < len ? hi : len) / 16, rem = len % 16;
 #pragma unroll 4
     for (uint32_t i = lo / 16 + tid; i < full; i += NT) dst[i] = src[i];
@@ -34,25 +34,18 @@ __device__ inline void copy_part(const GatherJob& j, uint64_t g, uint32_t lo, ui
 // of 256 KiB took 33 us. From the list and in parts they spread over the chip.
 __global__ void __launch_bounds__(NT) k_gather(GatherJob j) {
     if (j.stamp && blockIdx.x == 0 && threadIdx.x == 0) *j.stamp = wall_clock64();
-    const uint32_t C = j.C;
-    if (j.list) {
-        const uint32_t parts = C > kGatherPart ? C / kGatherPart : 1, len = C / parts;
-        const uint64_t items = *j.n_list * parts;
-        for (uint64_t i = blockIdx.x; i < items; i += gridDim.x) {
-            const uint32_t p = (uint32_t)(i % parts);
-            copy_part(j, j.list[i / parts], p * len, (p + 1) * len);
-        }
-        return;
+    const uint32_t C = j.C, parts = C > kGatherPart ? C / kGatherPart : 1, len = C / parts;
+    const uint64_t items = *j.n_list * parts;
+    for (uint64_t i = blockIdx.x; i < items; i += gridDim.x) {
+        const uint32_t p = (uint32_t)(i % parts);
+        copy_part(j, j.list[i / parts], p * len, (p + 1) * len);
     }
-    for (uint64_t g = j.g0 + blockIdx.x; g < j.g1; g += gridDim.x)
-        if (j.kind[g] == kData) copy_part(j, g, 0, C);   // the same on every lane
 }
 
 }  // namespace
 
 hipError_t launch_gather(const GatherJob& j, int grid, hipStream_t s) {
-    if (!j.amap || grid < 1) return hipErrorInvalidValue;
-    if (j.g1 <= j.g0) return hipSuccess;
+    if (!j.amap || !j.list || !j.n_list || grid < 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_gather, dim3(grid), dim3(NT), 0, s, j);
     return hipGetLastError();
 }

@@ -57,7 +57,7 @@ struct JobList {
     uint32_t pad;
 };
 
-// Payload offsets of every chunk from the kind table (restore).
+// Payload offsets of every chunk of a range from the kind table.
 struct OffJob {
     const AllocDesc* allocs;
     uint32_t n_allocs;
@@ -66,9 +66,7 @@ struct OffJob {
     uint64_t n_chunks;
     const uint8_t* kind;
     uint64_t* off;               // [n_chunks]
-    uint64_t per_window;         // chunks per staging window G
-    uint64_t* wb;                // [W + 1] payload offset at each window start, wb[W] = total
-    uint64_t n_windows;          // W
+    uint64_t* total;             // payload bytes of the range, or nullptr
     uint64_t* status;            // look-back, one word per tile
     uint32_t* ticket;
     unsigned long long* counts;  // [4]: zero, data, unchanged, invalid (zeroed before launch)
@@ -81,7 +79,7 @@ struct OffJob {
     uint64_t* status2;           // look-back of the list positions (with list), one word per tile
     uint64_t* stamp;             // k_offsets: device clock at the kernel's start, or nullptr
     uint64_t g_base;             // the scan covers global chunks [g_base, g_base + n_chunks); off, kind
-                                 // and amap are indexed globally, windows and wb relative to g_base
+                                 // and amap are indexed globally
 };
 
 // Per-allocation combine of chunk digests into the whole-allocation CRC.

@@ -1105,8 +1105,7 @@ __device__ inline void offsets_wg(const OffJob& job) {
             *job.n_list = s_pos + s_wcnt[0] + s_wcnt[1] + s_wcnt[2] + s_wcnt[3];
         if (g < job.n_chunks) {
             job.off[gg] = o;
-            if (g % job.per_window == 0) job.wb[g / job.per_window] = o;
-            if (g + 1 == job.n_chunks) job.wb[job.n_windows] = o + plen;
+            if (g + 1 == job.n_chunks && job.total) *job.total = o + plen;
         }
     }
 }

@@ -425,11 +425,8 @@ struct DigestPlan {
     uint8_t* base = nullptr;
     uint64_t off_crc = 0, off_out = 0, off_tk = 0;
 };
-// ec: the engine constants for the digest tile (T 256, C 16 KiB), or nullptr
-// to take them from the context's cache.
 hipError_t digest_prepare(ckpt_ctx* c, DevBuf* dig, const uint8_t* recs_crc, uint64_t len_a,
-                          const uint8_t* kinds_pad, uint64_t len_b, DigestPlan* p, hipStream_t s,
-                          const EngineConsts* ec = nullptr);
+                          const uint8_t* kinds_pad, uint64_t len_b, DigestPlan* p, hipStream_t s);
 hipError_t digest_enqueue(ckpt_ctx* c, const DigestPlan& p, uint32_t* out_host, hipStream_t s);
 
 }  // namespace mk

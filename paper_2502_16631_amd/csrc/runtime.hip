@@ -4,21 +4,29 @@
 // Dump of one table (paper section 3.1.1, checkpoint action):
 //   1. descriptors: per allocation the first chunk, the tail constants and
 //      the matching allocation of the previous image;
-//   2. per staging window (a range of whole chunks): one launch of the chunk
-//      engine in dump mode -- CRC, zero / unchanged test, look-back offsets
-//      and the gather into the window, in a single read of the data;
-//   3. the window's payload length is read back and the window is copied to
-//      the pinned image on a side stream while the next window is processed;
-//   4. per-allocation CRCs (combine), table digests, tables copied out,
-//      header written on the host.
+//   2. set-up in one launch: descriptors, chunk map, cleared words;
+//   3. a full dump: per staging window (a range of whole chunks) one launch of
+//      the chunk engine in dump mode -- CRC, zero test, look-back offsets and
+//      the gather into the window, in a single read of the data; a delta or
+//      codec dump: per piece the digest pass, the offsets scan, gather and
+//      encode;
+//   4. a window's or piece's payload length comes to pinned host memory, and its
+//      copy-out runs on a side stream beside the next one's launches;
+//   5. the end in one launch: per-allocation CRCs (combine) and the tables into
+//      the image; their digest and the header are made on the host.
+// A short full dump of whole tiles is one launch, which writes the image itself.
 // Restore (section 3.1.1, restore action; section 6, deterministic restore):
-//   1. header checked on the host; tables uploaded and their digest checked;
-//      payload offsets of every chunk from a scan of the kinds;
-//   2. a delta first verifies that every UNCHANGED chunk of the target holds
+//   1. header, tables and their digest checked on the host;
+//   2. tables up, payload offsets of every chunk from a scan of the kinds, and
+//      the per-allocation CRC check;
+//   3. a delta first verifies that every UNCHANGED chunk of the target holds
 //      the recorded digest (before anything is written);
-//   3. per window: the payload slice is copied to a staging window on a side
-//      stream, then scattered to the allocations and verified;
-//   4. per-allocation CRCs are checked.
+//   4. per window or part: the payload goes to staging on a side stream, then
+//      is scattered to the allocations and verified; a short payload of a
+//      pinned image is read where it is.
+// A short full restore of whole tiles from a pinned image is one launch. The
+// batched form of a pageable image is a captured graph that checks the tables
+// on the device.
 #include <hip/hip_runtime.h>
 #include <string.h>
 #include <sys/mman.h>
@@ -746,13 +754,11 @@ extern "C" void ckpt_ctx_destroy(ckpt_ctx* c) {
 // virtual descriptors; digest_enqueue only launches kernels and one D2H copy
 // (so a captured graph can hold it).
 hipError_t mk::digest_prepare(ckpt_ctx* c, DevBuf* dig, const uint8_t* recs_crc, uint64_t len_a,
-                              const uint8_t* kinds_pad, uint64_t len_b, DigestPlan* p, hipStream_t s,
-                              const EngineConsts* ec) {
+                              const uint8_t* kinds_pad, uint64_t len_b, DigestPlan* p, hipStream_t s) {
     const uint32_t Cd = 16384;
     pick_tile(Cd, 0, &p->T, &p->K);
-    hipError_t e = hipSuccess;
-    if (ec) p->ec = ec;
-    else if ((e = get_consts(c, p->T, Cd, &p->ec)) != hipSuccess) return e;
+    hipError_t e = get_consts(c, p->T, Cd, &p->ec);
+    if (e != hipSuccess) return e;
     AllocDesc hd[2];
     const uint64_t nk_a = ceil_div(len_a, Cd), nk_b = ceil_div(len_b, Cd);
     make_desc(&hd[0], 0, recs_crc, len_a, 0, kNoChunk, Cd);
@@ -1295,29 +1301,10 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     uint64_t pos = 0, t_link0 = 0, kern_ns = 0;
     hipError_t e = hipSuccess;
     const uint64_t len_a = 32ull * n + 4 * nc, len_b = tl - len_a - rl_bytes;
-    // A delta dump in one window takes three passes per piece (launch_delta):
-    // digests and kinds, the payload offsets (scan over the kinds), then the
-    // DATA chunks gathered to their records. A delta's kinds depend on the
-    // digests, so a single pass would hold every chunk's look-back until its
-    // digest is done; its payload is small, so the extra read of D costs
-    // little.
-    // the DATA chunks of [g0, g1) to their records at c->off, in staging
-    // from sp on, which holds the payload from offset base
-    auto gather_job = [&](uint64_t g0, uint64_t g1, uint8_t* sp, uint64_t base) {
-        GatherJob gj;
-        memset(&gj, 0, sizeof(gj));
-        gj.allocs = B.descs->as<AllocDesc>();
-        gj.amap = B.amap->as<uint32_t>();
-        gj.g0 = g0;
-        gj.g1 = g1;
-        gj.C = C;
-        gj.kind = kind_dev;
-        gj.off = B.off->as<uint64_t>();
-        gj.slot = sp;
-        gj.slot_base = base;
-        return gj;
-    };
-    // A delta or codec dump runs as a pipeline over its pieces. On the main
+    // A delta or codec dump runs as a pipeline over its pieces, in three passes
+    // per piece: a delta's kinds depend on the digests, so a single pass would
+    // hold every chunk's look-back until its digest is done; its payload is
+    // small, so the extra read of D costs little. On the main
     // stream, per piece: digests and kinds (classify; codec: record lengths,
     // DATA becoming PACKED where the record is shorter), the piece's payload
     // offsets relative to its own start (scan), and its DATA chunks gathered
@@ -1399,9 +1386,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         oj.g_base = g0;
         oj.kind = kind_dev;
         oj.off = B.off->as<uint64_t>();
-        oj.per_window = g1 - g0 + 1;
-        oj.wb = hw + kHwWords + 2 * i;   // pinned: the piece's length in the second word
-        oj.n_windows = 1;
+        oj.total = hw + kHwWords + 2 * i + 1;   // pinned
         oj.status = B.status->words();
         oj.ticket = tickets + 2 * i + 1;
         oj.counts = counts;
@@ -1418,7 +1403,13 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             return e;
         uint8_t* sp = gather_direct ? himg + kHeader + tl
                                     : B.staging->as<uint8_t>() + (ring ? (i % nslots) * slot : g0 * C);
-        GatherJob gj = gather_job(g0, g1, sp, 0);
+        GatherJob gj;
+        memset(&gj, 0, sizeof(gj));
+        gj.allocs = j.allocs;
+        gj.amap = j.amap;
+        gj.C = C;
+        gj.off = oj.off;
+        gj.slot = sp;
         gj.list = oj.list;
         gj.n_list = oj.n_list;
         gj.stamp = st ? st + 2 : nullptr;
@@ -2080,7 +2071,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     HIPCHK(c->kinds.ensure(tl + 16));
     HIPCHK(c->off.ensure(8 * std::max<uint64_t>(nc, 1)));
     if (codec) HIPCHK(c->rlen.ensure(4 * std::max<uint64_t>(nc, 1)));
-    HIPCHK(c->wb.ensure(8 * (W + 2)));
+    if (use_graph) HIPCHK(c->wb.ensure(8));
     if (!direct) HIPCHK(c->staging.ensure(staged ? v.D : (uint64_t)nslots * slot));
     const uint64_t tiles = ceil_div(nc, 256) + 64;   // look-back words of the offsets scan, twice
     HIPCHK(c->status.ensure(16 * tiles, c->s_main));
@@ -2208,9 +2199,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             oj.n_chunks = nc;
             oj.kind = kind_dev;
             oj.off = c->off.as<uint64_t>();
-            oj.per_window = nc + 1;
-            oj.wb = c->wb.as<uint64_t>();
-            oj.n_windows = 1;
+            oj.total = c->wb.as<uint64_t>();
             oj.status = ge->status.as<uint64_t>();
             oj.ticket = ticket;
             oj.counts = counts;
@@ -2222,7 +2211,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             gj.dig = reinterpret_cast<const uint32_t*>(dp.base + dp.off_out);
             gj.xlen = xpow8(len_b);
             gj.counts = counts;
-            gj.total = c->wb.as<uint64_t>() + 1;
+            gj.total = c->wb.as<uint64_t>();
             gj.n_chunks = nc;
             gj.expect = prm;
             gj.gate = gflag;
@@ -2263,7 +2252,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             cj.mode = kCombineCheck;
             step(launch_combine(cj, c->s_main));
             step(hipMemcpyAsync(hq, counts, 64, hipMemcpyDeviceToHost, c->s_main));   // counts, bad, bad2, err, bad3
-            step(hipMemcpyAsync(hg, c->wb.as<uint64_t>() + 1, 8, hipMemcpyDeviceToHost, c->s_main));
+            step(hipMemcpyAsync(hg, c->wb.as<uint64_t>(), 8, hipMemcpyDeviceToHost, c->s_main));
             step(hipMemcpyAsync(hg + 1, gflag, 4, hipMemcpyDeviceToHost, c->s_main));
             hipError_t ee = hipStreamEndCapture(c->s_main, &graph);
             if (ce == hipSuccess) ce = ee;
@@ -2513,9 +2502,6 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         oj.n_chunks = nc;
         oj.kind = kind_dev;
         oj.off = c->off.as<uint64_t>();
-        oj.per_window = nc + 1;
-        oj.wb = c->wb.as<uint64_t>();
-        oj.n_windows = 1;
         oj.status = c->status.words();
         oj.ticket = ticket;
         oj.counts = counts;

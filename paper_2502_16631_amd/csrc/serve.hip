@@ -58,7 +58,7 @@ constexpr uint64_t kTaskFailed = ~0ull;
 constexpr uint64_t kCopyPiece = 64ull << 20;
 
 struct Lane {
-    DevBuf descs, arc, kinds, ctl, off, wb, staging, prevcrc, amap;
+    DevBuf descs, arc, kinds, ctl, off, staging, prevcrc, amap;
     StatusBuf status;
     AllocDesc* hd = nullptr;   // pinned: the request's descriptors, which the set-up kernel reads
     uint64_t hd_cap = 0;
@@ -113,7 +113,7 @@ struct Lane {
         return hipSuccess;
     }
     void release() {
-        DevBuf* b[] = {&descs, &arc, &kinds, &ctl, &off, &wb, &staging, &prevcrc, &amap};
+        DevBuf* b[] = {&descs, &arc, &kinds, &ctl, &off, &staging, &prevcrc, &amap};
         for (DevBuf* x : b) x->release();
         status.release();
         for (hipEvent_t e : ev) hipEventDestroy(e);
@@ -511,7 +511,6 @@ void admit_restore(ckpt_server* s, Req* r) {
     SCHK(L.arc.ensure(v.tl + 16));
     SCHK(L.kinds.ensure(v.tl + 16));
     SCHK(L.off.ensure(8 * std::max<uint64_t>(v.n_chunks, 1)));
-    SCHK(L.wb.ensure(16));
     SCHK(L.status.ensure(8 * (ceil_div(v.n_chunks, 256) + 64), s->s_rest));
     // ctl: [0] offsets ticket | [8] counts[4] | [40] bad | [48] bad2 | [56] err
     SCHK(L.ctl.ensure(64));
@@ -555,9 +554,6 @@ void admit_restore(ckpt_server* s, Req* r) {
         oj.n_chunks = v.n_chunks;
         oj.kind = L.kinds.as<uint8_t>();
         oj.off = L.off.as<uint64_t>();
-        oj.per_window = v.n_chunks + 1;
-        oj.wb = L.wb.as<uint64_t>();
-        oj.n_windows = 1;
         oj.status = L.status.words();
         oj.ticket = reinterpret_cast<uint32_t*>(ctl);
         oj.counts = reinterpret_cast<unsigned long long*>(ctl + 8);
