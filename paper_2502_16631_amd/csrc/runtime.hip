@@ -1145,7 +1145,8 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         prev_dev = digest_lookup(c, prev->uid, pv.n_chunks);
         if (!prev_dev) {
             HIPCHK(B.prevcrc->ensure(4 * pv.n_chunks));
-            if (prev->pinned && !use_graph) sj.add_copy(B.prevcrc->p, pv.crcs, 4 * pv.n_chunks);
+            if (prev->pinned && !use_graph && 4 * pv.n_chunks <= kLinkBytes)
+                sj.add_copy(B.prevcrc->p, pv.crcs, 4 * pv.n_chunks);
             else HIPCHK(hipMemcpyAsync(B.prevcrc->p, pv.crcs, 4 * pv.n_chunks, hipMemcpyHostToDevice, c->s_main));
             prev_dev = B.prevcrc->as<uint32_t>();
         }
@@ -1664,9 +1665,10 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
     uint64_t D = pos;   // (a direct dump's comes with the results)
     if (!alloc_image(D)) return fail(hipErrorOutOfMemory);   // a table without chunks
     // The end, in one launch: per-allocation CRCs to AllocRec[], the tables
-    // into the image (a pageable one takes them by copies), the digest table
+    // into the image (a pageable one, and tables longer than kernels move over
+    // the link, by copies), the digest table
     // to its resident place, the results.
-    const bool tables_direct = na ? host_tables : im->pinned;
+    const bool tables_direct = (na ? host_tables : im->pinned) && tl <= kLinkBytes;
     uint8_t* htab = himg + kHeader;
     if (timing && !use_graph && (e = hipEventRecord(c->sev[2], c->s_main)) != hipSuccess) return fail(e);
     const uint32_t rep_words =
@@ -2478,7 +2480,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     sj.add_fill(err, 2, 0);
     sj.add_fill(bad3, 4, ~0u);   // bad3, bas
     sj.add_fill(bgate, 2 + 8 + W + 2, 0);   // and the stamps and tickets
-    if (img->pinned) {
+    if (img->pinned && tl <= kLinkBytes) {
         sj.add_copy(c->arc.p, v.recs, len_a);
         sj.add_copy(kind_dev, v.kinds, len_b);
         if (codec) sj.add_copy(c->rlen.p, v.rlens, 4 * nc);

@@ -415,9 +415,10 @@ def test_long_calls_leave_other_streams_their_speed(ctx, mib, call):
     assert len(calls) > 1 and beside <= 4 * alone
 
 
-@pytest.mark.parametrize("c,zero_mib", [(16, 1), (512, 1), (1024, 1), (1024, 100), (2048, 1)])
+@pytest.mark.parametrize("c,zero_mib", [(16, 1), (512, 1), (1024, 1), (1024, 100), (2048, 1), (16, 70)])
 def test_small_chunks_from_pinned_and_pageable_images(ctx, c, zero_mib):
-    """Chunk sizes on both sides of the least that kernels read over the link."""
+    """Chunk sizes on both sides of the least that kernels read over the link
+    (16 bytes, 70 MiB: tables longer than kernels move)."""
     test_restores_from_pinned_and_pageable_images(ctx, c, zero_mib, 0)
 
 
