@@ -1319,8 +1319,8 @@ __device__ inline void stream_tables(uint32_t* s_dt, const EngineConsts* ec) {
 // Short full dump, C = 16 T K, to a pinned image, set-up and end included.
 // Bound by latencies and the host link. As three launches (set-up, chunks,
 // end) a dump of 16 chunks of 64 KiB took 59 us inside the call, 18 of them
-// for its payload on the link; here 39 (64 of 64 KiB: 125 -> 104, 384: 515 ->
-// 487). The chunks' entries come over the link in one read each, and the end
+// for its payload on the link; here 39 (64 of 64 KiB: 125 -> 104, 256: 351 ->
+// 334). The chunks' entries come over the link in one read each, and the end
 // (the tables, the allocations' digests) runs while the payload drains, which
 // is why the payload is stored after the digest. A chunk's
 // work-group waits only for words that holders of lower tickets publish before

@@ -1098,7 +1098,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         for (uint64_t i = 0; i < n_pieces; ++i) max_win = std::max(max_win, 2 * ceil_div(piece[i + 1] - piece[i], 256));
     // A short dump of whole tiles runs as one launch if the image takes the
     // payload (below): 20 us less than three at any size up to there (256
-    // KiB: 41 against 27, 24 MiB: 515 against 487; small chunks too, 1 MiB in
+    // KiB: 41 against 27, 16 MiB: 351 against 334; small chunks too, 1 MiB in
     // 4 KiB: 71 against 47). Its work-groups read every predecessor's word, so
     // more chunks are left to the look-back.
     bool one_launch = small && C == 16ull * T * K && T >= 64 && nc + n <= kShortDump;
