@@ -2693,9 +2693,13 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     }
     for (uint64_t w = 0; w < W && !merged; ++w) {
         const int s = (int)(w % nslots);
-        // parts and the codec's windows go up one after another: two uploads at
-        // a time end together, a window later than one at a time
-        hipStream_t cs = c->s_copy[staged || tail || (codec && !(o && o->copy_streams)) ? 0 : w % ncs];
+        // parts and windows with places of their own go up one after another: two
+        // uploads at a time end together, a window later than one at a time; on
+        // a ring one stream would stand still whenever it waits for a slot (740
+        // MiB as codec windows of 16 MiB: 11.97 against 11.25 ms)
+        const bool own = staged || tail;
+        hipStream_t cs =
+            c->s_copy[own || (codec && W <= (uint64_t)nslots && !(o && o->copy_streams)) ? 0 : w % ncs];
         const uint64_t len = wend[w] - wbeg[w];
         if (gate && !gate->wait(kHeader + tl + wend[w])) {
             // the image's file could not be read: let queued work finish
@@ -2705,7 +2709,6 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
         }
         ChunkJob j = restore_job(w);
         if (!direct) {
-            const bool own = staged || tail;   // a place of its own in staging
             uint8_t* sp = c->staging.as<uint8_t>() + (own ? wbeg[w] : (uint64_t)s * slot);
             if (slot_used[s] && !own) HIPCHK(hipStreamWaitEvent(cs, ev[W + s], 0));
             slot_used[s] = true;

@@ -264,3 +264,33 @@ def test_served_loop_rejects_codec_images_and_takes_plain_ones(ctx):
         assert rc == 0 and np.array_equal(got["delta"][1].view(), want)
     finally:
         mk.ckpt_serve_destroy(srv)
+
+
+def test_small_codec_windows_restore_at_the_rate_of_two_streams():
+    """A codec restore through windows on a ring of slots takes what it takes
+    with two copy streams asked for (on one stream each upload waits out the
+    slot before it: 7 % more)."""
+    import statistics
+    import time
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    table = [(i, torch.randint(1, 256, (37 << 20,), dtype=torch.uint8, device="cuda", generator=gen)) for i in range(20)]
+    for _, t in table:
+        t[::2] &= 15
+    ctx = mk.ckpt_ctx_create(0, 4 << 30)
+    try:
+        rc, img, _ = mk.ckpt_dump(ctx, table, opts=mk.make_opts(flags=mk.OPT_CODEC))
+        assert rc == 0
+        times = {0: [], 2: []}
+        for rep in range(18):
+            for n in times:
+                opts = mk.make_opts(window_bytes=16 << 20, copy_streams=n)
+                t0 = time.perf_counter()
+                rc, res = mk.ckpt_restore(ctx, img, table, opts=opts)
+                if rep >= 3:
+                    times[n].append(time.perf_counter() - t0)
+                assert rc == 0 and res.windows == 47
+        a, b = (statistics.median(times[n]) for n in (0, 2))
+        print("default %.2f ms, two streams %.2f ms" % (a * 1e3, b * 1e3), flush=True)
+        assert a <= 1.04 * b
+    finally:
+        mk.ckpt_ctx_destroy(ctx)
