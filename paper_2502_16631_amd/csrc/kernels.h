@@ -209,12 +209,15 @@ struct GateJob {
 };
 
 // Digest pass over whole memory (classify and verify of chunks of at least
-// kScanMinChunk bytes): group width T of the engine constants for chunk size
-// C, and the launch. job.ec must hold the constants for (scan_width(C), C);
-// cus: CUs the launch may fill.
+// kScanMinChunk bytes): group width T of the engine constants for so many
+// chunks of C bytes, and the launch. job.ec must hold the constants for (T, C);
+// cus: CUs the launch may fill. A wave takes 20 us for a chunk of 64 KiB by
+// itself, a work-group of eight less: while there are chunks for a quarter of
+// the waves at most, that counts (16 MiB: 30 us by waves, 12 by work-groups; 64
+// MiB, 1024 chunks: 32 and 25; 128 MiB 38 and 42).
 constexpr uint32_t kScanMinChunk = 8192;
-inline int scan_width(uint32_t C) { return C <= 65536 ? 64 : 512; }
-hipError_t launch_scan(bool verify, const JobList& jl, int cus, hipStream_t s);
+inline int scan_width(uint32_t C, uint64_t chunks) { return C > 65536 || (C == 65536 && chunks <= 1024) ? 512 : 64; }
+hipError_t launch_scan(bool verify, int T, const JobList& jl, int cus, hipStream_t s);
 
 bool tile_supported(int T, int K);
 hipError_t launch_setup(const SetupJob& job, hipStream_t s);

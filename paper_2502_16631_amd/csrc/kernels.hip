@@ -1634,14 +1634,14 @@ hipError_t launch_short_restore(int T, int K, const ShortRestoreJob& job, hipStr
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_scan(bool verify, const JobList& jl, int cus, hipStream_t s) {
-    if (jl.n_jobs < 1 || jl.n_jobs > (uint32_t)kMaxJobs || cus < 1 || jl.job[0].C < kScanMinChunk)
+hipError_t launch_scan(bool verify, int T, const JobList& jl, int cus, hipStream_t s) {
+    if (jl.n_jobs < 1 || jl.n_jobs > (uint32_t)kMaxJobs || cus < 1 || (T != 64 && T != 512) ||
+        jl.job[0].C < 128u * T)   // a batch of eight rows
         return hipErrorInvalidValue;
     const uint64_t total = jl.prefix[jl.n_jobs];
     if (total == 0) return hipSuccess;
     if (!verify && (jl.n_jobs != 1 || total > 0xFFFFFFFFull)) return hipErrorInvalidValue;
     // two work-groups per CU (128 registers a lane)
-    const int T = scan_width(jl.job[0].C);
     const uint64_t wgs = T == 64 ? (total + 7) / 8 : total;
     const unsigned grid = (unsigned)(wgs < 2ull * cus ? wgs : 2ull * cus);
     if (T == 64) {

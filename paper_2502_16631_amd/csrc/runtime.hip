@@ -587,8 +587,9 @@ JobList one_job(const ChunkJob& j, uint32_t* ticket) {
 hipError_t launch_classify(ckpt_ctx* c, int T, int K, ChunkJob j, uint32_t* ticket, hipStream_t s) {
     hipError_t e;
     if (j.C >= kScanMinChunk) {
-        if ((e = get_consts(c, scan_width(j.C), j.C, &j.ec)) != hipSuccess) return e;
-        return launch_scan(false, one_job(j, ticket), c->num_cu, s);
+        const int w = scan_width(j.C, j.g1 - j.g0);
+        if ((e = get_consts(c, w, j.C, &j.ec)) != hipSuccess) return e;
+        return launch_scan(false, w, one_job(j, ticket), c->num_cu, s);
     }
     int grid;
     if ((e = grid_for(c, T, K, kModeClassify, j.g1 - j.g0, &grid)) != hipSuccess) return e;
@@ -601,9 +602,10 @@ hipError_t launch_verify(ckpt_ctx* c, int T, int K, JobList& jl, int cus, hipStr
     hipError_t e;
     if (C >= kScanMinChunk) {
         const EngineConsts* ec;
-        if ((e = get_consts(c, scan_width(C), C, &ec)) != hipSuccess) return e;
+        const int w = scan_width(C, jl.prefix[jl.n_jobs]);
+        if ((e = get_consts(c, w, C, &ec)) != hipSuccess) return e;
         for (uint32_t i = 0; i < jl.n_jobs; ++i) jl.job[i].ec = ec;
-        return launch_scan(true, jl, cus, s);
+        return launch_scan(true, w, jl, cus, s);
     }
     int grid;
     if ((e = grid_for(c, T, K, kModeVerify, jl.prefix[jl.n_jobs], &grid)) != hipSuccess) return e;
@@ -1055,7 +1057,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
             for (const Window& w : wins) piece.push_back(w.g0);   // the caller's windows
         } else {
             // whole rounds of the digest pass over its groups
-            const uint64_t round = C < kScanMinChunk ? 1 : 2ull * c->num_cu * (512 / scan_width(C));
+            const uint64_t round = C < kScanMinChunk ? 1 : 2ull * c->num_cu * (512 / scan_width(C, nc));
             piece = plan_pieces(nc, C, c->budget, wins.size() > 1, codec ? kCodecPiece : kDeltaPiece, round);
         }
         piece.push_back(nc);
@@ -2172,7 +2174,7 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
             int grid;
             if ((e = grid_for(c, T, K, kModeRestore, nc, &grid)) != hipSuccess) return drop(e);
             const EngineConsts* sec;   // of the strict re-read: made before the capture
-            if (C >= kScanMinChunk && (e = get_consts(c, scan_width(C), C, &sec)) != hipSuccess) return drop(e);
+            if (C >= kScanMinChunk && (e = get_consts(c, scan_width(C, nc), C, &sec)) != hipSuccess) return drop(e);
             int vgrid;
             if (C < kScanMinChunk && (e = grid_for(c, T, K, kModeVerify, nc, &vgrid)) != hipSuccess) return drop(e);
             // the digest plan's small tables are prepared; nothing of it is captured

@@ -499,3 +499,38 @@ def test_short_dumps_at_the_limit_of_kernels_on_the_link(ctx, chunks):
     """The last size that kernels write to the image themselves (20 MiB) and
     the first that a copy engine does."""
     test_short_dumps_in_one_launch(ctx, 65536, chunks)
+
+
+@pytest.mark.parametrize("chunks", [1, 300, 1023, 1024, 1025, 1300])
+def test_digest_pass_by_work_groups_and_by_waves(ctx, chunks):
+    """Deltas of 64 KiB chunks on both sides of the count from which the digest
+    pass gives a chunk to a wave: digests, kinds and payload against the
+    oracle, the base check's lowest differing chunk, and the strict re-read."""
+    c = 65536
+    gen = torch.Generator(device="cuda").manual_seed(chunks)
+    table = [(5, torch.randint(0, 256, (chunks * c - 100,), dtype=torch.uint8, device="cuda", generator=gen))]
+    t = table[0][1]
+    t[5 * c:7 * c] = 0
+    rc, base, _ = mk.ckpt_dump(ctx, table)
+    assert rc == 0
+    orc, obase = corc.dump(workloads.host_copy(table), c)
+    assert orc == 0 and np.array_equal(base.view(), obase)
+    before = blank(table)
+    t[-1] ^= 1
+    t[(chunks // 2) * c] ^= 3
+    if chunks > 9:
+        t[8 * c:9 * c] = 0
+    rc, delta, res = mk.ckpt_dump(ctx, table, prev=base)
+    assert rc == 0
+    orc, odelta = corc.dump(workloads.host_copy(table), c, prev=obase)
+    assert orc == 0 and np.array_equal(delta.view(), odelta)
+    assert mk.ckpt_restore(ctx, base, before, opts=mk.make_opts(strict_verify=1))[0] == 0
+    if res.n_unchanged > 20:
+        before[0][1][12 * c + 7] ^= 1
+        before[0][1][15 * c] ^= 1
+        rc, res = mk.ckpt_restore(ctx, delta, before)
+        assert rc == mk.CKPT_EBASE and res.first_bad_chunk == 12
+        before[0][1][12 * c + 7] ^= 1
+        before[0][1][15 * c] ^= 1
+    assert mk.ckpt_restore(ctx, delta, before, opts=mk.make_opts(strict_verify=1))[0] == 0
+    same(before, table)
