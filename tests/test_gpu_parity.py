@@ -669,3 +669,28 @@ def test_graph_restore_replays_and_rejects_corrupt_images(ctx):
     rc, r = mk.ckpt_restore(ctx, img, targets, opts=mk.make_opts(**gopts))
     assert (rc, r.first_bad_chunk) == want and rc == mk.CKPT_ECORRUPT
     img.free()
+
+
+def test_captured_deltas_of_small_chunks_stay_one_launch(ctx):
+    """A captured delta of 4 KiB chunks: 148 MB take about as much longer than
+    120 MB as they are more (as two launches they took three times as long)."""
+    import statistics
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    opts = mk.make_opts(chunk_size=4096, flags=mk.OPT_GRAPH)
+    med = []
+    for mb in (120, 148):
+        table = [(i, torch.randint(0, 256, (mb * 250000,), dtype=torch.uint8, device=DEV, generator=gen)) for i in range(4)]
+        rc, img, _ = mk.ckpt_dump(ctx, table, opts=opts)
+        assert rc == 0
+        for _, t in table:
+            t[:t.numel() // 100] += 1
+        ns = []
+        for _ in range(12):
+            rc, delta, res = mk.ckpt_dump(ctx, table, prev=img, opts=opts)
+            assert rc == 0 and 0 < res.n_data < res.n_chunks // 50
+            ns.append(res.ns_total)
+            delta.free()
+        med.append(statistics.median(ns[2:]))
+        img.free()
+    print("120 MB %.2f ms, 148 MB %.2f ms" % (med[0] / 1e6, med[1] / 1e6), flush=True)
+    assert med[1] <= 2 * med[0]
