@@ -273,12 +273,17 @@ constexpr uint64_t kShortDump = 2048;
 
 // First chunks of the pieces of a delta's or codec dump's pipeline over nc
 // chunks of C bytes: with `ring` round slots in a staging budget that holds
-// two chunks but not all of them, else each with a place of its own. `least`:
-// the least bytes of state worth a piece; `round`: chunks that the digest pass
-// takes at a time.
-inline std::vector<uint64_t> plan_pieces(uint64_t nc, uint32_t C, uint64_t budget, bool ring, uint64_t least,
+// two chunks but not all of them, else each with a place of its own. `round`:
+// chunks that the digest pass takes at a time.
+// The least bytes of state worth a piece: one of a delta costs 25 us of small
+// launches, 55 with the digests of chunks below 8 KiB; what the link waits for
+// once are the digests, 0.2 ms per GiB, of those small chunks 4 (220 MB of 4
+// KiB chunks, a third of them rewritten: 2064 us in one piece, 1652 in
+// three), a codec piece's passes 2.
+constexpr uint64_t kDeltaPiece = 128ull << 20, kSmallDeltaPiece = 64ull << 20, kCodecPiece = 16ull << 20;
+inline std::vector<uint64_t> plan_pieces(uint64_t nc, uint32_t C, uint64_t budget, bool ring, bool codec,
                                          uint64_t round) {
-    const uint64_t all = nc * C;
+    const uint64_t all = nc * C, least = codec ? kCodecPiece : C < kScanMinChunk ? kSmallDeltaPiece : kDeltaPiece;
     std::vector<uint64_t> piece;
     if (!ring && all < 8 * least) {
         const uint64_t p = std::min<uint64_t>(nc, std::max<uint64_t>(1, all / least));

@@ -926,11 +926,8 @@ constexpr uint64_t kRing = 4;
 constexpr uint32_t kStampPieces = 64, kStamps = 3 + 3 * kStampPieces;
 constexpr uint32_t kRepErr = kRing + 1, kRepStamps = kRing + 7;
 constexpr uint64_t kHwWords = kRepStamps + kStamps + 3;
-// Pieces of a delta's or a codec dump's pipeline (launch_pieces): at most this
-// many in a delta, and the least bytes of state worth one. (A piece of a delta
-// costs 25 us of small launches; a codec piece's passes take 2 ms per GiB,
-// which the link waits for once.)
-constexpr uint64_t kMaxDeltaPieces = 64, kDeltaPiece = 128ull << 20, kCodecPiece = 16ull << 20;
+// Pieces of a delta's pipeline (launch_pieces): at most this many.
+constexpr uint64_t kMaxDeltaPieces = 64;
 // A full dump's head: one chunk in so many. Its copy-out has to outlast the
 // rest's kernel, which is 50 times as fast as the link (1 GiB: 1.2 against
 // 0.4 ms).
@@ -1061,7 +1058,7 @@ static int dump_run(ckpt_ctx* c, const ckpt_alloc_table* table, const ckpt_image
         } else {
             // whole rounds of the digest pass over its groups
             const uint64_t round = C < kScanMinChunk ? 1 : 2ull * c->num_cu * (512 / scan_width(C, nc));
-            piece = plan_pieces(nc, C, c->budget, wins.size() > 1, codec ? kCodecPiece : kDeltaPiece, round);
+            piece = plan_pieces(nc, C, c->budget, wins.size() > 1, codec, round);
         }
         piece.push_back(nc);
         if (wins.size() > 1) {

@@ -317,13 +317,13 @@ def test_pieces_on_a_ring_leave_room_for_two():
                            os.path.join(ROOT, "tests", "emu", "piece_policy.cpp")])
     L = ctypes.CDLL(so)
     L.emu_plan_pieces.restype = ctypes.c_uint64
-    L.emu_plan_pieces.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int, ctypes.c_uint64,
+    L.emu_plan_pieces.argtypes = [ctypes.c_uint64, ctypes.c_uint32, ctypes.c_uint64, ctypes.c_int, ctypes.c_int,
                                   ctypes.c_uint64, ctypes.c_void_p, ctypes.c_uint64]
     out = np.zeros(4096, np.uint64)
 
-    def plan(nc, c, budget, ring):
+    def plan(nc, c, budget, ring, codec=0):
         rnd = 1 if c < 8192 else 4096 if c <= 65536 else 512   # 256 CUs
-        n = L.emu_plan_pieces(nc, c, budget, ring, 128 << 20, rnd, out.ctypes.data, out.size)
+        n = L.emu_plan_pieces(nc, c, budget, ring, codec, rnd, out.ctypes.data, out.size)
         return np.append(out[:min(n, out.size)], np.uint64(nc)).astype(np.int64), n
 
     rng = np.random.default_rng(11)
@@ -341,3 +341,6 @@ def test_pieces_on_a_ring_leave_room_for_two():
     # chunks of 64 MiB in 250 MiB: pieces of two chunks would need 256
     p, _ = plan(10, 64 << 20, 250 << 20, 1)
     assert list(p) == list(range(11))
+    # slow digests are not left in front of the whole copy-out
+    assert [plan((220 << 20) // c, c, 4 << 30, 0)[1] for c in (1024, 4096, 8192, 65536)] == [3, 3, 1, 1]
+    assert plan((220 << 20) // 4096, 4096, 4 << 30, 0, 1)[1] == 6
