@@ -683,7 +683,6 @@ k_dump_stream(JobList jl) {
 
     const int tid = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
-    stamp(jl.job[0].stamp);
     const EngineConsts* ec = jl.job[0].ec;
     for (int i = tid; i < 16 * 256; i += T) s_dt[i] = ec->dt[i];
     const uint32_t lanec = ec->lane[tid];
@@ -692,6 +691,7 @@ k_dump_stream(JobList jl) {
     if (tid == 0) {
         s_tk[0] = atomicAdd(jl.ticket, 1u);
         s_tk[1] = atomicAdd(jl.ticket, 1u);
+        stamp(jl.job[0].stamp);   // (at the kernel's top: 4 KiB chunks of a delta 30 % slower)
     }
     __syncthreads();
 
