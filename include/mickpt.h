@@ -151,7 +151,9 @@ typedef struct {
      *          host waits for it: wall time)  [2] host link: from the first
      *          payload work queued to the end, wall time  [3] scatter + fused
      *          verify kernels (codec decode and zero fill included; at the
-     *          link's rate where a short restore reads a pinned image in place)
+     *          link's rate where a short restore reads a pinned image in place;
+     *          from the first of them to the end, where a pinned image is
+     *          restored as one window)
      *          [4] strict re-read  [5] offsets scan and per-allocation check
      *          [6] unused  [7] whole call, wall time. */
     uint64_t ns_stage[8];

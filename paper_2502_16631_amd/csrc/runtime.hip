@@ -2088,9 +2088,9 @@ static int restore_run(ckpt_ctx* c, const ckpt_image* img, const ckpt_alloc_tabl
     HIPCHK(c->ctl.ensure(ctl_wtk + 4 * (W + 2) + 64));
     HIPCHK(ensure_hsmall(c, 8 * (W + 2) + 256));
     HIPCHK(ensure_events(c, std::max<size_t>(2 * W + (size_t)nslots + 2, ncs)));
-    // stage times: by stamps where the launches are few and read host memory,
-    // else by events
-    const bool stamped = direct && W <= 1 && !(o && (o->flags & CKPT_OPT_NO_TIMING));
+    // stage times: by stamps where the launches are few (one window of a pinned
+    // image: the events of a delta over 440 MB took 40 of 258 us), else by events
+    const bool stamped = (direct || staged) && W <= 1 && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     const bool timing = !stamped && !(o && (o->flags & CKPT_OPT_NO_TIMING));
     // pairs: the windows' launches, base check, zero fill
     if (timing) HIPCHK(ensure_tevents(c, 2 * W + 4));
